@@ -196,10 +196,9 @@ size_t soar_workspace_bytes(int64_t rows, int64_t cols, const soar_params *param
  * errors) is compared with the previous one for the early stop.  With T = 1,
  * beta = {1} and window candidates both paths return the same bytes.
  * search_mode on the iterated path: FULL evaluates the error of every pair; AUTO
- * (grids of 4 to 128 factors) first forms the codes of every factor and evaluates
- * errors only for the factors at which a block's codes change -- a pair whose codes
- * equal those of the factor before it has the same errors and can never be strictly
- * better.  Both return the same bytes.
+ * (ascending grids of four or more factors) evaluates, for each stored-scale candidate,
+ * the factors next to it and walks outwards only while it cannot show that no further
+ * factor computes to a smaller or an equal earlier error.  Both return the same bytes.
  *
  * d_w            in   weights, bf16 or fp32 (see conventions)
  * d_codes        out  rows*cols/2 bytes
@@ -370,9 +369,9 @@ typedef struct {
     float    beta_hi;
     int32_t  radius;         /* K, 0 .. 127                                          */
     int32_t  tiles_per_wg;   /* 0 = chosen by the library; a power of two <= 65536   */
-    int32_t  single_pass;    /* 0: the library's fastest exact search (grids of 4-128
-                                factors: codes of every factor first, errors only where a
-                                block's codes change); 1: evaluate every pair.  Same bytes. */
+    int32_t  single_pass;    /* 0: the library's fastest exact search (ascending grids of four or
+                                more factors: only the factors next to each stored-scale candidate);
+                                1: evaluate every factor.  Same bytes.                      */
     int32_t  streams;        /* soar_mxfp4_quantize_batch: 0 = launch groups alternate between
                                 the caller's stream and one internal stream (forked and joined
                                 by events); 1 = everything on the caller's stream            */

@@ -456,19 +456,28 @@ soar_status launch_group(const Batch &b, uint32_t wg_absmax, uint32_t wg_stats, 
     return SOAR_OK;
 }
 
-// dynamic LDS of k_iter (see there); the two-pass condition mirrors the kernel's
-size_t iter_lds_bytes(const Batch &b)
+// Which factor grids the nearest-factor search takes (joint_search_nearest, mx_search_nearest).  It needs a table
+// that ascends -- a grid narrower than the rounding of its own factors may not -- and evaluates at least two factors
+// per stored-scale candidate, so below four factors evaluating all of them is no more work.
+constexpr int kNearestMinBeta = 4;
+bool nearest_search(int n_beta, float lo, float hi)
 {
-    size_t bytes = ((size_t)b.n_beta * 4 + 255) / 256 * 256;
-    if (b.n_beta >= 4 && b.n_beta <= kMaxListBeta && !b.full_search) bytes += (size_t)b.n_beta * kWG;
-    return bytes;
+    if (n_beta < kNearestMinBeta || !(hi > lo)) return false;
+    float last = beta_factor(0, n_beta, lo, hi);
+    for (int k = 1; k < n_beta; ++k) {
+        const float f = beta_factor(k, n_beta, lo, hi);
+        if (!(f >= last)) return false;
+        last = f;
+    }
+    return true;
 }
 
 // absmax, the Eq. 1-2 state, then one launch per iteration; a tensor that has
 // stopped early (or is degenerate) makes its workgroups of the later launches return at once
 template <int DT>
-soar_status launch_group_iter(Batch &b, uint32_t wg_absmax, uint32_t total_wg, int iters, hipStream_t st)
+soar_status launch_group_iter(Batch &b, uint32_t wg_absmax, uint32_t total_wg, int iters, bool nearest, hipStream_t st)
 {
+    const size_t table = (size_t)b.n_beta * sizeof(float);
     {
         ScopedTimer t(SOAR_KERNEL_ABSMAX, st);
         hipLaunchKernelGGL(k_absmax<DT>, dim3(wg_absmax), dim3(kWG), 0, st, b);
@@ -485,7 +494,8 @@ soar_status launch_group_iter(Batch &b, uint32_t wg_absmax, uint32_t total_wg, i
     for (int it = 0; it < iters; ++it) {
         b.iter_t = it;
         if (b.arm == SOAR_METHOD_CJSO_ONLY) hipLaunchKernelGGL(k_cjso<DT>, dim3(total_wg), dim3(kWG), 0, st, b);
-        else hipLaunchKernelGGL(k_iter<DT>, dim3(total_wg), dim3(kWG), iter_lds_bytes(b), st, b);
+        else if (nearest) hipLaunchKernelGGL((k_iter<DT, true>), dim3(total_wg), dim3(kWG), table, st, b);
+        else hipLaunchKernelGGL((k_iter<DT, false>), dim3(total_wg), dim3(kWG), table, st, b);
         SOAR_LAUNCH_CHECK();
     }
     return SOAR_OK;
@@ -555,6 +565,8 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
     const int64_t cap = group_byte_cap(descs, params);
     const size_t lane_bytes = lane_workspace_bytes(max_group_per_block_bytes(n, descs, cap, &n_groups));
     const int lanes = (n_groups > 1 && params->streams != 1) ? kLanes : 1;
+    const bool nearest = iterated && params->search_mode == SOAR_SEARCH_AUTO &&
+                         nearest_search(params->n_beta, params->beta_lo, params->beta_hi);
     char *base = static_cast<char *>(d_workspace);
 
     hipStream_t lane_stream[kLanes] = {st, st};
@@ -588,6 +600,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         b.dd_mode = params->dd_mode;
         b.beta_lo = params->beta_lo;
         b.beta_hi = params->beta_hi;
+        b.index_per_beta = nearest ? (float)(params->n_beta - 1) / (params->beta_hi - params->beta_lo) : 0.0f;
         b.early_stop_rel = params->early_stop_rel;
         b.arm = params->method;
         // The searching iterated kernels are arithmetic-bound: up to 16 tiles per workgroup, as long as the launch
@@ -636,8 +649,8 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
             b.t[k - i] = t;
         }
         if (iterated)
-            result = descs[i].dtype == SOAR_BF16 ? launch_group_iter<SOAR_BF16>(b, wg_absmax, wg, params->iters, lane_stream[lane])
-                                                 : launch_group_iter<SOAR_FP32>(b, wg_absmax, wg, params->iters, lane_stream[lane]);
+            result = descs[i].dtype == SOAR_BF16 ? launch_group_iter<SOAR_BF16>(b, wg_absmax, wg, params->iters, nearest, lane_stream[lane])
+                                                 : launch_group_iter<SOAR_FP32>(b, wg_absmax, wg, params->iters, nearest, lane_stream[lane]);
         else
             result = descs[i].dtype == SOAR_BF16
                          ? launch_group<SOAR_BF16>(b, wg_absmax, wg, wg_search, params->method, lane_stream[lane])
@@ -1008,8 +1021,8 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
         if (hipGetLastError() != hipSuccess) result = SOAR_ERR_HIP;
     }
     if (lanes > 1 && result == SOAR_OK && !second->order(second->fork, st, lane_stream[1])) result = SOAR_ERR_HIP;
-    const bool two_pass = params->dss && params->single_pass == 0 && params->n_beta >= 4 && params->n_beta <= kMaxListBeta;
-    const size_t lds = ((size_t)params->n_beta * 4 + 255) / 256 * 256 + (two_pass ? (size_t)params->n_beta * kWG : 0);
+    const bool nearest = params->dss && params->single_pass == 0 && nearest_search(params->n_beta, params->beta_lo, params->beta_hi);
+    const size_t lds = (size_t)params->n_beta * sizeof(float);
     // consecutive tensors of one element type share a launch (up to kGroupMax); every kernel leaves the
     // control words of its slots as it found them, so the next group reuses them
     int32_t g = 0;
@@ -1055,7 +1068,8 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
             t.radius = params->radius;
             t.beta_lo = params->beta_lo;
             t.beta_hi = params->beta_hi;
-            t.two_pass = two_pass ? 1 : 0;
+            t.nearest = nearest ? 1 : 0;
+            t.index_per_beta = nearest ? (float)(params->n_beta - 1) / (params->beta_hi - params->beta_lo) : 0.0f;
         }
         ScopedTimer tm(SOAR_KERNEL_MX, lst);
         // the plain conversion is an instantiation of its own: it needs half the registers of the search

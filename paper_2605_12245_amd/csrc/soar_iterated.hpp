@@ -195,89 +195,102 @@ __device__ __forceinline__ void joint_search(const float w[16], float alpha, flo
     }
 }
 
-// assign_codes_rcp without the decoded values (codes only)
-template <bool FAST>
-__device__ __forceinline__ void codes_only_rcp(const float w[16], float scale, uint32_t nib[2])
-{
-    const float r = FAST ? rcp_midrange(scale) : 1.0f / scale;
-    float x[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) x[j] = w[j] * r;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        uint32_t v = nib[h];
-        v = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(v, x[8 * h + 0], x[8 * h + 1], 1.0f, 0);
-        v = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(v, x[8 * h + 2], x[8 * h + 3], 1.0f, 1);
-        v = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(v, x[8 * h + 4], x[8 * h + 5], 1.0f, 2);
-        v = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(v, x[8 * h + 6], x[8 * h + 7], 1.0f, 3);
-        nib[h] = v;
-    }
-}
+// The same joint search without walking the factor grid.  For ONE stored scale s the exact block error, as a
+// function of the factor, falls towards the assignment scale t = s and rises beyond it: the codes of one element
+// move through the E2M1 grid in one direction as t grows (t_k = alpha (Delta* beta_k), the reciprocal, the product
+// and the rounding are all monotone, in binary32 too), and while t_k <= s every |code| lies at or above the one
+// nearest to |w|/s, so each further step up moves away from w; for t_k >= s the mirror image.  The best factor
+// for s is therefore the last one below s (A) or the first one above it (B) -- 4 pairs of the paper's 202.
+// What binary32 rounding can change is covered by a certificate.  A factor beyond A that gives other codes moves
+// at least one code across a rounding threshold m (>= 0.25, codes >= 0.5 apart), and |w| <= m t_A up to the rounding
+// of the product, so its exact error exceeds that of A by at least 2 s^2 (0.5)(0.25)(s - t_A)/s = s (s - t_A) / 4; a
+// computed error is within 18 units of 2^-24 of the exact one (all terms non-negative).  If that rise exceeds the
+// rounding of both sides, no factor beyond A can compute to a value as small as A's, and factors with A's codes
+// have A's error.  Otherwise (s within about 1e-5 of t_A: one block in a thousand per side, or magnitudes at
+// which squares leave the normal range) the walk goes one factor further out and asks again, to the end of the
+// grid if need be: the result never depends on the shortcut.
+// "First pair wins a tie" (factors ascending, then the candidates in their order): between pairs of different
+// codes the smaller factor is the earlier one; pairs of the same codes belong to the same run of factors, and the
+// candidate tried first keeps the tie.
+// Needs an ascending factor table (checked on the host) and the reciprocal's range (FAST).
+// Bound by vector instructions: about 450 per block and iteration with two candidates, where forming the codes of all
+// 101 factors and the errors of those at which a block's codes change took 8 500.  One decoder layer (seven tensors,
+// 1.93e8 bf16 weights, 3 iterations): 7.65 -> 0.82 ms a call; with three candidates on 4096 x 4096 fp32: 958 -> 188 us.
+struct BestPair {
+    float err;
+    int k, code;
+    uint32_t nib[2];
+};
 
-constexpr int kMaxListBeta = 128;        // longest factor grid the two-pass form of the search handles
-
-// The same joint search in two passes.  Neighbouring factors very often give a block the same 16
-// codes (a quarter of the paper's 101 factors give new ones, on average, on heavy-tailed weights),
-// and a pair whose codes equal those of the factor before it has the same errors and can never be
-// strictly better.  Pass 1 walks all factors, forms the codes only and notes in LDS the factors at
-// which this block's codes change; pass 2 evaluates the errors for the noted factors alone (its
-// trip count is the longest list in the wave).  The result is that of joint_search, pair for pair.
-// list: kMaxListBeta x kWG bytes, entry e of this lane at list[e * kWG + threadIdx.x].
-template <bool FAST>
-__device__ __forceinline__ void joint_search_two_pass(const float w[16], float alpha, float delta_star,
-                                                      const float *s_beta, int n_beta, bool bracket, int c0,
-                                                      int radius, uint8_t *list, float &best_err, int &best_code,
-                                                      uint32_t best_nib[2], float q[16])
+__device__ __forceinline__ float try_pair(const float w[16], float t, int k, int code, float s, bool first, BestPair &best)
 {
     uint32_t nib[2] = {0u, 0u};
-    uint32_t p0 = 0u, p1 = 0u;
-    int n = 0;
-    for (int kb = 0; kb < n_beta; ++kb) {
-        codes_only_rcp<FAST>(w, alpha * (delta_star * s_beta[kb]), nib);
-        if (kb == 0 || nib[0] != p0 || nib[1] != p1) {
-            list[n * kWG + threadIdx.x] = (uint8_t)kb;
-            ++n;
-        }
-        p0 = nib[0];
-        p1 = nib[1];
-    }
-    float best = __builtin_inff();
-    float best_beta = s_beta[0];
-    const int lo = c0;
-    const int hi = min(lo + 1, (int)kE4M3Max);
-    const float s_lo = alpha * e4m3_value((uint32_t)lo);
-    const float s_hi = alpha * e4m3_value((uint32_t)hi);
-    best_code = c0;
-    for (int j = 0; __builtin_amdgcn_ballot_w64(j < n) != 0ull; ++j) {
-        if (j < n) {
-            const float bk = s_beta[list[j * kWG + threadIdx.x]];
-            assign_codes_rcp<FAST>(w, alpha * (delta_star * bk), nib, q);
-            if (bracket) {
-                const float e_lo = block_error(w, q, s_lo);
-                const float e_hi = block_error(w, q, s_hi);
-                const float m = fminf(fminf(best, e_lo), e_hi);
-                best_beta = (m < best) ? bk : best_beta;
-                best = m;
-            } else {
-                for (int c = 0; c <= 2 * radius; ++c) {
-                    const int o = (c + 1) >> 1;
-                    const int code = (c & 1) ? max(c0 - o, (int)kE4M3Min) : min(c0 + o, (int)kE4M3Max);
-                    const float e = block_error(w, q, alpha * e4m3_value((uint32_t)code));
-                    if (e < best) { best = e; best_beta = bk; best_code = code; }
-                }
+    float q[16];
+    assign_codes_rcp<true>(w, t, nib, q);
+    const float e = block_error(w, q, s);
+    bool win = first || e < best.err;
+    const bool tie = !first && e == best.err && k < best.k;
+    if (__builtin_amdgcn_ballot_w64(tie) != 0ull) win = win || (tie && (nib[0] != best.nib[0] || nib[1] != best.nib[1]));
+    best.err = win ? e : best.err;
+    best.k = win ? k : best.k;
+    best.code = win ? code : best.code;
+    best.nib[0] = win ? nib[0] : best.nib[0];
+    best.nib[1] = win ? nib[1] : best.nib[1];
+    return e;
+}
+
+// no factor on the far side of t (seen from s) can give other codes and an error as small as the computed e;
+// kRounding: four times twice the rounding of a block error, kSlack: the rounding of reciprocal and product
+template <int NELEM>
+__device__ __forceinline__ bool far_side_excluded(float s, float t, float e)
+{
+    constexpr float kRounding = NELEM == 16 ? 1.0e-5f : 1.8e-5f;      // 4 * 2 * 19 (35) * 2^-24, rounded up
+    static_assert(NELEM == 16 || NELEM == 32, "block sizes");
+    const float distance = fabsf(s - t) - 0x1p-22f * fmaxf(s, t);
+    return s < 0x1p60f && s * distance > __builtin_fmaf(kRounding, e, 0x1p-98f);
+}
+
+__device__ __forceinline__ void joint_search_nearest(const float w[16], float alpha, float delta_star, const float *s_beta,
+                                                     int n_beta, float beta_lo, float index_per_beta, bool bracket, int c0,
+                                                     int radius, float &best_err, int &best_code, uint32_t best_nib[2],
+                                                     float q[16])
+{
+    BestPair best;
+    best.err = 0.0f; best.k = 0; best.code = c0; best.nib[0] = best.nib[1] = 0u;
+    const float per_scale = __builtin_amdgcn_rcpf(alpha * delta_star);
+    const int ncand = bracket ? 2 : 2 * radius + 1;
+#pragma unroll 1
+    for (int c = 0; c < ncand; ++c) {
+        const int o = (c + 1) >> 1;
+        // bracket: c0, c0 + 1; window: c0, -1, +1, ...; a code clamped into [0x01, 0x7E] repeats an earlier candidate
+        const int code = (bracket || !(c & 1)) ? min(c0 + (bracket ? c : o), (int)kE4M3Max) : max(c0 - o, (int)kE4M3Min);
+        const float s = alpha * e4m3_value((uint32_t)code);
+        // the factor nearest to s decides where A and B lie; any error of this estimate is met by the walk
+        const float at = (s * per_scale - beta_lo) * index_per_beta;
+        const int km = (int)__builtin_rintf(fminf(fmaxf(at, 0.0f), (float)(n_beta - 1)));
+        const int split = km + ((alpha * (delta_star * s_beta[km]) <= s) ? 1 : 0);
+        int ka = max(split - 1, 0), kb = min(split, n_beta - 1);
+        const float ta = alpha * (delta_star * s_beta[ka]), tb = alpha * (delta_star * s_beta[kb]);
+        const float ea = try_pair(w, ta, ka, code, s, c == 0, best);
+        const float eb = try_pair(w, tb, kb, code, s, false, best);
+        bool down = ka > 0 && !(ta <= s && far_side_excluded<16>(s, ta, ea));
+        bool up = kb < n_beta - 1 && !(tb >= s && far_side_excluded<16>(s, tb, eb));
+        while (__builtin_amdgcn_ballot_w64(down || up) != 0ull) {
+            if (down || up) {
+                const int k = down ? --ka : ++kb;
+                const float t = alpha * (delta_star * s_beta[k]);
+                const float e = try_pair(w, t, k, code, s, false, best);
+                if (down) down = ka > 0 && !(t <= s && far_side_excluded<16>(s, t, e));
+                else up = kb < n_beta - 1 && !(t >= s && far_side_excluded<16>(s, t, e));
             }
         }
     }
-    assign_codes_rcp<FAST>(w, alpha * (delta_star * best_beta), best_nib, q);
-    if (bracket) {
-        const float e_lo = block_error(w, q, s_lo);
-        const float e_hi = block_error(w, q, s_hi);
-        const bool upper = e_hi < e_lo;
-        best_code = upper ? hi : lo;
-        best_err = upper ? e_hi : e_lo;
-    } else {
-        best_err = best;
-    }
+    best_err = best.err;
+    best_code = best.code;
+    best_nib[0] = best.nib[0];
+    best_nib[1] = best.nib[1];
+    fp4x8_values(best_nib[0], q);
+    fp4x8_values(best_nib[1], q + 8);
 }
 
 // The Eq. 1-2 state of Algorithm 1 (Delta^q = Delta^d = Delta0) for the iterated
@@ -387,18 +400,18 @@ __device__ __forceinline__ void finish_iteration(const Batch &batch, const Task 
 // after this iteration (exact adjacent-pair tree, so that the early-stop test
 // is reproducible), the stop flag and the next global scale.
 // A tensor whose stop flag is set is skipped by every later launch.
-template <int DT>
+// NEAREST: the pairs that can win are found without walking the grid (joint_search_nearest); otherwise every pair
+// is evaluated (joint_search: SOAR_SEARCH_FULL, grids of fewer than four factors, tables that do not ascend).
+template <int DT, bool NEAREST>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_iter(const Batch batch)
 {
+    __shared__ float4 s_blocks[kStage * kWG];
     __shared__ double s_wave[3][4];
     __shared__ double s_stack[3][32];
-    __shared__ double s_tree[kWG];
-    // dynamic LDS: the factor table (n_beta floats, rounded up to 256 bytes), then, for the two-pass
-    // search, the change lists (n_beta x kWG bytes)
-    extern __shared__ __align__(16) unsigned char s_dyn[];
-    float *s_beta = reinterpret_cast<float *>(s_dyn);
-    uint8_t *s_list = s_dyn + ((size_t)batch.n_beta * 4 + 255) / 256 * 256;
     __shared__ uint32_t s_last;
+    double *s_tree = reinterpret_cast<double *>(s_blocks);      // trees_of_partials, after the last group
+    extern __shared__ __align__(16) unsigned char s_dyn[];      // the factor table, n_beta floats
+    float *s_beta = reinterpret_cast<float *>(s_dyn);
 
     uint32_t lwg;
     const Task t = batch.t[find_task(batch, lwg)];
@@ -409,73 +422,64 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     if (degenerate ? batch.iter_t != 0 : t.ctrl->stopped != 0u) return;     // uniform over the tensor's workgroups
 
     const int n_beta = batch.n_beta;
-    for (int k = (int)tid; k < n_beta; k += kWG)
-        s_beta[k] = n_beta <= 1 ? batch.beta_lo
-                                : (batch.beta_lo * (float)(n_beta - 1 - k) + batch.beta_hi * (float)k) / (float)(n_beta - 1);
+    for (int k = (int)tid; k < n_beta; k += kWG) s_beta[k] = beta_factor(k, n_beta, batch.beta_lo, batch.beta_hi);
     __syncthreads();
 
     const float alpha = t.ctrl->alpha1;
     const bool bracket = batch.dd_mode == SOAR_DD_BRACKET;
     const int radius = batch.radius;
-    const bool two_pass = n_beta >= 4 && n_beta <= kMaxListBeta && !batch.full_search;
     const bool dss_only = batch.arm == SOAR_METHOD_DSS_ONLY;    // rho then always carries -Delta^d: the search centre
 
-    TileTree<3> tree{s_wave, s_stack};
+    StagedTree tree{s_blocks, s_wave, s_stack};
     const uint32_t tile0 = lwg * t.tiles_per_wg;
-    for (uint32_t k = 0; k < t.tiles_per_wg; ++k) {
-        const uint32_t i = (tile0 + k) * kWG + tid;
-        double term[3] = {0.0, 0.0, 0.0};
-        if (i < t.nblk && amax_bits < 0x7F800000u) {
-            float w[16], q[16];
-            uint32_t best_nib[2] = {0u, 0u};
-            int best_code = (int)kE4M3Min;
-            float best_err = 0.0f;
-            load_block<DT>(t.w, block_offset(t, i), w);
-            if (allzero) {
-                float x[16];
+    const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
+    for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
+        for (uint32_t kk = 0; kk < T; ++kk) {
+            const uint32_t i = (tile0 + kg + kk) * kWG + tid;
+            float a = 0.0f, b = 0.0f, d = 0.0f, best_err = 0.0f;
+            if (i < t.nblk && amax_bits < 0x7F800000u) {
+                float w[16], q[16];
+                uint32_t best_nib[2] = {0u, 0u};
+                int best_code = (int)kE4M3Min;
+                load_block<DT>(t.w, block_offset(t, i), w);
+                if (allzero) {
+                    float x[16];
 #pragma unroll
-                for (int j = 0; j < 16; ++j) x[j] = w[j];
-                best_nib[0] = fp4x8(x);
-                best_nib[1] = fp4x8(x + 8);
-            } else {
-                const float rho = t.rho[i];
-                const float delta_star = (rho < 0.0f) ? -rho : rho / alpha;
-                const int c0 = bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
-                // the reciprocal shortcut holds while the biased exponent of the scale stays in [1, 252];
-                // the scales of a block lie between those of the first and the last factor (to within
-                // rounding of the grid), which are asked to keep one binade of distance from both ends
-                const float s_first = alpha * (delta_star * s_beta[0]);
-                const float s_final = alpha * (delta_star * s_beta[n_beta - 1]);
-                const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
-                if (two_pass) {
-                    if (__builtin_amdgcn_ballot_w64(!mid) == 0ull)
-                        joint_search_two_pass<true>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, s_list,
-                                                    best_err, best_code, best_nib, q);
-                    else
-                        joint_search_two_pass<false>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, s_list,
-                                                     best_err, best_code, best_nib, q);
-                } else if (__builtin_amdgcn_ballot_w64(!mid) == 0ull) {
-                    joint_search<true>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err, best_code,
-                                       best_nib, q);
+                    for (int j = 0; j < 16; ++j) x[j] = w[j];
+                    best_nib[0] = fp4x8(x);
+                    best_nib[1] = fp4x8(x + 8);
                 } else {
-                    joint_search<false>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err, best_code,
-                                        best_nib, q);
+                    const float rho = t.rho[i];
+                    const float delta_star = (rho < 0.0f) ? -rho : rho / alpha;
+                    const int c0 = bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
+                    // the reciprocal shortcut holds while the biased exponent of the scale stays in [1, 252];
+                    // the scales of a block lie between those of the first and the last factor (to within
+                    // rounding of the grid), which are asked to keep one binade of distance from both ends
+                    const float s_first = alpha * (delta_star * s_beta[0]);
+                    const float s_final = alpha * (delta_star * s_beta[n_beta - 1]);
+                    const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
+                    if (__builtin_amdgcn_ballot_w64(!mid) != 0ull)
+                        joint_search<false>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err, best_code,
+                                            best_nib, q);
+                    else if constexpr (NEAREST)
+                        joint_search_nearest(w, alpha, delta_star, s_beta, n_beta, batch.beta_lo, batch.index_per_beta, bracket,
+                                             c0, radius, best_err, best_code, best_nib, q);
+                    else
+                        joint_search<true>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err, best_code,
+                                           best_nib, q);
+                    // the state the next iteration starts from
+                    block_sums(w, q, a, b);
+                    d = e4m3_value((uint32_t)best_code);
+                    t.rho[i] = (b == 0.0f || dss_only) ? -d : a / b;
                 }
-                // the state the next iteration starts from
-                float a, b;
-                block_sums(w, q, a, b);
-                const float d = e4m3_value((uint32_t)best_code);
-                term[0] = (double)a * (double)d;
-                term[1] = ((double)b * (double)d) * (double)d;
-                term[2] = (double)best_err;
-                t.rho[i] = (b == 0.0f || dss_only) ? -d : a / b;
+                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                u32x2 packed = {best_nib[0], best_nib[1]};
+                __builtin_nontemporal_store(packed, reinterpret_cast<u32x2 *>(t.codes) + i);
+                __builtin_nontemporal_store((uint8_t)best_code, t.scales + i);
             }
-            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-            u32x2 packed = {best_nib[0], best_nib[1]};
-            reinterpret_cast<u32x2 *>(t.codes)[i] = packed;
-            t.scales[i] = (uint8_t)best_code;
+            tree.stage(kk, a, b, d, best_err);
         }
-        tree.add_tile(k, term);
+        tree.close(kg / T, T);
     }
     uint32_t *counters = t.counters + 2 * kSlots * kSlotStride;
     if (tid == 0) {
