@@ -282,12 +282,16 @@ WantedShapes wanted_shapes(bool several_groups, int method, bool iterated, bool 
     return {(uint32_t)kStage, 8u, 16u};
 }
 
-// tiles per workgroup of an arithmetic-bound searching kernel over a launch of `tiles` tiles
-constexpr int64_t kSearchMinWg = 2048;
-uint32_t search_tiles_per_wg(int64_t tiles)
+// Tiles per workgroup of an arithmetic-bound searching kernel over a launch of `tiles` tiles: as many as leave
+// min_wg workgroups.  The iterations run at five waves per SIMD, 1280 workgroups at once, and each of the launches
+// after the early stop costs what its workgroups take to come and go (5 us for 2048, 3 us for 1024: 175 against
+// 181 us on 4096 x 4096 fp32); the MXFP4 search, one launch, balances better over 2048 (210 against 223 us on a
+// decoder layer).
+constexpr int64_t kIterMinWg = 1024, kMxMinWg = 2048;
+uint32_t search_tiles_per_wg(int64_t tiles, int64_t min_wg)
 {
     uint32_t tpw = 16;
-    while (tpw > 1 && tiles / tpw < kSearchMinWg) tpw >>= 1;
+    while (tpw > 1 && tiles / tpw < min_wg) tpw >>= 1;
     return tpw;
 }
 
@@ -462,7 +466,7 @@ soar_status launch_group(const Batch &b, uint32_t wg_absmax, uint32_t wg_stats, 
 constexpr int kNearestMinBeta = 4;
 bool nearest_search(int n_beta, float lo, float hi)
 {
-    if (n_beta < kNearestMinBeta || !(hi > lo)) return false;
+    if (n_beta < kNearestMinBeta || !(hi > lo) || lo < 0x1p-20f || hi > 0x1p20f) return false;
     float last = beta_factor(0, n_beta, lo, hi);
     for (int k = 1; k < n_beta; ++k) {
         const float f = beta_factor(k, n_beta, lo, hi);
@@ -603,17 +607,15 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         b.index_per_beta = nearest ? (float)(params->n_beta - 1) / (params->beta_hi - params->beta_lo) : 0.0f;
         b.early_stop_rel = params->early_stop_rel;
         b.arm = params->method;
-        // The searching iterated kernels are arithmetic-bound: up to 16 tiles per workgroup, as long as the launch
-        // keeps kSearchMinWg workgroups (a few rounds of what the GPU holds at once) to balance over: the
-        // full-model workload takes 267 ms per step that way, 299 with one tile per workgroup.  (The closed-form
-        // arm has no search and streams like the single-step kernels.)
+        // The searching iterated kernels are arithmetic-bound (see search_tiles_per_wg); the closed-form arm has no
+        // search and streams like the single-step kernels.
         const bool searching = iterated && params->method != SOAR_METHOD_CJSO_ONLY;
         const uint32_t tpw = (uint32_t)params->tiles_per_wg;
         uint32_t searching_tpw = 0;
         if (searching) {
             int64_t group_tiles = 0;
             for (int32_t k = i; k < j; ++k) group_tiles += (descs[k].rows * (descs[k].cols / 16) + kWG - 1) / kWG;
-            searching_tpw = search_tiles_per_wg(group_tiles);
+            searching_tpw = search_tiles_per_wg(group_tiles, kIterMinWg);
         }
         uint32_t wg = 0, wg_absmax = 0, wg_search = 0;
         char *per_block = lane_base + (size_t)kGroupMax * kSlotBytes;
@@ -1051,7 +1053,7 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
             t.contiguous = d.ld_elems == d.cols ? 1u : 0u;
             const uint32_t tiles = (t.nblk + kWG - 1) / kWG;
             // the search is arithmetic-bound (see search_tiles_per_wg); the plain conversion streams
-            uint32_t tpw = params->dss ? search_tiles_per_wg(group_tiles) : 2u;
+            uint32_t tpw = params->dss ? search_tiles_per_wg(group_tiles, kMxMinWg) : 2u;
             while (tpw > 1 && tpw > tiles) tpw >>= 1;
             if (params->tiles_per_wg) tpw = (uint32_t)params->tiles_per_wg;
             while ((tiles + tpw - 1) / tpw > (uint32_t)kMaxPartials) tpw <<= 1;

@@ -119,6 +119,18 @@ __device__ __forceinline__ float rcp_midrange(float s)
     return __builtin_fmaf(e, y, y);
 }
 
+// a / b, correctly rounded, from y = 1 / b correctly rounded (Markstein, IBM J. Res. Dev. 34, 1990: one fused residual
+// of a quotient within an ulp, one fused correction); the caller keeps a, b and a / b so far inside the normal range
+// that the residual is exact
+__device__ __forceinline__ float div_midrange(float a, float b, float y)
+{
+    const float q = a * y;
+    return __builtin_fmaf(__builtin_fmaf(-q, b, a), y, q);
+}
+
+// biased exponent within 60 of 1.0's
+__device__ __forceinline__ bool near_one(float x) { return ((__float_as_uint(x) >> 23) - 67u) < 120u; }
+
 // assign_codes with the reciprocal chosen at compile time; nib carries the previous codes in
 // (every byte is overwritten) so that no register has to be cleared first
 template <bool FAST>
@@ -145,7 +157,7 @@ __device__ __forceinline__ void assign_codes_rcp(const float w[16], float scale,
 // candidates in their order (bracket: c0 then c0+1; window: c0, -1, +1, ...), the first pair with
 // the smallest binary32 error wins.  Only the error and the winning factor are tracked in the
 // loop; the winner's codes are formed once more at the end.
-template <bool FAST>
+template <bool FAST, int UNROLL>
 __device__ __forceinline__ void joint_search(const float w[16], float alpha, float delta_star, const float *s_beta,
                                              int n_beta, bool bracket, int c0, int radius, float &best_err,
                                              int &best_code, uint32_t best_nib[2], float q[16])
@@ -159,7 +171,7 @@ __device__ __forceinline__ void joint_search(const float w[16], float alpha, flo
         const int hi = min(lo + 1, (int)kE4M3Max);           // hi == lo can never win
         const float s_lo = alpha * e4m3_value((uint32_t)lo);
         const float s_hi = alpha * e4m3_value((uint32_t)hi);
-#pragma unroll 4
+#pragma unroll UNROLL
         for (int kb = 0; kb < n_beta; ++kb) {
             const float bk = s_beta[kb];
             assign_codes_rcp<FAST>(w, alpha * (delta_star * bk), nib, q);
@@ -195,6 +207,9 @@ __device__ __forceinline__ void joint_search(const float w[16], float alpha, flo
     }
 }
 
+// four times twice the rounding of a block error of 16 or 32 elements, (n + 2) 2^-24, rounded up by a tenth
+constexpr float kFarSideRounding16 = 1.0e-5f, kFarSideRounding32 = 1.8e-5f;
+
 // The same joint search without walking the factor grid.  For ONE stored scale s the exact block error, as a
 // function of the factor, falls towards the assignment scale t = s and rises beyond it: the codes of one element
 // move through the E2M1 grid in one direction as t grows (t_k = alpha (Delta* beta_k), the reciprocal, the product
@@ -205,7 +220,7 @@ __device__ __forceinline__ void joint_search(const float w[16], float alpha, flo
 // at least one code across a rounding threshold m (>= 0.25, codes >= 0.5 apart), and |w| <= m t_A up to the rounding
 // of the product, so its exact error exceeds that of A by at least 2 s^2 (0.5)(0.25)(s - t_A)/s = s (s - t_A) / 4; a
 // computed error is within 18 units of 2^-24 of the exact one (all terms non-negative).  If that rise exceeds the
-// rounding of both sides, no factor beyond A can compute to a value as small as A's, and factors with A's codes
+// rounding of both sides -- s (|s - t_A| - 2^-21 s) > kFarSideRounding error, the 2^-21 for reciprocal and product --, no factor beyond A can compute to a value as small as A's, and factors with A's codes
 // have A's error.  Otherwise (s within about 1e-5 of t_A: one block in a thousand per side, or magnitudes at
 // which squares leave the normal range) the walk goes one factor further out and asks again, to the end of the
 // grid if need be: the result never depends on the shortcut.
@@ -213,82 +228,95 @@ __device__ __forceinline__ void joint_search(const float w[16], float alpha, flo
 // codes the smaller factor is the earlier one; pairs of the same codes belong to the same run of factors, and the
 // candidate tried first keeps the tie.
 // Needs an ascending factor table (checked on the host) and the reciprocal's range (FAST).
-// Bound by vector instructions: about 450 per block and iteration with two candidates, where forming the codes of all
-// 101 factors and the errors of those at which a block's codes change took 8 500.  One decoder layer (seven tensors,
-// 1.93e8 bf16 weights, 3 iterations): 7.65 -> 0.82 ms a call; with three candidates on 4096 x 4096 fp32: 958 -> 188 us.
-struct BestPair {
-    float err;
-    int k, code;
-    uint32_t nib[2];
+// Bound by vector issue: 520 instructions per block and iteration with two candidates (69 for each of the four
+// pairs), where forming the codes of all 101 factors and the errors of those at which a block's codes change took
+// 8 500.  One decoder layer (seven tensors, 1.93e8 bf16 weights, 3 iterations): 7.65 -> 0.74 ms a call; with three
+// candidates on 4096 x 4096 fp32: 958 -> 169 us.
+struct FactorGrid {
+    const float *table;          // LDS, n factors, ascending
+    int n;
+    float lo, index_per_beta;
 };
 
-__device__ __forceinline__ float try_pair(const float w[16], float t, int k, int code, float s, bool first, BestPair &best)
+// what one factor gives for the stored scale s: the codes and their error
+__device__ __forceinline__ float factor_error(const float w[16], float t, float s, uint32_t nib[2])
 {
-    uint32_t nib[2] = {0u, 0u};
     float q[16];
+    nib[0] = nib[1] = 0u;
     assign_codes_rcp<true>(w, t, nib, q);
-    const float e = block_error(w, q, s);
-    bool win = first || e < best.err;
-    const bool tie = !first && e == best.err && k < best.k;
-    if (__builtin_amdgcn_ballot_w64(tie) != 0ull) win = win || (tie && (nib[0] != best.nib[0] || nib[1] != best.nib[1]));
-    best.err = win ? e : best.err;
-    best.k = win ? k : best.k;
-    best.code = win ? code : best.code;
-    best.nib[0] = win ? nib[0] : best.nib[0];
-    best.nib[1] = win ? nib[1] : best.nib[1];
-    return e;
+    return block_error(w, q, s);
 }
 
-// no factor on the far side of t (seen from s) can give other codes and an error as small as the computed e;
-// kRounding: four times twice the rounding of a block error, kSlack: the rounding of reciprocal and product
-template <int NELEM>
-__device__ __forceinline__ bool far_side_excluded(float s, float t, float e)
+// The first factor with the smallest error for one stored scale s.  base_index: factor index per unit of s.
+__device__ __forceinline__ float best_factor(const float w[16], float alpha, float delta_star, float base_index,
+                                             const FactorGrid &grid, float s, uint32_t nib[2], int &k)
 {
-    constexpr float kRounding = NELEM == 16 ? 1.0e-5f : 1.8e-5f;      // 4 * 2 * 19 (35) * 2^-24, rounded up
-    static_assert(NELEM == 16 || NELEM == 32, "block sizes");
-    const float distance = fabsf(s - t) - 0x1p-22f * fmaxf(s, t);
-    return s < 0x1p60f && s * distance > __builtin_fmaf(kRounding, e, 0x1p-98f);
-}
-
-__device__ __forceinline__ void joint_search_nearest(const float w[16], float alpha, float delta_star, const float *s_beta,
-                                                     int n_beta, float beta_lo, float index_per_beta, bool bracket, int c0,
-                                                     int radius, float &best_err, int &best_code, uint32_t best_nib[2],
-                                                     float q[16])
-{
-    BestPair best;
-    best.err = 0.0f; best.k = 0; best.code = c0; best.nib[0] = best.nib[1] = 0u;
-    const float per_scale = __builtin_amdgcn_rcpf(alpha * delta_star);
-    const int ncand = bracket ? 2 : 2 * radius + 1;
-#pragma unroll 1
-    for (int c = 0; c < ncand; ++c) {
-        const int o = (c + 1) >> 1;
-        // bracket: c0, c0 + 1; window: c0, -1, +1, ...; a code clamped into [0x01, 0x7E] repeats an earlier candidate
-        const int code = (bracket || !(c & 1)) ? min(c0 + (bracket ? c : o), (int)kE4M3Max) : max(c0 - o, (int)kE4M3Min);
-        const float s = alpha * e4m3_value((uint32_t)code);
-        // the factor nearest to s decides where A and B lie; any error of this estimate is met by the walk
-        const float at = (s * per_scale - beta_lo) * index_per_beta;
-        const int km = (int)__builtin_rintf(fminf(fmaxf(at, 0.0f), (float)(n_beta - 1)));
-        const int split = km + ((alpha * (delta_star * s_beta[km]) <= s) ? 1 : 0);
-        int ka = max(split - 1, 0), kb = min(split, n_beta - 1);
-        const float ta = alpha * (delta_star * s_beta[ka]), tb = alpha * (delta_star * s_beta[kb]);
-        const float ea = try_pair(w, ta, ka, code, s, c == 0, best);
-        const float eb = try_pair(w, tb, kb, code, s, false, best);
-        bool down = ka > 0 && !(ta <= s && far_side_excluded<16>(s, ta, ea));
-        bool up = kb < n_beta - 1 && !(tb >= s && far_side_excluded<16>(s, tb, eb));
+    // where s lies in the grid; any error of this estimate is met by the walk
+    const float at = __builtin_fmaf(s, base_index, -grid.lo * grid.index_per_beta);
+    const int ka = (int)__builtin_amdgcn_fmed3f(at, 0.0f, (float)(grid.n - 2));
+    const float ta = alpha * (delta_star * grid.table[ka]), tb = alpha * (delta_star * grid.table[ka + 1]);
+    uint32_t nib_b[2];
+    float err = factor_error(w, ta, s, nib);
+    const float err_b = factor_error(w, tb, s, nib_b);
+    // s (|s - t| - 2^-21 s) / kRounding > error: see above; s - t is negative where the estimate was off
+    const float per_error = s * (1.0f / kFarSideRounding16), slack = s * (0x1p-21f * per_error);
+    const bool far_a = __builtin_fmaf(s - ta, per_error, -slack) > err;
+    const bool far_b = __builtin_fmaf(tb - s, per_error, -slack) > err_b;
+    k = ka;
+    const bool take_b = err_b < err;             // the smaller factor keeps a tie
+    err = take_b ? err_b : err;
+    nib[0] = take_b ? nib_b[0] : nib[0];
+    nib[1] = take_b ? nib_b[1] : nib[1];
+    k = take_b ? ka + 1 : ka;
+    if (__builtin_amdgcn_ballot_w64(!(far_a && far_b)) != 0ull) {
+        int lo = ka, hi = ka + 1;
+        bool down = !far_a && lo > 0, up = !far_b && hi < grid.n - 1;
         while (__builtin_amdgcn_ballot_w64(down || up) != 0ull) {
             if (down || up) {
-                const int k = down ? --ka : ++kb;
-                const float t = alpha * (delta_star * s_beta[k]);
-                const float e = try_pair(w, t, k, code, s, false, best);
-                if (down) down = ka > 0 && !(t <= s && far_side_excluded<16>(s, t, e));
-                else up = kb < n_beta - 1 && !(t >= s && far_side_excluded<16>(s, t, e));
+                const int kk = down ? --lo : ++hi;
+                const float t = alpha * (delta_star * grid.table[kk]);
+                const float e = factor_error(w, t, s, nib_b);
+                const bool far = __builtin_fmaf(down ? s - t : t - s, per_error, -slack) > e;
+                if (e < err || (e == err && kk < k)) { err = e; k = kk; nib[0] = nib_b[0]; nib[1] = nib_b[1]; }
+                if (down) down = !far && lo > 0;
+                else up = !far && hi < grid.n - 1;
             }
         }
     }
-    best_err = best.err;
-    best_code = best.code;
-    best_nib[0] = best.nib[0];
-    best_nib[1] = best.nib[1];
+    return err;
+}
+
+__device__ __forceinline__ void joint_search_nearest(const float w[16], float alpha, float delta_star, const FactorGrid &grid,
+                                                     bool bracket, int c0, int radius, float &best_err, int &best_code,
+                                                     uint32_t best_nib[2], float q[16])
+{
+    const float base_index = __builtin_amdgcn_rcpf(alpha * delta_star) * grid.index_per_beta;
+    int best_k;
+    best_code = c0;
+    best_err = best_factor(w, alpha, delta_star, base_index, grid, alpha * e4m3_value((uint32_t)c0), best_nib, best_k);
+    auto next = [&](int code) {
+        uint32_t nib[2];
+        int k;
+        const float err = best_factor(w, alpha, delta_star, base_index, grid, alpha * e4m3_value((uint32_t)code), nib, k);
+        bool win = err < best_err;
+        const bool tie = err == best_err && k < best_k;
+        if (__builtin_amdgcn_ballot_w64(tie) != 0ull) win = win || (tie && (nib[0] != best_nib[0] || nib[1] != best_nib[1]));
+        best_err = win ? err : best_err;
+        best_code = win ? code : best_code;
+        best_k = win ? k : best_k;
+        best_nib[0] = win ? nib[0] : best_nib[0];
+        best_nib[1] = win ? nib[1] : best_nib[1];
+    };
+    // a code clamped into [0x01, 0x7E] repeats an earlier candidate
+    if (bracket) {
+        next(min(c0 + 1, (int)kE4M3Max));
+    } else {
+#pragma unroll 1
+        for (int c = 1; c <= 2 * radius; ++c) {
+            const int o = (c + 1) >> 1;
+            next((c & 1) ? max(c0 - o, (int)kE4M3Min) : min(c0 + o, (int)kE4M3Max));
+        }
+    }
     fp4x8_values(best_nib[0], q);
     fp4x8_values(best_nib[1], q + 8);
 }
@@ -400,10 +428,12 @@ __device__ __forceinline__ void finish_iteration(const Batch &batch, const Task 
 // after this iteration (exact adjacent-pair tree, so that the early-stop test
 // is reproducible), the stop flag and the next global scale.
 // A tensor whose stop flag is set is skipped by every later launch.
+// Five waves per SIMD: six spill (737 against 740 us on the decoder layer, 175 against 169 on the fp32 matrix), eight
+// spill a tenth of the registers (929, 199).
 // NEAREST: the pairs that can win are found without walking the grid (joint_search_nearest); otherwise every pair
 // is evaluated (joint_search: SOAR_SEARCH_FULL, grids of fewer than four factors, tables that do not ascend).
 template <int DT, bool NEAREST>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_iter(const Batch batch)
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5 : 4, 8))) void k_iter(const Batch batch)
 {
     __shared__ float4 s_blocks[kStage * kWG];
     __shared__ double s_wave[3][4];
@@ -429,6 +459,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     const bool bracket = batch.dd_mode == SOAR_DD_BRACKET;
     const int radius = batch.radius;
     const bool dss_only = batch.arm == SOAR_METHOD_DSS_ONLY;    // rho then always carries -Delta^d: the search centre
+    const FactorGrid grid{s_beta, n_beta, batch.beta_lo, batch.index_per_beta};
+    const float inv_alpha = 1.0f / alpha;
+    // Scales and weights so far from the ends of the binary32 range that neither the reciprocals nor the squares of
+    // the nearest-factor search leave it (factors within 2^-20 .. 2^20: the host): alpha Delta* is about rho, stored
+    // scales are alpha times [2^-9, 448].  Everything else takes the plain loop.
+    const bool uniform_ok = alpha > 0x1p-35f && alpha < 0x1p50f && f_of(amax_bits) < 0x1p60f;
 
     StagedTree tree{s_blocks, s_wave, s_stack};
     const uint32_t tile0 = lwg * t.tiles_per_wg;
@@ -450,27 +486,34 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                     best_nib[1] = fp4x8(x + 8);
                 } else {
                     const float rho = t.rho[i];
-                    const float delta_star = (rho < 0.0f) ? -rho : rho / alpha;
-                    const int c0 = bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
-                    // the reciprocal shortcut holds while the biased exponent of the scale stays in [1, 252];
-                    // the scales of a block lie between those of the first and the last factor (to within
-                    // rounding of the grid), which are asked to keep one binade of distance from both ends
-                    const float s_first = alpha * (delta_star * s_beta[0]);
-                    const float s_final = alpha * (delta_star * s_beta[n_beta - 1]);
-                    const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
-                    if (__builtin_amdgcn_ballot_w64(!mid) != 0ull)
-                        joint_search<false>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err, best_code,
-                                            best_nib, q);
-                    else if constexpr (NEAREST)
-                        joint_search_nearest(w, alpha, delta_star, s_beta, n_beta, batch.beta_lo, batch.index_per_beta, bracket,
-                                             c0, radius, best_err, best_code, best_nib, q);
-                    else
-                        joint_search<true>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err, best_code,
-                                           best_nib, q);
-                    // the state the next iteration starts from
-                    block_sums(w, q, a, b);
-                    d = e4m3_value((uint32_t)best_code);
-                    t.rho[i] = (b == 0.0f || dss_only) ? -d : a / b;
+                    if (NEAREST && uniform_ok && __builtin_amdgcn_ballot_w64(rho >= 0.0f && !near_one(rho)) == 0ull) {
+                        const float delta_star = (rho < 0.0f) ? -rho : div_midrange(rho, alpha, inv_alpha);
+                        const int c0 = bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
+                        joint_search_nearest(w, alpha, delta_star, grid, bracket, c0, radius, best_err, best_code, best_nib, q);
+                        block_sums(w, q, a, b);
+                        d = e4m3_value((uint32_t)best_code);
+                        const float ratio = div_midrange(a, b, rcp_midrange(b));
+                        t.rho[i] = (b == 0.0f || dss_only) ? -d : ratio;
+                    } else {
+                        const float delta_star = (rho < 0.0f) ? -rho : rho / alpha;
+                        const int c0 = bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
+                        // the reciprocal shortcut holds while the biased exponent of the scale stays in [1, 252];
+                        // the scales of a block lie between those of the first and the last factor (to within
+                        // rounding of the grid), which are asked to keep one binade of distance from both ends
+                        const float s_first = alpha * (delta_star * s_beta[0]);
+                        const float s_final = alpha * (delta_star * s_beta[n_beta - 1]);
+                        const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
+                        if (NEAREST || __builtin_amdgcn_ballot_w64(!mid) != 0ull)
+                            joint_search<false, NEAREST ? 1 : 4>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err,
+                                                                 best_code, best_nib, q);
+                        else
+                            joint_search<true, 4>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err, best_code,
+                                                  best_nib, q);
+                        // the state the next iteration starts from
+                        block_sums(w, q, a, b);
+                        d = e4m3_value((uint32_t)best_code);
+                        t.rho[i] = (b == 0.0f || dss_only) ? -d : a / b;
+                    }
                 }
                 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
                 u32x2 packed = {best_nib[0], best_nib[1]};

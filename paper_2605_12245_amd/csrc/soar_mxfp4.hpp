@@ -164,69 +164,87 @@ __device__ __forceinline__ void mx_search(const float w[32], int e0, const float
 
 // mx_search without walking the factor grid: joint_search_nearest's argument, with the power of two X0 in the place
 // of alpha Delta* -- so which factors enclose a candidate scale is the same for every block of the launch
-// (the paper's grid and K = 1: six pairs of 303).  One decoder layer (1.93e8 bf16 weights): 3.70 -> 0.22 ms a call.
-struct MxBest {
-    float err;
-    int k, code;
-    uint32_t nib[4];
-};
-
-__device__ __forceinline__ float mx_try_pair(const float w[32], float t, int k, int code, float s, bool first, MxBest &best)
+// (the paper's grid and K = 1: seven pairs of 303).  One decoder layer (1.93e8 bf16 weights): 3.70 -> 0.21 ms a call.
+__device__ __forceinline__ float mx_factor_error(const float w[32], float t, float s, uint32_t nib[4])
 {
-    uint32_t nib[4] = {0u, 0u, 0u, 0u};
     float q[32];
+    nib[0] = nib[1] = nib[2] = nib[3] = 0u;
     mx_assign<true>(w, t, nib, q);
-    const float e = mx_block_error(w, q, s);
-    bool win = first || e < best.err;
-    const bool tie = !first && e == best.err && k < best.k;
-    if (__builtin_amdgcn_ballot_w64(tie) != 0ull)
-        win = win || (tie && (nib[0] != best.nib[0] || nib[1] != best.nib[1] || nib[2] != best.nib[2] || nib[3] != best.nib[3]));
-    best.err = win ? e : best.err;
-    best.k = win ? k : best.k;
-    best.code = win ? code : best.code;
-#pragma unroll
-    for (int h = 0; h < 4; ++h) best.nib[h] = win ? nib[h] : best.nib[h];
-    return e;
+    return mx_block_error(w, q, s);
 }
 
-__device__ __forceinline__ void mx_search_nearest(const float w[32], int e0, const float *s_beta, int n_beta, float beta_lo,
-                                                  float index_per_beta, int radius, float &best_err, int &best_code,
-                                                  uint32_t best_nib[4])
+// best_factor for one stored scale s = ratio * x0 (ratio uniform over the wave)
+__device__ __forceinline__ float mx_best_factor(const float w[32], float x0, float ratio, const FactorGrid &grid, float s,
+                                                uint32_t nib[4], int &k)
+{
+    const int last = grid.n - 1;
+    const float at = (ratio - grid.lo) * grid.index_per_beta;
+    // one factor where s lies beyond an end of the grid, else the two around it
+    int lo = __builtin_amdgcn_readfirstlane((int)__builtin_amdgcn_fmed3f(at, 0.0f, (float)last));
+    int hi = at < 0.0f ? lo : min(lo + 1, last);
+    const float per_error = s * (1.0f / kFarSideRounding32), slack = s * (0x1p-21f * per_error);
+    auto excluded = [&](float distance, float e) { return __builtin_fmaf(distance, per_error, -slack) > e; };
+    const float ta = x0 * grid.table[lo];
+    float err = mx_factor_error(w, ta, s, nib);
+    k = lo;
+    bool down = lo > 0 && !excluded(s - ta, err), up;
+    uint32_t nib_b[4];
+    if (hi != lo) {
+        const float tb = x0 * grid.table[hi];
+        const float err_b = mx_factor_error(w, tb, s, nib_b);
+        up = hi < last && !excluded(tb - s, err_b);
+        const bool take_b = err_b < err;             // the smaller factor keeps a tie
+        err = take_b ? err_b : err;
+        k = take_b ? hi : lo;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) nib[h] = take_b ? nib_b[h] : nib[h];
+    } else {
+        up = hi < last && !excluded(ta - s, err);
+    }
+    while (__builtin_amdgcn_ballot_w64(down || up) != 0ull) {
+        if (down || up) {
+            const int kk = down ? --lo : ++hi;
+            const float t = x0 * grid.table[kk];
+            const float e = mx_factor_error(w, t, s, nib_b);
+            const bool far = excluded(down ? s - t : t - s, e);
+            if (e < err || (e == err && kk < k)) {
+                err = e;
+                k = kk;
+#pragma unroll
+                for (int h = 0; h < 4; ++h) nib[h] = nib_b[h];
+            }
+            if (down) down = !far && lo > 0;
+            else up = !far && hi < last;
+        }
+    }
+    return err;
+}
+
+__device__ __forceinline__ void mx_search_nearest(const float w[32], int e0, const FactorGrid &grid, int radius, float &best_err,
+                                                  int &best_code, uint32_t best_nib[4])
 {
     const float x0 = e8m0_value(e0);
-    MxBest best;
-    best.err = 0.0f; best.k = 0; best.code = e0;
-    best.nib[0] = best.nib[1] = best.nib[2] = best.nib[3] = 0u;
+    int best_k = 0;
+    best_code = e0;
+    best_err = 0.0f;
 #pragma unroll 1
     for (int c = 0; c <= 2 * radius; ++c) {
         const int code = mx_candidate(e0, c);
-        const float s = e8m0_value(code);
         const int o = (c + 1) >> 1;
-        // the ratio s / X0 of an unclamped candidate; any error of this estimate is met by the walk
         const float ratio = f_of((uint32_t)(127 + ((c & 1) ? -min(o, 126) : min(o, 127))) << 23);
-        const float at = (ratio - beta_lo) * index_per_beta;
-        const int km = (int)__builtin_rintf(fminf(fmaxf(at, 0.0f), (float)(n_beta - 1)));
-        const int split = km + (s_beta[km] <= ratio ? 1 : 0);
-        int ka = max(split - 1, 0), kb = min(split, n_beta - 1);
-        const float ta = x0 * s_beta[ka], tb = x0 * s_beta[kb];
-        const float ea = mx_try_pair(w, ta, ka, code, s, c == 0, best);
-        const float eb = kb != ka ? mx_try_pair(w, tb, kb, code, s, false, best) : ea;
-        bool down = ka > 0 && !(ta <= s && far_side_excluded<32>(s, ta, ea));
-        bool up = kb < n_beta - 1 && !(tb >= s && far_side_excluded<32>(s, tb, eb));
-        while (__builtin_amdgcn_ballot_w64(down || up) != 0ull) {
-            if (down || up) {
-                const int k = down ? --ka : ++kb;
-                const float t = x0 * s_beta[k];
-                const float e = mx_try_pair(w, t, k, code, s, false, best);
-                if (down) down = ka > 0 && !(t <= s && far_side_excluded<32>(s, t, e));
-                else up = kb < n_beta - 1 && !(t >= s && far_side_excluded<32>(s, t, e));
-            }
-        }
-    }
-    best_err = best.err;
-    best_code = best.code;
+        uint32_t nib[4];
+        int k;
+        const float err = mx_best_factor(w, x0, ratio, grid, e8m0_value(code), nib, k);
+        bool win = c == 0 || err < best_err;
+        const bool tie = !win && err == best_err && k < best_k;
+        if (__builtin_amdgcn_ballot_w64(tie) != 0ull)
+            win = win || (tie && (nib[0] != best_nib[0] || nib[1] != best_nib[1] || nib[2] != best_nib[2] || nib[3] != best_nib[3]));
+        best_err = win ? err : best_err;
+        best_code = win ? code : best_code;
+        best_k = win ? k : best_k;
 #pragma unroll
-    for (int h = 0; h < 4; ++h) best_nib[h] = best.nib[h];
+        for (int h = 0; h < 4; ++h) best_nib[h] = win ? nib[h] : best_nib[h];
+    }
 }
 
 template <int DT, bool DSS>
@@ -251,6 +269,7 @@ __global__ __launch_bounds__(kWG) void k_mx(const MxBatch batch)
     for (int k = (int)tid; k < n_beta; k += kWG) s_beta[k] = beta_factor(k, n_beta, t.beta_lo, t.beta_hi);
     __syncthreads();
 
+    const FactorGrid grid{s_beta, n_beta, t.beta_lo, t.index_per_beta};
     TileTree<1> tree{s_wave, s_stack};
     bool nonfinite = false;
     const uint32_t tile0 = lwg * t.tiles_per_wg;
@@ -293,13 +312,18 @@ __global__ __launch_bounds__(kWG) void k_mx(const MxBatch batch)
                 mx_assign<false>(w, x0, nib, q);
                 err = mx_block_error(w, q, x0);
             } else {
-                // the reciprocal shortcut needs the scales X0 beta_k to stay within biased exponents [1, 252]
-                const float s_first = e8m0_value(e0) * s_beta[0], s_final = e8m0_value(e0) * s_beta[n_beta - 1];
-                const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
-                const bool fast = __builtin_amdgcn_ballot_w64(!mid) == 0ull;
-                if (!fast) mx_search<false>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
-                else if (t.nearest) mx_search_nearest(w, e0, s_beta, n_beta, t.beta_lo, t.index_per_beta, t.radius, err, code, nib);
-                else mx_search<true>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
+                // far enough from the ends of the binary32 range for the nearest-factor search (factors within
+                // 2^-20 .. 2^20: the host); elsewhere the plain loop, whose reciprocal shortcut needs the scales
+                // X0 beta_k to stay within biased exponents [1, 252]
+                const bool near = (uint32_t)(e0 - 67) < 120u;
+                if (t.nearest && __builtin_amdgcn_ballot_w64(!near) == 0ull) {
+                    mx_search_nearest(w, e0, grid, t.radius, err, code, nib);
+                } else {
+                    const float s_first = e8m0_value(e0) * s_beta[0], s_final = e8m0_value(e0) * s_beta[n_beta - 1];
+                    const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
+                    if (__builtin_amdgcn_ballot_w64(!mid) == 0ull) mx_search<true>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
+                    else mx_search<false>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
+                }
             }
             term[0] = (double)err;
             u32x4 packed = {nib[0], nib[1], nib[2], nib[3]};
