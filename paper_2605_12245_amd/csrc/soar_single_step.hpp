@@ -533,23 +533,26 @@ __device__ __forceinline__ bool resident_gather(const ResidentGrid &r, const uin
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t want = (r.tok << PBITS) >> PBITS, gone_field = (~r.tok << PBITS) >> PBITS;
     for (uint64_t round = 0;; ++round) {
-        bool pending = false, gone = false;
+        // all loads of a round first, whatever the registers: one trip to memory a round, not one per word
+        uint64_t v[K][NW];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const uint32_t e = lane + 64u * (uint32_t)k;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) pay[k][w] = 0ull;
-            if (e < count) {
-#pragma unroll
-                for (int w = 0; w < NW; ++w) {
-                    const uint64_t v = __hip_atomic_load(src + w * stride + first + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const uint64_t field = v >> PBITS;
-                    gone = gone || field == gone_field;
-                    pending = pending || field != want;
-                    pay[k][w] = v & ((1ull << PBITS) - 1ull);
-                }
-            }
+            for (int w = 0; w < NW; ++w)
+                v[k][w] = e < count ? __hip_atomic_load(src + w * stride + first + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : want << PBITS;
         }
+        __builtin_amdgcn_sched_barrier(0);
+        bool pending = false, gone = false;
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const uint64_t field = v[k][w] >> PBITS;
+                gone = gone | (field == gone_field);
+                pending = pending | (field != want);
+                pay[k][w] = v[k][w] & ((1ull << PBITS) - 1ull);
+            }
         if (__builtin_amdgcn_ballot_w64(gone) != 0ull) return false;
         if (__builtin_amdgcn_ballot_w64(pending) == 0ull) return true;
         if (resident_time_is_up(r, round)) return false;
