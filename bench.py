@@ -300,6 +300,7 @@ def run(args):
     if paper and not args.no_kernel_timing:
         n_prof = min(args.steps, 2)
         p_one = iterated_params(B, args, 1)
+        p_one.resident = B.SOAR_RESIDENT_NEVER      # a single tensor too: the kernels of the path in launches of their own
         B.soar_kernel_timing_enable(True)
         for _ in range(n_prof):
             B.quantize_batch(descs, p_one, ws)
@@ -328,6 +329,7 @@ def run(args):
             # the same kernel where every launch has work: three iterations, no early stop
             B.soar_kernel_timing_enable(True)          # drops the events of the pass above
             p_work = B.soar_arm_params(B.SOAR_METHOD_CJSO_ONLY, iters=3, early_stop_rel=0.0, tiles_per_wg=args.tpw, streams=1)
+            p_work.resident = B.SOAR_RESIDENT_NEVER
             for _ in range(n_prof):
                 B.quantize_batch(descs, p_work, ws)
             torch.cuda.synchronize()

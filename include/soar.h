@@ -132,15 +132,16 @@ typedef struct {
     int32_t  resident;       /* soar_resident_mode: may one tensor handed over alone (single-
                                 step settings, tiles_per_wg 0, at most 4096 blocks per compute
                                 unit: 2^20 blocks = 32 MiB of bf16 on an MI355X) take ONE
-                                launch that keeps the tensor in registers and crosses its two
-                                tensor-wide dependencies (Eq. 1 maximum, Eq. 5 sums) inside
-                                the kernel?  Same bytes as the three-pass path, the weights
-                                are read once.  It needs every workgroup of its grid (at most
+                                launch that keeps the tensor in registers (iterated path: in the
+                                caches) and crosses its tensor-wide dependencies (Eq. 1 maximum,
+                                Eq. 5 sums) inside the kernel?  Same bytes as the path of several
+                                launches; on the single-step path the weights are read once.  It needs every workgroup of its grid (at most
                                 one per compute unit) on the GPU at the same time and waits
                                 for that at most resident_wait_us.  A call that arrives on
                                 another stream while an earlier such kernel may still run
-                                takes the three-pass path instead (two of them started at
-                                once could each hold part of the GPU and wait for the rest) */
+                                takes the other path instead (two of them started at once could
+                                each hold part of the GPU and wait for the rest), and so does an
+                                iterated call that is being captured into a graph             */
     int32_t  resident_wait_us; /* 0 = library default (2 s); > 0: the bound, in microseconds,
                                 after which a workgroup of that kernel stops waiting, sets
                                 SOAR_STATUS_GAVE_UP and leaves (every workgroup then does)   */

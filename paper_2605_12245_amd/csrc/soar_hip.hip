@@ -41,6 +41,7 @@
 #include "soar_device.hpp"
 #include "soar_single_step.hpp"
 #include "soar_iterated.hpp"
+#include "soar_resident_iterated.hpp"
 #include "soar_mxfp4.hpp"
 #include "soar_stored_form.hpp"
 
@@ -175,6 +176,45 @@ void launch_resident(const ResidentPlan &plan, const Task &t, const ResidentArgs
     else if (plan.R == 1) hipLaunchKernelGGL((k_resident<DT, METHOD, 1024, 1>), grid, dim3(1024), 0, st, t, a);
     else if (plan.R == 2) hipLaunchKernelGGL((k_resident<DT, METHOD, 1024, 2>), grid, dim3(1024), 0, st, t, a);
     else hipLaunchKernelGGL((k_resident<DT, METHOD, 1024, 4>), grid, dim3(1024), 0, st, t, a);
+}
+
+// The same for the iterated path (k_iter_resident).  A power of two tiles per workgroup can leave compute units
+// without work, where a launch per iteration spreads the tiles evenly.  Up to four tiles what the launches cost
+// outweighs that (paper settings, 4096 columns of bf16, a launch per iteration / one launch: 1030 rows 93 / 56 us,
+// 2060: 98 / 84, 4096: 122 / 90); with eight the lines cross at 5/8 of the units (4110: 133 / 145, 6200: 167 / 149,
+// 8192: 185 / 153), with sixteen at 7/8 (14000: 270 / 273, 16384: 317 / 279).  A search over more than three
+// candidates weighs more than the launches: it has to fill the units.
+// A launch being captured keeps to the launch-per-iteration path: a graph replays it at little cost, and two replays
+// that meet on the GPU need no bounded wait.
+bool iter_resident_plan(int64_t nblk, int cu, int ncand, ResidentPlan &plan)
+{
+    const int64_t wgs = cu < kResMaxWG ? cu : kResMaxWG;
+    if (wgs < 1) return false;
+    plan.L = nblk <= 256 * wgs ? 256 : 1024;
+    plan.R = 1;
+    while (plan.R <= kIterResMaxTiles && nblk > (int64_t)plan.L * plan.R * wgs) plan.R <<= 1;
+    if (plan.R > kIterResMaxTiles) return false;
+    plan.G = (uint32_t)((nblk + (int64_t)plan.L * plan.R - 1) / ((int64_t)plan.L * plan.R));
+    if (plan.L == 256) return true;
+    const int64_t eighths = ncand > 3 || plan.R == 16 ? 7 : plan.R == 8 ? 5 : 0;
+    return 8 * (int64_t)plan.G >= eighths * wgs;
+}
+
+bool being_captured(hipStream_t st)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+}
+
+template <int DT>
+void launch_iter_resident(const ResidentPlan &plan, const Task &t, const IterResidentArgs &a, hipStream_t st)
+{
+    const dim3 grid(plan.G);
+    const bool closed = a.arm == SOAR_METHOD_CJSO_ONLY;
+    if (plan.L == 256 && closed) hipLaunchKernelGGL((k_iter_resident<DT, 256, true>), grid, dim3(256), 0, st, t, a);
+    else if (plan.L == 256) hipLaunchKernelGGL((k_iter_resident<DT, 256, false>), grid, dim3(256), 0, st, t, a);
+    else if (closed) hipLaunchKernelGGL((k_iter_resident<DT, 1024, true>), grid, dim3(1024), 0, st, t, a);
+    else hipLaunchKernelGGL((k_iter_resident<DT, 1024, false>), grid, dim3(1024), 0, st, t, a);
 }
 
 thread_local bool t_no_event_timing = false;      // set while an entry point that must not create events runs
@@ -505,6 +545,33 @@ soar_status launch_group_iter(Batch &b, uint32_t wg_absmax, uint32_t total_wg, i
     return SOAR_OK;
 }
 
+// the Task and the arguments of a one-launch kernel; only the slot's control words and crossing words are used
+Task single_task(const soar_tensor_desc &d, void *d_workspace)
+{
+    Task t = make_task(d.d_w, d.rows, d.cols, d.ld_elems, WantedShapes{0u, 0u, 0u}, WantedShapes{1u, 1u, 1u});
+    t.codes = d.d_codes;
+    t.scales = d.d_scales;
+    t.gscale = d.d_global_scale;
+    t.sse = d.d_sse;
+    t.status = d.d_status;
+    char *slot = static_cast<char *>(d_workspace);
+    t.ctrl = reinterpret_cast<Ctrl *>(slot);
+    t.part = reinterpret_cast<double *>(slot + kZeroedBytes);
+    return t;
+}
+
+ResidentArgs resident_args(const soar_params *params)
+{
+    ResidentArgs a;
+    a.radius = params->dss_radius;
+    a.full_search = params->search_mode == SOAR_SEARCH_FULL ? 1 : 0;
+    a.search_stats = search_stats_address();
+    a.nonce = next_nonce();
+    const uint64_t us = params->resident_wait_us > 0 ? (uint64_t)params->resident_wait_us : 2000000ull;
+    a.wait_ticks = us * (uint64_t)device_facts().wall_clock_khz / 1000ull;
+    return a;
+}
+
 soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_params *params, void *d_workspace,
                       size_t workspace_bytes, hipStream_t st)
 {
@@ -536,22 +603,8 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         resident_plan(descs[0].rows * (descs[0].cols / 16), device_facts().compute_units, plan) &&
         (plan.G == 1 || resident_may_start(st))) {
         const soar_tensor_desc &d = descs[0];
-        Task t = make_task(d.d_w, d.rows, d.cols, d.ld_elems, WantedShapes{0u, 0u, 0u}, wanted_shapes(false, params->method, false, false, 0));
-        t.codes = d.d_codes;
-        t.scales = d.d_scales;
-        t.gscale = d.d_global_scale;
-        t.sse = d.d_sse;
-        t.status = d.d_status;
-        char *slot = static_cast<char *>(d_workspace);
-        t.ctrl = reinterpret_cast<Ctrl *>(slot);
-        t.part = reinterpret_cast<double *>(slot + kZeroedBytes);
-        ResidentArgs a;
-        a.radius = params->dss_radius;
-        a.full_search = params->search_mode == SOAR_SEARCH_FULL ? 1 : 0;
-        a.search_stats = search_stats_address();
-        a.nonce = next_nonce();
-        const uint64_t us = params->resident_wait_us > 0 ? (uint64_t)params->resident_wait_us : 2000000ull;
-        a.wait_ticks = us * (uint64_t)device_facts().wall_clock_khz / 1000ull;
+        const Task t = single_task(d, d_workspace);
+        const ResidentArgs a = resident_args(params);
         const bool rtn = params->method == SOAR_METHOD_RTN;
         ScopedTimer tm(SOAR_KERNEL_RESIDENT, st);
         if (d.dtype == SOAR_BF16) {
@@ -565,12 +618,44 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         return SOAR_OK;
     }
 
+    const bool nearest = iterated && params->search_mode == SOAR_SEARCH_AUTO &&
+                         nearest_search(params->n_beta, params->beta_lo, params->beta_hi);
+    const float index_per_beta = nearest ? (float)(params->n_beta - 1) / (params->beta_hi - params->beta_lo) : 0.0f;
+
+    // the same for the iterated path, where the search is the nearest-factor one or there is none (see k_iter_resident)
+    if (n == 1 && iterated && params->tiles_per_wg == 0 && params->tiles_per_wg_absmax == 0 && params->tiles_per_wg_search == 0 &&
+        params->resident == SOAR_RESIDENT_AUTO &&
+        (params->method == SOAR_METHOD_CJSO_ONLY || (nearest && params->n_beta <= kIterResMaxBeta)) &&
+        iter_resident_plan(descs[0].rows * (descs[0].cols / 16), device_facts().compute_units,
+                           params->dd_mode == SOAR_DD_BRACKET ? 2 : 2 * params->dss_radius + 1, plan) && !being_captured(st) &&
+        (plan.G == 1 || resident_may_start(st))) {
+        const soar_tensor_desc &d = descs[0];
+        Task t = single_task(d, d_workspace);
+        t.iters_run = d.d_iters_run;
+        t.trace = d.d_sse_trace;
+        t.rho = reinterpret_cast<float *>(static_cast<char *>(d_workspace) + (size_t)kGroupMax * kSlotBytes);
+        IterResidentArgs a;
+        a.r = resident_args(params);
+        a.iters = params->iters;
+        a.n_beta = params->n_beta;
+        a.bracket = params->dd_mode == SOAR_DD_BRACKET ? 1 : 0;
+        a.arm = params->method;
+        a.beta_lo = params->beta_lo;
+        a.beta_hi = params->beta_hi;
+        a.index_per_beta = index_per_beta;
+        a.early_stop_rel = params->early_stop_rel;
+        a.tiles = (uint32_t)plan.R;
+        ScopedTimer tm(SOAR_KERNEL_RESIDENT, st);
+        if (d.dtype == SOAR_BF16) launch_iter_resident<SOAR_BF16>(plan, t, a, st);
+        else launch_iter_resident<SOAR_FP32>(plan, t, a, st);
+        SOAR_LAUNCH_CHECK();
+        return SOAR_OK;
+    }
+
     int32_t n_groups = 0;
     const int64_t cap = group_byte_cap(descs, params);
     const size_t lane_bytes = lane_workspace_bytes(max_group_per_block_bytes(n, descs, cap, &n_groups));
     const int lanes = (n_groups > 1 && params->streams != 1) ? kLanes : 1;
-    const bool nearest = iterated && params->search_mode == SOAR_SEARCH_AUTO &&
-                         nearest_search(params->n_beta, params->beta_lo, params->beta_hi);
     char *base = static_cast<char *>(d_workspace);
 
     hipStream_t lane_stream[kLanes] = {st, st};
@@ -604,7 +689,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         b.dd_mode = params->dd_mode;
         b.beta_lo = params->beta_lo;
         b.beta_hi = params->beta_hi;
-        b.index_per_beta = nearest ? (float)(params->n_beta - 1) / (params->beta_hi - params->beta_lo) : 0.0f;
+        b.index_per_beta = index_per_beta;
         b.early_stop_rel = params->early_stop_rel;
         b.arm = params->method;
         // The searching iterated kernels are arithmetic-bound (see search_tiles_per_wg); the closed-form arm has no

@@ -44,14 +44,16 @@ struct TileTree {
 // tree, the four waves and the binary-counter stack finish the group -- the adjacent-pair tree again
 // (k_stats does the same for its two sums).  Per group of T tiles: stage() once per tile by every lane,
 // then close() by every lane; after the last group lane 0 holds the sums (N, M, error) in wg[].
+template <int LANES = kWG>
 struct StagedTree {
-    float4 *s_blocks;        // [kStage * kWG]: a, b, d, err; zeros for a block that does not exist
-    double (*s_wave)[4];     // [3][4]
-    double (*s_stack)[32];   // [3][32]
+    static constexpr int kWaves = LANES / 64;
+    float4 *s_blocks;            // [kStage * LANES]: a, b, d, err; zeros for a block that does not exist
+    double (*s_wave)[kWaves];    // [3][kWaves]
+    double (*s_stack)[32];       // [3][32]
     double wg[3] = {};
     __device__ __forceinline__ void stage(uint32_t kk, float a, float b, float d, float err)
     {
-        s_blocks[kk * kWG + threadIdx.x] = make_float4(a, b, d, err);
+        s_blocks[kk * LANES + threadIdx.x] = make_float4(a, b, d, err);
     }
     static __device__ __forceinline__ void terms(const float4 &x, double v[3])
     {
@@ -85,14 +87,20 @@ struct StagedTree {
 #pragma unroll
             for (int n = 0; n < 3; ++n) s_wave[n][threadIdx.x >> 6] = v[n];
         __syncthreads();
-        if (threadIdx.x == 0) {
+        if (threadIdx.x < (kWaves == 4 ? 1u : 64u)) {
 #pragma unroll
             for (int n = 0; n < 3; ++n) {
-                double y = (s_wave[n][0] + s_wave[n][1]) + (s_wave[n][2] + s_wave[n][3]);
-                uint32_t lvl = 0;
-                while ((k >> lvl) & 1u) { y = s_stack[n][lvl] + y; ++lvl; }
-                s_stack[n][lvl] = y;
-                wg[n] = y;
+                double y;
+                if constexpr (kWaves == 4)
+                    y = (s_wave[n][0] + s_wave[n][1]) + (s_wave[n][2] + s_wave[n][3]);
+                else
+                    y = wave_pair_tree(threadIdx.x < (uint32_t)kWaves ? s_wave[n][threadIdx.x] : 0.0);
+                if (threadIdx.x == 0) {
+                    uint32_t lvl = 0;
+                    while ((k >> lvl) & 1u) { y = s_stack[n][lvl] + y; ++lvl; }
+                    s_stack[n][lvl] = y;
+                    wg[n] = y;
+                }
             }
         }
     }
@@ -321,6 +329,19 @@ __device__ __forceinline__ void joint_search_nearest(const float w[16], float al
     fp4x8_values(best_nib[1], q + 8);
 }
 
+// the Eq. 1-2 state of a block: a, b, the scale's value, the error and the ratio for Eq. 6 (keep_scale: -Delta0, the
+// search centre of the arm that leaves the closed-form stage out)
+__device__ __forceinline__ void init_block(const float w[16], float alpha0, float alpha0_m, bool keep_scale, float &a, float &b,
+                                           float &delta0, float &err, float &rho)
+{
+    float q[16];
+    uint32_t nib[2], c0;
+    block_init(w, alpha0, alpha0_m, c0, delta0, nib, q);
+    block_sums(w, q, a, b);
+    err = block_error(w, q, alpha0 * delta0);
+    rho = (b == 0.0f || keep_scale) ? -delta0 : a / b;
+}
+
 // The Eq. 1-2 state of Algorithm 1 (Delta^q = Delta^d = Delta0) for the iterated
 // path: per block the ratio a/b for Eq. 6 and the error of that state; per tensor
 // the sums of Eq. 5 (-> the global scale of iteration 0) and the error before any
@@ -343,7 +364,7 @@ __global__ __launch_bounds__(kWG) void k_iter_init(const Batch batch)
     const float alpha0 = f_of(amax_bits) / 2688.0f;
     const float alpha0_m = alpha0 * 6.0f;
 
-    StagedTree tree{s_blocks, s_wave, s_stack};
+    StagedTree<> tree{s_blocks, s_wave, s_stack};
     const uint32_t tile0 = lwg * t.tiles_per_wg;
     const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
     for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
@@ -353,13 +374,9 @@ __global__ __launch_bounds__(kWG) void k_iter_init(const Batch batch)
             if (i < t.nblk) {
                 float rho = 0.0f;
                 if (!degenerate) {
-                    float w[16], q[16];
-                    uint32_t nib[2], c0;
+                    float w[16];
                     load_block<DT>(t.w, block_offset(t, i), w);
-                    block_init(w, alpha0, alpha0_m, c0, delta0, nib, q);
-                    block_sums(w, q, a, b);
-                    err = block_error(w, q, alpha0 * delta0);
-                    rho = (b == 0.0f || batch.arm == SOAR_METHOD_DSS_ONLY) ? -delta0 : a / b;
+                    init_block(w, alpha0, alpha0_m, batch.arm == SOAR_METHOD_DSS_ONLY, a, b, delta0, err, rho);
                 }
                 t.rho[i] = rho;
             }
@@ -390,6 +407,96 @@ __global__ __launch_bounds__(kWG) void k_iter_init(const Batch batch)
         if (!degenerate && t.trace) t.trace[0] = E;
     }
     reset_counters(counters, &t.ctrl->top[1]);
+}
+
+// What an iteration leaves of one block: codes and stored scale, their error, their sums a and b with the scale's
+// value d (the Eq. 5 terms of the next iteration), and the ratio a/b (or -d) for the next Eq. 6.
+struct BlockState {
+    uint32_t nib[2], code;
+    float a, b, d, err, rho;
+};
+
+// what the joint search of one tensor needs beside the block
+struct JointSearch {
+    FactorGrid grid;
+    float alpha, inv_alpha;
+    int radius;
+    bool bracket, dss_only;      // dss_only: rho always carries -Delta^d, the search centre
+    // Scales and weights so far from the ends of the binary32 range that neither the reciprocals nor the squares of
+    // the nearest-factor search leave it (factors within 2^-20 .. 2^20: the host): alpha Delta* is about rho, stored
+    // scales are alpha times [2^-9, 448].  Everything else takes the plain loop.
+    bool in_range;
+    __device__ __forceinline__ void set_alpha(float alpha_, uint32_t amax_bits)
+    {
+        alpha = alpha_;
+        inv_alpha = 1.0f / alpha_;
+        in_range = alpha_ > 0x1p-35f && alpha_ < 0x1p50f && f_of(amax_bits) < 0x1p60f;
+    }
+};
+
+template <bool NEAREST>
+__device__ __forceinline__ void iterate_block(const float w[16], float rho, const JointSearch &js, BlockState &x)
+{
+    float q[16];
+    int code;
+    if (NEAREST && js.in_range && __builtin_amdgcn_ballot_w64(rho >= 0.0f && !near_one(rho)) == 0ull) {
+        const float delta_star = (rho < 0.0f) ? -rho : div_midrange(rho, js.alpha, js.inv_alpha);
+        const int c0 = js.bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
+        joint_search_nearest(w, js.alpha, delta_star, js.grid, js.bracket, c0, js.radius, x.err, code, x.nib, q);
+        block_sums(w, q, x.a, x.b);
+        x.d = e4m3_value((uint32_t)code);
+        const float ratio = div_midrange(x.a, x.b, rcp_midrange(x.b));
+        x.rho = (x.b == 0.0f || js.dss_only) ? -x.d : ratio;
+    } else {
+        const float delta_star = (rho < 0.0f) ? -rho : rho / js.alpha;
+        const int c0 = js.bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
+        // the reciprocal shortcut holds while the biased exponent of the scale stays in [1, 252];
+        // the scales of a block lie between those of the first and the last factor (to within
+        // rounding of the grid), which are asked to keep one binade of distance from both ends
+        const float s_first = js.alpha * (delta_star * js.grid.table[0]);
+        const float s_final = js.alpha * (delta_star * js.grid.table[js.grid.n - 1]);
+        const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
+        if (NEAREST || __builtin_amdgcn_ballot_w64(!mid) != 0ull)
+            joint_search<false, NEAREST ? 1 : 4>(w, js.alpha, delta_star, js.grid.table, js.grid.n, js.bracket, c0, js.radius, x.err,
+                                                 code, x.nib, q);
+        else
+            joint_search<true, 4>(w, js.alpha, delta_star, js.grid.table, js.grid.n, js.bracket, c0, js.radius, x.err, code, x.nib, q);
+        block_sums(w, q, x.a, x.b);
+        x.d = e4m3_value((uint32_t)code);
+        x.rho = (x.b == 0.0f || js.dss_only) ? -x.d : x.a / x.b;
+    }
+    x.code = (uint32_t)code;
+}
+
+// the same for the closed-form arm: the projected scale assigns the codes and is stored
+__device__ __forceinline__ void closed_form_block(const float w[16], float rho, float alpha, BlockState &x)
+{
+    float q[16];
+    const float delta_star = (rho < 0.0f) ? -rho : rho / alpha;          // Eq. 6
+    x.code = e4m3_project(delta_star);
+    x.d = e4m3_value(x.code);
+    const float sd = alpha * x.d;
+    assign_codes(w, sd, x.nib, q);
+    block_sums(w, q, x.a, x.b);
+    x.err = block_error(w, q, sd);
+    x.rho = (x.b == 0.0f) ? -x.d : x.a / x.b;
+}
+
+// a block of an all-zero tensor: smallest scale, zero codes carrying the sign
+__device__ __forceinline__ void zero_block(const float w[16], BlockState &x)
+{
+    x.nib[0] = fp4x8(w);
+    x.nib[1] = fp4x8(w + 8);
+    x.code = kE4M3Min;
+    x.a = x.b = x.d = x.err = x.rho = 0.0f;
+}
+
+__device__ __forceinline__ void store_block(const Task &t, uint32_t i, const BlockState &x)
+{
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 packed = {x.nib[0], x.nib[1]};
+    __builtin_nontemporal_store(packed, reinterpret_cast<u32x2 *>(t.codes) + i);
+    __builtin_nontemporal_store((uint8_t)x.code, t.scales + i);
 }
 
 // What the last workgroup of a tensor does after an iteration (one lane): the outputs that describe the
@@ -456,71 +563,31 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5
     __syncthreads();
 
     const float alpha = t.ctrl->alpha1;
-    const bool bracket = batch.dd_mode == SOAR_DD_BRACKET;
-    const int radius = batch.radius;
-    const bool dss_only = batch.arm == SOAR_METHOD_DSS_ONLY;    // rho then always carries -Delta^d: the search centre
-    const FactorGrid grid{s_beta, n_beta, batch.beta_lo, batch.index_per_beta};
-    const float inv_alpha = 1.0f / alpha;
-    // Scales and weights so far from the ends of the binary32 range that neither the reciprocals nor the squares of
-    // the nearest-factor search leave it (factors within 2^-20 .. 2^20: the host): alpha Delta* is about rho, stored
-    // scales are alpha times [2^-9, 448].  Everything else takes the plain loop.
-    const bool uniform_ok = alpha > 0x1p-35f && alpha < 0x1p50f && f_of(amax_bits) < 0x1p60f;
+    const bool dss_only = batch.arm == SOAR_METHOD_DSS_ONLY;
+    JointSearch js{{s_beta, n_beta, batch.beta_lo, batch.index_per_beta}, 0.0f, 0.0f, batch.radius,
+                   batch.dd_mode == SOAR_DD_BRACKET, dss_only, false};
+    js.set_alpha(alpha, amax_bits);
 
-    StagedTree tree{s_blocks, s_wave, s_stack};
+    StagedTree<> tree{s_blocks, s_wave, s_stack};
     const uint32_t tile0 = lwg * t.tiles_per_wg;
     const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
     for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
         for (uint32_t kk = 0; kk < T; ++kk) {
             const uint32_t i = (tile0 + kg + kk) * kWG + tid;
-            float a = 0.0f, b = 0.0f, d = 0.0f, best_err = 0.0f;
+            BlockState x;
+            x.a = x.b = x.d = x.err = 0.0f;
             if (i < t.nblk && amax_bits < 0x7F800000u) {
-                float w[16], q[16];
-                uint32_t best_nib[2] = {0u, 0u};
-                int best_code = (int)kE4M3Min;
+                float w[16];
                 load_block<DT>(t.w, block_offset(t, i), w);
                 if (allzero) {
-                    float x[16];
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) x[j] = w[j];
-                    best_nib[0] = fp4x8(x);
-                    best_nib[1] = fp4x8(x + 8);
+                    zero_block(w, x);
                 } else {
-                    const float rho = t.rho[i];
-                    if (NEAREST && uniform_ok && __builtin_amdgcn_ballot_w64(rho >= 0.0f && !near_one(rho)) == 0ull) {
-                        const float delta_star = (rho < 0.0f) ? -rho : div_midrange(rho, alpha, inv_alpha);
-                        const int c0 = bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
-                        joint_search_nearest(w, alpha, delta_star, grid, bracket, c0, radius, best_err, best_code, best_nib, q);
-                        block_sums(w, q, a, b);
-                        d = e4m3_value((uint32_t)best_code);
-                        const float ratio = div_midrange(a, b, rcp_midrange(b));
-                        t.rho[i] = (b == 0.0f || dss_only) ? -d : ratio;
-                    } else {
-                        const float delta_star = (rho < 0.0f) ? -rho : rho / alpha;
-                        const int c0 = bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
-                        // the reciprocal shortcut holds while the biased exponent of the scale stays in [1, 252];
-                        // the scales of a block lie between those of the first and the last factor (to within
-                        // rounding of the grid), which are asked to keep one binade of distance from both ends
-                        const float s_first = alpha * (delta_star * s_beta[0]);
-                        const float s_final = alpha * (delta_star * s_beta[n_beta - 1]);
-                        const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
-                        if (NEAREST || __builtin_amdgcn_ballot_w64(!mid) != 0ull)
-                            joint_search<false, NEAREST ? 1 : 4>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err,
-                                                                 best_code, best_nib, q);
-                        else
-                            joint_search<true, 4>(w, alpha, delta_star, s_beta, n_beta, bracket, c0, radius, best_err, best_code,
-                                                  best_nib, q);
-                        // the state the next iteration starts from
-                        block_sums(w, q, a, b);
-                        d = e4m3_value((uint32_t)best_code);
-                        t.rho[i] = (b == 0.0f || dss_only) ? -d : a / b;
-                    }
+                    iterate_block<NEAREST>(w, t.rho[i], js, x);
+                    t.rho[i] = x.rho;
                 }
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                u32x2 packed = {best_nib[0], best_nib[1]};
-                __builtin_nontemporal_store(packed, reinterpret_cast<u32x2 *>(t.codes) + i);
-                __builtin_nontemporal_store((uint8_t)best_code, t.scales + i);
+                store_block(t, i, x);
             }
-            tree.stage(kk, a, b, d, best_err);
+            tree.stage(kk, x.a, x.b, x.d, x.err);
         }
         tree.close(kg / T, T);
     }
@@ -565,41 +632,26 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8))) void k
     if (degenerate ? batch.iter_t != 0 : t.ctrl->stopped != 0u) return;     // uniform over the tensor's workgroups
     const float alpha = t.ctrl->alpha1;
 
-    StagedTree tree{s_blocks, s_wave, s_stack};
+    StagedTree<> tree{s_blocks, s_wave, s_stack};
     const uint32_t tile0 = lwg * t.tiles_per_wg;
     const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
     for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
         for (uint32_t kk = 0; kk < T; ++kk) {
             const uint32_t i = (tile0 + kg + kk) * kWG + tid;
-            float a = 0.0f, b = 0.0f, d = 0.0f, err = 0.0f;
+            BlockState x;
+            x.a = x.b = x.d = x.err = 0.0f;
             if (i < t.nblk && amax_bits < 0x7F800000u) {
-                float w[16], q[16];
-                uint32_t nib[2] = {0u, 0u};
-                uint32_t code = kE4M3Min;
+                float w[16];
                 load_block<DT>(t.w, block_offset(t, i), w);
                 if (allzero) {
-                    float x[16];
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) x[j] = w[j];
-                    nib[0] = fp4x8(x);
-                    nib[1] = fp4x8(x + 8);
+                    zero_block(w, x);
                 } else {
-                    const float rho = t.rho[i];
-                    const float delta_star = (rho < 0.0f) ? -rho : rho / alpha;          // Eq. 6
-                    code = e4m3_project(delta_star);
-                    d = e4m3_value(code);
-                    const float sd = alpha * d;
-                    assign_codes(w, sd, nib, q);
-                    block_sums(w, q, a, b);
-                    err = block_error(w, q, sd);
-                    t.rho[i] = (b == 0.0f) ? -d : a / b;
+                    closed_form_block(w, t.rho[i], alpha, x);
+                    t.rho[i] = x.rho;
                 }
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                u32x2 packed = {nib[0], nib[1]};
-                __builtin_nontemporal_store(packed, reinterpret_cast<u32x2 *>(t.codes) + i);
-                __builtin_nontemporal_store((uint8_t)code, t.scales + i);
+                store_block(t, i, x);
             }
-            tree.stage(kk, a, b, d, err);
+            tree.stage(kk, x.a, x.b, x.d, x.err);
         }
         tree.close(kg / T, T);
     }

@@ -1,0 +1,333 @@
+// The iterated path of one tensor handed over alone, in one launch: k_iter_resident.
+#pragma once
+#include "soar_iterated.hpp"
+#include "soar_single_step.hpp"      // the crossings of the one-launch kernels
+
+namespace {
+
+// A tensor handed over alone pays, on the launch-per-iteration path, 18 dependent launches for the paper's 15
+// iterations, 12 of them idle after the usual stop at the third; below some ten million weights they, and not the
+// search, are what a call takes.  k_iter_resident does the whole path -- Eq. 1 maximum, Eq. 1-2 state, the iterations
+// until the stop -- in ONE launch of at most one workgroup per compute unit.  Workgroup g owns the R * L consecutive
+// blocks from g * R * L on, as R tiles of one block per lane (R a power of two, so its sums are nodes of the
+// adjacent-pair tree); it re-reads them in every iteration, from the L2 or the last-level cache, and keeps its
+// blocks' ratios in the workspace, where only the lane that wrote one reads it.  The tensor-wide sums cross the grid
+// as in k_resident (tokens, no counters, bounded waits), three binary64 values a crossing; every workgroup forms the
+// next global scale and the stop decision for itself from the same bits.
+// Words of consecutive crossings alternate between two buffers: a workgroup publishes crossing c + 2 only after it has
+// gathered c + 1, for which every workgroup had published, and had therefore gathered c.  Each crossing has a token of
+// its own; the complement of the launch's token says at any of them that its writer has given up.
+// 1024 x 4096 bf16, paper settings: 72-88 -> 44 us a call (loads 1, maximum 2, state 3, sums 3, an iteration 5-6 and
+// its crossing 4 us); 4096 x 4096 fp32, search-only arm: 169 -> 140 us, 33 of them an iteration's search.
+// A crossing's words lie entry by entry (kSumWords of one workgroup or group side by side), and a wave reads them as
+// they lie, one word per lane: reads past the L2 are served line by line, and a gather by kinds of word -- nine loads
+// of 64 words 2 KB apart -- took 3 to 4 us a hop where this takes
+// 1.6 to 2.  Groups of 16 workgroups: 144 words, nine lines, at either level (groups of 64 would be 36 lines
+// for the gathering workgroup).
+constexpr uint32_t kSumWords = 9;                        // three binary64 values in thirds
+constexpr uint32_t kSumGroup = 16;                       // workgroups per group, and groups at most
+constexpr uint32_t kSumCopies = 7;                       // of a group's result: 7 * 9 words are one store instruction
+constexpr uint32_t kSumCopyStride = 160;                 // words
+constexpr uint32_t kSumLevel1 = 12288;                   // [2 buffers][kResMaxWG][kSumWords]
+constexpr uint32_t kSumLevel2 = kSumLevel1 + 2 * kResMaxWG * kSumWords;      // [2 buffers][kSumCopies][kSumCopyStride]
+static_assert(kResNM2 + kResCopies * kResCopyStride <= kSumLevel1 && kSumLevel2 + 2 * kSumCopies * kSumCopyStride <= 3 * kMaxPartials &&
+              kSumGroup * kSumWords <= kSumCopyStride && kSumGroup * kSumGroup >= (uint32_t)kResMaxWG && kSumCopies * kSumWords <= 64,
+              "layout of the crossing words");
+
+// Wave 0, all lanes: wait until the `count` entries from `src` on carry the token; lane e then holds the three values
+// of entry e (zeros from `count` on).  lds: kSumGroup * kSumWords words.
+__device__ __forceinline__ bool gather_sums(const ResidentGrid &r, const uint64_t *src, uint32_t count, uint64_t *lds, double v[3])
+{
+    constexpr int P = kResSumBits;
+    constexpr uint32_t kLoads = (kSumGroup * kSumWords + 63) / 64;
+    const uint32_t lane = threadIdx.x & 63u, n = count * kSumWords;
+    const uint64_t want = (r.tok << P) >> P, gone_field = (~r.base << P) >> P;
+    uint64_t x[kLoads];
+    for (uint64_t round = 0;; ++round) {
+#pragma unroll
+        for (uint32_t k = 0; k < kLoads; ++k)
+            x[k] = lane + 64u * k < n ? __hip_atomic_load(src + lane + 64u * k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : want << P;
+        __builtin_amdgcn_sched_barrier(0);               // one trip to memory a round
+        bool pending = false, gone = false;
+#pragma unroll
+        for (uint32_t k = 0; k < kLoads; ++k) {
+            const uint64_t field = x[k] >> P;
+            gone = gone | (field == gone_field);
+            pending = pending | (field != want);
+        }
+        if (__builtin_amdgcn_ballot_w64(gone) != 0ull) return false;
+        if (__builtin_amdgcn_ballot_w64(pending) == 0ull) break;
+        if (resident_time_is_up(r, round)) return false;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kLoads; ++k)
+        if (lane + 64u * k < kSumGroup * kSumWords) lds[lane + 64u * k] = x[k] & ((1ull << P) - 1ull);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint64_t *mine = lds + min(lane, kSumGroup - 1u) * kSumWords;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) v[j] = lane < count ? resident_join(mine + 3 * j) : 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    return true;
+}
+
+// Wave 0, all lanes: entry `e` of `copies` copies of the words, from the values v (uniform)
+__device__ __forceinline__ void publish_sums(const ResidentGrid &r, uint64_t *dst, uint32_t e, uint32_t copies, const double v[3])
+{
+    uint64_t pay[kSumWords];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) resident_split(v[j], pay + 3 * j);
+    const uint32_t lane = threadIdx.x & 63u, copy = lane / kSumWords, w = lane - copy * kSumWords;
+    uint64_t x = pay[0];
+#pragma unroll
+    for (uint32_t j = 1; j < kSumWords; ++j) x = w == j ? pay[j] : x;
+    if (copy < copies)
+        __hip_atomic_store(dst + copy * kSumCopyStride + e * kSumWords + w, (r.tok << kResSumBits) | x, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Wave 0, all lanes, every workgroup: the adjacent-pair tree sums of three binary64 values (lane 0's on entry) over the
+// grid, uniform on return.  buffer: 0 or 1, alternating from crossing to crossing.
+__device__ __forceinline__ bool cross_three_sums(const ResidentGrid &r, uint32_t buffer, uint64_t *lds, double v[3])
+{
+    uint64_t *level1 = r.words + kSumLevel1 + buffer * kResMaxWG * kSumWords;
+    uint64_t *level2 = r.words + kSumLevel2 + buffer * kSumCopies * kSumCopyStride;
+    const uint32_t grp = r.g / kSumGroup, groups = (r.G + kSumGroup - 1u) / kSumGroup;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) v[j] = readlane_f64(v[j], 0);
+    publish_sums(r, level1, r.g, 1u, v);
+    auto tree = [&]() {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) v[j] = wave_pair_tree(v[j]);
+    };
+    if (r.G > kSumGroup) {
+        if (r.g % kSumGroup == 0u) {
+            if (!gather_sums(r, level1 + grp * kSumGroup * kSumWords, min(kSumGroup, r.G - grp * kSumGroup), lds, v)) return false;
+            tree();
+            publish_sums(r, level2, grp, kSumCopies, v);
+        }
+        if (!gather_sums(r, level2 + (r.g % kSumCopies) * kSumCopyStride, groups, lds, v)) return false;
+    } else if (!gather_sums(r, level1, r.G, lds, v)) {
+        return false;
+    }
+    tree();
+    return true;
+}
+
+constexpr int kIterResMaxBeta = 2048;     // factor table in LDS
+constexpr int kIterResMaxTiles = 16;      // R
+
+struct IterResidentArgs {
+    ResidentArgs r;
+    int32_t  iters, n_beta, bracket, arm;
+    float    beta_lo, beta_hi, index_per_beta, early_stop_rel;
+    uint32_t tiles;                       // R
+};
+
+// CLOSED_FORM: the arm without a search; otherwise the nearest-factor search (the host sends the others elsewhere)
+template <int DT, int L, bool CLOSED_FORM>
+__global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterResidentArgs args)
+{
+    static_assert(L == 256 || L == 1024, "workgroup of 4 or 16 waves");
+    constexpr int kWaves = L / 64;
+    constexpr int kP = pieces_per_block<DT, 16>();
+    constexpr int kMaxBits = DT == SOAR_BF16 ? 15 : 31;
+    __shared__ float4 s_blocks[kStage * L];
+    __shared__ double s_wave[3][kWaves];
+    __shared__ double s_stack[3][32];
+    __shared__ float s_beta[CLOSED_FORM ? 1 : kIterResMaxBeta];
+    __shared__ uint64_t s_cross[kSumGroup * kSumWords];
+    __shared__ uint32_t s_max[kWaves];
+    __shared__ uint32_t s_amax, s_gone, s_stop;
+    __shared__ float s_alpha;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    const uint32_t R = args.tiles, first = blockIdx.x * R * (uint32_t)L + tid;      // this lane's block of tile 0
+    const bool keep_scale = args.arm == SOAR_METHOD_DSS_ONLY;
+
+    ResidentGrid grid;
+    grid.g = blockIdx.x;
+    grid.G = gridDim.x;
+    grid.tok = grid.base = 0;
+    grid.t0 = 0;
+    grid.ticks = args.r.wait_ticks;
+    grid.words = reinterpret_cast<uint64_t *>(t.part);
+    uint64_t *epoch_p = &t.ctrl->epoch;
+    uint64_t epoch = 0;
+    if (grid.G > 1u) {
+        epoch = __hip_atomic_load(epoch_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        grid.tok = grid.base = args.r.nonce ^ (epoch * kResOdd);
+    }
+    // one lane: leave the launch and tell the others, at whichever crossing they are
+    auto give_up = [&]() {
+        const uint64_t gone = ~grid.base << kResSumBits, gone_max = ~grid.base << kMaxBits;
+        auto put = [&](uint32_t at, uint64_t v) { __hip_atomic_store(grid.words + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+        put(kResMax1 + grid.g, gone_max);
+        if (grid.g % kResGroup == 0u)
+            for (uint32_t c = 0; c < (uint32_t)kResCopies; ++c) put(kResMax2 + c * kResCopyStride + grid.g / kResGroup, gone_max);
+        for (uint32_t b = 0; b < 2; ++b) {
+            put(kSumLevel1 + (b * kResMaxWG + grid.g) * kSumWords, gone);
+            if (grid.g % kSumGroup == 0u)
+                for (uint32_t c = 0; c < kSumCopies; ++c)
+                    put(kSumLevel2 + (b * kSumCopies + c) * kSumCopyStride + grid.g / kSumGroup * kSumWords, gone);
+        }
+        __hip_atomic_fetch_add(epoch_p, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (t.status) *t.status = SOAR_STATUS_GAVE_UP;
+    };
+    // wave 0, every workgroup: the sums of crossing c over the grid
+    auto cross = [&](uint32_t c, double v[3]) -> bool {
+        if (grid.G == 1u) return true;
+        grid.tok = grid.base ^ ((uint64_t)(c + 1u) * 0xBF58476D1CE4E5B9ull);
+        grid.t0 = (uint64_t)wall_clock64();
+        return cross_three_sums(grid, c & 1u, s_cross, v);
+    };
+
+    if constexpr (!CLOSED_FORM)
+        for (int k = (int)tid; k < args.n_beta; k += L) s_beta[k] = beta_factor(k, args.n_beta, args.beta_lo, args.beta_hi);
+
+    // ---- Eq. 1 maximum
+    uint32_t m = 0;
+#pragma unroll 4
+    for (uint32_t k = 0; k < R; ++k) {
+        const uint32_t i = first + k * (uint32_t)L;
+        if (i >= t.nblk) break;
+        const char *p = static_cast<const char *>(t.w) + block_offset(t, i) * (DT == SOAR_BF16 ? 2 : 4);
+#pragma unroll
+        for (int c = 0; c < kP; ++c) {
+            const u32x4 v = load16<false>(p + 16 * c);
+            m = absmax_accumulate<DT>(m, make_uint4(v.x, v.y, v.z, v.w));
+        }
+    }
+    if constexpr (DT == SOAR_BF16) m = max(m & 0xFFFFu, m >> 16) << 16;
+    m = wave_max_u32(m);
+    if (lane == 0) s_max[wave] = m;
+    __syncthreads();
+    if (wave == 0) {
+        uint32_t amax = wave_max_u32(lane < (uint32_t)kWaves ? s_max[lane] : 0u);
+        bool ok = true;
+        if (grid.G > 1u) {
+            uint32_t value = DT == SOAR_BF16 ? amax >> 16 : amax;
+            grid.t0 = (uint64_t)wall_clock64();
+            ok = resident_cross_max<kMaxBits>(grid, value);
+            amax = DT == SOAR_BF16 ? value << 16 : value;
+            if (lane == 0) {
+                if (!ok) give_up();
+                else if (grid.g == 0u)     // every workgroup has read the epoch by now: the next launch gets a new token
+                    __hip_atomic_store(epoch_p, epoch + 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        if (lane == 0) { s_amax = amax; s_gone = ok ? 0u : 1u; }
+    }
+    __syncthreads();
+    if (s_gone) return;
+    const uint32_t amax_bits = s_amax;
+    const bool allzero = amax_bits == 0u, nonfinite = amax_bits >= 0x7F800000u;
+    if (allzero || nonfinite) {                              // uniform over the grid
+        if (allzero) {
+            for (uint32_t k = 0; k < R; ++k) {
+                const uint32_t i = first + k * (uint32_t)L;
+                if (i >= t.nblk) break;
+                float w[16];
+                BlockState x;
+                load_block<DT>(t.w, block_offset(t, i), w);
+                zero_block(w, x);
+                store_block(t, i, x);
+            }
+        }
+        if (grid.g == 0u && tid == 0) {
+            *t.gscale = allzero ? 1.0f : __builtin_nanf("");
+            if (t.sse) *t.sse = allzero ? 0.0 : __builtin_nan("");
+            if (t.status) *t.status = allzero ? SOAR_STATUS_ALLZERO : SOAR_STATUS_NONFINITE;
+            if (t.iters_run) *t.iters_run = 0;
+        }
+        return;
+    }
+
+    // ---- Eq. 1-2 state; the scale of iteration 0 (Eq. 5, unless the closed-form stage is left out)
+    const float alpha0 = f_of(amax_bits) / 2688.0f;
+    const float alpha0_m = alpha0 * 6.0f;
+    const uint32_t T = R < (uint32_t)kStage ? R : (uint32_t)kStage;
+    double prev = 0.0;                                       // wave 0: the error before the iteration now running
+    {
+        StagedTree<L> tree{s_blocks, s_wave, s_stack};
+        for (uint32_t kg = 0; kg < R; kg += T) {
+            for (uint32_t kk = 0; kk < T; ++kk) {
+                const uint32_t i = first + (kg + kk) * (uint32_t)L;
+                float a = 0.0f, b = 0.0f, delta0 = 0.0f, err = 0.0f;
+                if (i < t.nblk) {
+                    float w[16], rho;
+                    load_block<DT>(t.w, block_offset(t, i), w);
+                    init_block(w, alpha0, alpha0_m, keep_scale, a, b, delta0, err, rho);
+                    t.rho[i] = rho;
+                }
+                tree.stage(kk, a, b, delta0, err);
+            }
+            tree.close(kg / T, T);
+        }
+        if (wave == 0) {
+            double v[3] = {tree.wg[0], tree.wg[1], tree.wg[2]};          // lane 0's
+            const bool ok = cross(0u, v);
+            if (lane == 0) {
+                if (!ok) give_up();
+                s_gone = ok ? 0u : 1u;
+                s_alpha = (v[1] > 0.0 && !keep_scale) ? (float)(v[0] / v[1]) : alpha0;
+                if (ok && grid.g == 0u && t.trace) t.trace[0] = v[2];
+            }
+            prev = v[2];
+        }
+    }
+    __syncthreads();
+    if (s_gone) return;
+
+    // ---- the iterations
+    JointSearch js{{s_beta, args.n_beta, args.beta_lo, args.index_per_beta}, 0.0f, 0.0f, args.r.radius, args.bracket != 0, keep_scale, false};
+    for (uint32_t it = 0; it < (uint32_t)args.iters; ++it) {
+        const float alpha = s_alpha;
+        js.set_alpha(alpha, amax_bits);
+        StagedTree<L> tree{s_blocks, s_wave, s_stack};
+        for (uint32_t kg = 0; kg < R; kg += T) {
+            for (uint32_t kk = 0; kk < T; ++kk) {
+                const uint32_t i = first + (kg + kk) * (uint32_t)L;
+                BlockState x;
+                x.a = x.b = x.d = x.err = 0.0f;
+                if (i < t.nblk) {
+                    float w[16];
+                    load_block<DT>(t.w, block_offset(t, i), w);
+                    if constexpr (CLOSED_FORM) closed_form_block(w, t.rho[i], alpha, x);
+                    else iterate_block<true>(w, t.rho[i], js, x);
+                    t.rho[i] = x.rho;
+                    store_block(t, i, x);
+                }
+                tree.stage(kk, x.a, x.b, x.d, x.err);
+            }
+            tree.close(kg / T, T);
+        }
+        if (wave == 0) {
+            double v[3] = {tree.wg[0], tree.wg[1], tree.wg[2]};
+            const bool ok = cross(it + 1u, v);
+            const double cur = v[2];
+            const bool stop = args.early_stop_rel > 0.0f && (prev - cur) < (double)args.early_stop_rel * prev;
+            prev = cur;
+            if (lane == 0) {
+                if (!ok) give_up();
+                s_gone = ok ? 0u : 1u;
+                s_stop = stop ? 1u : 0u;
+                s_alpha = (v[1] > 0.0 && !keep_scale) ? (float)(v[0] / v[1]) : alpha;      // Eq. 5 for the next iteration
+                if (ok && grid.g == 0u) {
+                    if (t.trace) t.trace[it + 1u] = cur;
+                    if (stop || it + 1u == (uint32_t)args.iters) {
+                        *t.gscale = alpha;
+                        if (t.sse) *t.sse = cur;
+                        if (t.status) *t.status = 0;
+                        if (t.iters_run) *t.iters_run = (int32_t)(it + 1u);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (s_gone || s_stop) return;
+    }
+}
+
+}  // namespace

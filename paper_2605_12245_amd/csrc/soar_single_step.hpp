@@ -495,7 +495,7 @@ struct ResidentArgs {
 // what wave 0 of a workgroup needs for its crossings
 struct ResidentGrid {
     uint32_t g, G;
-    uint64_t tok, t0, ticks;
+    uint64_t tok, base, t0, ticks;        // token of the crossing and of the launch
     uint64_t *words;                      // Task::part
 };
 
@@ -531,7 +531,7 @@ __device__ __forceinline__ bool resident_gather(const ResidentGrid &r, const uin
                                                 uint32_t count, uint64_t pay[K][NW])
 {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t want = (r.tok << PBITS) >> PBITS, gone_field = (~r.tok << PBITS) >> PBITS;
+    const uint64_t want = (r.tok << PBITS) >> PBITS, gone_field = (~r.base << PBITS) >> PBITS;
     for (uint64_t round = 0;; ++round) {
         // all loads of a round first, whatever the registers: one trip to memory a round, not one per word
         uint64_t v[K][NW];
@@ -682,14 +682,14 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
     ResidentGrid grid;
     grid.g = blockIdx.x;
     grid.G = gridDim.x;
-    grid.tok = 0;
+    grid.tok = grid.base = 0;
     grid.t0 = 0;
     grid.ticks = args.wait_ticks;
     grid.words = reinterpret_cast<uint64_t *>(t.part);
     uint64_t epoch = 0;
     if (grid.G > 1u) {
         epoch = __hip_atomic_load(epoch_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        grid.tok = args.nonce ^ (epoch * kResOdd);
+        grid.tok = grid.base = args.nonce ^ (epoch * kResOdd);
         grid.t0 = (uint64_t)wall_clock64();
     }
     // one lane: leave the launch and tell the others -- whoever gathers this workgroup's words, now or at a
