@@ -117,28 +117,6 @@ __device__ __forceinline__ int e4m3_floor_code(float y)
     return min(max(code, (int)kE4M3Min), (int)kE4M3Max);
 }
 
-// 1 / s for s > 0 whose biased exponent lies in [1, 252]: the hardware estimate and one fused
-// Newton step.  Compared with the correctly rounded division on every binary32 pattern: identical
-// over that whole range (the patterns that differ are subnormal inputs and subnormal quotients).
-__device__ __forceinline__ float rcp_midrange(float s)
-{
-    const float y = __builtin_amdgcn_rcpf(s);
-    const float e = __builtin_fmaf(-s, y, 1.0f);
-    return __builtin_fmaf(e, y, y);
-}
-
-// a / b, correctly rounded, from y = 1 / b correctly rounded (Markstein, IBM J. Res. Dev. 34, 1990: one fused residual
-// of a quotient within an ulp, one fused correction); the caller keeps a, b and a / b so far inside the normal range
-// that the residual is exact
-__device__ __forceinline__ float div_midrange(float a, float b, float y)
-{
-    const float q = a * y;
-    return __builtin_fmaf(__builtin_fmaf(-q, b, a), y, q);
-}
-
-// biased exponent within 60 of 1.0's
-__device__ __forceinline__ bool near_one(float x) { return ((__float_as_uint(x) >> 23) - 67u) < 120u; }
-
 // assign_codes with the reciprocal chosen at compile time; nib carries the previous codes in
 // (every byte is overwritten) so that no register has to be cleared first
 template <bool FAST>
@@ -307,8 +285,10 @@ __device__ __forceinline__ void joint_search_nearest(const float w[16], float al
         int k;
         const float err = best_factor(w, alpha, delta_star, base_index, grid, alpha * e4m3_value((uint32_t)code), nib, k);
         bool win = err < best_err;
-        const bool tie = err == best_err && k < best_k;
-        if (__builtin_amdgcn_ballot_w64(tie) != 0ull) win = win || (tie && (nib[0] != best_nib[0] || nib[1] != best_nib[1]));
+        if (__builtin_amdgcn_ballot_w64(err == best_err) != 0ull) {
+            asm volatile("");                    // rare: kept out of the straight line
+            win = win || (err == best_err && k < best_k && (nib[0] != best_nib[0] || nib[1] != best_nib[1]));
+        }
         best_err = win ? err : best_err;
         best_code = win ? code : best_code;
         best_k = win ? k : best_k;
@@ -331,15 +311,15 @@ __device__ __forceinline__ void joint_search_nearest(const float w[16], float al
 
 // the Eq. 1-2 state of a block: a, b, the scale's value, the error and the ratio for Eq. 6 (keep_scale: -Delta0, the
 // search centre of the arm that leaves the closed-form stage out)
-__device__ __forceinline__ void init_block(const float w[16], float alpha0, float alpha0_m, bool keep_scale, float &a, float &b,
-                                           float &delta0, float &err, float &rho)
+__device__ __forceinline__ void init_block(const float w[16], const GlobalScale &g, bool keep_scale, float &a, float &b, float &delta0,
+                                           float &err, float &rho)
 {
     float q[16];
     uint32_t nib[2], c0;
-    block_init(w, alpha0, alpha0_m, c0, delta0, nib, q);
+    block_init(w, g, c0, delta0, nib, q);
     block_sums(w, q, a, b);
-    err = block_error(w, q, alpha0 * delta0);
-    rho = (b == 0.0f || keep_scale) ? -delta0 : a / b;
+    err = block_error(w, q, g.alpha0 * delta0);
+    rho = keep_scale ? -delta0 : block_ratio(a, b, delta0, g.fast);
 }
 
 // The Eq. 1-2 state of Algorithm 1 (Delta^q = Delta^d = Delta0) for the iterated
@@ -361,8 +341,8 @@ __global__ __launch_bounds__(kWG) void k_iter_init(const Batch batch)
     const uint32_t tid = threadIdx.x;
     const uint32_t amax_bits = t.ctrl->amax_bits;
     const bool degenerate = amax_bits == 0u || amax_bits >= 0x7F800000u;
-    const float alpha0 = f_of(amax_bits) / 2688.0f;
-    const float alpha0_m = alpha0 * 6.0f;
+    const GlobalScale gs(amax_bits);
+    const float alpha0 = gs.alpha0;
 
     StagedTree<> tree{s_blocks, s_wave, s_stack};
     const uint32_t tile0 = lwg * t.tiles_per_wg;
@@ -376,7 +356,7 @@ __global__ __launch_bounds__(kWG) void k_iter_init(const Batch batch)
                 if (!degenerate) {
                     float w[16];
                     load_block<DT>(t.w, block_offset(t, i), w);
-                    init_block(w, alpha0, alpha0_m, batch.arm == SOAR_METHOD_DSS_ONLY, a, b, delta0, err, rho);
+                    init_block(w, gs, batch.arm == SOAR_METHOD_DSS_ONLY, a, b, delta0, err, rho);
                 }
                 t.rho[i] = rho;
             }
@@ -416,21 +396,32 @@ struct BlockState {
     float a, b, d, err, rho;
 };
 
+// Scales and weights so far from the ends of the binary32 range that neither the reciprocals nor the squares of the
+// nearest-factor search leave it (factors within 2^-20 .. 2^20: the host): alpha Delta* is about the block's ratio, stored
+// scales are alpha times [2^-9, 448].
+__device__ __forceinline__ bool scales_in_range(float alpha, uint32_t amax_bits)
+{
+    return alpha > 0x1p-35f && alpha < 0x1p50f && f_of(amax_bits) < 0x1p60f;
+}
+
+// every ratio of the wave is near one, or stands for a stored scale (negative)
+__device__ __forceinline__ bool all_near_one(float rho)
+{
+    return __builtin_amdgcn_ballot_w64(rho >= 0.0f && !near_one(rho)) == 0ull;
+}
+
 // what the joint search of one tensor needs beside the block
 struct JointSearch {
     FactorGrid grid;
     float alpha, inv_alpha;
     int radius;
     bool bracket, dss_only;      // dss_only: rho always carries -Delta^d, the search centre
-    // Scales and weights so far from the ends of the binary32 range that neither the reciprocals nor the squares of
-    // the nearest-factor search leave it (factors within 2^-20 .. 2^20: the host): alpha Delta* is about rho, stored
-    // scales are alpha times [2^-9, 448].  Everything else takes the plain loop.
-    bool in_range;
+    bool in_range;               // scales_in_range; everything else takes the plain loop
     __device__ __forceinline__ void set_alpha(float alpha_, uint32_t amax_bits)
     {
         alpha = alpha_;
         inv_alpha = 1.0f / alpha_;
-        in_range = alpha_ > 0x1p-35f && alpha_ < 0x1p50f && f_of(amax_bits) < 0x1p60f;
+        in_range = scales_in_range(alpha_, amax_bits);
     }
 };
 
@@ -439,7 +430,7 @@ __device__ __forceinline__ void iterate_block(const float w[16], float rho, cons
 {
     float q[16];
     int code;
-    if (NEAREST && js.in_range && __builtin_amdgcn_ballot_w64(rho >= 0.0f && !near_one(rho)) == 0ull) {
+    if (NEAREST && js.in_range && all_near_one(rho)) {
         const float delta_star = (rho < 0.0f) ? -rho : div_midrange(rho, js.alpha, js.inv_alpha);
         const int c0 = js.bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
         joint_search_nearest(w, js.alpha, delta_star, js.grid, js.bracket, c0, js.radius, x.err, code, x.nib, q);
@@ -468,18 +459,19 @@ __device__ __forceinline__ void iterate_block(const float w[16], float rho, cons
     x.code = (uint32_t)code;
 }
 
-// the same for the closed-form arm: the projected scale assigns the codes and is stored
-__device__ __forceinline__ void closed_form_block(const float w[16], float rho, float alpha, BlockState &x)
+// the same for the closed-form arm: the projected scale assigns the codes and is stored (fast: alpha and the block's
+// ratio are near one, see scales_in_range; stored scales are alpha times [2^-9, 448])
+__device__ __forceinline__ void closed_form_block(const float w[16], float rho, float alpha, float inv_alpha, bool fast, BlockState &x)
 {
     float q[16];
-    const float delta_star = (rho < 0.0f) ? -rho : rho / alpha;          // Eq. 6
+    const float delta_star = (rho < 0.0f) ? -rho : quotient(rho, alpha, inv_alpha, fast);          // Eq. 6
     x.code = e4m3_project(delta_star);
     x.d = e4m3_value(x.code);
     const float sd = alpha * x.d;
-    assign_codes(w, sd, x.nib, q);
+    assign_codes(w, sd, fast, x.nib, q);
     block_sums(w, q, x.a, x.b);
     x.err = block_error(w, q, sd);
-    x.rho = (x.b == 0.0f) ? -x.d : x.a / x.b;
+    x.rho = block_ratio(x.a, x.b, x.d, fast);
 }
 
 // a block of an all-zero tensor: smallest scale, zero codes carrying the sign
@@ -630,7 +622,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8))) void k
     const bool allzero = amax_bits == 0u;
     const bool degenerate = allzero || amax_bits >= 0x7F800000u;
     if (degenerate ? batch.iter_t != 0 : t.ctrl->stopped != 0u) return;     // uniform over the tensor's workgroups
-    const float alpha = t.ctrl->alpha1;
+    const float alpha = t.ctrl->alpha1, inv_alpha = 1.0f / alpha;
+    const bool fast = scales_in_range(alpha, amax_bits);
 
     StagedTree<> tree{s_blocks, s_wave, s_stack};
     const uint32_t tile0 = lwg * t.tiles_per_wg;
@@ -646,7 +639,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8))) void k
                 if (allzero) {
                     zero_block(w, x);
                 } else {
-                    closed_form_block(w, t.rho[i], alpha, x);
+                    const float rho = t.rho[i];
+                    closed_form_block(w, rho, alpha, inv_alpha, fast && all_near_one(rho), x);
                     t.rho[i] = x.rho;
                 }
                 store_block(t, i, x);

@@ -40,10 +40,8 @@ struct MxBatch {
 // 2^(e-127) for an E8M0 code e in [0, 254]; e = 0 is the binary32 subnormal 2^-127
 __device__ __forceinline__ float e8m0_value(int e) { return f_of(e > 0 ? (uint32_t)e << 23 : 0x00400000u); }
 
-template <bool FAST>
-__device__ __forceinline__ void mx_assign(const float w[32], float scale, uint32_t nib[4], float q[32])
+__device__ __forceinline__ void mx_assign_rcp(const float w[32], float r, uint32_t nib[4], float q[32])
 {
-    const float r = FAST ? rcp_midrange(scale) : 1.0f / scale;
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
         float x[8];
@@ -57,6 +55,12 @@ __device__ __forceinline__ void mx_assign(const float w[32], float scale, uint32
         nib[h] = v;
         fp4x8_values(v, q + 8 * h);
     }
+}
+
+template <bool FAST>
+__device__ __forceinline__ void mx_assign(const float w[32], float scale, uint32_t nib[4], float q[32])
+{
+    mx_assign_rcp(w, FAST ? rcp_midrange(scale) : 1.0f / scale, nib, q);
 }
 
 // Eq. 8 with alpha = 1 over the 32 elements: one ascending chain of fused operations
@@ -309,7 +313,7 @@ __global__ __launch_bounds__(kWG) void k_mx(const MxBatch batch)
             float err;
             if constexpr (!DSS) {
                 const float x0 = e8m0_value(e0);
-                mx_assign<false>(w, x0, nib, q);
+                mx_assign_rcp(w, e8m0_value(254 - e0), nib, q);        // 1 / X0, exact for every code
                 err = mx_block_error(w, q, x0);
             } else {
                 // far enough from the ends of the binary32 range for the nearest-factor search (factors within

@@ -245,8 +245,8 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
     }
 
     // ---- Eq. 1-2 state; the scale of iteration 0 (Eq. 5, unless the closed-form stage is left out)
-    const float alpha0 = f_of(amax_bits) / 2688.0f;
-    const float alpha0_m = alpha0 * 6.0f;
+    const GlobalScale gs(amax_bits);
+    const float alpha0 = gs.alpha0;
     const uint32_t T = R < (uint32_t)kStage ? R : (uint32_t)kStage;
     double prev = 0.0;                                       // wave 0: the error before the iteration now running
     {
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
                 if (i < t.nblk) {
                     float w[16], rho;
                     load_block<DT>(t.w, block_offset(t, i), w);
-                    init_block(w, alpha0, alpha0_m, keep_scale, a, b, delta0, err, rho);
+                    init_block(w, gs, keep_scale, a, b, delta0, err, rho);
                     t.rho[i] = rho;
                 }
                 tree.stage(kk, a, b, delta0, err);
@@ -294,8 +294,11 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
                 if (i < t.nblk) {
                     float w[16];
                     load_block<DT>(t.w, block_offset(t, i), w);
-                    if constexpr (CLOSED_FORM) closed_form_block(w, t.rho[i], alpha, x);
-                    else iterate_block<true>(w, t.rho[i], js, x);
+                    const float rho = t.rho[i];
+                    if constexpr (CLOSED_FORM)
+                        closed_form_block(w, rho, alpha, js.inv_alpha, js.in_range && all_near_one(rho), x);
+                    else
+                        iterate_block<true>(w, rho, js, x);
                     t.rho[i] = x.rho;
                     store_block(t, i, x);
                 }

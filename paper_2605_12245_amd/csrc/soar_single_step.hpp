@@ -115,8 +115,8 @@ __global__ __launch_bounds__(kWG) void k_stats(const Batch batch)
     const uint32_t tid = threadIdx.x;
     const uint32_t amax_bits = t.ctrl->amax_bits;
     const bool degenerate = amax_bits == 0u || amax_bits >= 0x7F800000u;
-    const float alpha0 = f_of(amax_bits) / 2688.0f;
-    const float alpha0_m = alpha0 * 6.0f;
+    const GlobalScale gs(amax_bits);
+    const float alpha0 = gs.alpha0;
 
     double wgN = 0.0, wgM = 0.0;
     const uint32_t tile0 = lwg * t.tiles_per_wg;
@@ -132,11 +132,11 @@ __global__ __launch_bounds__(kWG) void k_stats(const Batch batch)
                     uint32_t nib[2], c0;
                     float delta0, a, b;
                     load_block<DT, kStreamStats>(t.w, block_offset(t, i), w);
-                    block_init(w, alpha0, alpha0_m, c0, delta0, nib, q);
+                    block_init(w, gs, c0, delta0, nib, q);
                     block_sums(w, q, a, b);
+                    rho = block_ratio(a, b, delta0, gs.fast);
                     tN = (double)a * (double)delta0;
                     tM = ((double)b * (double)delta0) * (double)delta0;
-                    rho = (b == 0.0f) ? -delta0 : a / b;      // first half of Eq. 6
                 }
                 __builtin_nontemporal_store(rho, t.rho + i);
             }
@@ -305,6 +305,15 @@ __device__ __forceinline__ void count_search(unsigned long long *stats, bool cer
     }
 }
 
+// Eq. 6 and the new assignment; returns the projection of Delta* (fast: GlobalScale::fast, and alpha1 near one as well)
+__device__ __forceinline__ int new_codes(const float w[16], float rho, float alpha1, float inv_alpha1, bool fast, uint32_t nib[2],
+                                         float q[16])
+{
+    const float delta_star = (rho < 0.0f) ? -rho : quotient(rho, alpha1, inv_alpha1, fast);
+    assign_codes(w, alpha1 * delta_star, fast, nib, q);
+    return (int)e4m3_project(delta_star);
+}
+
 // Eq. 6, projection, new assignment, Eq. 8 search, packing, error sum.
 // METHOD RTN emits the Eq. 1-2 state instead.
 // (bf16: held to 64 registers, eight waves per SIMD; left to itself the compiler takes 83 for a shorter schedule and loses more in
@@ -338,10 +347,11 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(DT == SOAR_
         amax_bits = bad_amax ? 0x7FC00000u : __float_as_uint(given);
     }
     const bool allzero = amax_bits == 0u;
-    const float alpha0 = f_of(amax_bits) / 2688.0f;
-    const float alpha0_m = alpha0 * 6.0f;
+    const GlobalScale gs(amax_bits, METHOD == SOAR_METHOD_SOAR || !t.amax_in);
+    const float alpha0 = gs.alpha0;
     const float alpha1 = (METHOD == SOAR_METHOD_SOAR) ? t.ctrl->alpha1 : alpha0;
-    const float inv_alpha1 = __builtin_amdgcn_rcpf(alpha1);
+    const float inv_alpha1 = 1.0f / alpha1;
+    const bool fast = gs.fast && near_one(alpha1);
 
     // tiles dealt round-robin over the tensor's workgroups (see k_absmax)
     double sse = 0.0;
@@ -373,14 +383,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(DT == SOAR_
         } else if constexpr (METHOD == SOAR_METHOD_RTN) {
             uint32_t c0;
             float delta0;
-            block_init(w, alpha0, alpha0_m, c0, delta0, nib, q);
+            block_init(w, gs, c0, delta0, nib, q);
             out_code = c0;
             out_err = block_error(w, q, alpha0 * delta0);
         } else {
             const float rho = __builtin_nontemporal_load(t.rho + i);                // a / b >= 0, or -Delta0 where b == 0
-            const float delta_star = (rho < 0.0f) ? -rho : rho / alpha1;
-            const int centre = (int)e4m3_project(delta_star);
-            assign_codes(w, alpha1 * delta_star, nib, q);
+            const int centre = new_codes(w, rho, alpha1, inv_alpha1, fast, nib, q);
             int best;
             float best_err;
             bool done = false;
@@ -768,8 +776,8 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
     const uint32_t amax_bits = s_amax;
     const bool allzero = amax_bits == 0u;
     const bool degenerate = allzero || amax_bits >= 0x7F800000u;
-    const float alpha0 = f_of(amax_bits) / 2688.0f;
-    const float alpha0_m = alpha0 * 6.0f;
+    const GlobalScale gs(amax_bits);
+    const float alpha0 = gs.alpha0;
 
     auto widen = [&](int k, float w[16]) {
         if constexpr (DT == SOAR_BF16) {
@@ -826,11 +834,11 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
                     uint32_t nib[2], c0;
                     float delta0, a, b;
                     widen(k, w);
-                    block_init(w, alpha0, alpha0_m, c0, delta0, nib, q);
+                    block_init(w, gs, c0, delta0, nib, q);
                     block_sums(w, q, a, b);
+                    rho[k] = block_ratio(a, b, delta0, gs.fast);
                     tN[k] = (double)a * (double)delta0;
                     tM[k] = ((double)b * (double)delta0) * (double)delta0;
-                    rho[k] = (b == 0.0f) ? -delta0 : a / b;      // first half of Eq. 6
                 }
             }
             wave_sum_to_lds(0, tN);
@@ -856,7 +864,8 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
         }
         if (blockIdx.x == 0u && tid == 0) *t.gscale = alpha1;
     }
-    const float inv_alpha1 = __builtin_amdgcn_rcpf(alpha1);
+    const float inv_alpha1 = 1.0f / alpha1;
+    const bool fast = gs.fast && near_one(alpha1);
     const bool full_search = args.full_search != 0;
 
     // ---- Eq. 6, new assignment, Eq. 8 search (k_search, per block); the lane's bytes leave together
@@ -882,13 +891,11 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
             } else if constexpr (METHOD == SOAR_METHOD_RTN) {
                 uint32_t c0;
                 float delta0;
-                block_init(w, alpha0, alpha0_m, c0, delta0, nibs[k], q);
+                block_init(w, gs, c0, delta0, nibs[k], q);
                 out_code = c0;
                 out_err = block_error(w, q, alpha0 * delta0);
             } else {
-                const float delta_star = (rho[k] < 0.0f) ? -rho[k] : rho[k] / alpha1;
-                const int centre = (int)e4m3_project(delta_star);
-                assign_codes(w, alpha1 * delta_star, nibs[k], q);
+                const int centre = new_codes(w, rho[k], alpha1, inv_alpha1, fast, nibs[k], q);
                 int best;
                 float best_err;
                 bool done = false;
