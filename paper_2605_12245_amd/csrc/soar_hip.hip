@@ -60,6 +60,7 @@ namespace {
 
 // ------------------------------------------------------------------ host side
 constexpr int kMaxDevices = 64;
+constexpr int64_t kLastLevelCache = (int64_t)1 << 28;
 
 std::atomic<bool> g_search_stats{false};
 
@@ -307,18 +308,22 @@ size_t per_block_bytes(int64_t rows, int64_t cols)
 }
 
 // Tiles per workgroup the three passes of the single-step path ask for.  A call of one launch group runs its
-// kernels one after the other, and four tiles suit each of them best.  A call of several groups has kernels of
+// kernels one after the other, and four tiles suit the maximum and the search; the statistics, with two barriers and a
+// tree per four tiles, take eight as long as those leave 1024 workgroups (96 MiB of bf16: 25.0 -> 22.9 us, 224 MiB 48.5
+// -> 47.0, 448 MiB 107 -> 102; 40 MiB, 640 workgroups: slower).  A call of several groups has kernels of
 // two groups on the machine at once (see SecondLane), and how their workgroups share the compute units decides
 // the step: with 8 tiles per workgroup in the statistics pass and 16 in the search the full-model workload
 // takes 7.26 ms instead of 8.08 (swept over 1..4 x 4..32 x 8..32: profiles/config4_launch_shape_sweep.md),
 // although the search alone is 5 % slower that way; plain NVFP4 (two passes) likes 8 in its search.
 struct WantedShapes { uint32_t absmax, stats, search; };
-WantedShapes wanted_shapes(bool several_groups, int method, bool iterated, bool one_pass, int64_t bytes)
+constexpr int64_t kStatsEightTiles = 8192;       // tiles of a launch group from which the statistics take eight a workgroup
+WantedShapes wanted_shapes(bool several_groups, int method, bool iterated, bool one_pass, int64_t bytes, int64_t group_tiles)
 {
-    if (!several_groups || iterated || one_pass) return {(uint32_t)kStage, (uint32_t)kStage, (uint32_t)kStage};
+    if (iterated || one_pass) return {(uint32_t)kStage, (uint32_t)kStage, (uint32_t)kStage};
+    if (!several_groups) return {(uint32_t)kStage, group_tiles >= kStatsEightTiles ? 8u : (uint32_t)kStage, (uint32_t)kStage};
     // a tensor that is a launch group by itself and larger than the last-level cache streams from HBM in every
     // pass; plain NVFP4 has two passes only
-    if (method == SOAR_METHOD_RTN || bytes > kGroupByteCap) return {(uint32_t)kStage, (uint32_t)kStage, 8u};
+    if (method == SOAR_METHOD_RTN || bytes > kLastLevelCache) return {(uint32_t)kStage, (uint32_t)kStage, 8u};
     return {(uint32_t)kStage, 8u, 16u};
 }
 
@@ -388,15 +393,6 @@ int64_t weight_bytes(const soar_tensor_desc &d) { return d.rows * d.cols * (d.dt
 
 constexpr int64_t kOnePassByteCap = (int64_t)1 << 29;    // larger launches gain nothing more (measured: 2^29 .. 2^31)
 
-// bytes of weights one launch may cover (beyond its first tensor)
-int64_t group_byte_cap(const soar_tensor_desc *descs, const soar_params *params)
-{
-    // with the maximum supplied there is one pass only: nothing to keep in the last-level cache
-    if (descs[0].d_amax_in) return kOnePassByteCap;
-    (void)params;
-    return kGroupByteCap;      // a group stays in the 256 MiB last-level cache from pass to pass, iteration to iteration
-}
-
 int32_t group_end(int32_t n, const soar_tensor_desc *descs, int32_t first, int64_t cap)
 {
     int64_t bytes = weight_bytes(descs[first]);
@@ -407,6 +403,16 @@ int32_t group_end(int32_t n, const soar_tensor_desc *descs, int32_t first, int64
         ++j;
     }
     return j;
+}
+
+// bytes of weights one launch may cover (beyond its first tensor)
+int64_t group_byte_cap(int32_t n, const soar_tensor_desc *descs)
+{
+    // with the maximum supplied there is one pass only: nothing to keep in the last-level cache
+    if (descs[0].d_amax_in) return kOnePassByteCap;
+    // what is one group up to the size of the cache stays on the caller's stream (and may be captured into a graph)
+    if (group_end(n, descs, 0, kLastLevelCache) == n) return kLastLevelCache;
+    return kGroupByteCap;      // a group stays in the last-level cache from pass to pass, iteration to iteration
 }
 
 // most per-block workspace any one launch of the batch needs
@@ -433,10 +439,10 @@ size_t max_group_per_block_bytes(int32_t n, const soar_tensor_desc *descs, int64
 
 size_t lane_workspace_bytes(size_t group_per_block) { return (size_t)kGroupMax * kSlotBytes + group_per_block; }
 
-size_t batch_workspace_bytes(int32_t n, const soar_tensor_desc *descs, const soar_params *params)
+size_t batch_workspace_bytes(int32_t n, const soar_tensor_desc *descs)
 {
     int32_t groups = 0;
-    const size_t most = max_group_per_block_bytes(n, descs, group_byte_cap(descs, params), &groups);
+    const size_t most = max_group_per_block_bytes(n, descs, group_byte_cap(n, descs), &groups);
     return (groups > 1 ? kLanes : 1) * lane_workspace_bytes(most);
 }
 
@@ -593,7 +599,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
 
     if (n == 0) return SOAR_OK;
     if (!d_workspace || reinterpret_cast<uintptr_t>(d_workspace) % 256 != 0) return SOAR_ERR_WORKSPACE;
-    if (workspace_bytes < batch_workspace_bytes(n, descs, params)) return SOAR_ERR_WORKSPACE;
+    if (workspace_bytes < batch_workspace_bytes(n, descs)) return SOAR_ERR_WORKSPACE;
 
     // one tensor, single-step settings, default launch shape: the whole path in one launch that keeps the
     // tensor in registers, if its grid fits the GPU (see k_resident); only the slot's flag words are used
@@ -653,7 +659,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
     }
 
     int32_t n_groups = 0;
-    const int64_t cap = group_byte_cap(descs, params);
+    const int64_t cap = group_byte_cap(n, descs);
     const size_t lane_bytes = lane_workspace_bytes(max_group_per_block_bytes(n, descs, cap, &n_groups));
     const int lanes = (n_groups > 1 && params->streams != 1) ? kLanes : 1;
     char *base = static_cast<char *>(d_workspace);
@@ -696,12 +702,9 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         // search and streams like the single-step kernels.
         const bool searching = iterated && params->method != SOAR_METHOD_CJSO_ONLY;
         const uint32_t tpw = (uint32_t)params->tiles_per_wg;
-        uint32_t searching_tpw = 0;
-        if (searching) {
-            int64_t group_tiles = 0;
-            for (int32_t k = i; k < j; ++k) group_tiles += (descs[k].rows * (descs[k].cols / 16) + kWG - 1) / kWG;
-            searching_tpw = search_tiles_per_wg(group_tiles, kIterMinWg);
-        }
+        int64_t group_tiles = 0;
+        for (int32_t k = i; k < j; ++k) group_tiles += (descs[k].rows * (descs[k].cols / 16) + kWG - 1) / kWG;
+        const uint32_t searching_tpw = searching ? search_tiles_per_wg(group_tiles, kIterMinWg) : 0u;
         uint32_t wg = 0, wg_absmax = 0, wg_search = 0;
         char *per_block = lane_base + (size_t)kGroupMax * kSlotBytes;
         for (int32_t k = i; k < j; ++k) {
@@ -710,7 +713,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
                                          params->tiles_per_wg_search ? (uint32_t)params->tiles_per_wg_search : tpw};
             const WantedShapes want = searching ? WantedShapes{searching_tpw, searching_tpw, searching_tpw}
                                                 : wanted_shapes(n_groups > 1, params->method, iterated, d.d_amax_in != nullptr,
-                                                                weight_bytes(d));
+                                                                weight_bytes(d), group_tiles);
             Task t = make_task(d.d_w, d.rows, d.cols, d.ld_elems, forced, want);
             t.iters_run = d.d_iters_run;
             t.trace = d.d_sse_trace;
@@ -906,7 +909,7 @@ size_t soar_batch_workspace_bytes(int32_t n, const soar_tensor_desc *descs, cons
     if (n <= 0 || !descs || !valid_params(params)) return 0;
     for (int32_t k = 0; k < n; ++k)
         if (check_shape(descs[k].rows, descs[k].cols, descs[k].ld_elems) != SOAR_OK) return 0;
-    return batch_workspace_bytes(n, descs, params);
+    return batch_workspace_bytes(n, descs);
 }
 
 soar_status soar_quantize(const void *d_w, soar_dtype dtype, int64_t rows, int64_t cols, int64_t ld_elems,
