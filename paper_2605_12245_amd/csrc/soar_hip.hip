@@ -42,6 +42,7 @@
 #include "soar_single_step.hpp"
 #include "soar_iterated.hpp"
 #include "soar_resident_iterated.hpp"
+#include "soar_once.hpp"
 #include "soar_mxfp4.hpp"
 #include "soar_stored_form.hpp"
 
@@ -551,6 +552,11 @@ soar_status launch_group_iter(Batch &b, uint32_t wg_absmax, uint32_t total_wg, i
     return SOAR_OK;
 }
 
+// The largest tensor k_rtn_once takes.  Above, 256 workgroups keep too few reads in flight (in a graph, k_init and k_search /
+// k_rtn_once: 16 x 4096 bf16 8.2 / 4.6 us, 256 rows 8.8 / 5.4, 1024 rows 10.6 / 9.6, 2048 rows 11.6 / 14.2; fp32 256 rows
+// 12 / 7.2, 1024 rows 12.2 / 13.1).
+constexpr int64_t kOnceMaxTiles = 4 * (int64_t)kOnceMaxWG, kOnceMaxBytes = (int64_t)1 << 23;
+
 // the Task and the arguments of a one-launch kernel; only the slot's control words and crossing words are used
 Task single_task(const soar_tensor_desc &d, void *d_workspace)
 {
@@ -620,6 +626,23 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
             if (rtn) launch_resident<SOAR_FP32, SOAR_METHOD_RTN>(plan, t, a, st);
             else launch_resident<SOAR_FP32, SOAR_METHOD_SOAR>(plan, t, a, st);
         }
+        SOAR_LAUNCH_CHECK();
+        return SOAR_OK;
+    }
+
+    // one small tensor with its maximum supplied: one launch, nothing to clear and nobody to wait for (see k_rtn_once)
+    const int64_t tiles0 = (descs[0].rows * (descs[0].cols / 16) + kWG - 1) / kWG;
+    if (n == 1 && descs[0].d_amax_in && params->tiles_per_wg == 0 && params->tiles_per_wg_absmax == 0 && params->tiles_per_wg_search == 0 &&
+        params->resident == SOAR_RESIDENT_AUTO && tiles0 <= kOnceMaxTiles && weight_bytes(descs[0]) <= kOnceMaxBytes) {
+        const soar_tensor_desc &d = descs[0];
+        Task t = single_task(d, d_workspace);
+        t.amax_in = d.d_amax_in;
+        t.tiles_per_wg = (uint32_t)((tiles0 + kOnceMaxWG - 1) / kOnceMaxWG);
+        const dim3 grid((uint32_t)((tiles0 + t.tiles_per_wg - 1) / t.tiles_per_wg));
+        const OnceArgs a = {next_nonce()};
+        ScopedTimer tm(SOAR_KERNEL_SEARCH, st);
+        if (d.dtype == SOAR_BF16) hipLaunchKernelGGL(k_rtn_once<SOAR_BF16>, grid, dim3(kWG), 0, st, t, a);
+        else hipLaunchKernelGGL(k_rtn_once<SOAR_FP32>, grid, dim3(kWG), 0, st, t, a);
         SOAR_LAUNCH_CHECK();
         return SOAR_OK;
     }
@@ -1105,7 +1128,11 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
         lane_stream[1] = second->stream;
     }
     soar_status result = SOAR_OK;
-    {
+    // one small tensor: finished without counters, so nothing has to be cleared (see once_sum); the search takes one
+    // tile a workgroup there, the plain conversion two
+    const int64_t tiles0 = (descs[0].rows * (descs[0].cols / 32) + kWG - 1) / kWG;
+    const bool once = n == 1 && params->tiles_per_wg == 0 && tiles0 <= (int64_t)kOnceMaxWG * (params->dss ? 1 : 2);
+    if (!once) {
         ScopedTimer tm(SOAR_KERNEL_INIT, st);
         hipLaunchKernelGGL(k_init, dim3(lanes * slots * kInitSplit), dim3(kWG), 0, st, base);
         if (hipGetLastError() != hipSuccess) result = SOAR_ERR_HIP;
@@ -1124,6 +1151,8 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
         MxBatch b;
         std::memset(&b, 0, sizeof(b));
         b.n = (uint32_t)(j - i);
+        b.once = once ? 1u : 0u;
+        if (once) b.once_args.nonce = next_nonce();
         uint32_t wg = 0;
         int64_t group_tiles = 0;
         for (int32_t k = i; k < j; ++k) group_tiles += (descs[k].rows * (descs[k].cols / 32) + kWG - 1) / kWG;

@@ -2,7 +2,8 @@
 // decoupled scale search of Sec. 3.3 carried over to it (Sec. 4.3): k_mx.
 #pragma once
 #include "soar_device.hpp"
-#include "soar_iterated.hpp"      // TileTree, rcp_midrange
+#include "soar_iterated.hpp"      // TileTree, FactorGrid
+#include "soar_once.hpp"
 
 namespace {
 
@@ -35,6 +36,8 @@ struct MxTask {
 struct MxBatch {
     MxTask   t[kGroupMax];
     uint32_t n;
+    uint32_t once;           // one tensor of at most kOnceMaxWG workgroups: finished by once_sum, no counters
+    OnceArgs once_args;
 };
 
 // 2^(e-127) for an E8M0 code e in [0, 254]; e = 0 is the binary32 subnormal 2^-127
@@ -275,6 +278,8 @@ __global__ __launch_bounds__(kWG) void k_mx(const MxBatch batch)
 
     const FactorGrid grid{s_beta, n_beta, t.beta_lo, t.index_per_beta};
     TileTree<1> tree{s_wave, s_stack};
+    uint64_t epoch = 0;
+    if (batch.once && t.n_wg > 1u) epoch = __hip_atomic_load(&t.ctrl->epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     bool nonfinite = false;
     const uint32_t tile0 = lwg * t.tiles_per_wg;
     for (uint32_t k = 0; k < t.tiles_per_wg; ++k) {
@@ -335,6 +340,17 @@ __global__ __launch_bounds__(kWG) void k_mx(const MxBatch batch)
             __builtin_nontemporal_store((uint8_t)code, t.scales + i);
         }
         tree.add_tile(k, term);
+    }
+    if (batch.once) {
+        bool flag = __syncthreads_or(nonfinite ? 1 : 0) != 0;
+        if (tid >= 64u) return;
+        double total = readlane_f64(tree.wg[0], 0);
+        if (once_sum(reinterpret_cast<uint64_t *>(t.part) + kOnceWords, &t.ctrl->epoch, epoch, batch.once_args.nonce, lwg, t.n_wg, total,
+                     flag) && tid == 0) {
+            if (t.sse) *t.sse = total;
+            if (t.status) *t.status = flag ? SOAR_STATUS_NONFINITE : 0;
+        }
+        return;
     }
     if (nonfinite) {
         __hip_atomic_fetch_or(&t.ctrl->amax_bits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
