@@ -205,7 +205,11 @@ bool iter_resident_plan(int64_t nblk, int cu, int ncand, ResidentPlan &plan)
 bool being_captured(hipStream_t st)
 {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();       // the question's error, not one of the launches that follow
+        return true;
+    }
+    return cap != hipStreamCaptureStatusNone;
 }
 
 template <int DT>
