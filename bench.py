@@ -42,7 +42,7 @@ def pmc_entry(algorithm, workload, dtype, kernel, layers=0, search="auto"):
             table = json.load(f)
     except (OSError, ValueError) as e:
         return None, f"{os.path.relpath(PMC_TABLE, ROOT)} not readable ({e.__class__.__name__})"
-    for e in table.get("entries", []):
+    for e in table.get("entries", []) + table.get("searches", []):
         if (e["algorithm"], e["workload"], e["dtype"], e["kernel"], e.get("search", "auto")) == \
                 (algorithm, f"config{workload}", dtype, kernel, search):
             return e, e.get("source", "")
@@ -82,10 +82,13 @@ def alu_roofline(kernel, algorithm, workload, dtype, search, layers, steps_block
     published 157.3 TFLOP/s is this rate x 2 for fused multiply-add x 2 for packed FP32, which this build does not
     emit).  The executed count per (block, factor) comes from a SQ_INSTS_VALU counter run (profiles/pmc_table.json);
     without one the plain loop's instruction count stands in and the line says so.  The method-definition
-    floating-point rate is reported beside it."""
+    floating-point rate is reported beside it; it counts every factor of the grid, most of which the nearest-factor
+    search (--search auto) excludes without evaluating them, so there it is no rate of executed operations."""
     e, why = pmc_entry(algorithm, workload, dtype, kernel, layers, search)
     if e is not None and "valu_lane_insts_per_block_factor" in e:
         per_step, source = e["valu_lane_insts_per_block_factor"], why
+    elif e is not None and "valu_lane_insts_per_block_search" in e:      # the nearest-factor search, spread over its grid
+        per_step, source = e["valu_lane_insts_per_block_search"] / e["factors"], why
     else:
         per_step, source = iter_lane_ops_per_block_beta(ncand, nelem), "modelled (plain loop): " + why
     lane_ops = steps_blocks_factors * per_step
