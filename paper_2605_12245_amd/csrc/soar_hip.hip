@@ -634,10 +634,12 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         return SOAR_OK;
     }
 
-    // one small tensor with its maximum supplied: one launch, nothing to clear and nobody to wait for (see k_rtn_once)
+    // one small tensor with its maximum supplied: one launch, nothing to clear and nobody to wait for (see k_rtn_once).
+    // Not under capture: replays share a nonce, and whatever reuses the workspace between them could bring an epoch back.
     const int64_t tiles0 = (descs[0].rows * (descs[0].cols / 16) + kWG - 1) / kWG;
     if (n == 1 && descs[0].d_amax_in && params->tiles_per_wg == 0 && params->tiles_per_wg_absmax == 0 && params->tiles_per_wg_search == 0 &&
-        params->resident == SOAR_RESIDENT_AUTO && tiles0 <= kOnceMaxTiles && weight_bytes(descs[0]) <= kOnceMaxBytes) {
+        params->resident == SOAR_RESIDENT_AUTO && tiles0 <= kOnceMaxTiles && weight_bytes(descs[0]) <= kOnceMaxBytes &&
+        !being_captured(st)) {
         const soar_tensor_desc &d = descs[0];
         Task t = single_task(d, d_workspace);
         t.amax_in = d.d_amax_in;
@@ -1133,9 +1135,10 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
     }
     soar_status result = SOAR_OK;
     // one small tensor: finished without counters, so nothing has to be cleared (see once_sum); the search takes one
-    // tile a workgroup there, the plain conversion two
+    // tile a workgroup there, the plain conversion two; not under capture, as in run_batch
     const int64_t tiles0 = (descs[0].rows * (descs[0].cols / 32) + kWG - 1) / kWG;
-    const bool once = n == 1 && params->tiles_per_wg == 0 && tiles0 <= (int64_t)kOnceMaxWG * (params->dss ? 1 : 2);
+    const bool once = n == 1 && params->tiles_per_wg == 0 && tiles0 <= (int64_t)kOnceMaxWG * (params->dss ? 1 : 2) &&
+                      !being_captured(st);
     if (!once) {
         ScopedTimer tm(SOAR_KERNEL_INIT, st);
         hipLaunchKernelGGL(k_init, dim3(lanes * slots * kInitSplit), dim3(kWG), 0, st, base);

@@ -9,8 +9,8 @@ constexpr uint32_t kOnceMaxWG = 256;
 constexpr uint32_t kOnceWords = 40960;               // place inside the slot's partial sums: 3 kinds of kOnceMaxWG words
 static_assert(kOnceWords + 3 * kOnceMaxWG <= 3 * kMaxPartials, "layout of the words");
 
-// What a launch needs to know: the token is nonce ^ epoch * odd as in k_resident (the epoch, advanced by every launch
-// that completes, makes a replayed graph's tokens new).
+// What a launch needs to know: the token is nonce ^ epoch * odd as in k_resident.  The nonce is new for every call, and
+// captured calls do not come here, so no token is used twice.
 struct OnceArgs {
     uint64_t nonce;
 };

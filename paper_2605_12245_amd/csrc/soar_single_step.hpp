@@ -5,14 +5,19 @@
 
 namespace {
 
-// clears the control words, arrival counters and partial maxima of every slot
+// clears the control words, arrival counters and partial maxima of every slot, except the epoch: a captured one-launch
+// call takes its token from a nonce that its replays share and from the epoch, which must not return to an earlier value
+// while words with that token lie in the workspace
 constexpr int kInitSplit = 8;             // workgroups per slot
+constexpr uint32_t kEpochPiece = offsetof(Ctrl, epoch) / 16;
 static_assert(kZeroedBytes % 16 == 0, "control region is cleared with 16-byte stores");
+static_assert(offsetof(Ctrl, epoch) % 16 == 8 && kSlotBytes % 16 == 0, "the epoch is the second half of its piece");
 __global__ __launch_bounds__(kWG) void k_init(char *slots_base)
 {
     uint4 *p = reinterpret_cast<uint4 *>(slots_base + (size_t)(blockIdx.x / kInitSplit) * kSlotBytes);
     for (uint32_t k = (blockIdx.x % kInitSplit) * kWG + threadIdx.x; k < kZeroedBytes / 16; k += kInitSplit * kWG)
-        p[k] = make_uint4(0u, 0u, 0u, 0u);
+        if (k == kEpochPiece) *reinterpret_cast<uint2 *>(p + k) = make_uint2(0u, 0u);
+        else p[k] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // max |w| over a tensor.  |bits| of finite floats order like the values; NaN

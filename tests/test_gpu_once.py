@@ -99,3 +99,36 @@ def test_replayed_from_a_graph_on_changing_data():
         torch.cuda.synchronize()
         same(o, rtn(w, amax, B.SOAR_RESIDENT_NEVER, B.new_workspace(200, 4096, p, DEV)), rep)
         same(m, B.mx_quantize(w, B.soar_mx_default_params(dss=False, tiles_per_wg=2)), rep)
+
+
+@pytest.mark.parametrize("rows", [200, 2048], ids=["path with counters", "one-launch kernel"])
+def test_another_call_clears_the_workspace_between_replays(rows):
+    """the captured call's words stay in the workspace: a call that clears the control words there must not bring back
+    the token they carry"""
+    w, amax = weights(rows, 4096, torch.bfloat16).contiguous(), torch.ones(1, device=DEV)
+    o = B.new_outputs(rows, 4096, DEV)
+    p = B.soar_default_params(B.SOAR_METHOD_SOAR, 0)
+    never = B.soar_default_params(B.SOAR_METHOD_SOAR, 0)
+    never.resident = B.SOAR_RESIDENT_NEVER
+    ws = B.new_workspace(rows, 4096, p, DEV)
+    small = weights(16, 64, torch.bfloat16).contiguous()
+    so, ref = B.new_outputs(16, 64, DEV), B.new_outputs(rows, 4096, DEV)
+    run = (lambda: B.quantize_rtn_amax(w, amax, ws, o)) if rows == 200 else (lambda: B.quantize_batch([B.make_desc(w, o)], p, ws))
+    run()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        run()
+    gen = torch.Generator(device=DEV).manual_seed(2)
+    for rep in range(5):
+        w.copy_((torch.randn(w.shape, generator=gen, device=DEV) * 2.0 ** -rep).to(torch.bfloat16))
+        amax.copy_(w.abs().max().float().reshape(1))
+        B.quantize_batch([B.make_desc(small, so)], never, ws)
+        g.replay()
+        torch.cuda.synchronize()
+        if rows == 200:
+            same(o, rtn(w, amax, B.SOAR_RESIDENT_NEVER, B.new_workspace(rows, 4096, p, DEV)), rep)
+        else:
+            B.quantize_batch([B.make_desc(w, ref)], never, B.new_workspace(rows, 4096, p, DEV))
+            torch.cuda.synchronize()
+            same(o, ref, rep)
