@@ -267,7 +267,9 @@ typedef struct {
                                     amax/(6*448), block scales clipped to 448, values above
                                     amax saturate at +-6.  Not finite or not > 0:
                                     SOAR_STATUS_BAD_AMAX.  The weights are not scanned for
-                                    non-finite values in this mode.                      */
+                                    non-finite values in this mode.  d_global_scale, d_sse and
+                                    d_status are written after the last read of the maximum and
+                                    may be the same memory.                              */
 } soar_tensor_desc;
 
 /*

@@ -81,10 +81,6 @@ __global__ __launch_bounds__(kWG) void k_rtn_once(const Task t, const OnceArgs a
     const float given = *t.amax_in;
     const bool bad_amax = !(given > 0.0f) || __float_as_uint(given) >= 0x7F800000u;
     const GlobalScale gs(bad_amax ? 0x7FC00000u : __float_as_uint(given), false);
-    if (g == 0u && tid == 0) {
-        *t.gscale = gs.alpha0;
-        if (t.status) *t.status = bad_amax ? SOAR_STATUS_BAD_AMAX : 0;
-    }
     double sse = 0.0;
     for (uint32_t k = 0; k < t.tiles_per_wg; ++k) {
         const uint32_t i = (g * t.tiles_per_wg + k) * kWG + tid, wave_first = i - (tid & 63u);
@@ -102,15 +98,19 @@ __global__ __launch_bounds__(kWG) void k_rtn_once(const Task t, const OnceArgs a
         __builtin_nontemporal_store(packed, reinterpret_cast<u32x2 *>(t.codes) + i);
         __builtin_nontemporal_store((uint8_t)c0, t.scales + i);
     }
-    if (!t.sse) return;
     sse = wave_pair_tree(sse);
     if ((tid & 63u) == 0u) s_wave[tid >> 6] = sse;
     __syncthreads();
     if (tid >= 64u) return;
     double total = (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]);
     bool flag = false;
-    if (once_sum(reinterpret_cast<uint64_t *>(t.part) + kOnceWords, &t.ctrl->epoch, epoch, args.nonce, g, G, total, flag) && tid == 0)
-        *t.sse = total;
+    // whoever has seen all G words: by then every workgroup has read the supplied maximum, so a caller may have the global
+    // scale (or the sum, or the status) written where the maximum lies, as on the path with counters
+    if (once_sum(reinterpret_cast<uint64_t *>(t.part) + kOnceWords, &t.ctrl->epoch, epoch, args.nonce, g, G, total, flag) && tid == 0) {
+        *t.gscale = gs.alpha0;
+        if (t.sse) *t.sse = total;
+        if (t.status) *t.status = bad_amax ? SOAR_STATUS_BAD_AMAX : 0;
+    }
 }
 
 }  // namespace

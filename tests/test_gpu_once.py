@@ -56,6 +56,27 @@ def test_supplied_maximum(rows, cols, dtype):
         assert int(o.status.item()) == B.SOAR_STATUS_BAD_AMAX
 
 
+@pytest.mark.parametrize("rows,cols", SHAPES + [(2048, 4096)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+def test_supplied_maximum_and_returned_scale_share_a_float(rows, cols, dtype):
+    """the scale is written after the last read of the maximum, whichever path the size takes"""
+    w = weights(rows, cols, dtype)
+    ws = B.new_workspace(rows, cols, B.soar_default_params(B.SOAR_METHOD_RTN, 0), DEV)
+    for rep in range(6):
+        amax = w.abs().max().float().reshape(1) * (0.25 + rep)
+        want = rtn(w, amax, B.SOAR_RESIDENT_NEVER, ws)
+        for wanted in ((1, 1), (0, 1), (0, 0)):          # sse and status, status, neither
+            o = B.new_outputs(rows, cols, DEV)
+            o.global_scale.copy_(amax)
+            d = B.make_desc(w, o, o.global_scale)
+            d.d_sse, d.d_status = (d.d_sse if wanted[0] else None), (d.d_status if wanted[1] else None)
+            B.quantize_batch([d], B.soar_default_params(B.SOAR_METHOD_RTN, 0), ws)
+            assert torch.equal(o.codes, want.codes) and torch.equal(o.scales, want.scales), (rep, wanted)
+            assert torch.equal(o.global_scale, want.global_scale), (rep, wanted)
+            assert not wanted[0] or math.isclose(o.sse.item(), want.sse.item(), rel_tol=1e-12)
+            assert not wanted[1] or int(o.status.item()) == 0
+
+
 # tiles of 256 blocks of 32: 1, 2, 255, 256, 257, 511, 512, 513
 @pytest.mark.parametrize("rows,cols", [(1, 32), (5, 3072), (510, 4096), (512, 4096), (513, 4096), (1022, 4096), (1024, 4096), (1025, 4096)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
