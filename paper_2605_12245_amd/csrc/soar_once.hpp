@@ -33,8 +33,7 @@ __device__ __forceinline__ bool once_sum(uint64_t *words, uint64_t *epoch_p, uin
     const uint64_t x = lane == 0u ? mine[0] : lane == 1u ? mine[1] : mine[2];
     if (lane < 3u)
         __hip_atomic_store(words + lane * kOnceMaxWG + g, (tok << P) | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_s_waitcnt(0);                                       // performed at the memory side
+    wait_then_read();
     uint64_t w[K][3];
 #pragma unroll
     for (int k = 0; k < K; ++k)
