@@ -82,7 +82,7 @@ typedef enum {
 /* the one-launch kernel for a single tensor, see soar_params.resident */
 typedef enum {
     SOAR_RESIDENT_AUTO = 0,  /* used when the tensor fits and the grid fits the GPU     */
-    SOAR_RESIDENT_NEVER = 1  /* always the three-pass path                              */
+    SOAR_RESIDENT_NEVER = 1  /* always the path of several launches                     */
 } soar_resident_mode;
 
 /* which E4M3 codes are candidates for the stored scale Delta^d (Sec. 3.3 (ii)) */
@@ -98,8 +98,10 @@ typedef enum {
                                      unspecified                                     */
 #define SOAR_STATUS_GAVE_UP   8   /* the one-launch kernel (see soar_params.resident) did not
                                      get all of its workgroups onto the GPU within
-                                     resident_wait_us and left: outputs unspecified; run the
-                                     call again, or with resident = SOAR_RESIDENT_NEVER    */
+                                     resident_wait_us.  Single-step: outputs unspecified; run
+                                     the call again, or with resident = SOAR_RESIDENT_NEVER.
+                                     Iterated path: set only if resident_wait_us was; the
+                                     outputs are complete                              */
 
 typedef struct {
     uint32_t struct_size;    /* sizeof(soar_params), for forward compatibility      */
@@ -129,22 +131,38 @@ typedef struct {
                                 the internal stream is shared by all callers, and a
                                 capture that pulls it in would swallow their work  */
     int32_t  dd_mode;        /* soar_dd_mode; dss_radius is ignored for BRACKET     */
-    int32_t  resident;       /* soar_resident_mode: may one tensor handed over alone (single-
-                                step settings, tiles_per_wg 0, at most 4096 blocks per compute
-                                unit: 2^20 blocks = 32 MiB of bf16 on an MI355X) take ONE
-                                launch that keeps the tensor in registers (iterated path: in the
-                                caches) and crosses its tensor-wide dependencies (Eq. 1 maximum,
-                                Eq. 5 sums) inside the kernel?  Same bytes as the path of several
-                                launches; on the single-step path the weights are read once.  It needs every workgroup of its grid (at most
-                                one per compute unit) on the GPU at the same time and waits
-                                for that at most resident_wait_us.  A call that arrives on
-                                another stream while an earlier such kernel may still run
-                                takes the other path instead (two of them started at once could
-                                each hold part of the GPU and wait for the rest), and so does an
-                                iterated call that is being captured into a graph             */
+    int32_t  resident;       /* soar_resident_mode: may one tensor handed over alone, with no
+                                tiles_per_wg* set, take ONE launch that crosses its tensor-wide
+                                dependencies (Eq. 1 maximum, Eq. 5 sums) inside the kernel?
+                                Same bytes as the path of several launches.  Sizes:
+                                - single-step settings: at most 4096 blocks per compute unit
+                                  (2^20 blocks = 32 MiB of bf16 on an MI355X), kept in
+                                  registers, so that the weights are read once;
+                                - iterated path, where the search is the nearest-factor one
+                                  or there is none: at most 16384 blocks per compute unit
+                                  (2^22 blocks), re-read from the caches; not while the call
+                                  is being captured into a graph.
+                                The launch needs every workgroup of its grid (at most one per
+                                compute unit) on the GPU at the same time and waits for that
+                                at most resident_wait_us.  A call that arrives on another
+                                stream while an earlier such kernel may still run takes the
+                                other path instead (two of them started at once could each
+                                hold part of the GPU and wait for the rest).  Where other
+                                processes or long-running kernels keep part of the GPU busy
+                                for longer than the bound, or the stream is restricted to
+                                some compute units, SOAR_RESIDENT_NEVER is the better choice */
     int32_t  resident_wait_us; /* 0 = library default (2 s); > 0: the bound, in microseconds,
-                                after which a workgroup of that kernel stops waiting, sets
-                                SOAR_STATUS_GAVE_UP and leaves (every workgroup then does)   */
+                                after which a workgroup of that kernel stops waiting for the
+                                others to arrive (every workgroup then does).  Single-step: all
+                                leave and set SOAR_STATUS_GAVE_UP; the bound covers a
+                                workgroup's waits together.  Iterated path: one of them, the
+                                last to leave, finishes the tensor by itself (a compute unit's
+                                speed), so the outputs are complete; the status says
+                                SOAR_STATUS_GAVE_UP beside its other bits if this field was
+                                set, and is that of a call that did not wait if it was 0.  Once
+                                all workgroups have arrived, the iterated path waits for as
+                                long as they work (at most the greater of the bound and 10 s
+                                a time)                                                       */
     int32_t  tiles_per_wg_absmax; /* single-step path: the maximum pass and the search pass   */
     int32_t  tiles_per_wg_search; /* have launch shapes of their own (the library picks them by
                                 the schedule: kernels of two launch groups share the GPU in a

@@ -680,6 +680,9 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         a.index_per_beta = index_per_beta;
         a.early_stop_rel = params->early_stop_rel;
         a.tiles = (uint32_t)plan.R;
+        a.tell = params->resident_wait_us > 0 ? (uint32_t)SOAR_STATUS_GAVE_UP : 0u;
+        const uint64_t ten_seconds = 10000ull * (uint64_t)device_facts().wall_clock_khz;
+        a.later_ticks = a.r.wait_ticks > ten_seconds ? a.r.wait_ticks : ten_seconds;
         ScopedTimer tm(SOAR_KERNEL_RESIDENT, st);
         if (d.dtype == SOAR_BF16) launch_iter_resident<SOAR_BF16>(plan, t, a, st);
         else launch_iter_resident<SOAR_FP32>(plan, t, a, st);

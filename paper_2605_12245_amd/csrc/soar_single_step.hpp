@@ -501,7 +501,8 @@ constexpr uint32_t kResDirect = 16;       // up to this many workgroups read eac
 struct ResidentArgs {
     int32_t  radius, full_search;
     uint64_t nonce;                       // new for every call
-    uint64_t wait_ticks;                  // bound of the waits of a workgroup together, in ticks of the wall clock
+    uint64_t wait_ticks;                  // in ticks of the wall clock: k_resident, bound of the waits of a workgroup together;
+                                          // k_iter_resident, of its wait for the grid to arrive
     unsigned long long *search_stats;     // null, or the diagnostic counters of count_search
 };
 

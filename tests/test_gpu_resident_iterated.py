@@ -104,6 +104,30 @@ def test_bounded_wait_gives_up_and_the_next_call_is_unaffected():
         same(*both(w, p, ws), rep)
 
 
+@pytest.mark.parametrize("rows,cols", [(65, 4096), (1024, 4096), (2047, 4096), (5500, 4096)])      # 17 to 256 workgroups, 1 to 8 tiles
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+def test_a_call_that_gives_up_is_finished_all_the_same(rows, cols, dtype):
+    """one microsecond is over before the first crossing is complete: the last workgroup to leave does the tensor"""
+    zero = torch.zeros(rows, cols, dtype=dtype, device=DEV)
+    zero[rows - 1, cols - 1] = -0.0
+    bad = heavy(rows, cols, 4, dtype)
+    bad[rows // 2, 7] = float("nan")
+    cases = [("all zero", zero, B.SOAR_METHOD_SOAR, B.SOAR_STATUS_ALLZERO), ("non-finite", bad, B.SOAR_METHOD_SOAR, B.SOAR_STATUS_NONFINITE)]
+    cases += [(arm, heavy(rows, cols, rows, dtype), arm, 0) for arm in (B.SOAR_METHOD_SOAR, B.SOAR_METHOD_CJSO_ONLY, B.SOAR_METHOD_DSS_ONLY)]
+    for what, w, arm, status in cases:
+        p = settings(arm, iters=3)
+        ws = B.new_workspace(rows, cols, p, DEV)
+        for fill in (0xFF, 0):
+            ws.fill_(fill)
+            p.resident_wait_us = 1
+            got, want = both(w, p, ws)
+            assert int(got.status.item()) == B.SOAR_STATUS_GAVE_UP | status, what
+            got.status.fill_(status)
+            same(got, want, (what, fill))
+            p.resident_wait_us = 0
+            same(*both(w, p, ws), (what, fill, "the next call"))
+
+
 def test_capture_keeps_to_the_other_path_and_two_streams_at_once():
     w = heavy(1024, 4096, 11, torch.bfloat16)
     p = settings(B.SOAR_METHOD_SOAR, iters=4)
