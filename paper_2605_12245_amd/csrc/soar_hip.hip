@@ -333,11 +333,11 @@ WantedShapes wanted_shapes(bool several_groups, int method, bool iterated, bool 
 }
 
 // Tiles per workgroup of an arithmetic-bound searching kernel over a launch of `tiles` tiles: as many as leave
-// min_wg workgroups.  The iterations run at five waves per SIMD, 1280 workgroups at once, and each of the launches
-// after the early stop costs what its workgroups take to come and go (5 us for 2048, 3 us for 1024: 175 against
+// min_wg workgroups.  The nearest-factor iterations run at five waves per SIMD, 1280 workgroups at once, and each of the
+// launches after the early stop costs what its workgroups take to come and go (5 us for 2048, 3 us for 1024: 175 against
 // 181 us on 4096 x 4096 fp32); the MXFP4 search, one launch, balances better over 2048 (210 against 223 us on a
-// decoder layer).
-constexpr int64_t kIterMinWg = 1024, kMxMinWg = 2048;
+// decoder layer), and so do iterations that last ten times as long.
+constexpr int64_t kNearestIterMinWg = 1024, kSearchMinWg = 2048;
 uint32_t search_tiles_per_wg(int64_t tiles, int64_t min_wg)
 {
     uint32_t tpw = 16;
@@ -511,9 +511,8 @@ soar_status launch_group(const Batch &b, uint32_t wg_absmax, uint32_t wg_stats, 
     return SOAR_OK;
 }
 
-// Which factor grids the nearest-factor search takes (joint_search_nearest, mx_search_nearest).  It needs a table
-// that ascends -- a grid narrower than the rounding of its own factors may not -- and evaluates at least two factors
-// per stored-scale candidate, so below four factors evaluating all of them is no more work.
+// Which factor grids the nearest-factor search can take (joint_search_nearest, mx_search_nearest): it needs a table that
+// ascends -- a grid narrower than the rounding of its own factors may not.
 constexpr int kNearestMinBeta = 4;
 bool nearest_search(int n_beta, float lo, float hi)
 {
@@ -526,6 +525,15 @@ bool nearest_search(int n_beta, float lo, float hi)
     }
     return true;
 }
+
+// Where it is also the faster one.  It evaluates two factors or more per stored-scale candidate, however few the grid has,
+// and walks the whole grid for a candidate so far below the others that a factor's step moves the error by less than
+// its rounding; the search over the changes of the codes forms every factor's codes once, and MXFP4 then takes one error per
+// change whatever the radius.  2048 x 4096 bf16, heavy-tailed or uniform, nearest / changes (window of radius K,
+// n factors): n = 4: 0.95 at K = 2, 1.05 at 3; n = 6: 0.92 at 5, 1.0 at 12; n = 101 in [0.9, 1.1]: 0.5 at 48, 1.6 at 64.  MXFP4, n = 4: 0.8 at
+// K = 1, 1.05 at 2; n = 8: 0.9 at 5, 1.1 at 6; n = 101: 0.15 to 0.25 at 5, 0.3 to 1.4 at 6, 4 to 7 at 12, 60 to 100 at 127.
+bool nearest_pays(int n_beta, int radius) { return radius <= (n_beta >= 8 ? 48 : n_beta >= 6 ? 3 * n_beta - 13 : 2); }
+bool mx_nearest_pays(int n_beta, int radius) { return radius <= 5 && radius <= n_beta - 3; }
 
 // absmax, the Eq. 1-2 state, then one launch per iteration; a tensor that has
 // stopped early (or is degenerate) makes its workgroups of the later launches return at once
@@ -654,6 +662,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
     }
 
     const bool nearest = iterated && params->search_mode == SOAR_SEARCH_AUTO &&
+                         nearest_pays(params->n_beta, params->dd_mode == SOAR_DD_BRACKET ? 0 : params->dss_radius) &&
                          nearest_search(params->n_beta, params->beta_lo, params->beta_hi);
     const float index_per_beta = nearest ? (float)(params->n_beta - 1) / (params->beta_hi - params->beta_lo) : 0.0f;
 
@@ -736,7 +745,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         const uint32_t tpw = (uint32_t)params->tiles_per_wg;
         int64_t group_tiles = 0;
         for (int32_t k = i; k < j; ++k) group_tiles += (descs[k].rows * (descs[k].cols / 16) + kWG - 1) / kWG;
-        const uint32_t searching_tpw = searching ? search_tiles_per_wg(group_tiles, kIterMinWg) : 0u;
+        const uint32_t searching_tpw = searching ? search_tiles_per_wg(group_tiles, nearest ? kNearestIterMinWg : kSearchMinWg) : 0u;
         uint32_t wg = 0, wg_absmax = 0, wg_search = 0;
         char *per_block = lane_base + (size_t)kGroupMax * kSlotBytes;
         for (int32_t k = i; k < j; ++k) {
@@ -1148,7 +1157,9 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
         if (hipGetLastError() != hipSuccess) result = SOAR_ERR_HIP;
     }
     if (lanes > 1 && result == SOAR_OK && !second->order(second->fork, st, lane_stream[1])) result = SOAR_ERR_HIP;
-    const bool nearest = params->dss && params->single_pass == 0 && nearest_search(params->n_beta, params->beta_lo, params->beta_hi);
+    const bool every = params->single_pass != 0 || params->n_beta < kChangesMinBeta;
+    const bool nearest = !every && mx_nearest_pays(params->n_beta, params->radius) &&
+                         nearest_search(params->n_beta, params->beta_lo, params->beta_hi);
     const size_t lds = (size_t)params->n_beta * sizeof(float);
     // consecutive tensors of one element type share a launch (up to kGroupMax); every kernel leaves the
     // control words of its slots as it found them, so the next group reuses them
@@ -1180,7 +1191,7 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
             t.contiguous = d.ld_elems == d.cols ? 1u : 0u;
             const uint32_t tiles = (t.nblk + kWG - 1) / kWG;
             // the search is arithmetic-bound (see search_tiles_per_wg); the plain conversion streams
-            uint32_t tpw = params->dss ? search_tiles_per_wg(group_tiles, kMxMinWg) : 2u;
+            uint32_t tpw = params->dss ? search_tiles_per_wg(group_tiles, kSearchMinWg) : 2u;
             while (tpw > 1 && tpw > tiles) tpw >>= 1;
             if (params->tiles_per_wg) tpw = (uint32_t)params->tiles_per_wg;
             while ((tiles + tpw - 1) / tpw > (uint32_t)kMaxPartials) tpw <<= 1;
@@ -1192,24 +1203,20 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
             t.ctrl = reinterpret_cast<Ctrl *>(slot);
             t.counters = reinterpret_cast<uint32_t *>(slot + kCtrlBytes);
             t.part = reinterpret_cast<double *>(slot + kZeroedBytes);
-            t.dss = params->dss;
             t.n_beta = params->n_beta;
             t.radius = params->radius;
             t.beta_lo = params->beta_lo;
             t.beta_hi = params->beta_hi;
-            t.nearest = nearest ? 1 : 0;
             t.index_per_beta = nearest ? (float)(params->n_beta - 1) / (params->beta_hi - params->beta_lo) : 0.0f;
         }
         ScopedTimer tm(SOAR_KERNEL_MX, lst);
-        // the plain conversion is an instantiation of its own: it needs half the registers of the search
+        // an instantiation each: the plain conversion needs half the registers of a search
         const bool bf16 = descs[i].dtype == SOAR_BF16;
-        if (params->dss) {
-            if (bf16) hipLaunchKernelGGL((k_mx<SOAR_BF16, true>), dim3(wg), dim3(kWG), lds, lst, b);
-            else hipLaunchKernelGGL((k_mx<SOAR_FP32, true>), dim3(wg), dim3(kWG), lds, lst, b);
-        } else {
-            if (bf16) hipLaunchKernelGGL((k_mx<SOAR_BF16, false>), dim3(wg), dim3(kWG), lds, lst, b);
-            else hipLaunchKernelGGL((k_mx<SOAR_FP32, false>), dim3(wg), dim3(kWG), lds, lst, b);
-        }
+        auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(wg), dim3(kWG), lds, lst, b); };
+        if (!params->dss) launch(bf16 ? k_mx<SOAR_BF16, Mx::PLAIN> : k_mx<SOAR_FP32, Mx::PLAIN>);
+        else if (nearest) launch(bf16 ? k_mx<SOAR_BF16, Mx::NEAREST> : k_mx<SOAR_FP32, Mx::NEAREST>);
+        else if (every) launch(bf16 ? k_mx<SOAR_BF16, Mx::EVERY> : k_mx<SOAR_FP32, Mx::EVERY>);
+        else launch(bf16 ? k_mx<SOAR_BF16, Mx::CHANGES> : k_mx<SOAR_FP32, Mx::CHANGES>);
         if (hipGetLastError() != hipSuccess) result = SOAR_ERR_HIP;
         i = j;
     }

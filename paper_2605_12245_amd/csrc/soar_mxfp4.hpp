@@ -27,11 +27,15 @@ struct MxTask {
     Ctrl     *ctrl;          // amax_bits is used as the "saw a non-finite value" flag
     uint32_t *counters;
     double   *part;
-    int32_t  dss, n_beta, radius;
-    int32_t  nearest;        // search: only the factors that can win (mx_search_nearest)
+    int32_t  n_beta, radius;
     float    beta_lo, beta_hi;
     float    index_per_beta;
 };
+
+// What k_mx does with a block.  NEAREST: the factors that can win are found without walking the grid (mx_search_nearest,
+// see nearest_search); CHANGES: codes of every factor, errors where they change (mx_search_changes); EVERY: all factors
+// (mx_search: single_pass, grids of fewer than kChangesMinBeta factors)
+enum class Mx { PLAIN, EVERY, CHANGES, NEAREST };
 
 struct MxBatch {
     MxTask   t[kGroupMax];
@@ -169,6 +173,70 @@ __device__ __forceinline__ void mx_search(const float w[32], int e0, const float
     }
 }
 
+template <bool FAST>
+__device__ __forceinline__ void mx_codes_only(const float w[32], float scale, uint32_t nib[4])
+{
+    const float r = FAST ? rcp_midrange(scale) : 1.0f / scale;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = w[8 * h + j] * r;
+        uint32_t v = nib[h];
+        v = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(v, x[0], x[1], 1.0f, 0);
+        v = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(v, x[2], x[3], 1.0f, 1);
+        v = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(v, x[4], x[5], 1.0f, 2);
+        v = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(v, x[6], x[7], 1.0f, 3);
+        nib[h] = v;
+    }
+}
+
+// mx_search in two passes, as joint_search_changes: codes of every factor first, errors only where this block's change;
+// one window minimum per change, whatever the radius
+template <bool FAST>
+__device__ __forceinline__ void mx_search_changes(const float w[32], int e0, const float *s_beta, int n_beta, int radius,
+                                                  float &best_err, int &best_code, uint32_t best_nib[4], float q[32])
+{
+    const float x0 = e8m0_value(e0);
+    uint32_t nib[4] = {0u, 0u, 0u, 0u}, even[4] = {0u, 0u, 0u, 0u}, odd[4] = {0u, 0u, 0u, 0u};
+    auto differ = [&]() { return ((even[0] ^ odd[0]) | (even[1] ^ odd[1]) | (even[2] ^ odd[2]) | (even[3] ^ odd[3])) != 0u; };
+    float best = __builtin_inff();
+    float best_beta = s_beta[0];
+    for (int base = 0; base < n_beta; base += kStretch) {
+        ChangeSet set;
+        for (int first = base; first < min(n_beta, base + kStretch); first += 32) {
+            uint32_t word = first == 0 ? 1u : 0u;
+            for (int k = 0; k < min(n_beta - first, 32); k += 2) {
+                mx_codes_only<FAST>(w, x0 * s_beta[first + k], even);
+                word |= differ() ? 1u << k : 0u;
+                if (first + k + 1 == n_beta) break;
+                mx_codes_only<FAST>(w, x0 * s_beta[first + k + 1], odd);
+                word |= differ() ? 2u << k : 0u;
+            }
+            set.push(word);
+        }
+        set.settle();
+        while (__builtin_amdgcn_ballot_w64(!set.empty()) != 0ull) {
+            if (!set.empty()) {
+                const float bk = s_beta[base + set.pop()];
+                mx_assign<FAST>(w, x0 * bk, nib, q);
+                const float m = mx_window_min(w, q, e0, radius);
+                best_beta = (m < best) ? bk : best_beta;
+                best = fminf(best, m);
+            }
+        }
+    }
+    best_nib[0] = best_nib[1] = best_nib[2] = best_nib[3] = 0u;
+    mx_assign<FAST>(w, x0 * best_beta, best_nib, q);
+    best_code = e0;
+    best_err = mx_block_error(w, q, x0);
+    for (int c = 1; c <= 2 * radius; ++c) {
+        const int code = mx_candidate(e0, c);
+        const float e = mx_block_error(w, q, e8m0_value(code));
+        if (e < best_err) { best_err = e; best_code = code; }
+    }
+}
+
 // mx_search without walking the factor grid: joint_search_nearest's argument, with the power of two X0 in the place
 // of alpha Delta* -- so which factors enclose a candidate scale is the same for every block of the launch
 // (the paper's grid and K = 1: seven pairs of 303).  One decoder layer (1.93e8 bf16 weights): 3.70 -> 0.21 ms a call.
@@ -254,9 +322,10 @@ __device__ __forceinline__ void mx_search_nearest(const float w[32], int e0, con
     }
 }
 
-template <int DT, bool DSS>
+template <int DT, Mx MODE>
 __global__ __launch_bounds__(kWG) void k_mx(const MxBatch batch)
 {
+    constexpr bool DSS = MODE != Mx::PLAIN;
     __shared__ double s_wave[1][4];
     __shared__ double s_stack[1][32];
     __shared__ double s_tree[kWG];
@@ -322,16 +391,22 @@ __global__ __launch_bounds__(kWG) void k_mx(const MxBatch batch)
                 err = mx_block_error(w, q, x0);
             } else {
                 // far enough from the ends of the binary32 range for the nearest-factor search (factors within
-                // 2^-20 .. 2^20: the host); elsewhere the plain loop, whose reciprocal shortcut needs the scales
-                // X0 beta_k to stay within biased exponents [1, 252]
+                // 2^-20 .. 2^20: the host)?  Elsewhere the reciprocal shortcut needs the scales X0 beta_k to stay within
+                // biased exponents [1, 252].
                 const bool near = (uint32_t)(e0 - 67) < 120u;
-                if (t.nearest && __builtin_amdgcn_ballot_w64(!near) == 0ull) {
+                if (MODE == Mx::NEAREST && __builtin_amdgcn_ballot_w64(!near) == 0ull) {
                     mx_search_nearest(w, e0, grid, t.radius, err, code, nib);
                 } else {
                     const float s_first = e8m0_value(e0) * s_beta[0], s_final = e8m0_value(e0) * s_beta[n_beta - 1];
                     const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
-                    if (__builtin_amdgcn_ballot_w64(!mid) == 0ull) mx_search<true>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
-                    else mx_search<false>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
+                    const bool fast = __builtin_amdgcn_ballot_w64(!mid) == 0ull;
+                    if constexpr (MODE == Mx::EVERY) {
+                        if (fast) mx_search<true>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
+                        else mx_search<false>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
+                    } else {
+                        if (fast) mx_search_changes<true>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
+                        else mx_search_changes<false>(w, e0, s_beta, n_beta, t.radius, err, code, nib, q);
+                    }
                 }
             }
             term[0] = (double)err;

@@ -332,7 +332,7 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
         }
 
         // ---- the iterations
-        JointSearch js{{s_beta, args.n_beta, args.beta_lo, args.index_per_beta}, 0.0f, 0.0f, args.r.radius, args.bracket != 0, keep_scale, false};
+        JointSearch js{{s_beta, args.n_beta, args.beta_lo, args.index_per_beta}, 0.0f, 0.0f, args.r.radius, args.bracket != 0, keep_scale, false, false};
         for (uint32_t it = 0; it < (uint32_t)args.iters; ++it) {
             const float alpha = s_alpha;
             js.set_alpha(alpha, amax_bits);

@@ -175,3 +175,81 @@ def test_mxfp4_search_modes_agree(kw, dtype):
             out = [B.mx_quantize(w, B.soar_mx_default_params(single_pass=single, **kw)) for single in (False, True)]
             torch.cuda.synchronize()
             same(*out, (name, cols, kw))
+
+
+# Both sides of the lines at which AUTO changes from the factors next to a candidate to the changes of the codes (radius
+# 48; fewer than eight factors: 2 to 8), the widest window, and grids around the 128 factors that are looked through at once
+WIDE = [dict(n_beta=4, dss_radius=2), dict(n_beta=4, dss_radius=3), dict(n_beta=5, dss_radius=3), dict(n_beta=6, dss_radius=5),
+        dict(n_beta=6, dss_radius=6), dict(n_beta=7, dss_radius=8), dict(n_beta=7, dss_radius=9), dict(n_beta=8, dss_radius=48),
+        dict(n_beta=8, dss_radius=49), dict(dss_radius=48), dict(dss_radius=49), dict(dss_radius=125), dict(n_beta=32, dss_radius=125),
+        dict(n_beta=33, dss_radius=60), dict(n_beta=127, dss_radius=60), dict(n_beta=128, dss_radius=60), dict(n_beta=129, dss_radius=60),
+        dict(n_beta=161, beta_lo=0.01, beta_hi=30.0, dss_radius=60), dict(n_beta=300, dss_radius=125)]
+
+
+def ends_of_the_range(dtype, cols, low, high):
+    """rows whose largest magnitudes run through the powers of two around both ends of a range"""
+    g = torch.Generator(device="cpu").manual_seed(cols + 1)
+    return [("low end", torch.cat([torch.randn(4, cols, generator=g) * 2.0 ** e for e in range(low - 3, low + 4)]).to(dtype).to(DEV)),
+            ("high end", torch.cat([torch.randn(4, cols, generator=g) * 2.0 ** e for e in range(high - 3, high + 4)]).to(dtype).to(DEV))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("kw", WIDE, ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()))
+def test_nvfp4_wide_windows_and_ends_of_the_range_agree(kw, dtype):
+    # the global scale, about 1/2688 of the maximum, leaves the nearest search at 2^-35 and 2^50; the maximum at 2^60
+    tensors = inputs(dtype, 272) + ends_of_the_range(dtype, 48, -24, 58) + [(f"2^{e}", inputs(dtype, 48)[0][1] * 2.0 ** e) for e in (-18, -19, -20)]
+    for arm in (None, B.SOAR_METHOD_DSS_ONLY):
+        for name, w in tensors:
+            out = []
+            for mode, resident in ((B.SOAR_SEARCH_AUTO, 0), (B.SOAR_SEARCH_AUTO, 1), (B.SOAR_SEARCH_FULL, 0)):
+                k = dict(kw, iters=2, early_stop_rel=0.0)
+                p = B.soar_arm_params(arm, **k) if arm else B.soar_paper_params(dd_mode=B.SOAR_DD_WINDOW, **k)
+                p.search_mode, p.resident = mode, resident
+                out.append(B.quantize_iter(w, p))
+            torch.cuda.synchronize()
+            same(out[0], out[2], (name, kw, arm))
+            same(out[1], out[2], (name, kw, arm))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("kw", [dict(n_beta=n, radius=r) for n, r in ((4, 1), (4, 2), (5, 2), (5, 3), (7, 4), (7, 5), (8, 5), (8, 6), (101, 5), (101, 6),
+                                                                      (101, 8), (101, 16), (101, 127), (128, 16), (129, 16), (31, 127), (300, 127))],
+                         ids=lambda kw: "-".join(f"{k}{v}" for k, v in kw.items()))
+def test_mxfp4_wide_windows_and_ends_of_the_range_agree(kw, dtype):
+    # block scales leave the nearest search below 2^(67 - 127) and above 2^(186 - 127), that is maxima below 2^-58 and above 2^61
+    for name, w in inputs(dtype, 288) + ends_of_the_range(dtype, 96, -59, 60) + ends_of_the_range(dtype, 96, -118, 120):
+        out = [B.mx_quantize(w, B.soar_mx_default_params(single_pass=single, **kw)) for single in (False, True)]
+        torch.cuda.synchronize()
+        same(*out, (name, kw))
+
+
+def milliseconds(run):
+    run()
+    times = []
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record(); run(); b.record()
+        torch.cuda.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
+
+
+@pytest.mark.gpu
+def test_the_default_search_is_not_the_slower_one():
+    """whatever the radius, the grid and the magnitudes: evaluating every pair takes no less time (half as long again is
+    allowed for noise; wide windows once took up to twelve times as long)"""
+    w = inputs(torch.bfloat16, 4096)[0][1].repeat(4, 1)
+    for n, r in ((4, 1), (4, 16), (101, 1), (101, 8), (101, 16), (101, 127), (400, 32)):
+        auto, every = (milliseconds(lambda: B.mx_quantize(w, B.soar_mx_default_params(n_beta=n, radius=r, single_pass=s))) for s in (False, True))
+        assert auto <= 1.5 * every, ("mxfp4", n, r, auto, every)
+    for f in (1.0, 2.0 ** -30):
+        for n, r in ((4, 1), (4, 16), (16, 1.0), (101, 2), (101, 64), (101, 125), (400, 32)):
+            out = []
+            for mode in (B.SOAR_SEARCH_AUTO, B.SOAR_SEARCH_FULL):
+                p = B.soar_paper_params(iters=2, early_stop_rel=0.0, n_beta=n, dd_mode=B.SOAR_DD_WINDOW, dss_radius=int(r),
+                                        **(dict(beta_lo=1.0, beta_hi=1.0) if r == 1.0 and n == 16 else {}))
+                p.search_mode = mode
+                out.append(milliseconds(lambda: B.quantize_iter(w * f, p)))
+            assert out[0] <= 1.5 * out[1], ("nvfp4", f, n, r, out)
