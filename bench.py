@@ -492,7 +492,7 @@ def run(args):
         "weights_per_s": E / (ms_per_step * 1e-3),
         "hbm_frac_3pass": (BYTES_3PASS * E / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS) if not rtn_amax else None,
         "hbm_frac_3pass_note": "algorithmic bytes per weight (three reads of the weights, codes and scales written once) / "
-                               "time / 8 TB/s: a rate of bytes the method has to touch.  Launch groups of at most 208 MiB "
+                               "time / 8 TB/s: a rate of bytes the method has to touch.  Launch groups of at most 256 MiB "
                                "are found in the last-level cache by the second and third pass, so this is not a DRAM "
                                "rate for workloads 1-4; workload 5 (470 MB tensors: nothing stays cached) is",
         "hbm_frac_single_touch": BYTES_SEARCH * E / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,

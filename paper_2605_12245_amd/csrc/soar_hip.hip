@@ -398,8 +398,28 @@ int64_t weight_bytes(const soar_tensor_desc &d) { return d.rows * d.cols * (d.dt
 
 constexpr int64_t kOnePassByteCap = (int64_t)1 << 29;    // larger launches gain nothing more (measured: 2^29 .. 2^31)
 
-int32_t group_end(int32_t n, const soar_tensor_desc *descs, int32_t first, int64_t cap)
+// Bytes of weights one launch may cover beyond its first tensor, by element type.
+struct GroupCaps { int64_t bf16, fp32; };
+
+// Two launch groups are on the machine at once (see SecondLane), and how much of the 256 MiB last-level cache each takes
+// -- weights, ratios, outputs -- decides what the later passes still find there.  256 MiB of fp32 weights hold half the
+// blocks of as many bytes of bf16.  Measured as 208 / 256 MiB over ten layer widths, hidden 2560 to 8192 (us a call, two
+// to four runs that differ by less than 1 %):
+//   bf16, three passes, 8 layers   12288 wide 1660 / 1733, 14336 1941 / 2075, 11008 1708 / 1785, 13824 2742 / 2887, 8192
+//                                  975 / 1005, 9728 855 / 869; 16384, 18944, 22016: the same
+//   bf16, iterated without search  11008 2168 / 2277, 13824 3351 / 3540, 12288 2194 / 2216, 8192 1276 / 1265, others the same
+//   fp32, three passes, 4 layers   11008 1755 / 1710, 13824 (k, v of 1024) 2437 / 2336, 12288 1624 / 1641, others within 1 %
+//   fp32, iterated without search  11008 3532 / 3658, 9728 1736 / 1862, 8192 1957 / 1898, others within 2 %
+//   bf16, plain (two passes)       36 layers 12288 wide 4796 / 4645, 8 layers 1092 / 1067, 13824 1757 / 1833, others within 2 %
+// So 208 MiB where bf16 weights are read three times or more: there no width loses more than 1 %.  Elsewhere some widths
+// gain and others lose by how their matrices happen to fall into groups, and a group may fill the cache.  With 160 to 190 MiB,
+// which part the two largest matrices of a 12288 wide layer, the three passes took 7.7 ms for 36 layers, with 208 7.2.
+constexpr int64_t kThreePassByteCap = (int64_t)208 << 20;
+constexpr GroupCaps kCacheCaps = {kLastLevelCache, kLastLevelCache};
+
+int32_t group_end(int32_t n, const soar_tensor_desc *descs, int32_t first, const GroupCaps &caps)
 {
+    const int64_t cap = descs[first].dtype == SOAR_BF16 ? caps.bf16 : caps.fp32;
     int64_t bytes = weight_bytes(descs[first]);
     int32_t j = first + 1;
     while (j < n && j - first < kGroupMax && descs[j].dtype == descs[first].dtype &&
@@ -410,23 +430,22 @@ int32_t group_end(int32_t n, const soar_tensor_desc *descs, int32_t first, int64
     return j;
 }
 
-// bytes of weights one launch may cover (beyond its first tensor)
-int64_t group_byte_cap(int32_t n, const soar_tensor_desc *descs)
+GroupCaps group_caps(int32_t n, const soar_tensor_desc *descs, int method)
 {
     // with the maximum supplied there is one pass only: nothing to keep in the last-level cache
-    if (descs[0].d_amax_in) return kOnePassByteCap;
+    if (descs[0].d_amax_in) return {kOnePassByteCap, kOnePassByteCap};
     // what is one group up to the size of the cache stays on the caller's stream (and may be captured into a graph)
-    if (group_end(n, descs, 0, kLastLevelCache) == n) return kLastLevelCache;
-    return kGroupByteCap;      // a group stays in the last-level cache from pass to pass, iteration to iteration
+    if (method == SOAR_METHOD_RTN || group_end(n, descs, 0, kCacheCaps) == n) return kCacheCaps;
+    return {kThreePassByteCap, kLastLevelCache};
 }
 
 // most per-block workspace any one launch of the batch needs
-size_t max_group_per_block_bytes(int32_t n, const soar_tensor_desc *descs, int64_t cap, int32_t *n_groups)
+size_t max_group_per_block_bytes(int32_t n, const soar_tensor_desc *descs, const GroupCaps &caps, int32_t *n_groups)
 {
     size_t most = 0;
     int32_t groups = 0;
     for (int32_t i = 0; i < n;) {
-        const int32_t j = group_end(n, descs, i, cap);
+        const int32_t j = group_end(n, descs, i, caps);
         size_t sum = 0;
         for (int32_t k = i; k < j; ++k) sum += per_block_bytes(descs[k].rows, descs[k].cols);
         if (sum > most) most = sum;
@@ -444,11 +463,18 @@ size_t max_group_per_block_bytes(int32_t n, const soar_tensor_desc *descs, int64
 
 size_t lane_workspace_bytes(size_t group_per_block) { return (size_t)kGroupMax * kSlotBytes + group_per_block; }
 
+// The same for every method, so that a workspace sized once serves calls of all of them: the larger of what each grouping
+// needs
 size_t batch_workspace_bytes(int32_t n, const soar_tensor_desc *descs)
 {
-    int32_t groups = 0;
-    const size_t most = max_group_per_block_bytes(n, descs, group_byte_cap(n, descs), &groups);
-    return (groups > 1 ? kLanes : 1) * lane_workspace_bytes(most);
+    size_t bytes = 0;
+    for (int method : {(int)SOAR_METHOD_RTN, (int)SOAR_METHOD_SOAR}) {
+        int32_t groups = 0;
+        const size_t most = max_group_per_block_bytes(n, descs, group_caps(n, descs, method), &groups);
+        const size_t need = (groups > 1 ? kLanes : 1) * lane_workspace_bytes(most);
+        bytes = need > bytes ? need : bytes;
+    }
+    return bytes;
 }
 
 // What a batch of two or more launch groups needs beside the caller's stream: one stream per GPU
@@ -700,8 +726,8 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
     }
 
     int32_t n_groups = 0;
-    const int64_t cap = group_byte_cap(n, descs);
-    const size_t lane_bytes = lane_workspace_bytes(max_group_per_block_bytes(n, descs, cap, &n_groups));
+    const GroupCaps caps = group_caps(n, descs, params->method);
+    const size_t lane_bytes = lane_workspace_bytes(max_group_per_block_bytes(n, descs, caps, &n_groups));
     const int lanes = (n_groups > 1 && params->streams != 1) ? kLanes : 1;
     char *base = static_cast<char *>(d_workspace);
 
@@ -723,7 +749,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
     if (lanes > 1 && result == SOAR_OK && !second->order(second->fork, st, lane_stream[1])) result = SOAR_ERR_HIP;
     int32_t g = 0;
     for (int32_t i = 0; i < n && result == SOAR_OK; ++g) {
-        const int32_t j = group_end(n, descs, i, cap);
+        const int32_t j = group_end(n, descs, i, caps);
         const int lane = g % lanes;
         char *lane_base = base + (size_t)lane * lane_bytes;
         Batch b;

@@ -239,7 +239,7 @@ def milliseconds(run):
 @pytest.mark.gpu
 def test_the_default_search_is_not_the_slower_one():
     """whatever the radius, the grid and the magnitudes: evaluating every pair takes no less time (half as long again is
-    allowed for noise; wide windows once took up to twelve times as long)"""
+    allowed for noise; wide windows and short grids took several times as long with the nearest-factor search alone)"""
     w = inputs(torch.bfloat16, 4096)[0][1].repeat(4, 1)
     for n, r in ((4, 1), (4, 16), (101, 1), (101, 8), (101, 16), (101, 127), (400, 32)):
         auto, every = (milliseconds(lambda: B.mx_quantize(w, B.soar_mx_default_params(n_beta=n, radius=r, single_pass=s))) for s in (False, True))
