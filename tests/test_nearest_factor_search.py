@@ -4,117 +4,202 @@ On the CPU a numpy model of the rule (which factors are evaluated, when the walk
 is compared with the plain double loop; on the GPU the kernels' two search modes are compared with each other, over
 the orders, grids, magnitudes and inputs that the rule accepts.  Everything has to be equal bit for bit.
 """
+import os
+import re
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
 from paper_2605_12245_amd import binding as B
+from paper_2605_12245_amd import build
 
 F = np.float32
 DEV = "cuda:0"
 
 
 # ------------------------------------------------------------------ CPU: the rule itself
+SOURCE = "".join(open(os.path.join(build.HERE, "csrc", f)).read() for f in ("soar_iterated.hpp", "soar_mxfp4.hpp"))
+FAR_SIDE = {n: F(re.search(rf"kFarSideRounding{n} = ([0-9.e-]+)f", SOURCE).group(1)) for n in (16, 32)}
+SLACK = F(2.0 ** -21)
+
+
 def grid_of(n, lo, hi):
-    return [F(F(F(lo) * F(n - 1 - k)) + F(F(hi) * F(k))) / F(n - 1) for k in range(n)]
+    return np.array([F(F(F(lo) * F(n - 1 - k)) + F(F(hi) * F(k))) / F(n - 1) for k in range(n)], dtype=np.float32)
 
 
-def codes_at(w, t):
-    with np.errstate(all="ignore"):
-        return oracle.e2m1_nibble_many(w * (F(1.0) / t))
+def fma(a, b, c):
+    """binary64 operations rounded to binary32 stand in for the fused ones"""
+    return F(float(a) * float(b) + float(c))
 
 
 VALUES = np.array([0, .5, 1, 1.5, 2, 3, 4, 6, -0., -.5, -1, -1.5, -2, -3, -4, -6], dtype=np.float64)
 
 
-def error_of(w, nib, s):
-    """the ascending fused chain (binary64 operations rounded to binary32 stand in for the fused ones)"""
-    err = F(0.0)
-    for x, q in zip(w, VALUES[nib]):
-        e = F(float(x) - q * float(s))
-        err = F(float(e) * float(e) + float(err))
-    return err
+class Block:
+    """codes of a block at every factor, and errors for a stored scale by the ascending fused chain"""
+
+    def __init__(self, w, base, grid):
+        with np.errstate(all="ignore"):
+            self.t = (F(base) * grid).astype(np.float32)
+            self.nib = np.stack([oracle.e2m1_nibble_many((w * (F(1.0) / t)).astype(np.float32)) for t in self.t])
+        self.w, self.grid, self.base = w, grid, F(base)
+
+    def errors(self, s):
+        err = np.zeros(len(self.grid), np.float32)
+        with np.errstate(over="ignore"):
+            for j, x in enumerate(self.w):
+                e = (float(x) - VALUES[self.nib[:, j]] * float(s)).astype(np.float32).astype(np.float64)
+                err = (e * e + err.astype(np.float64)).astype(np.float32)
+        return err
 
 
-def plain_loop(w, base, grid, scales):
-    best = None
-    for k, beta in enumerate(grid):
-        nib = codes_at(w, F(base * beta))
-        for c, s in enumerate(scales):
-            e = error_of(w, nib, s)
-            if best is None or e < best[0]:
-                best = (e, c, tuple(nib))
-    return best
+def plain_loop(block, scales):
+    """factors ascending, for each the candidates in their order, the first smallest error wins"""
+    table = np.stack([block.errors(s) for s in scales], axis=1)
+    k, c = divmod(int(table.reshape(-1).argmin()), len(scales))
+    return table[k, c], c, tuple(block.nib[k])
 
 
-def excluded(s, t, e):
-    rounding = F(1.0e-5)
-    distance = F(abs(F(s - t)) - F(2.0 ** -22) * max(s, t))
-    return s < F(2.0 ** 60) and F(s * distance) > F(float(rounding) * float(e) + 2.0 ** -98)
+def best_factor(block, err, s, ka, kb, rounding, slack):
+    """the kernels' best_factor and mx_best_factor from the pair ka <= kb on: the walks outwards and their certificate"""
+    last = len(block.grid) - 1
+    per_error = F(s * F(F(1.0) / rounding))
+    slack = F(s * F(slack * per_error))
+
+    def far(distance, e):
+        with np.errstate(over="ignore"):
+            return fma(distance, per_error, -slack) > e
+
+    t, best, k, seen = block.t, err[ka], ka, 1 + (kb != ka)
+    if err[kb] < best:
+        best, k = err[kb], kb
+    lo, hi = ka, kb
+    down = lo > 0 and not far(F(s - t[ka]), err[ka])
+    up = hi < last and not far(F(t[kb] - s), err[kb])
+    while down or up:
+        kk = lo = lo - 1 if down else lo
+        if not down:
+            kk = hi = hi + 1
+        seen += 1
+        gone = far(F(s - t[kk]) if down else F(t[kk] - s), err[kk])
+        if err[kk] < best or (err[kk] == best and kk < k):
+            best, k = err[kk], kk
+        if down:
+            down = not gone and lo > 0
+        else:
+            up = not gone and hi < last
+    return best, k, seen
 
 
-def nearest(w, base, grid, scales, offset):
-    """offset: how far off the estimate of the enclosing pair is (the result must not depend on it)"""
-    n, best, count = len(grid), None, 0
+def start_pair(block, s, off):
+    """joint_search_nearest: the estimate of where s lies, off by `off`, clamped to the grid"""
+    n = len(block.grid)
+    per_beta = F(F(n - 1) / F(block.grid[-1] - block.grid[0]))
+    at = fma(s, F(F(F(1.0) / block.base) * per_beta), -F(block.grid[0] * per_beta))
+    ka = int(min(max(at, F(0.0)), F(n - 2)))
+    ka = min(max(ka + off, 0), n - 2)
+    return ka, ka + 1
 
-    def pair(k, c, s):
-        nonlocal best, count
-        t = F(base * grid[k])
-        nib = tuple(codes_at(w, t))
-        e = error_of(w, np.array(nib), s)
-        count += 1
-        if best is None or e < best[0] or (e == best[0] and k < best[3] and nib != best[2]):
-            best = (e, c, nib, k)
-        return t, e
 
+def start_pair_mx(block, s, off):
+    """mx_search_nearest: one factor where s lies below the grid, else the two around it"""
+    n = len(block.grid)
+    at = F(F(F(s / block.base) - block.grid[0]) * F(F(n - 1) / F(block.grid[-1] - block.grid[0])))
+    lo = int(min(max(at, F(0.0)), F(n - 1)))
+    lo = min(max(lo + off, 0), n - 1)
+    return lo, lo if at < 0 else min(lo + 1, n - 1)
+
+
+def nearest(block, scales, off=0, weaken=1.0, slack=SLACK):
+    """candidates in their order; a tie goes to the smaller factor unless both give the same codes"""
+    size = len(block.w)
+    win, seen = None, 0
     for c, s in enumerate(scales):
-        km = min(range(n), key=lambda k: abs(float(base) * float(grid[k]) - float(s)))
-        km = min(max(km + offset, 0), n - 1)
-        split = km + (1 if F(base * grid[km]) <= s else 0)
-        ka, kb = max(split - 1, 0), min(split, n - 1)
-        t, e = pair(ka, c, s)
-        while ka > 0 and not (t <= s and excluded(s, t, e)):
-            ka -= 1
-            t, e = pair(ka, c, s)
-        t, e = pair(kb, c, s)
-        while kb < n - 1 and not (t >= s and excluded(s, t, e)):
-            kb += 1
-            t, e = pair(kb, c, s)
-    return best[:3], count
+        err = block.errors(s)
+        ka, kb = (start_pair if size == 16 else start_pair_mx)(block, s, off)
+        e, k, n = best_factor(block, err, s, ka, kb, F(FAR_SIDE[size] * F(weaken)), slack)
+        seen += n
+        nib = tuple(block.nib[k])
+        if win is None or e < win[0] or (e == win[0] and k < win[3] and nib != win[2]):
+            win = (e, c, nib, k)
+    return win[:3], seen
 
 
+def blocks(size, rng, trials):
+    """weights and base scales: heavy-tailed, on the grid, on the thresholds, a dominating outlier, sparse, zero; magnitudes
+    over the range in which the kernels take this search (global scales 2^-35 .. 2^50 times stored scales; E8M0 codes 67 .. 186)"""
+    for trial in range(trials):
+        kind = trial % 6
+        e = int(rng.integers(-30, 30)) if trial % 3 else (int(rng.choice([-44, -43, 55, 56])) if size == 16 else int(rng.choice([-60, -59, 58, 59])))
+        scale = F(2.0 ** e)
+        w = rng.standard_t(4, size).astype(np.float32)
+        if kind == 1:
+            w = rng.integers(-6, 7, size).astype(np.float32)
+        elif kind == 2:
+            w = rng.choice(np.array([0, .25, .75, 1.25, 1.75, 2.5, 3.5, 5], np.float32), size)
+        elif kind == 3:
+            w[3] = 13.0
+        elif kind == 4:
+            w[rng.random(size) < 0.8] = 0.0
+        elif kind == 5:
+            w[:] = 0.0
+            w[rng.integers(0, size)] = -0.0
+        base = scale if size == 32 or kind in (1, 2) else F(scale * F(rng.uniform(0.3, 1.2)))
+        yield trial, kind, (w * scale).astype(np.float32), base
+
+
+@pytest.mark.parametrize("size", [16, 32])
 @pytest.mark.parametrize("n,lo,hi", [(101, 0.5, 1.5), (4, 0.9, 1.1), (21, 0.3, 0.7), (33, 1.25, 4.0), (257, 0.95, 1.05)])
-def test_rule_equals_the_plain_loop(n, lo, hi):
-    rng = np.random.default_rng(n)
+def test_rule_equals_the_plain_loop(n, lo, hi, size):
     grid = grid_of(n, lo, hi)
     assert all(a <= b for a, b in zip(grid, grid[1:]))
     evaluated = total = 0
-    for trial in range(24):
-        scale = F(2.0 ** rng.integers(-30, 30))
-        kind = trial % 6
-        w = rng.standard_t(4, 16).astype(np.float32)
-        if kind == 1:
-            w = rng.integers(-6, 7, 16).astype(np.float32)              # exact ties at and between the thresholds
-        elif kind == 2:
-            w = rng.choice(np.array([0, .25, .75, 1.25, 1.75, 2.5, 3.5, 5], np.float32), 16)   # on the thresholds
-        elif kind == 3:
-            w[3] = 40.0                                                 # far beyond the largest code
-        elif kind == 4:
-            w[rng.random(16) < 0.8] = 0.0
-        elif kind == 5:
-            w[:] = 0.0
-            w[rng.integers(0, 16)] = -0.0
-        w = (w * scale).astype(np.float32)
-        base = F(scale * F(1.0 if kind in (1, 2) else rng.uniform(0.3, 1.2)))
-        for scales in ([F(base * F(0.9375)), F(base * F(1.0))], [base, F(base * F(0.5)), F(base * F(2.0))], [F(base * F(0.25)), F(base * F(8.0))]):
-            want = plain_loop(w, base, grid, scales)
-            for offset in (0, -1, 1) if trial % 4 == 0 else (0,):
-                got, count = nearest(w, base, grid, scales, offset)
-                assert got[0] == want[0] and got[1] == want[1] and got[2] == want[2], (trial, kind, scales, offset)
-                if offset == 0:
-                    evaluated, total = evaluated + count, total + n * len(scales)
+    for trial, kind, w, base in blocks(size, np.random.default_rng(n + size), 24):
+        block = Block(w, base, grid)
+        if size == 16:
+            windows = ([F(base * F(0.9375)), base], [base, F(base * F(0.5)), F(base * F(2.0))], [F(base * F(0.25)), F(base * F(8.0))],
+                       [F(base * F(2.0 ** -o)) for o in range(0, 12, 3)])
+        else:
+            windows = ([base, F(base / 2), F(base * 2)], [base] + [F(base * F(2.0 ** o)) for k in range(1, 7) for o in (-k, k)])
+        for scales in windows:
+            want = plain_loop(block, scales)
+            for off in (0, -1, 1, 3, -n) if size == 16 else (0,):       # the estimate may be off; the power of two is exact
+                got, seen = nearest(block, scales, off)
+                assert got == want, (trial, kind, scales, off)
+                if off == 0 and len(scales) < 5:
+                    evaluated, total = evaluated + seen, total + n * len(scales)
     assert evaluated < total / (2 if n > 20 else 1)
+
+
+@pytest.mark.parametrize("size", [16, 32])
+@pytest.mark.parametrize("weaken,slack,sound", [(1.0, SLACK, True), (2.0 ** -8, SLACK, False), (1.0e-20, F(0.0), False)],
+                         ids=["as it is", "a 256th of the rounding", "no rounding"])
+def test_certificate_is_needed_and_no_weaker_one_will_do(size, weaken, slack, sound):
+    """Elements on the smallest thresholds of the factors next to a stored scale, and one that dominates the error: a factor
+    further out computes to the same error although its exact one is larger, and being the earlier one it wins."""
+    rng = np.random.default_rng(7)
+    grid = grid_of(401, 0.95, 1.05)
+    wrong = 0
+    for trial in range(150):
+        k = int(rng.integers(50, 350)) if size == 16 else 200
+        s = F(rng.uniform(grid[k], grid[k + 1])) if size == 16 else F(1.0)
+        w = (rng.choice([.25, .75], size) * rng.uniform(grid[k - 4], grid[k + 4], size)).astype(np.float32)
+        w[0] = 2.0 ** rng.uniform(3.0, 8.0)
+        block = Block(w, F(1.0), grid)
+        wrong += nearest(block, [s], 0, weaken, slack)[0] != plain_loop(block, [s])
+    assert (wrong == 0) if sound else (wrong > 0), wrong
+
+
+def test_the_rule_modelled_here_is_the_one_in_the_source():
+    """the constants that the model does not read, and the gates in front of the search"""
+    assert FAR_SIDE[16] == F(1.0e-5) and FAR_SIDE[32] == F(1.8e-5)
+    # four times twice the rounding of a chain of n elements: 2 (n + 2) units of 2^-24
+    assert all(FAR_SIDE[n] > 4 * 2 * (n + 2) * 2.0 ** -24 for n in (16, 32))
+    assert SOURCE.count("slack = s * (0x1p-21f * per_error)") == 2
+    assert "return alpha > 0x1p-35f && alpha < 0x1p50f && f_of(amax_bits) < 0x1p60f;" in SOURCE
+    assert "const bool near = (uint32_t)(e0 - 67) < 120u;" in SOURCE
 
 
 # ------------------------------------------------------------------ GPU: the two search modes of the kernels
