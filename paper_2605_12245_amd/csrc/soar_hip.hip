@@ -557,7 +557,7 @@ bool nearest_search(int n_beta, float lo, float hi)
 // its rounding; the search over the changes of the codes forms every factor's codes once, and MXFP4 then takes one error per
 // change whatever the radius.  2048 x 4096 bf16, heavy-tailed or uniform, nearest / changes (window of radius K,
 // n factors): n = 4: 0.95 at K = 2, 1.05 at 3; n = 6: 0.92 at 5, 1.0 at 12; n = 101 in [0.9, 1.1]: 0.5 at 48, 1.6 at 64.  MXFP4, n = 4: 0.8 at
-// K = 1, 1.05 at 2; n = 8: 0.9 at 5, 1.1 at 6; n = 101: 0.15 to 0.25 at 5, 0.3 to 1.4 at 6, 4 to 7 at 12, 60 to 100 at 127.
+// K = 1, 1.05 at 2; n = 8: 0.9 at 5, 1.1 at 6; n = 101: 0.15 to 0.25 at 5, 0.3 to 1.4 at 6, 4 to 7 at 12, 60 to 100 at 125.
 bool nearest_pays(int n_beta, int radius) { return radius <= (n_beta >= 8 ? 48 : n_beta >= 6 ? 3 * n_beta - 13 : 2); }
 bool mx_nearest_pays(int n_beta, int radius) { return radius <= 5 && radius <= n_beta - 3; }
 

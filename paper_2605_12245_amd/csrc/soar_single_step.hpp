@@ -469,7 +469,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(DT == SOAR_
 //    launch itself once every workgroup has read it (workgroup 0, after the first crossing), so that a
 //    replayed HIP graph -- same kernel arguments -- still sees a new token every time.  Memory the library
 //    never wrote matches a token field with probability 2^-42 (2^-33) per word;
-//  - up to 64 workgroups read each other's words directly (one trip); above that the first workgroup of
+//  - up to 16 workgroups (kResDirect) read each other's words directly (one trip); above that the first workgroup of
 //    every group of 64 gathers its group and publishes the group's result, and everybody gathers the at
 //    most 4 group results (two trips, little traffic); the error sum, which only workgroup 0 needs, is
 //    gathered by workgroup 0 alone in one trip.
