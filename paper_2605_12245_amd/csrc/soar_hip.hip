@@ -555,11 +555,13 @@ bool nearest_search(int n_beta, float lo, float hi)
 // Where it is also the faster one.  It evaluates two factors or more per stored-scale candidate, however few the grid has,
 // and walks the whole grid for a candidate so far below the others that a factor's step moves the error by less than
 // its rounding; the search over the changes of the codes forms every factor's codes once, and MXFP4 then takes one error per
-// change whatever the radius.  2048 x 4096 bf16, heavy-tailed or uniform, nearest / changes (window of radius K,
-// n factors): n = 4: 0.95 at K = 2, 1.05 at 3; n = 6: 0.92 at 5, 1.0 at 12; n = 101 in [0.9, 1.1]: 0.5 at 48, 1.6 at 64.  MXFP4, n = 4: 0.8 at
-// K = 1, 1.05 at 2; n = 8: 0.9 at 5, 1.1 at 6; n = 101: 0.15 to 0.25 at 5, 0.3 to 1.4 at 6, 4 to 7 at 12, 60 to 100 at 125.
+// change whatever the radius.  2048 x 4096 bf16, time of the nearest factors over that of the changes (window of radius
+// K, n factors; heavy-tailed and uniform weights, both in the range given): n = 4: 0.95 at K = 2, 1.05 at 3; n = 6: 0.92 at 5,
+// 1.0 at 12; n = 101 in [0.9, 1.1]: 0.5 at 48, 1.6 at 64.  MXFP4, n = 4: 0.8 to 1.05 at K = 2, 0.85 to 1.05 at 3; n = 8: 0.8 to 1.1
+// at 6, 0.95 to 1.35 at 7; n = 101: 0.15 to 0.25 at 5, 0.25 to 0.7 at 6 (uniform weights in [0.9, 1.1] 1.4), 0.4 to 2.5 at 7, 4 to
+// 7 at 12, 60 to 100 at 125.
 bool nearest_pays(int n_beta, int radius) { return radius <= (n_beta >= 8 ? 48 : n_beta >= 6 ? 3 * n_beta - 13 : 2); }
-bool mx_nearest_pays(int n_beta, int radius) { return radius <= 5 && radius <= n_beta - 3; }
+bool mx_nearest_pays(int n_beta, int radius) { return radius <= 6 && radius <= n_beta - 2; }
 
 // absmax, the Eq. 1-2 state, then one launch per iteration; a tensor that has
 // stopped early (or is degenerate) makes its workgroups of the later launches return at once
