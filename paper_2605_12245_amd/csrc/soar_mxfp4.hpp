@@ -238,8 +238,9 @@ __device__ __forceinline__ void mx_search_changes(const float w[32], int e0, con
 }
 
 // mx_search without walking the factor grid: joint_search_nearest's argument, with the power of two X0 in the place
-// of alpha Delta* -- so which factors enclose a candidate scale is the same for every block of the launch
-// (the paper's grid and K = 1: seven pairs of 303).  One decoder layer (1.93e8 bf16 weights): 3.70 -> 0.21 ms a call.
+// of alpha Delta* -- so which factors enclose a candidate scale is the same for every block of the launch.  Bound by vector issue.
+// One decoder layer (1.93e8 bf16 weights, the paper's grid, K = 1): all 303 pairs 3.70 ms a call, the two factors around every
+// candidate (six pairs) 0.208, the three that are left below 0.132.
 __device__ __forceinline__ float mx_factor_error(const float w[32], float t, float s, uint32_t nib[4])
 {
     float q[32];
@@ -248,33 +249,45 @@ __device__ __forceinline__ float mx_factor_error(const float w[32], float t, flo
     return mx_block_error(w, q, s);
 }
 
-// best_factor for one stored scale s = ratio * x0 (ratio uniform over the wave)
-__device__ __forceinline__ float mx_best_factor(const float w[32], float x0, float ratio, const FactorGrid &grid, float s,
+// best_factor for one stored scale s = ratio * x0; `wanted`: the lane takes part.
+// A factor that IS the ratio (the default grid holds 0.5 and 1) assigns the codes nearest to w / s: with them the exact error is
+// the least for s, and a larger factor can at best tie.  On bf16 weights (GRID16) binary32 does not change that: w / s is a bf16
+// number y, the codes another factor moves from q to q' lie across a midpoint m of the E2M1 grid, and either y = m -- the
+// residual only changes its sign, computed errors are equal, the smaller factor keeps the tie -- or |y - m| is a whole unit of y's last
+// place, at least 2^-10, and the error rises by 2 |q - q'| |y - m| s^2 >= 2^-10 s^2: more than the rounding of two errors (34 units of
+// 2^-24 each) below 200 s^2.  So nothing above such a factor is evaluated; the factor below it is, because of the ties.
+template <bool GRID16>
+__device__ __forceinline__ float mx_best_factor(const float w[32], float x0, float ratio, const FactorGrid &grid, float s, bool wanted,
                                                 uint32_t nib[4], int &k)
 {
     const int last = grid.n - 1;
     const float at = (ratio - grid.lo) * grid.index_per_beta;
     // one factor where s lies beyond an end of the grid, else the two around it
-    int lo = __builtin_amdgcn_readfirstlane((int)__builtin_amdgcn_fmed3f(at, 0.0f, (float)last));
+    int lo = (int)__builtin_amdgcn_fmed3f(at, 0.0f, (float)last);
     int hi = at < 0.0f ? lo : min(lo + 1, last);
+    if (grid.table[lo] == ratio) {               // the upper of the two, or the only one
+        hi = lo;
+        lo = max(lo - 1, 0);
+    }
     const float per_error = s * (1.0f / kFarSideRounding32), slack = s * (0x1p-21f * per_error);
     auto excluded = [&](float distance, float e) { return __builtin_fmaf(distance, per_error, -slack) > e; };
+    auto nothing_above = [&](float t, float e) { return excluded(t - s, e) || (GRID16 && t == s && e < 200.0f * (s * s)); };
     const float ta = x0 * grid.table[lo];
     float err = mx_factor_error(w, ta, s, nib);
     k = lo;
-    bool down = lo > 0 && !excluded(s - ta, err), up;
+    bool down = wanted && lo > 0 && !excluded(s - ta, err), up = wanted && hi < last;
     uint32_t nib_b[4];
-    if (hi != lo) {
-        const float tb = x0 * grid.table[hi];
+    if (__builtin_amdgcn_ballot_w64(wanted && hi != lo) != 0ull) {
+        const float tb = x0 * grid.table[hi];    // once more the same where there is only one
         const float err_b = mx_factor_error(w, tb, s, nib_b);
-        up = hi < last && !excluded(tb - s, err_b);
-        const bool take_b = err_b < err;             // the smaller factor keeps a tie
+        up = up && !nothing_above(tb, err_b);
+        const bool take_b = err_b < err;         // the smaller factor keeps a tie
         err = take_b ? err_b : err;
         k = take_b ? hi : lo;
 #pragma unroll
         for (int h = 0; h < 4; ++h) nib[h] = take_b ? nib_b[h] : nib[h];
     } else {
-        up = hi < last && !excluded(ta - s, err);
+        up = up && !nothing_above(ta, err);
     }
     while (__builtin_amdgcn_ballot_w64(down || up) != 0ull) {
         if (down || up) {
@@ -295,23 +308,33 @@ __device__ __forceinline__ float mx_best_factor(const float w[32], float x0, flo
     return err;
 }
 
-__device__ __forceinline__ void mx_search_nearest(const float w[32], int e0, const FactorGrid &grid, int radius, float &best_err,
-                                                  int &best_code, uint32_t best_nib[4])
+// The candidates of one distance from X0, X0 2^-o and X0 2^o, are asked of different blocks, so that one evaluation with a
+// scale of its own per lane usually serves both:
+//  - X0 2^-o is left out where the largest weight alone, which its codes cannot reach, makes an error above the best so far
+//    (a rounding of 34 units of 2^-24 is allowed for);
+//  - X0 2^o is left out for bf16 weights whose block ends at or below 6 X0, if the grid holds the factor 1: up to 6 X0 every point of
+//    its grid is a point of X0's, so the codes nearest under X0 are at least as good, by 2^-10 X0^2 or more unless all residuals
+//    are equal up to sign (see mx_best_factor; the error under X0 is at most 32 X0^2), and in that tie X0 comes first: for the largest
+//    weight, 4 X0 or more, to take a code of 3.5 or less -- as it has to under X0 2^o -- the factor must exceed 1.
+// Pairs evaluated per block of the default grid: three (50 and 49 for X0, one for either side), where the two around every candidate
+// and the one beyond an equal factor were six.
+template <bool GRID16>
+__device__ __forceinline__ void mx_search_nearest(const float w[32], float bmax, int e0, const FactorGrid &grid, int radius,
+                                                  float &best_err, int &best_code, uint32_t best_nib[4])
 {
     const float x0 = e8m0_value(e0);
-    int best_k = 0;
+    int best_k;
     best_code = e0;
-    best_err = 0.0f;
-#pragma unroll 1
-    for (int c = 0; c <= 2 * radius; ++c) {
-        const int code = mx_candidate(e0, c);
-        const int o = (c + 1) >> 1;
-        const float ratio = f_of((uint32_t)(127 + ((c & 1) ? -min(o, 126) : min(o, 127))) << 23);
+    best_err = mx_best_factor<GRID16>(w, x0, 1.0f, grid, x0, true, best_nib, best_k);
+    const int at_one = (int)__builtin_amdgcn_fmed3f((1.0f - grid.lo) * grid.index_per_beta, 0.0f, (float)(grid.n - 1));
+    const bool holds_one = grid.table[at_one] == 1.0f || grid.table[min(at_one + 1, grid.n - 1)] == 1.0f;
+    const bool no_larger = GRID16 && holds_one && bmax <= 6.0f * x0;
+    auto candidate = [&](int code, float ratio, bool wanted) {
         uint32_t nib[4];
         int k;
-        const float err = mx_best_factor(w, x0, ratio, grid, e8m0_value(code), nib, k);
-        bool win = c == 0 || err < best_err;
-        const bool tie = !win && err == best_err && k < best_k;
+        const float err = mx_best_factor<GRID16>(w, x0, ratio, grid, ratio * x0, wanted, nib, k);
+        bool win = wanted && err < best_err;
+        const bool tie = wanted && err == best_err && k < best_k;
         if (__builtin_amdgcn_ballot_w64(tie) != 0ull)
             win = win || (tie && (nib[0] != best_nib[0] || nib[1] != best_nib[1] || nib[2] != best_nib[2] || nib[3] != best_nib[3]));
         best_err = win ? err : best_err;
@@ -319,6 +342,19 @@ __device__ __forceinline__ void mx_search_nearest(const float w[32], int e0, con
         best_k = win ? k : best_k;
 #pragma unroll
         for (int h = 0; h < 4; ++h) best_nib[h] = win ? nib[h] : best_nib[h];
+    };
+    // e0 and the radius are such (k_mx, mx_nearest_pays) that no candidate leaves the range of the stored codes
+#pragma unroll 1
+    for (int o = 1; o <= radius; ++o) {
+        const float below = f_of((uint32_t)(127 - o) << 23), above = f_of((uint32_t)(127 + o) << 23);
+        const float miss = fmaxf(__builtin_fmaf(below * x0, -6.0f, bmax), 0.0f);
+        bool lower = !(0.9999f * (miss * miss) > best_err), upper = !no_larger;
+        // the lower one first, in a round of its own where a block asks for both
+        while (__builtin_amdgcn_ballot_w64(lower || upper) != 0ull) {
+            candidate(lower ? e0 - o : e0 + o, lower ? below : above, lower || upper);
+            upper = upper && lower;
+            lower = false;
+        }
     }
 }
 
@@ -395,7 +431,7 @@ __global__ __launch_bounds__(kWG) void k_mx(const MxBatch batch)
                 // biased exponents [1, 252].
                 const bool near = (uint32_t)(e0 - 67) < 120u;
                 if (MODE == Mx::NEAREST && __builtin_amdgcn_ballot_w64(!near) == 0ull) {
-                    mx_search_nearest(w, e0, grid, t.radius, err, code, nib);
+                    mx_search_nearest<DT == SOAR_BF16>(w, bmax, e0, grid, t.radius, err, code, nib);
                 } else {
                     const float s_first = e8m0_value(e0) * s_beta[0], s_final = e8m0_value(e0) * s_beta[n_beta - 1];
                     const bool mid = ((__float_as_uint(s_first) >> 23) - 2u) < 250u && ((__float_as_uint(s_final) >> 23) - 2u) < 250u;
