@@ -333,16 +333,40 @@ WantedShapes wanted_shapes(bool several_groups, int method, bool iterated, bool 
 }
 
 // Tiles per workgroup of an arithmetic-bound searching kernel over a launch of `tiles` tiles: as many as leave
-// min_wg workgroups.  The nearest-factor iterations run at five waves per SIMD, 1280 workgroups at once, and each of the
-// launches after the early stop costs what its workgroups take to come and go (5 us for 2048, 3 us for 1024: 175 against
-// 181 us on 4096 x 4096 fp32); the MXFP4 search, one launch, balances better over 2048 (210 against 223 us on a
-// decoder layer), and so do iterations that last ten times as long.
-constexpr int64_t kNearestIterMinWg = 1024, kSearchMinWg = 2048;
-uint32_t search_tiles_per_wg(int64_t tiles, int64_t min_wg)
+// 2048 workgroups (the MXFP4 search; iterations that evaluate or form the codes of every factor).
+constexpr int64_t kSearchMinWg = 2048;
+uint32_t search_tiles_per_wg(int64_t tiles)
 {
     uint32_t tpw = 16;
-    while (tpw > 1 && tiles / tpw < min_wg) tpw >>= 1;
+    while (tpw > 1 && tiles / tpw < kSearchMinWg) tpw >>= 1;
     return tpw;
+}
+
+// The nearest-factor iterations fill the GPU once: as many workgroups as are on it at a time, each with the same share of
+// its tensor's chunks (the binary64 sums of a chunk are a node of the tree).  With 16 consecutive tiles a workgroup, 1472
+// workgroups for half a decoder layer, 192 of them ran by themselves at the end: an iteration 106.5 -> 103.8 us, search only on
+// fp32 85.1 -> 82.5.  A chunk is four tiles where a workgroup gets two or more of those, and larger where a tensor would have
+// more than 4096 (one workgroup adds up a tensor's chunks, 1024 at a time).
+constexpr int kIterWgPerCu = 5;          // workgroups of k_iter<., true> on a compute unit (waves_per_eu there)
+constexpr int64_t kIterMaxChunks = 4096;
+struct IterShape { uint32_t chunk_tiles; int64_t chunks, places; };
+IterShape iter_shape(int64_t group_tiles, int64_t largest_tiles, int compute_units)
+{
+    IterShape s;
+    s.places = (int64_t)kIterWgPerCu * (compute_units > 0 ? compute_units : 256);
+    s.chunk_tiles = (uint32_t)kStage;
+    while (s.chunk_tiles > 1 && group_tiles < 2 * s.places * s.chunk_tiles) s.chunk_tiles >>= 1;
+    while (largest_tiles > kIterMaxChunks * s.chunk_tiles) s.chunk_tiles <<= 1;
+    s.chunks = (group_tiles + s.chunk_tiles - 1) / s.chunk_tiles;
+    return s;
+}
+void deal_chunks(Task &t, const IterShape &s)
+{
+    const uint32_t tiles = (t.nblk + kWG - 1) / kWG;
+    t.tiles_per_wg = s.chunk_tiles;
+    t.n_chunks = (tiles + s.chunk_tiles - 1) / s.chunk_tiles;
+    const int64_t share = s.places * (int64_t)t.n_chunks / s.chunks;
+    t.n_wg = (uint32_t)(share < 1 ? 1 : share < (int64_t)t.n_chunks ? share : (int64_t)t.n_chunks);
 }
 
 // addressing and launch shapes of one tensor; the workspace fields and the first workgroups stay unset
@@ -369,7 +393,7 @@ Task make_task(const void *w, int64_t rows, int64_t cols, int64_t ld, const Want
     };
     const Shape base = shape(want.stats, forced.stats);
     t.tiles_per_wg = base.tiles_per_wg;
-    t.n_wg = base.n_wg;
+    t.n_wg = t.n_chunks = base.n_wg;
     t.absmax = shape(want.absmax, forced.absmax);
     t.search = shape(want.search, forced.search);
     return t;
@@ -771,16 +795,21 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         // search and streams like the single-step kernels.
         const bool searching = iterated && params->method != SOAR_METHOD_CJSO_ONLY;
         const uint32_t tpw = (uint32_t)params->tiles_per_wg;
-        int64_t group_tiles = 0;
-        for (int32_t k = i; k < j; ++k) group_tiles += (descs[k].rows * (descs[k].cols / 16) + kWG - 1) / kWG;
-        const uint32_t searching_tpw = searching ? search_tiles_per_wg(group_tiles, nearest ? kNearestIterMinWg : kSearchMinWg) : 0u;
+        int64_t group_tiles = 0, largest_tiles = 0;
+        for (int32_t k = i; k < j; ++k) {
+            const int64_t tiles = (descs[k].rows * (descs[k].cols / 16) + kWG - 1) / kWG;
+            group_tiles += tiles;
+            largest_tiles = tiles > largest_tiles ? tiles : largest_tiles;
+        }
+        const uint32_t searching_tpw = searching ? search_tiles_per_wg(group_tiles) : 0u;
+        const IterShape dealt = iter_shape(group_tiles, largest_tiles, device_facts().compute_units);
         uint32_t wg = 0, wg_absmax = 0, wg_search = 0;
         char *per_block = lane_base + (size_t)kGroupMax * kSlotBytes;
         for (int32_t k = i; k < j; ++k) {
             const soar_tensor_desc &d = descs[k];
             const WantedShapes forced = {params->tiles_per_wg_absmax ? (uint32_t)params->tiles_per_wg_absmax : tpw, tpw,
                                          params->tiles_per_wg_search ? (uint32_t)params->tiles_per_wg_search : tpw};
-            const WantedShapes want = searching ? WantedShapes{searching_tpw, searching_tpw, searching_tpw}
+            const WantedShapes want = searching ? WantedShapes{(uint32_t)kStage, searching_tpw, searching_tpw}
                                                 : wanted_shapes(n_groups > 1, params->method, iterated, d.d_amax_in != nullptr,
                                                                 weight_bytes(d), group_tiles);
             Task t = make_task(d.d_w, d.rows, d.cols, d.ld_elems, forced, want);
@@ -792,6 +821,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
             t.gscale = d.d_global_scale;
             t.sse = d.d_sse;
             t.status = d.d_status;
+            if (searching && nearest && tpw == 0) deal_chunks(t, dealt);
             t.wg_begin = wg;
             wg += t.n_wg;
             t.absmax.wg_begin = wg_absmax;
@@ -1219,7 +1249,7 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
             t.contiguous = d.ld_elems == d.cols ? 1u : 0u;
             const uint32_t tiles = (t.nblk + kWG - 1) / kWG;
             // the search is arithmetic-bound (see search_tiles_per_wg); the plain conversion streams
-            uint32_t tpw = params->dss ? search_tiles_per_wg(group_tiles, kSearchMinWg) : 2u;
+            uint32_t tpw = params->dss ? search_tiles_per_wg(group_tiles) : 2u;
             while (tpw > 1 && tpw > tiles) tpw >>= 1;
             if (params->tiles_per_wg) tpw = (uint32_t)params->tiles_per_wg;
             while ((tiles + tpw - 1) / tpw > (uint32_t)kMaxPartials) tpw <<= 1;

@@ -467,36 +467,38 @@ __global__ __launch_bounds__(kWG) void k_iter_init(const Batch batch)
     const float alpha0 = gs.alpha0;
 
     StagedTree<> tree{s_blocks, s_wave, s_stack};
-    const uint32_t tile0 = lwg * t.tiles_per_wg;
     const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
-    for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
-        for (uint32_t kk = 0; kk < T; ++kk) {
-            const uint32_t i = (tile0 + kg + kk) * kWG + tid;
-            float a = 0.0f, b = 0.0f, delta0 = 0.0f, err = 0.0f;
-            if (i < t.nblk) {
-                float rho = 0.0f;
-                if (!degenerate) {
-                    float w[16];
-                    load_block<DT>(t.w, block_offset(t, i), w);
-                    init_block(w, gs, batch.arm == SOAR_METHOD_DSS_ONLY, a, b, delta0, err, rho);
+    for (uint32_t chunk = lwg; chunk < t.n_chunks; chunk += t.n_wg) {
+        const uint32_t tile0 = chunk * t.tiles_per_wg;
+        for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
+            for (uint32_t kk = 0; kk < T; ++kk) {
+                const uint32_t i = (tile0 + kg + kk) * kWG + tid;
+                float a = 0.0f, b = 0.0f, delta0 = 0.0f, err = 0.0f;
+                if (i < t.nblk) {
+                    float rho = 0.0f;
+                    if (!degenerate) {
+                        float w[16];
+                        load_block<DT>(t.w, block_offset(t, i), w);
+                        init_block(w, gs, batch.arm == SOAR_METHOD_DSS_ONLY, a, b, delta0, err, rho);
+                    }
+                    t.rho[i] = rho;
                 }
-                t.rho[i] = rho;
+                tree.stage(kk, a, b, delta0, err);
             }
-            tree.stage(kk, a, b, delta0, err);
+            tree.close(kg / T, T);
         }
-        tree.close(kg / T, T);
+        if (tid == 0) {
+            publish(t.part + chunk, tree.wg[0]);
+            publish(t.part + kMaxPartials + chunk, tree.wg[1]);
+            publish(t.part + 2 * kMaxPartials + chunk, tree.wg[2]);
+        }
     }
     uint32_t *counters = t.counters + 1 * kSlots * kSlotStride;
-    if (tid == 0) {
-        publish(t.part + lwg, tree.wg[0]);
-        publish(t.part + kMaxPartials + lwg, tree.wg[1]);
-        publish(t.part + 2 * kMaxPartials + lwg, tree.wg[2]);
-        s_last = arrive_is_last(counters, &t.ctrl->top[1], t.n_wg, lwg) ? 1u : 0u;
-    }
+    if (tid == 0) s_last = arrive_is_last(counters, &t.ctrl->top[1], t.n_wg, lwg) ? 1u : 0u;
     __syncthreads();
     if (!s_last) return;
     double NME[3];
-    trees_of_partials<3>(t.part, t.n_wg, s_tree, &s_stack[0][0], NME);
+    trees_of_partials<3>(t.part, t.n_chunks, s_tree, &s_stack[0][0], NME);
     const double N = NME[0], M = NME[1], E = NME[2];
     if (tid == 0) {
         t.ctrl->alpha0 = alpha0;
@@ -693,39 +695,41 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5
     js.set_alpha(alpha, amax_bits);
 
     StagedTree<> tree{s_blocks, s_wave, s_stack};
-    const uint32_t tile0 = lwg * t.tiles_per_wg;
     const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
-    for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
-        for (uint32_t kk = 0; kk < T; ++kk) {
-            const uint32_t i = (tile0 + kg + kk) * kWG + tid;
-            BlockState x;
-            x.a = x.b = x.d = x.err = 0.0f;
-            if (i < t.nblk && amax_bits < 0x7F800000u) {
-                float w[16];
-                load_block<DT>(t.w, block_offset(t, i), w);
-                if (allzero) {
-                    zero_block(w, x);
-                } else {
-                    iterate_block<NEAREST>(w, t.rho[i], js, x);
-                    t.rho[i] = x.rho;
+    for (uint32_t chunk = lwg; chunk < t.n_chunks; chunk += t.n_wg) {
+        const uint32_t tile0 = chunk * t.tiles_per_wg;
+        for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
+            for (uint32_t kk = 0; kk < T; ++kk) {
+                const uint32_t i = (tile0 + kg + kk) * kWG + tid;
+                BlockState x;
+                x.a = x.b = x.d = x.err = 0.0f;
+                if (i < t.nblk && amax_bits < 0x7F800000u) {
+                    float w[16];
+                    load_block<DT>(t.w, block_offset(t, i), w);
+                    if (allzero) {
+                        zero_block(w, x);
+                    } else {
+                        iterate_block<NEAREST>(w, t.rho[i], js, x);
+                        t.rho[i] = x.rho;
+                    }
+                    store_block(t, i, x);
                 }
-                store_block(t, i, x);
+                tree.stage(kk, x.a, x.b, x.d, x.err);
             }
-            tree.stage(kk, x.a, x.b, x.d, x.err);
+            tree.close(kg / T, T);
         }
-        tree.close(kg / T, T);
+        if (tid == 0) {
+            publish(t.part + chunk, tree.wg[0]);
+            publish(t.part + kMaxPartials + chunk, tree.wg[1]);
+            publish(t.part + 2 * kMaxPartials + chunk, tree.wg[2]);
+        }
     }
     uint32_t *counters = t.counters + 2 * kSlots * kSlotStride;
-    if (tid == 0) {
-        publish(t.part + lwg, tree.wg[0]);
-        publish(t.part + kMaxPartials + lwg, tree.wg[1]);
-        publish(t.part + 2 * kMaxPartials + lwg, tree.wg[2]);
-        s_last = arrive_is_last(counters, &t.ctrl->top[2], t.n_wg, lwg) ? 1u : 0u;
-    }
+    if (tid == 0) s_last = arrive_is_last(counters, &t.ctrl->top[2], t.n_wg, lwg) ? 1u : 0u;
     __syncthreads();
     if (!s_last) return;
     double NME[3];
-    trees_of_partials<3>(t.part, t.n_wg, s_tree, &s_stack[0][0], NME);
+    trees_of_partials<3>(t.part, t.n_chunks, s_tree, &s_stack[0][0], NME);
     const double N = NME[0], M = NME[1], cur = NME[2];
     if (tid == 0) finish_iteration(batch, t, N, M, cur, alpha, degenerate, allzero, dss_only);
     reset_counters(counters, &t.ctrl->top[2]);
@@ -758,40 +762,42 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8))) void k
     const bool fast = scales_in_range(alpha, amax_bits);
 
     StagedTree<> tree{s_blocks, s_wave, s_stack};
-    const uint32_t tile0 = lwg * t.tiles_per_wg;
     const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
-    for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
-        for (uint32_t kk = 0; kk < T; ++kk) {
-            const uint32_t i = (tile0 + kg + kk) * kWG + tid;
-            BlockState x;
-            x.a = x.b = x.d = x.err = 0.0f;
-            if (i < t.nblk && amax_bits < 0x7F800000u) {
-                float w[16];
-                load_block<DT>(t.w, block_offset(t, i), w);
-                if (allzero) {
-                    zero_block(w, x);
-                } else {
-                    const float rho = t.rho[i];
-                    closed_form_block(w, rho, alpha, inv_alpha, fast && all_near_one(rho), x);
-                    t.rho[i] = x.rho;
+    for (uint32_t chunk = lwg; chunk < t.n_chunks; chunk += t.n_wg) {
+        const uint32_t tile0 = chunk * t.tiles_per_wg;
+        for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
+            for (uint32_t kk = 0; kk < T; ++kk) {
+                const uint32_t i = (tile0 + kg + kk) * kWG + tid;
+                BlockState x;
+                x.a = x.b = x.d = x.err = 0.0f;
+                if (i < t.nblk && amax_bits < 0x7F800000u) {
+                    float w[16];
+                    load_block<DT>(t.w, block_offset(t, i), w);
+                    if (allzero) {
+                        zero_block(w, x);
+                    } else {
+                        const float rho = t.rho[i];
+                        closed_form_block(w, rho, alpha, inv_alpha, fast && all_near_one(rho), x);
+                        t.rho[i] = x.rho;
+                    }
+                    store_block(t, i, x);
                 }
-                store_block(t, i, x);
+                tree.stage(kk, x.a, x.b, x.d, x.err);
             }
-            tree.stage(kk, x.a, x.b, x.d, x.err);
+            tree.close(kg / T, T);
         }
-        tree.close(kg / T, T);
+        if (tid == 0) {
+            publish(t.part + chunk, tree.wg[0]);
+            publish(t.part + kMaxPartials + chunk, tree.wg[1]);
+            publish(t.part + 2 * kMaxPartials + chunk, tree.wg[2]);
+        }
     }
     uint32_t *counters = t.counters + 2 * kSlots * kSlotStride;
-    if (tid == 0) {
-        publish(t.part + lwg, tree.wg[0]);
-        publish(t.part + kMaxPartials + lwg, tree.wg[1]);
-        publish(t.part + 2 * kMaxPartials + lwg, tree.wg[2]);
-        s_last = arrive_is_last(counters, &t.ctrl->top[2], t.n_wg, lwg) ? 1u : 0u;
-    }
+    if (tid == 0) s_last = arrive_is_last(counters, &t.ctrl->top[2], t.n_wg, lwg) ? 1u : 0u;
     __syncthreads();
     if (!s_last) return;
     double NME[3];
-    trees_of_partials<3>(t.part, t.n_wg, s_tree, &s_stack[0][0], NME);
+    trees_of_partials<3>(t.part, t.n_chunks, s_tree, &s_stack[0][0], NME);
     const double N = NME[0], M = NME[1], cur = NME[2];
     if (tid == 0) finish_iteration(batch, t, N, M, cur, alpha, degenerate, allzero, false);
     reset_counters(counters, &t.ctrl->top[2]);
