@@ -1,7 +1,7 @@
 // The iterated path of one tensor handed over alone, in one launch: k_iter_resident.
 #pragma once
 #include "soar_iterated.hpp"
-#include "soar_single_step.hpp"      // the crossings of the one-launch kernels
+#include "soar_single_step.hpp"      // ResidentArgs
 
 namespace {
 
@@ -26,105 +26,15 @@ namespace {
 // tiles (G rounded up to a power of two), the same tree, no crossings.  So a call always finishes, as it does with a
 // launch per iteration.  Beyond the first crossing every workgroup is running and the waits last as long as the slowest
 // one's share; their bound (later_ticks) is there for a machine that has stopped working.
-// 1024 x 4096 bf16, paper settings: 72-88 -> 44 us a call (loads 1, maximum 2, state 3, sums 3, an iteration 5-6 and
+// 1024 x 4096 bf16, paper settings: 72-88 -> 42 us a call (loads 1, maximum 2, state 3, sums 3, an iteration 5-6 and
 // its crossing 4 us); 4096 x 4096 fp32, search-only arm: 169 -> 140 us, 33 of them an iteration's search.
-// A crossing's words lie entry by entry (kSumWords of one workgroup or group side by side), and a wave reads them as
-// they lie, one word per lane: reads past the L2 are served line by line, and a gather by kinds of word -- nine loads
-// of 64 words 2 KB apart -- took 3 to 4 us a hop where this takes
-// 1.6 to 2.  Groups of 16 workgroups: 144 words, nine lines, at either level (groups of 64 would be 36 lines
-// for the gathering workgroup).
-constexpr uint32_t kSumWords = 9;                        // three binary64 values in thirds
-constexpr uint32_t kSumGroup = 16;                       // workgroups per group, and groups at most
-constexpr uint32_t kSumCopies = 7;                       // of a group's result: 7 * 9 words are one store instruction
-constexpr uint32_t kSumCopyStride = 160;                 // words
-constexpr uint32_t kSumLevel1 = 12288;                   // [2 buffers][kResMaxWG][kSumWords]
-constexpr uint32_t kSumLevel2 = kSumLevel1 + 2 * kResMaxWG * kSumWords;      // [2 buffers][kSumCopies][kSumCopyStride]
-constexpr uint32_t kSumLeft = kSumLevel2 + 2 * kSumCopies * kSumCopyStride;  // how many workgroups have given up
-static_assert(kResNM2 + kResCopies * kResCopyStride <= kSumLevel1 && kSumLeft < 3 * kMaxPartials &&
-              kSumGroup * kSumWords <= kSumCopyStride && kSumGroup * kSumGroup >= (uint32_t)kResMaxWG && kSumCopies * kSumWords <= 64,
-              "layout of the crossing words");
-
-// Wave 0, all lanes: wait until the `count` entries from `src` on carry the token; lane e then holds the three values
-// of entry e (zeros from `count` on).  lds: kSumGroup * kSumWords words.
-__device__ __forceinline__ bool gather_sums(const ResidentGrid &r, const uint64_t *src, uint32_t count, uint64_t *lds, double v[3])
-{
-    constexpr int P = kResSumBits;
-    constexpr uint32_t kLoads = (kSumGroup * kSumWords + 63) / 64;
-    const uint32_t lane = threadIdx.x & 63u, n = count * kSumWords;
-    const uint64_t want = (r.tok << P) >> P, gone_field = (~r.base << P) >> P;
-    uint64_t x[kLoads];
-    for (uint64_t round = 0;; ++round) {
-#pragma unroll
-        for (uint32_t k = 0; k < kLoads; ++k)
-            x[k] = lane + 64u * k < n ? __hip_atomic_load(src + lane + 64u * k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : want << P;
-        __builtin_amdgcn_sched_barrier(0);               // one trip to memory a round
-        bool pending = false, gone = false;
-#pragma unroll
-        for (uint32_t k = 0; k < kLoads; ++k) {
-            const uint64_t field = x[k] >> P;
-            gone = gone | (field == gone_field);
-            pending = pending | (field != want);
-        }
-        if (__builtin_amdgcn_ballot_w64(gone) != 0ull) return false;
-        if (__builtin_amdgcn_ballot_w64(pending) == 0ull) break;
-        if (resident_time_is_up(r, round)) return false;
-    }
-#pragma unroll
-    for (uint32_t k = 0; k < kLoads; ++k)
-        if (lane + 64u * k < kSumGroup * kSumWords) lds[lane + 64u * k] = x[k] & ((1ull << P) - 1ull);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint64_t *mine = lds + min(lane, kSumGroup - 1u) * kSumWords;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) v[j] = lane < count ? resident_join(mine + 3 * j) : 0.0;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    return true;
-}
-
-// Wave 0, all lanes: entry `e` of `copies` copies of the words, from the values v (uniform)
-__device__ __forceinline__ void publish_sums(const ResidentGrid &r, uint64_t *dst, uint32_t e, uint32_t copies, const double v[3])
-{
-    uint64_t pay[kSumWords];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) resident_split(v[j], pay + 3 * j);
-    const uint32_t lane = threadIdx.x & 63u, copy = lane / kSumWords, w = lane - copy * kSumWords;
-    uint64_t x = pay[0];
-#pragma unroll
-    for (uint32_t j = 1; j < kSumWords; ++j) x = w == j ? pay[j] : x;
-    if (copy < copies)
-        __hip_atomic_store(dst + copy * kSumCopyStride + e * kSumWords + w, (r.tok << kResSumBits) | x, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Wave 0, all lanes, every workgroup: the adjacent-pair tree sums of three binary64 values (lane 0's on entry) over the
-// grid, uniform on return.  buffer: 0 or 1, alternating from crossing to crossing.
-__device__ __forceinline__ bool cross_three_sums(const ResidentGrid &r, uint32_t buffer, uint64_t *lds, double v[3])
-{
-    uint64_t *level1 = r.words + kSumLevel1 + buffer * kResMaxWG * kSumWords;
-    uint64_t *level2 = r.words + kSumLevel2 + buffer * kSumCopies * kSumCopyStride;
-    const uint32_t grp = r.g / kSumGroup, groups = (r.G + kSumGroup - 1u) / kSumGroup;
-#pragma unroll
-    for (int j = 0; j < 3; ++j) v[j] = readlane_f64(v[j], 0);
-    publish_sums(r, level1, r.g, 1u, v);
-    auto tree = [&]() {
-#pragma unroll
-        for (int j = 0; j < 3; ++j) v[j] = wave_pair_tree(v[j]);
-    };
-    if (r.G > kSumGroup) {
-        if (r.g % kSumGroup == 0u) {
-            if (!gather_sums(r, level1 + grp * kSumGroup * kSumWords, min(kSumGroup, r.G - grp * kSumGroup), lds, v)) return false;
-            tree();
-            publish_sums(r, level2, grp, kSumCopies, v);
-        }
-        if (!gather_sums(r, level2 + (r.g % kSumCopies) * kSumCopyStride, groups, lds, v)) return false;
-    } else if (!gather_sums(r, level1, r.G, lds, v)) {
-        return false;
-    }
-    tree();
-    return true;
-}
+// The crossing words inside Task::part, apart from those of other kernels
+struct IterResidentWords {
+    uint64_t max[kMaxEnd];
+    SumWords<3> sums[2];                  // of alternating crossings
+    uint64_t left;                        // how many workgroups have given up
+};
+static_assert(sizeof(IterResidentWords) <= kPartialsBytes, "layout of the crossing words");
 
 // One lane of a workgroup that gives up: the number of workgroups that have, this one included.  The word may hold
 // anything before the launch's first: the count stands beside 48 bits of the token.  An exchange fails only where
@@ -161,7 +71,7 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
     __shared__ double s_wave[3][kWaves];
     __shared__ double s_stack[3][32];
     __shared__ float s_beta[CLOSED_FORM ? 1 : kIterResMaxBeta];
-    __shared__ uint64_t s_cross[kSumGroup * kSumWords];
+    __shared__ uint64_t s_cross[kSumDirect * SumWords<3>::kW];
     __shared__ uint32_t s_max[kWaves];
     __shared__ uint32_t s_amax, s_gone, s_stop;
     __shared__ float s_alpha;
@@ -174,21 +84,13 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
     grid.tok = grid.base = args.r.nonce;
     grid.t0 = 0;
     grid.ticks = args.r.wait_ticks;
-    grid.words = reinterpret_cast<uint64_t *>(t.part);
+    IterResidentWords &words = *reinterpret_cast<IterResidentWords *>(t.part);
+    grid.words = words.max;
     uint32_t R = args.tiles, told = 0u;
     // one lane: leave the launch and tell the others, at whichever crossing they are
     auto give_up = [&]() {
-        const uint64_t gone = ~grid.base << kResSumBits, gone_max = ~grid.base << kMaxBits;
-        auto put = [&](uint32_t at, uint64_t v) { __hip_atomic_store(grid.words + at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-        put(kResMax1 + grid.g, gone_max);
-        if (grid.g % kResGroup == 0u)
-            for (uint32_t c = 0; c < (uint32_t)kResCopies; ++c) put(kResMax2 + c * kResCopyStride + grid.g / kResGroup, gone_max);
-        for (uint32_t b = 0; b < 2; ++b) {
-            put(kSumLevel1 + (b * kResMaxWG + grid.g) * kSumWords, gone);
-            if (grid.g % kSumGroup == 0u)
-                for (uint32_t c = 0; c < kSumCopies; ++c)
-                    put(kSumLevel2 + (b * kSumCopies + c) * kSumCopyStride + grid.g / kSumGroup * kSumWords, gone);
-        }
+        leave_max(grid, ~grid.base << kMaxBits);
+        for (uint32_t b = 0; b < 2; ++b) leave_sums(grid, words.sums[b], ~grid.base << kResSumBits);
         if (t.status) *t.status = SOAR_STATUS_GAVE_UP;
     };
     // every lane of a workgroup that has given up: true in the last one to leave, which finds itself the only workgroup
@@ -196,7 +98,7 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
     auto last_to_leave = [&]() -> bool {
         __threadfence();
         __syncthreads();
-        if (tid == 0) s_stop = count_out(grid.words + kSumLeft, grid.base) == grid.G ? 1u : 0u;
+        if (tid == 0) s_stop = count_out(&words.left, grid.base) == grid.G ? 1u : 0u;
         __syncthreads();
         if (s_stop == 0u) return false;
         __threadfence();
@@ -213,7 +115,7 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
         grid.tok = grid.base ^ ((uint64_t)(c + 1u) * 0xBF58476D1CE4E5B9ull);
         grid.t0 = (uint64_t)wall_clock64();
         grid.ticks = args.later_ticks;
-        return cross_three_sums(grid, c & 1u, s_cross, v);
+        return cross_sums<3>(grid, words.sums[c & 1u], s_cross, v);
     };
 
     if constexpr (!CLOSED_FORM)
@@ -244,7 +146,7 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
             if (grid.G > 1u) {
                 uint32_t value = DT == SOAR_BF16 ? amax >> 16 : amax;
                 grid.t0 = (uint64_t)wall_clock64();
-                ok = resident_cross_max<kMaxBits>(grid, value);
+                ok = cross_max<kMaxBits>(grid, value);
                 amax = DT == SOAR_BF16 ? value << 16 : value;
                 if (lane == 0 && !ok) give_up();
             }

@@ -1,6 +1,7 @@
 // The single-step path (Algorithm 1 with T = 1, beta = {1}): k_init, k_absmax (Eq. 1), k_stats
 // (Eq. 1-2, 5) and k_search (Eq. 6, 8, packing); k_search also serves the plain conversion of Sec. 3.1.
 #pragma once
+#include "soar_crossing.hpp"
 #include "soar_device.hpp"
 
 namespace {
@@ -456,47 +457,15 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(DT == SOAR_
 // tree, a workgroup per lane) and then over the at most 4 groups.  Same arithmetic, same trees as the
 // three-pass path: identical bytes.
 //
-// Crossing the grid.  All workgroups of the launch must be on the machine at the same time (the host
-// launches at most one per compute unit and takes the three-pass path otherwise).  A trip through memory
-// from one workgroup to another takes about 1.4 us on this part, and 256 workgroups that each read all
-// 256 results queue for several microseconds more, so:
-//  - there is no counter and no separate "ready" flag, hence no word that has to be cleared beforehand and
-//    no second trip for the value: every word a workgroup publishes (an agent-scope atomic store) carries
-//    the launch's TOKEN beside its payload, and a reader accepts a word only with that token.  A binary64
-//    sum travels as three words of 22 payload bits and 42 token bits; the first crossing's word holds the
-//    bf16 / fp32 maximum in 15 / 31 bits beside 49 / 33 token bits.  The token is `nonce ^ epoch * odd`:
-//    the nonce comes from the host (new for every call), the epoch from the workspace, advanced by the
-//    launch itself once every workgroup has read it (workgroup 0, after the first crossing), so that a
-//    replayed HIP graph -- same kernel arguments -- still sees a new token every time.  Memory the library
-//    never wrote matches a token field with probability 2^-42 (2^-33) per word;
-//  - up to 16 workgroups (kResDirect) read each other's words directly (one trip); above that the first workgroup of
-//    every group of 64 gathers its group and publishes the group's result, and everybody gathers the at
-//    most 4 group results (two trips, little traffic); the error sum, which only workgroup 0 needs, is
-//    gathered by workgroup 0 alone in one trip.
-// Every wait is BOUNDED: a workgroup whose time is up publishes the complemented token in its words (so
-// that the others leave at once instead of waiting out the limit), sets SOAR_STATUS_GAVE_UP and returns;
-// every wave of the grid then reaches its end.
-constexpr int kResMaxWG = 256;            // workgroups of one launch, at most
 constexpr int kResMaxPer = 4;             // blocks per lane, at most
-constexpr int kResGroup = 64;             // workgroups per group: a wave gathers one with a workgroup per lane
-constexpr int kResGroups = kResMaxWG / kResGroup;
-constexpr uint64_t kResOdd = 0x9E3779B97F4A7C15ull;
-constexpr int kResSumBits = 22;           // payload bits of a word that carries a third of a binary64 value
-// Places inside Task::part, in 8-byte words.  First level: per kind of word kResMaxWG entries (one per
-// workgroup).  Second level: kResGroups entries (one per group) per kind, in kResCopies copies
-// kResCopyStride words apart: every workgroup polls the second level, and a few lines polled by 250
-// workgroups at once queue at their memory channel (the publisher's stores behind them); a reader polls
-// the copy of its own number modulo kResCopies.
-constexpr int kResCopies = 8;
-constexpr uint32_t kResCopyStride = 544;                                          // 17 * 256 bytes
-constexpr uint32_t kResMax1 = 0;                                                  // 1 kind: token | maximum
-constexpr uint32_t kResNM1 = 512;                                                 // 6 kinds: N and M in thirds
-constexpr uint32_t kResErr1 = 2304;                                               // 3 kinds: the error sum in thirds
-constexpr uint32_t kResMax2 = 3072, kResNM2 = kResMax2 + kResCopies * kResCopyStride;
-static_assert(kResMax1 + kResMaxWG <= kResNM1 && kResNM1 + 6 * kResMaxWG <= kResErr1 && kResErr1 + 3 * kResMaxWG <= kResMax2 &&
-              6 * kResGroups <= kResCopyStride && kResNM2 + kResCopies * kResCopyStride <= 3 * kMaxPartials,
-              "layout of the crossing words");
-constexpr uint32_t kResDirect = 16;       // up to this many workgroups read each other's words directly
+
+// The crossing words inside Task::part
+struct ResidentWords {
+    uint64_t max[kMaxEnd];
+    SumWords<2> nm;
+    uint64_t err[3 * kResMaxWG];
+};
+static_assert(sizeof(ResidentWords) <= kPartialsBytes, "layout of the crossing words");
 
 struct ResidentArgs {
     int32_t  radius, full_search;
@@ -505,166 +474,6 @@ struct ResidentArgs {
                                           // k_iter_resident, of its wait for the grid to arrive
     unsigned long long *search_stats;     // null, or the diagnostic counters of count_search
 };
-
-// what wave 0 of a workgroup needs for its crossings
-struct ResidentGrid {
-    uint32_t g, G;
-    uint64_t tok, base, t0, ticks;        // token of the crossing and of the launch
-    uint64_t *words;                      // Task::part
-};
-
-// The bound of a wait: the wall clock (100 MHz on this part), and -- should that clock ever stand still -- a
-// number of polling rounds that takes several times as long (a round is at least one trip to memory).
-__device__ __forceinline__ bool resident_time_is_up(const ResidentGrid &r, uint64_t round)
-{
-    return (uint64_t)wall_clock64() - r.t0 > r.ticks || round > 1024ull + r.ticks / 8ull;
-}
-
-// one lane: NW kinds of words for entry e; kind w of entry e sits at dst[w * stride + e]
-template <int NW, int PBITS>
-__device__ __forceinline__ void resident_publish(uint64_t *dst, uint32_t stride, uint32_t e, uint64_t tok, const uint64_t pay[NW])
-{
-#pragma unroll
-    for (int w = 0; w < NW; ++w)
-        __hip_atomic_store(dst + w * stride + e, (tok << PBITS) | pay[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// wave 0, all lanes: a group's result into every copy of the second level (lane c writes copy c)
-template <int NW, int PBITS>
-__device__ __forceinline__ void resident_publish_copies(uint64_t *dst, uint32_t grp, uint64_t tok, const uint64_t pay[NW])
-{
-    const uint32_t lane = threadIdx.x & 63u;
-    if (lane < (uint32_t)kResCopies) resident_publish<NW, PBITS>(dst + lane * kResCopyStride, kResGroups, grp, tok, pay);
-}
-
-// Wave 0, all lanes: wait until entries first .. first + count - 1 (count <= 64 * K) of all NW kinds carry the
-// token; lane l then holds the payloads of entries first + l + 64 k in pay[k][.] (zeros from `count` on).
-// False when somebody has given up (a word with the complemented token) or the time is up.
-template <int NW, int PBITS, int K>
-__device__ __forceinline__ bool resident_gather(const ResidentGrid &r, const uint64_t *src, uint32_t stride, uint32_t first,
-                                                uint32_t count, uint64_t pay[K][NW])
-{
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t want = (r.tok << PBITS) >> PBITS, gone_field = (~r.base << PBITS) >> PBITS;
-    for (uint64_t round = 0;; ++round) {
-        // all loads of a round first, whatever the registers: one trip to memory a round, not one per word
-        uint64_t v[K][NW];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const uint32_t e = lane + 64u * (uint32_t)k;
-#pragma unroll
-            for (int w = 0; w < NW; ++w)
-                v[k][w] = e < count ? __hip_atomic_load(src + w * stride + first + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : want << PBITS;
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        bool pending = false, gone = false;
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const uint64_t field = v[k][w] >> PBITS;
-                gone = gone | (field == gone_field);
-                pending = pending | (field != want);
-                pay[k][w] = v[k][w] & ((1ull << PBITS) - 1ull);
-            }
-        if (__builtin_amdgcn_ballot_w64(gone) != 0ull) return false;
-        if (__builtin_amdgcn_ballot_w64(pending) == 0ull) return true;
-        if (resident_time_is_up(r, round)) return false;
-    }
-}
-
-// Wave 0, all lanes: the maximum of `value` over the grid (uniform on return).
-template <int PBITS>
-__device__ __forceinline__ bool resident_cross_max(const ResidentGrid &r, uint32_t &value)
-{
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t grp = r.g / kResGroup, groups = (r.G + kResGroup - 1) / kResGroup;
-    uint64_t pay[1][1] = {{value}};
-    if (lane == 0) resident_publish<1, PBITS>(r.words + kResMax1, kResMaxWG, r.g, r.tok, pay[0]);
-    if (r.G > kResDirect) {
-        if (r.g % kResGroup == 0u) {
-            if (!resident_gather<1, PBITS, 1>(r, r.words + kResMax1, kResMaxWG, grp * kResGroup,
-                                              min((uint32_t)kResGroup, r.G - grp * kResGroup), pay)) return false;
-            pay[0][0] = wave_max_u32((uint32_t)pay[0][0]);
-            resident_publish_copies<1, PBITS>(r.words + kResMax2, grp, r.tok, pay[0]);
-        }
-        if (!resident_gather<1, PBITS, 1>(r, r.words + kResMax2 + (r.g % kResCopies) * kResCopyStride, kResGroups, 0u, groups, pay))
-            return false;
-    } else if (!resident_gather<1, PBITS, 1>(r, r.words + kResMax1, kResMaxWG, 0u, r.G, pay)) {
-        return false;
-    }
-    value = wave_max_u32((uint32_t)pay[0][0]);
-    return true;
-}
-
-__device__ __forceinline__ void resident_split(double v, uint64_t pay[3])
-{
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    pay[0] = b & ((1ull << kResSumBits) - 1ull);
-    pay[1] = (b >> kResSumBits) & ((1ull << kResSumBits) - 1ull);
-    pay[2] = b >> (2 * kResSumBits);
-}
-
-__device__ __forceinline__ double resident_join(const uint64_t pay[3])
-{
-    return __longlong_as_double((long long)(pay[0] | pay[1] << kResSumBits | pay[2] << (2 * kResSumBits)));
-}
-
-// Wave 0, all lanes, every workgroup: the adjacent-pair tree sums of NV binary64 values (one set per
-// workgroup, in workgroup order, zero-padded) over the grid; uniform on return.
-template <int NV>
-__device__ __forceinline__ bool resident_cross_sums(const ResidentGrid &r, uint32_t at1, uint32_t at2, double v[NV])
-{
-    constexpr int NW = 3 * NV, P = kResSumBits;
-    static_assert(NW * kResGroups <= (int)kResCopyStride, "a copy holds every kind");
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t grp = r.g / kResGroup, groups = (r.G + kResGroup - 1) / kResGroup;
-    uint64_t pay[1][NW];
-    auto split = [&]() {
-#pragma unroll
-        for (int n = 0; n < NV; ++n) resident_split(v[n], &pay[0][3 * n]);
-    };
-    auto tree = [&]() {                   // lane e holds entry e
-#pragma unroll
-        for (int n = 0; n < NV; ++n) v[n] = wave_pair_tree(resident_join(&pay[0][3 * n]));
-    };
-    split();
-    if (lane == 0) resident_publish<NW, P>(r.words + at1, kResMaxWG, r.g, r.tok, pay[0]);
-    if (r.G > kResDirect) {
-        if (r.g % kResGroup == 0u) {
-            if (!resident_gather<NW, P, 1>(r, r.words + at1, kResMaxWG, grp * kResGroup,
-                                           min((uint32_t)kResGroup, r.G - grp * kResGroup), pay)) return false;
-            tree();
-            split();
-            resident_publish_copies<NW, P>(r.words + at2, grp, r.tok, pay[0]);
-        }
-        if (!resident_gather<NW, P, 1>(r, r.words + at2 + (r.g % kResCopies) * kResCopyStride, kResGroups, 0u, groups, pay))
-            return false;
-    } else if (!resident_gather<NW, P, 1>(r, r.words + at1, kResMaxWG, 0u, r.G, pay)) {
-        return false;
-    }
-    tree();
-    return true;
-}
-
-// Wave 0, all lanes: the same sum of ONE value, wanted by workgroup 0 only, which gathers all workgroups in
-// one trip (lane l holds workgroups l, l + 64, ...: the tree of a group is a wave tree, the groups follow);
-// the other workgroups return as soon as they have published.
-__device__ __forceinline__ bool resident_collect_sum(const ResidentGrid &r, uint32_t at1, double &v)
-{
-    const uint32_t lane = threadIdx.x & 63u;
-    uint64_t pay[kResGroups][3];
-    resident_split(v, pay[0]);
-    if (lane == 0) resident_publish<3, kResSumBits>(r.words + at1, kResMaxWG, r.g, r.tok, pay[0]);
-    if (r.g != 0u) return true;
-    if (!resident_gather<3, kResSumBits, kResGroups>(r, r.words + at1, kResMaxWG, 0u, r.G, pay)) return false;
-    double s[kResGroups];
-#pragma unroll
-    for (int k = 0; k < kResGroups; ++k) s[k] = wave_pair_tree(resident_join(pay[k]));
-    static_assert(kResGroups == 4, "the tree over the groups is written out");
-    v = (s[0] + s[1]) + (s[2] + s[3]);
-    return true;
-}
 
 template <int DT, int METHOD, int L, int R>
 __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs args)
@@ -683,6 +492,7 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
     constexpr int kMaxBits = DT == SOAR_BF16 ? 15 : 31;
     __shared__ uint32_t s_max[kWaves];
     __shared__ double s_part[3][kParts];
+    __shared__ uint64_t s_cross[kSumDirect * SumWords<2>::kW];
     __shared__ float s_alpha1;
     __shared__ uint32_t s_amax, s_gone;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
@@ -699,7 +509,8 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
     grid.tok = grid.base = 0;
     grid.t0 = 0;
     grid.ticks = args.wait_ticks;
-    grid.words = reinterpret_cast<uint64_t *>(t.part);
+    ResidentWords &words = *reinterpret_cast<ResidentWords *>(t.part);
+    grid.words = words.max;
     uint64_t epoch = 0;
     if (grid.G > 1u) {
         epoch = __hip_atomic_load(epoch_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -709,18 +520,10 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
     // one lane: leave the launch and tell the others -- whoever gathers this workgroup's words, now or at a
     // later crossing, finds the complemented token in the first of them
     auto give_up = [&]() {
-        const uint64_t gone = ~grid.tok << kResSumBits, gone_max = ~grid.tok << kMaxBits;
-        __hip_atomic_store(grid.words + kResMax1 + grid.g, gone_max, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(grid.words + kResNM1 + grid.g, gone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(grid.words + kResErr1 + grid.g, gone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (grid.g % kResGroup == 0u) {
-            for (int c = 0; c < kResCopies; ++c) {
-                __hip_atomic_store(grid.words + kResMax2 + c * kResCopyStride + grid.g / kResGroup, gone_max, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(grid.words + kResNM2 + c * kResCopyStride + grid.g / kResGroup, gone, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
+        const uint64_t gone = ~grid.tok << kResSumBits;
+        leave_max(grid, ~grid.tok << kMaxBits);
+        leave_sums(grid, words.nm, gone);
+        __hip_atomic_store(words.err + grid.g, gone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // any change of the epoch will do for the next launch
         __hip_atomic_fetch_add(epoch_p, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (t.status) *t.status = SOAR_STATUS_GAVE_UP;
@@ -767,7 +570,7 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
         bool ok = true;
         if (grid.G > 1u) {
             uint32_t value = DT == SOAR_BF16 ? amax >> 16 : amax;
-            ok = resident_cross_max<kMaxBits>(grid, value);
+            ok = cross_max<kMaxBits>(grid, value);
             amax = DT == SOAR_BF16 ? value << 16 : value;
             if (lane == 0) {
                 if (!ok) give_up();
@@ -854,7 +657,7 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
                 double NM[2] = {workgroup_sum(0), workgroup_sum(1)};
                 bool ok = true;
                 if (grid.G > 1u) {
-                    ok = resident_cross_sums<2>(grid, kResNM1, kResNM2, NM);
+                    ok = cross_sums<2>(grid, words.nm, s_cross, NM);
                     if (!ok && lane == 0) give_up();
                 }
                 if (lane == 0) {
@@ -956,8 +759,9 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
     double total = workgroup_sum(2);
     bool ok = true;
     if (grid.G > 1u) {
-        if (t.sse) ok = resident_collect_sum(grid, kResErr1, total);
-        if (ok && grid.g != 0u) return;
+        if (t.sse) publish_sum(grid, words.err, total);
+        if (grid.g != 0u) return;
+        if (t.sse) ok = collect_sum(grid, words.err, total);
     }
     if (lane == 0) {
         if (!ok) { give_up(); return; }
