@@ -1,9 +1,11 @@
 """ctypes view of the HIP library's C-ABI (``include/soar.h``).
 
 Argument marshalling only: every step of the method runs inside the HIP
-kernels.  torch is used for device memory and streams.  There is no CPU
-fallback -- if ``libsoar_hip.so`` has not been built, or no GPU is present,
-the entry points raise.
+kernels.  torch is used for device memory and streams.  Calls that bring no
+buffers of their own go through the compiled module ``soar_host``, which
+allocates them and makes the same C call.  There is no CPU fallback -- if
+``libsoar_hip.so`` or the module has not been built, or no GPU is present, the
+entry points raise.
 """
 from __future__ import annotations
 
@@ -169,8 +171,26 @@ def lib():
     L.soar_status_string.restype = C.c_char_p
     L.soar_version.argtypes = []
     L.soar_version.restype = C.c_uint32
+    _bind_host(L)
     _lib = L
     return L
+
+
+_host = None
+
+
+def _bind_host(L):
+    """Load the compiled marshalling module and hand it the library's entry points (in the order of its EntryPoints)."""
+    global _host
+    try:
+        from . import soar_host
+    except ImportError as e:
+        raise RuntimeError(f"the module soar_host could not be loaded ({e}): build it with `python -m paper_2605_12245_amd.build` "
+                           "(there is no CPU fallback)") from e
+    soar_host.bind(*(C.cast(f, C.c_void_p).value for f in (
+        L.soar_workspace_bytes, L.soar_quantize_batch, L.soar_mxfp4_workspace_bytes, L.soar_mxfp4_quantize,
+        L.soar_dequantize_batch, L.soar_mxfp4_dequantize_batch, L.soar_recon_error_batch)))
+    _host = soar_host
 
 
 # ------------------------------------------------------------------ raw entry points
@@ -429,11 +449,23 @@ def new_batch_workspace(descs: Sequence[soar_tensor_desc], params: soar_params, 
     return torch.empty(n, dtype=torch.uint8, device=device)
 
 
+def _quantize_new(w, params, trace: bool, amax_in, where: str) -> Quantized:
+    """One tensor with new outputs and a workspace of its own."""
+    if not w.is_cuda:
+        _check_matrix(w)          # raises
+    *parts, rc = _host.quantize(w, C.addressof(params), trace, amax_in, _stream())
+    if rc != SOAR_OK:
+        raise SoarError(2, "soar_workspace_bytes") if rc < 0 else SoarError(rc, where)
+    return Quantized(*parts)
+
+
 def quantize(w: torch.Tensor, method: int = SOAR_METHOD_SOAR, dss_radius: int = 4,
              search_mode: int = SOAR_SEARCH_AUTO, workspace: Optional[torch.Tensor] = None,
              out: Optional[Quantized] = None, tiles_per_wg: int = 0) -> Quantized:
-    rows, cols, ld = _check_matrix(w)
     p = soar_default_params(method, dss_radius, search_mode, tiles_per_wg)
+    if out is None and workspace is None:
+        return _quantize_new(w, p, False, None, "soar_quantize")
+    rows, cols, ld = _check_matrix(w)
     dev = w.device
     if out is None:
         out = Quantized(torch.empty((rows, cols // 2), dtype=torch.uint8, device=dev),
@@ -478,6 +510,9 @@ def make_desc(w: torch.Tensor, out: Quantized, amax_in: Optional[torch.Tensor] =
 def quantize_iter(w: torch.Tensor, params: soar_params, workspace: Optional[torch.Tensor] = None,
                   out: Optional[Quantized] = None) -> Quantized:
     """One tensor through the iterated path (soar_quantize_batch with n = 1), with the error trace."""
+    if out is None and workspace is None and params.iters > 0:
+        lib()
+        return _quantize_new(w, params, True, None, "soar_quantize_batch")
     rows, cols, _ = _check_matrix(w)
     if out is None:
         out = new_outputs(rows, cols, w.device, params.iters)
@@ -497,6 +532,8 @@ def quantize_batch(descs: Sequence[soar_tensor_desc], params: soar_params, works
 def quantize_rtn_amax(w: torch.Tensor, amax_in: torch.Tensor, workspace: Optional[torch.Tensor] = None,
                       out: Optional[Quantized] = None) -> Quantized:
     """Plain NVFP4 (Sec. 3.1) of one tensor with its maximum supplied: a single pass over the data."""
+    if out is None and workspace is None:
+        return _quantize_new(w, soar_default_params(SOAR_METHOD_RTN, 0), False, amax_in, "soar_quantize_batch")
     rows, cols, _ = _check_matrix(w)
     if amax_in.dtype != torch.float32 or not amax_in.is_cuda:
         raise TypeError("amax_in must be a float32 tensor on the GPU")
@@ -532,24 +569,30 @@ def quantize_tensors(weights: Sequence[torch.Tensor], params: Optional[soar_para
     return outs
 
 
-def dequantize(q: Quantized, out_dtype=torch.bfloat16) -> torch.Tensor:
-    rows, cols = q.scales.shape[0], q.scales.shape[1] * 16
-    out = torch.empty((rows, cols), dtype=out_dtype, device=q.codes.device)
-    rc = soar_dequantize(q.codes.data_ptr(), q.scales.data_ptr(), q.global_scale.data_ptr(), rows, cols,
-                         _dtype_code(out), out.data_ptr(), cols, _stream())
+def _dequantize_new(qs: list, mx: bool, out_dtype, where: str) -> list:
+    if out_dtype not in (torch.bfloat16, torch.float32):
+        raise TypeError("weights must be bfloat16 or float32")
+    lib()
+    outs, rc = _host.dequantize(qs, mx, out_dtype == torch.float32, _stream())
     if rc != SOAR_OK:
-        raise SoarError(rc, "soar_dequantize")
-    return out
+        raise SoarError(rc, where)
+    return outs
+
+
+def dequantize(q: Quantized, out_dtype=torch.bfloat16) -> torch.Tensor:
+    return _dequantize_new([q], False, out_dtype, "soar_dequantize")[0]
+
+
+def _recon_error_new(weights: list, qs: list, where: str) -> torch.Tensor:
+    lib()
+    sums, rc = _host.recon_error(weights, qs, _stream())
+    if rc != SOAR_OK:
+        raise SoarError(rc, where)
+    return sums
 
 
 def recon_error(w: torch.Tensor, q: Quantized) -> torch.Tensor:
-    rows, cols, ld = _check_matrix(w)
-    sse = torch.empty(1, dtype=torch.float64, device=w.device)
-    rc = soar_recon_error(w.data_ptr(), _dtype_code(w), rows, cols, ld, q.codes.data_ptr(),
-                          q.scales.data_ptr(), q.global_scale.data_ptr(), sse.data_ptr(), _stream())
-    if rc != SOAR_OK:
-        raise SoarError(rc, "soar_recon_error")
-    return sse
+    return _recon_error_new([w], [q], "soar_recon_error")
 
 
 def stored_desc(q: Quantized, w: Optional[torch.Tensor] = None, out: Optional[torch.Tensor] = None,
@@ -569,23 +612,14 @@ def stored_desc(q: Quantized, w: Optional[torch.Tensor] = None, out: Optional[to
 
 def dequantize_batch(qs: Sequence[Quantized], out_dtype=torch.bfloat16) -> list:
     """Eq. 3 for a list of stored tensors in a handful of launches."""
-    outs = [torch.empty((q.scales.shape[0], q.scales.shape[1] * 16), dtype=out_dtype, device=q.codes.device) for q in qs]
-    rc = soar_dequantize_batch([stored_desc(q, out=o) for q, o in zip(qs, outs)], _stream())
-    if rc != SOAR_OK:
-        raise SoarError(rc, "soar_dequantize_batch")
-    return outs
+    return _dequantize_new(list(qs), False, out_dtype, "soar_dequantize_batch")
 
 
 def recon_error_batch(weights: Sequence[torch.Tensor], qs: Sequence[Quantized]) -> torch.Tensor:
     """Eq. 4 for a list of tensors in a handful of launches: one binary64 sum per tensor."""
     if not weights:
         return torch.empty(0, dtype=torch.float64)
-    sses = torch.empty(len(weights), dtype=torch.float64, device=weights[0].device)
-    rc = soar_recon_error_batch([stored_desc(q, w=w, sse=sses[k:k + 1]) for k, (w, q) in enumerate(zip(weights, qs))],
-                                _stream())
-    if rc != SOAR_OK:
-        raise SoarError(rc, "soar_recon_error_batch")
-    return sses
+    return _recon_error_new(list(weights), list(qs), "soar_recon_error_batch")
 
 
 # ------------------------------------------------------------------ MXFP4
@@ -600,6 +634,12 @@ def mx_new_outputs(rows: int, cols: int, device) -> Quantized:
 def mx_quantize(w: torch.Tensor, params: soar_mx_params, workspace: Optional[torch.Tensor] = None,
                 out: Optional[Quantized] = None) -> Quantized:
     """MXFP4 conversion of one tensor (plain or with the decoupled scale search); scales are E8M0 bytes."""
+    if out is None and workspace is None and w.is_cuda:
+        lib()
+        *parts, rc = _host.mx_quantize(w, C.addressof(params), _stream())
+        if rc != SOAR_OK:
+            raise SoarError(2, "soar_mxfp4_workspace_bytes") if rc < 0 else SoarError(rc, "soar_mxfp4_quantize")
+        return Quantized(*parts)
     rows, cols, ld = _check_matrix(w)
     if out is None:
         out = mx_new_outputs(rows, cols, w.device)
@@ -645,18 +685,8 @@ def mx_stored_desc(q: Quantized, out: torch.Tensor) -> "soar_stored_desc":
 
 def mx_dequantize_batch(qs: Sequence[Quantized], out_dtype=torch.bfloat16) -> list:
     """MXFP4 tensors back to bf16 / fp32 in a handful of launches."""
-    outs = [torch.empty((q.scales.shape[0], q.scales.shape[1] * 32), dtype=out_dtype, device=q.codes.device) for q in qs]
-    rc = soar_mxfp4_dequantize_batch([mx_stored_desc(q, o) for q, o in zip(qs, outs)], _stream())
-    if rc != SOAR_OK:
-        raise SoarError(rc, "soar_mxfp4_dequantize_batch")
-    return outs
+    return _dequantize_new(list(qs), True, out_dtype, "soar_mxfp4_dequantize_batch")
 
 
 def mx_dequantize(q: Quantized, out_dtype=torch.bfloat16) -> torch.Tensor:
-    rows, cols = q.scales.shape[0], q.scales.shape[1] * 32
-    out = torch.empty((rows, cols), dtype=out_dtype, device=q.codes.device)
-    rc = soar_mxfp4_dequantize(q.codes.data_ptr(), q.scales.data_ptr(), rows, cols, _dtype_code(out),
-                               out.data_ptr(), cols, _stream())
-    if rc != SOAR_OK:
-        raise SoarError(rc, "soar_mxfp4_dequantize")
-    return out
+    return _dequantize_new([q], True, out_dtype, "soar_mxfp4_dequantize")[0]

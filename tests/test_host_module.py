@@ -1,0 +1,74 @@
+"""The compiled marshalling module: the errors that the Python checks raised before, and on the GPU the same results and lifetimes
+as calls with buffers of their own."""
+import pytest
+import torch
+
+from paper_2605_12245_amd import binding as B
+
+DEV = "cuda:0"
+
+
+def test_module_is_built_and_bound():
+    B.lib()
+    assert B._host is not None
+    with pytest.raises(TypeError, match="addresses"):
+        B._host.bind(1, 2)
+    with pytest.raises(ValueError, match="no address"):
+        B._host.bind(*([0] * 7))
+
+
+def test_errors_before_anything_is_enqueued():
+    w = torch.zeros(4, 32)
+    for call in (lambda: B.quantize(w), lambda: B.quantize_rtn_amax(w, torch.ones(1)), lambda: B.quantize_iter(w, B.soar_paper_params()),
+                 lambda: B.mx_quantize(w, B.soar_mx_default_params())):
+        with pytest.raises(RuntimeError, match="must live on the GPU"):
+            call()
+    q = B.Quantized(w, w, w, w, w)
+    for call in (lambda: B.dequantize(q, torch.float16), lambda: B.mx_dequantize_batch([q], torch.float64)):
+        with pytest.raises(TypeError, match="bfloat16 or float32"):
+            call()
+    assert B.recon_error_batch([], []).numel() == 0
+
+
+@pytest.mark.gpu
+def test_same_as_calls_that_bring_their_buffers():
+    w = (torch.randn(37, 272, device=DEV) * 0.02).to(torch.bfloat16)[:, :256]
+    p = B.soar_paper_params(iters=5)
+    a, b = B.quantize_iter(w, p), B.quantize_iter(w, p, out=B.new_outputs(37, 256, DEV, 5))
+    m, n = B.mx_quantize(w, B.soar_mx_default_params()), B.mx_quantize(w, B.soar_mx_default_params(), out=B.mx_new_outputs(37, 256, DEV))
+    c, d = B.quantize(w, dss_radius=2), B.quantize(w, dss_radius=2, out=B.new_outputs(37, 256, DEV))
+    amax = w.abs().max().float().reshape(1)
+    e, f = B.quantize_rtn_amax(w, amax), B.quantize_rtn_amax(w, amax, out=B.new_outputs(37, 256, DEV))
+    torch.cuda.synchronize()
+    for x, y in ((a, b), (m, n), (c, d), (e, f)):
+        for name in ("codes", "scales", "global_scale", "sse", "status", "iters_run", "sse_trace"):
+            s, t = getattr(x, name), getattr(y, name)
+            assert (s is None) == (t is None), name
+            if s is not None:
+                assert s.dtype == t.dtype and s.shape == t.shape and s.is_contiguous() and s.device == t.device, name
+                assert torch.equal(torch.nan_to_num(s, nan=-1.0) if s.is_floating_point() else s,
+                                   torch.nan_to_num(t, nan=-1.0) if t.is_floating_point() else t), name
+    assert torch.equal(B.dequantize(c), B.dequantize_batch((c, e))[0]) and B.dequantize(c, torch.float32).dtype == torch.float32
+    assert torch.equal(B.mx_dequantize(m), B.mx_dequantize_batch([m])[0])
+    assert torch.equal(B.recon_error_batch((w, w), (c, e))[:1], B.recon_error(w, c))
+    # a degenerate tensor: no iteration is carried out and no entry of the trace written
+    z = B.quantize_iter(torch.zeros_like(w), p)
+    torch.cuda.synchronize()
+    assert int(z.iters_run.item()) == 0 and bool(z.sse_trace.isnan().all())
+
+
+@pytest.mark.gpu
+def test_errors_with_tensors_on_the_gpu():
+    w = torch.zeros(8, 64, device=DEV)
+    for bad, error in ((w.half(), TypeError), (w.t(), ValueError), (w[0], ValueError)):
+        for call in (lambda: B.quantize(bad), lambda: B.mx_quantize(bad, B.soar_mx_default_params()),
+                     lambda: B.quantize_iter(bad, B.soar_paper_params()), lambda: B.quantize_rtn_amax(bad, torch.ones(1, device=DEV))):
+            with pytest.raises(error):
+                call()
+    with pytest.raises(B.SoarError):
+        B.quantize(torch.zeros(8, 40, device=DEV))             # columns: no multiple of 16
+    with pytest.raises(B.SoarError):
+        B.quantize(w, dss_radius=1000)
+    for amax in (torch.ones(1), torch.ones(1, device=DEV).double(), 1.0):
+        with pytest.raises(TypeError, match="amax_in"):
+            B.quantize_rtn_amax(w, amax)
