@@ -118,6 +118,9 @@ __global__ __launch_bounds__(kWG) void k_stats(const Batch batch)
 
     uint32_t lwg;
     const Task t = batch.t[find_task(batch, lwg)];
+    // backwards through the tensor: what the maximum read last is still in the last-level cache, and the search begins with what
+    // this pass reads last (28672 x 8192 bf16, 470 MB: 300.5 -> 296.6 us, fp32 579 -> 575; tensors the cache holds: no change)
+    lwg = t.n_wg - 1u - lwg;
     const uint32_t tid = threadIdx.x;
     const uint32_t amax_bits = t.ctrl->amax_bits;
     const bool degenerate = amax_bits == 0u || amax_bits >= 0x7F800000u;
