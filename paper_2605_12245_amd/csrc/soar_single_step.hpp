@@ -105,9 +105,9 @@ __global__ __launch_bounds__(kWG) void k_absmax(const Batch batch)
 // of kStage consecutive tiles are staged in LDS; lane t then folds the kStage
 // adjacent terms t*kStage.. in registers and one wave tree finishes the group,
 // which is the same adjacent-pair tree at a fraction of the cross-lane work.
-// Each block's a/b -- or -Delta0 when its codes are all zero -- is kept for the
-// search kernel.
-template <int DT>
+// CARRY: each block's a/b -- or -Delta0 when its codes are all zero -- is kept for the
+// search kernel, which otherwise forms it again (see carries_ratios).
+template <int DT, bool CARRY>
 __global__ __launch_bounds__(kWG) void k_stats(const Batch batch)
 {
     __shared__ double2 s_terms[kStage * kWG];
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kWG) void k_stats(const Batch batch)
                     tN = (double)a * (double)delta0;
                     tM = ((double)b * (double)delta0) * (double)delta0;
                 }
-                __builtin_nontemporal_store(rho, t.rho + i);
+                if constexpr (CARRY) __builtin_nontemporal_store(rho, t.rho + i);
             }
             s_terms[kk * kWG + tid] = make_double2(tN, tM);
         }
@@ -327,7 +327,7 @@ __device__ __forceinline__ int new_codes(const float w[16], float rho, float alp
 // METHOD RTN emits the Eq. 1-2 state instead.
 // (bf16: held to 64 registers, eight waves per SIMD; left to itself the compiler takes 83 for a shorter schedule and loses more in
 // occupancy than it gains)
-template <int DT, int METHOD>
+template <int DT, int METHOD, bool CARRY = false>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(DT == SOAR_BF16 ? 8 : 4))) void k_search(const Batch batch)
 {
     __shared__ double s_wave[4];
@@ -396,7 +396,16 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(DT == SOAR_
             out_code = c0;
             out_err = block_error(w, q, alpha0 * delta0);
         } else {
-            const float rho = __builtin_nontemporal_load(t.rho + i);                // a / b >= 0, or -Delta0 where b == 0
+            float rho = 0.0f;                                                       // a / b >= 0, or -Delta0 where b == 0
+            if constexpr (CARRY) {
+                rho = __builtin_nontemporal_load(t.rho + i);
+            } else if (amax_bits < 0x7F800000u) {
+                uint32_t c0;
+                float delta0, a, b;
+                block_init(w, gs, c0, delta0, nib, q);
+                block_sums(w, q, a, b);
+                rho = block_ratio(a, b, delta0, gs.fast);
+            }
             const int centre = new_codes(w, rho, alpha1, inv_alpha1, fast, nib, q);
             int best;
             float best_err;
