@@ -153,7 +153,8 @@ typedef struct {
                                 some compute units, SOAR_RESIDENT_NEVER is the better choice */
     int32_t  resident_wait_us; /* 0 = library default (2 s); > 0: the bound, in microseconds,
                                 after which a workgroup of that kernel stops waiting for the
-                                others to arrive (every workgroup then does).  Single-step: all
+                                others to arrive (every workgroup then does), counted from that
+                                workgroup's start.  Single-step: all
                                 leave and set SOAR_STATUS_GAVE_UP; the bound covers a
                                 workgroup's waits together.  Iterated path: one of them, the
                                 last to leave, finishes the tensor by itself (a compute unit's
