@@ -350,7 +350,8 @@ struct FactorGrid {
 __device__ __forceinline__ float factor_error(const float w[16], float t, float s, uint32_t nib[2])
 {
     float q[16];
-    nib[0] = nib[1] = 0u;
+    nib[0] = any_word();
+    nib[1] = any_word();
     assign_codes_rcp<true>(w, t, nib, q);
     return block_error(w, q, s);
 }
@@ -396,7 +397,7 @@ __device__ __forceinline__ float best_factor(const float w[16], float alpha, flo
 
 __device__ __forceinline__ void joint_search_nearest(const float w[16], float alpha, float delta_star, const FactorGrid &grid,
                                                      bool bracket, int c0, int radius, float &best_err, int &best_code,
-                                                     uint32_t best_nib[2], float q[16])
+                                                     uint32_t best_nib[2])
 {
     const float base_index = __builtin_amdgcn_rcpf(alpha * delta_star) * grid.index_per_beta;
     int best_k;
@@ -427,8 +428,6 @@ __device__ __forceinline__ void joint_search_nearest(const float w[16], float al
             next((c & 1) ? max(c0 - o, (int)kE4M3Min) : min(c0 + o, (int)kE4M3Max));
         }
     }
-    fp4x8_values(best_nib[0], q);
-    fp4x8_values(best_nib[1], q + 8);
 }
 
 // the Eq. 1-2 state of a block: a, b, the scale's value, the error and the ratio for Eq. 6 (keep_scale: -Delta0, the
@@ -560,8 +559,8 @@ __device__ __forceinline__ void iterate_block(const float w[16], float rho, cons
     if (NEAREST && __builtin_expect(js.in_range && all_near_one(rho), 1)) {
         const float delta_star = (rho < 0.0f) ? -rho : div_midrange(rho, js.alpha, js.inv_alpha);
         const int c0 = js.bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
-        joint_search_nearest(w, js.alpha, delta_star, js.grid, js.bracket, c0, js.radius, x.err, code, x.nib, q);
-        block_sums(w, q, x.a, x.b);
+        joint_search_nearest(w, js.alpha, delta_star, js.grid, js.bracket, c0, js.radius, x.err, code, x.nib);
+        code_sums(w, x.nib, x.a, x.b);
         x.d = e4m3_value((uint32_t)code);
         const float ratio = div_midrange(x.a, x.b, rcp_midrange(x.b));
         x.rho = (x.b == 0.0f || js.dss_only) ? -x.d : ratio;

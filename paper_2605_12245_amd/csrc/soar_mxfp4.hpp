@@ -244,7 +244,8 @@ __device__ __forceinline__ void mx_search_changes(const float w[32], int e0, con
 __device__ __forceinline__ float mx_factor_error(const float w[32], float t, float s, uint32_t nib[4])
 {
     float q[32];
-    nib[0] = nib[1] = nib[2] = nib[3] = 0u;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) nib[h] = any_word();
     mx_assign<true>(w, t, nib, q);
     return mx_block_error(w, q, s);
 }

@@ -651,12 +651,12 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
             for (int k = 0; k < R; ++k) {
                 tN[k] = tM[k] = 0.0;
                 if (blk(k) < t.nblk) {
-                    float w[16], q[16];
+                    float w[16];
                     uint32_t nib[2], c0;
                     float delta0, a, b;
                     widen(k, w);
-                    block_init(w, gs, c0, delta0, nib, q);
-                    block_sums(w, q, a, b);
+                    block_init(w, gs, c0, delta0, nib);
+                    code_sums(w, nib, a, b);
                     rho[k] = block_ratio(a, b, delta0, gs.fast);
                     tN[k] = (double)a * (double)delta0;
                     tM[k] = ((double)b * (double)delta0) * (double)delta0;
