@@ -28,7 +28,7 @@ namespace {
 // one's share; their bound (later_ticks) is there for a machine that has stopped working.
 // 1024 x 4096 bf16, paper settings: 72-88 -> 42 us a call (loads 1, maximum 2, state 3, sums 3, an iteration 5-6 and
 // its crossing 4 us); 4096 x 4096 fp32, search-only arm: 169 -> 140 us, 33 of them an iteration's search.
-// The crossing words inside Task::part, apart from those of other kernels
+// The crossing words inside Task::part (where other kernels' words may lie: theirs carry other tokens)
 struct IterResidentWords {
     uint64_t max[kMaxEnd];
     SumWords<3> sums[2];                  // of alternating crossings

@@ -465,10 +465,9 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(DT == SOAR_
 // fp32 blocks per lane a wave's range is two packets).  So the first levels of the tree are additions in
 // registers, one DPP wave tree covers a packet of the whole wave, the L/64 wave sums, in block order, go
 // through the wave tree once more, and a lane's scale bytes and code bytes leave in one or two stores.
-// Packed rows are read through the coalescing wave exchange (load_wave_pieces).  Across workgroups the tree continues over groups of 64 consecutive workgroups (one wave
-// tree, a workgroup per lane) and then over the at most 4 groups.  Same arithmetic, same trees as the
-// three-pass path: identical bytes.
-//
+// Packed rows are read through the coalescing wave exchange (load_wave_pieces).  Across workgroups the tree continues over groups of
+// consecutive workgroups (one wave tree, a workgroup per lane) and then over the groups (cross_sums).  Same arithmetic, same trees
+// as the three-pass path: identical bytes.
 constexpr int kResMaxPer = 4;             // blocks per lane, at most
 
 // The crossing words inside Task::part
