@@ -20,12 +20,12 @@ namespace {
 // is the call's nonce alone, without the epoch: calls being captured do not come here, and a workgroup that starts after
 // others have given up has to recognise their words.
 // The one wait that may not end is the first: the GPU may hold the rest of the grid back, behind another process's or
-// stream's kernels or a mask of compute units.  It is bounded by wait_ticks, from the workgroup's start on.  A workgroup whose time is up tells the
-// others, which then leave as well, at the first crossing or -- those that found the first complete -- at the second;
-// whoever leaves counts itself out, and the last to do so does the whole tensor alone: all blocks are then its own R * G
-// tiles (G rounded up to a power of two), the same tree, no crossings.  So a call always finishes, as it does with a
-// launch per iteration.  Beyond the first crossing every workgroup is running and the waits last as long as the slowest
-// one's share; their bound (later_ticks) is there for a machine that has stopped working.
+// stream's kernels or a mask of compute units.  It is bounded by wait_ticks, from where the workgroup has read its blocks and
+// begins to wait.  A workgroup whose time is up tells the others, which then leave as well, at the first crossing or -- those
+// that found the first complete -- at the second; whoever leaves counts itself out, and the last to do so does the whole
+// tensor alone: all blocks are then its own R * G tiles (G rounded up to a power of two), the same tree, no crossings.  So a
+// call always finishes, as it does with a launch per iteration.  Beyond the first crossing every workgroup is running and the
+// waits last as long as the slowest one's share; their bound (later_ticks) is there for a machine that has stopped working.
 // 1024 x 4096 bf16, paper settings: 72-88 -> 42 us a call (loads 1, maximum 2, state 3, sums 3, an iteration 5-6 and
 // its crossing 4 us); 4096 x 4096 fp32, search-only arm: 169 -> 140 us, 33 of them an iteration's search.
 // The crossing words inside Task::part (where other kernels' words may lie: theirs carry other tokens)
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
     grid.g = blockIdx.x;
     grid.G = gridDim.x;
     grid.tok = grid.base = args.r.nonce;
-    grid.t0 = (uint64_t)wall_clock64();   // of the first wait: a bound of a microsecond is over before the grid can have met
+    grid.t0 = 0;
     grid.ticks = args.r.wait_ticks;
     IterResidentWords &words = *reinterpret_cast<IterResidentWords *>(t.part);
     grid.words = words.max;
@@ -145,6 +145,7 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
             bool ok = true;
             if (grid.G > 1u) {
                 uint32_t value = DT == SOAR_BF16 ? amax >> 16 : amax;
+                grid.t0 = (uint64_t)wall_clock64();
                 ok = cross_max<kMaxBits>(grid, value);
                 amax = DT == SOAR_BF16 ? value << 16 : value;
                 if (lane == 0 && !ok) give_up();

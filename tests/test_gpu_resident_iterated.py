@@ -90,18 +90,42 @@ def test_strided_degenerate_absent_outputs_and_any_workspace():
     assert o.sse.item() == -1.0 and o.status.item() == -1 and o.global_scale.item() == full.global_scale.item()
 
 
+def gives_up(w, p, ws, fill=None):
+    """a call whose bound of one microsecond is over, and the same call on the other path.  A crossing takes two trips through
+    memory, 2 us and more, but a workgroup that arrives late may find everything there: such a call is made again"""
+    p.resident_wait_us = 1
+    for _ in range(20):
+        if fill is not None:
+            ws.fill_(fill)
+        got, want = both(w, p, ws)
+        if int(got.status.item()) & B.SOAR_STATUS_GAVE_UP:
+            break
+    p.resident_wait_us = 0
+    return got, want
+
+
 def test_bounded_wait_gives_up_and_the_next_call_is_unaffected():
     """one microsecond is over before a crossing is complete: every workgroup says so and leaves"""
     w = heavy(2047, 4096, 9, torch.bfloat16)
     p = settings(B.SOAR_METHOD_SOAR, iters=4)
     ws = B.new_batch_workspace([B.make_desc(w, B.new_outputs(2047, 4096, DEV, 4))], p, DEV)
     for rep in range(3):
-        p.resident, p.resident_wait_us = B.SOAR_RESIDENT_AUTO, 1
-        o = B.quantize_iter(w, p, workspace=ws)
-        torch.cuda.synchronize()
+        o, _ = gives_up(w, p, ws)
         assert int(o.status.item()) == B.SOAR_STATUS_GAVE_UP
-        p.resident_wait_us = 0
         same(*both(w, p, ws), rep)
+
+
+def test_the_bound_does_not_count_the_time_of_the_loads():
+    """90 MB take more than 11 us to read; the workgroups arrive within 4 us of one another"""
+    w = heavy(5500, 4096, 9, torch.float32)
+    p = settings(B.SOAR_METHOD_CJSO_ONLY, iters=2)
+    p.resident_wait_us = 9
+    ws = B.new_workspace(5500, 4096, p, DEV)
+    statuses = []
+    for _ in range(20):
+        o = B.quantize_iter(w, p, workspace=ws)
+        statuses.append(int(o.status.item()))
+    assert statuses.count(0) >= 10, statuses
 
 
 @pytest.mark.parametrize("rows,cols", [(65, 4096), (1024, 4096), (2047, 4096), (5500, 4096)])      # 17 to 256 workgroups, 1 to 8 tiles
@@ -118,13 +142,10 @@ def test_a_call_that_gives_up_is_finished_all_the_same(rows, cols, dtype):
         p = settings(arm, iters=3)
         ws = B.new_workspace(rows, cols, p, DEV)
         for fill in (0xFF, 0):
-            ws.fill_(fill)
-            p.resident_wait_us = 1
-            got, want = both(w, p, ws)
+            got, want = gives_up(w, p, ws, fill)
             assert int(got.status.item()) == B.SOAR_STATUS_GAVE_UP | status, what
             got.status.fill_(status)
             same(got, want, (what, fill))
-            p.resident_wait_us = 0
             same(*both(w, p, ws), (what, fill, "the next call"))
 
 
