@@ -532,10 +532,10 @@ def quantize_batch(descs: Sequence[soar_tensor_desc], params: soar_params, works
 def quantize_rtn_amax(w: torch.Tensor, amax_in: torch.Tensor, workspace: Optional[torch.Tensor] = None,
                       out: Optional[Quantized] = None) -> Quantized:
     """Plain NVFP4 (Sec. 3.1) of one tensor with its maximum supplied: a single pass over the data."""
-    if out is None and workspace is None:
+    if out is None and workspace is None and amax_in is not None:      # None there would mean: measure it
         return _quantize_new(w, soar_default_params(SOAR_METHOD_RTN, 0), False, amax_in, "soar_quantize_batch")
     rows, cols, _ = _check_matrix(w)
-    if amax_in.dtype != torch.float32 or not amax_in.is_cuda:
+    if not isinstance(amax_in, torch.Tensor) or amax_in.dtype != torch.float32 or not amax_in.is_cuda or amax_in.numel() == 0:
         raise TypeError("amax_in must be a float32 tensor on the GPU")
     if out is None:
         out = new_outputs(rows, cols, w.device)

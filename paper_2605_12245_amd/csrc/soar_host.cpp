@@ -99,8 +99,9 @@ PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     if (PyErr_Occurred()) return nullptr;
     soar_tensor_desc d = {};
     if (!check_matrix(w, d.dtype)) return nullptr;
-    if (args[3] != Py_None &&
-        !(THPVariable_Check(args[3]) && THPVariable_Unpack(args[3]).scalar_type() == at::kFloat && THPVariable_Unpack(args[3]).is_cuda())) {
+    if (args[3] != Py_None &&       // an empty tensor has no address, which would mean: measure it
+        !(THPVariable_Check(args[3]) && THPVariable_Unpack(args[3]).scalar_type() == at::kFloat && THPVariable_Unpack(args[3]).is_cuda() &&
+          THPVariable_Unpack(args[3]).numel() > 0)) {
         PyErr_SetString(PyExc_TypeError, "amax_in must be a float32 tensor on the GPU");
         return nullptr;
     }

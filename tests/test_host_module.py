@@ -72,3 +72,12 @@ def test_errors_with_tensors_on_the_gpu():
     for amax in (torch.ones(1), torch.ones(1, device=DEV).double(), 1.0):
         with pytest.raises(TypeError, match="amax_in"):
             B.quantize_rtn_amax(w, amax)
+
+
+@pytest.mark.gpu
+def test_a_maximum_that_is_missing_is_not_measured_instead():
+    w = (torch.randn(16, 64, device=DEV) * 0.02).to(torch.bfloat16)
+    for amax in (None, torch.empty(0, device=DEV)):
+        for more in ({}, {"out": B.new_outputs(16, 64, DEV)}):
+            with pytest.raises(TypeError, match="amax_in"):
+                B.quantize_rtn_amax(w, amax, **more)
