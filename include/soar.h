@@ -274,7 +274,8 @@ typedef struct {
     double     *d_sse;           /* may be NULL */
     int32_t    *d_status;        /* may be NULL */
     int32_t    *d_iters_run;     /* may be NULL; 1 int32: iterations carried out (0 for an
-                                    all-zero or non-finite tensor)                      */
+                                    all-zero or non-finite tensor); written by every call
+                                    that returns SOAR_OK                                */
     double     *d_sse_trace;     /* may be NULL; iters+1 doubles: [0] the error of the
                                     Eq. 1-2 state, [t] the error after iteration t;
                                     entries after an early stop are not written         */

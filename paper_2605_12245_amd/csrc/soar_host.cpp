@@ -113,12 +113,10 @@ PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     const at::Tensor codes = empty({d.rows, d.cols / 2}, at::kByte, device), scales = empty({d.rows, d.cols / 16}, at::kByte, device);
     const at::Tensor gscale = empty({1}, at::kFloat, device), sse = empty({1}, at::kDouble, device), status = empty({1}, at::kInt, device);
     if (trace_wanted) {
-        // NaN where an entry is not written; the number of iterations starts as the zero in the low half of one more NaN, so
-        // that one fill serves both
-        const at::Tensor both = at::full({params->iters + 2}, std::numeric_limits<double>::quiet_NaN(),
-                                         at::TensorOptions().dtype(at::kDouble).device(device));
-        trace = both.narrow(0, 0, params->iters + 1);
-        iters_run = both.narrow(0, params->iters + 1, 1).view(at::kInt).narrow(0, 0, 1);
+        // NaN where an entry is not written; the number of iterations is written by every call that is carried out
+        trace = at::full({(int64_t)params->iters + 1}, std::numeric_limits<double>::quiet_NaN(),
+                         at::TensorOptions().dtype(at::kDouble).device(device));
+        iters_run = empty({1}, at::kInt, device);
         d.d_iters_run = static_cast<int32_t *>(iters_run.data_ptr());
         d.d_sse_trace = static_cast<double *>(trace.data_ptr());
     }

@@ -92,6 +92,7 @@ __global__ __launch_bounds__(L) void k_iter_resident(const Task t, const IterRes
         leave_max(grid, ~grid.base << kMaxBits);
         for (uint32_t b = 0; b < 2; ++b) leave_sums(grid, words.sums[b], ~grid.base << kResSumBits);
         if (t.status) *t.status = SOAR_STATUS_GAVE_UP;
+        if (t.iters_run) *t.iters_run = 0;
     };
     // every lane of a workgroup that has given up: true in the last one to leave, which finds itself the only workgroup
     // of a launch over the whole tensor, with everybody's stores performed before its own

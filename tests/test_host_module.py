@@ -81,3 +81,15 @@ def test_a_maximum_that_is_missing_is_not_measured_instead():
         for more in ({}, {"out": B.new_outputs(16, 64, DEV)}):
             with pytest.raises(TypeError, match="amax_in"):
                 B.quantize_rtn_amax(w, amax, **more)
+
+
+@pytest.mark.gpu
+def test_outputs_have_storages_of_their_own():
+    w = (torch.randn(64, 256, device=DEV) * 0.02).to(torch.bfloat16)
+    q = B.quantize_iter(w, B.soar_paper_params(iters=5))
+    outs = (q.codes, q.scales, q.global_scale, q.sse, q.status, q.iters_run, q.sse_trace)
+    assert len({t.untyped_storage().data_ptr() for t in outs}) == len(outs)
+    for t in outs:
+        assert t.untyped_storage().nbytes() == t.numel() * t.element_size() and not t._is_view() and t.storage_offset() == 0
+    q.sse_trace.resize_(2)
+    assert 1 <= int(q.iters_run.item()) <= 5
