@@ -110,6 +110,9 @@ PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     d.ld_elems = w.stride(0);
     const at::Device device = w.device();
     at::Tensor iters_run, trace;
+    // before the outputs: their sizes come from the parameters that this checks
+    const size_t bytes = entry.workspace_bytes(d.rows, d.cols, params);
+    if (bytes == 0) return result({}, {}, {}, {}, {}, {}, {}, kNoWorkspace);
     const at::Tensor codes = empty({d.rows, d.cols / 2}, at::kByte, device), scales = empty({d.rows, d.cols / 16}, at::kByte, device);
     const at::Tensor gscale = empty({1}, at::kFloat, device), sse = empty({1}, at::kDouble, device), status = empty({1}, at::kInt, device);
     if (trace_wanted) {
@@ -121,8 +124,6 @@ PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
         d.d_sse_trace = static_cast<double *>(trace.data_ptr());
     }
     if (args[3] != Py_None) d.d_amax_in = static_cast<const float *>(THPVariable_Unpack(args[3]).data_ptr());
-    const size_t bytes = entry.workspace_bytes(d.rows, d.cols, params);
-    if (bytes == 0) return result(codes, scales, gscale, sse, status, iters_run, trace, kNoWorkspace);
     const at::Tensor workspace = empty({(int64_t)bytes}, at::kByte, device);
     d.d_w = w.data_ptr();
     d.d_codes = static_cast<uint8_t *>(codes.data_ptr());

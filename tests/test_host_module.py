@@ -93,3 +93,11 @@ def test_outputs_have_storages_of_their_own():
         assert t.untyped_storage().nbytes() == t.numel() * t.element_size() and not t._is_view() and t.storage_offset() == 0
     q.sse_trace.resize_(2)
     assert 1 <= int(q.iters_run.item()) <= 5
+
+
+@pytest.mark.gpu
+def test_a_number_of_iterations_out_of_range_is_a_parameter_error():
+    w = torch.zeros(8, 64, device=DEV)
+    for iters in (2**31 - 1, 2**31 - 2):
+        with pytest.raises(B.SoarError, match="soar_workspace_bytes"):
+            B.quantize_iter(w, B.soar_paper_params(iters=iters))
