@@ -31,6 +31,16 @@ struct EntryPoints {
 };
 EntryPoints entry;
 
+// The interpreter lock given back for a scope: taken again also where the call ends in a C++ exception, which
+// END_HANDLE_TH_ERRORS turns into a Python one.
+struct Unlocked {
+    PyThreadState *state = PyEval_SaveThread();
+    Unlocked() = default;
+    ~Unlocked() { PyEval_RestoreThread(state); }
+    Unlocked(const Unlocked &) = delete;
+    Unlocked &operator=(const Unlocked &) = delete;
+};
+
 constexpr int kNoWorkspace = -1;          // the library names no workspace size: its parameter error
 
 at::Tensor empty(at::IntArrayRef sizes, at::ScalarType type, const at::Device &device)
@@ -133,9 +143,10 @@ PyObject *quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     d.d_status = static_cast<int32_t *>(status.data_ptr());
     void *ws = workspace.data_ptr();
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = entry.quantize_batch(1, &d, params, ws, bytes, stream);
-    Py_END_ALLOW_THREADS
+    {
+        const Unlocked scope;
+        rc = entry.quantize_batch(1, &d, params, ws, bytes, stream);
+    }
     return result(codes, scales, gscale, sse, status, iters_run, trace, rc);
     END_HANDLE_TH_ERRORS
 }
@@ -168,9 +179,10 @@ PyObject *mx_quantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     int32_t *st = static_cast<int32_t *>(status.data_ptr());
     void *ws = workspace.data_ptr();
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = entry.mx_quantize(p, (soar_dtype)dtype, rows, cols, ld, params, c, s, e, st, ws, bytes, stream);
-    Py_END_ALLOW_THREADS
+    {
+        const Unlocked scope;
+        rc = entry.mx_quantize(p, (soar_dtype)dtype, rows, cols, ld, params, c, s, e, st, ws, bytes, stream);
+    }
     return result(codes, scales, at::Tensor(), sse, status, at::Tensor(), at::Tensor(), rc);
     END_HANDLE_TH_ERRORS
 }
@@ -233,9 +245,10 @@ PyObject *dequantize(PyObject *, PyObject *const *args, Py_ssize_t n)
         d.d_out = outs[(size_t)k].data_ptr();
     }
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = (mx ? entry.mx_dequantize_batch : entry.dequantize_batch)((int32_t)count, descs.data(), stream);
-    Py_END_ALLOW_THREADS
+    {
+        const Unlocked scope;
+        rc = (mx ? entry.mx_dequantize_batch : entry.dequantize_batch)((int32_t)count, descs.data(), stream);
+    }
     const Ref list(PyList_New(count));
     if (!list.o) return nullptr;
     for (Py_ssize_t k = 0; k < count; ++k) {
@@ -277,9 +290,10 @@ PyObject *recon_error(PyObject *, PyObject *const *args, Py_ssize_t n)
         d.d_sse = static_cast<double *>(sums.data_ptr()) + k;
     }
     int rc;
-    Py_BEGIN_ALLOW_THREADS
-    rc = entry.recon_error_batch((int32_t)count, descs.data(), stream);
-    Py_END_ALLOW_THREADS
+    {
+        const Unlocked scope;
+        rc = entry.recon_error_batch((int32_t)count, descs.data(), stream);
+    }
     const Ref o(THPVariable_Wrap(sums));
     return o.o ? Py_BuildValue("(Oi)", o.o, rc) : nullptr;
     END_HANDLE_TH_ERRORS

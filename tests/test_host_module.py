@@ -1,5 +1,9 @@
 """The compiled marshalling module: the errors that the Python checks raised before, and on the GPU the same results and lifetimes
 as calls with buffers of their own."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -28,6 +32,31 @@ def test_errors_before_anything_is_enqueued():
         with pytest.raises(TypeError, match="bfloat16 or float32"):
             call()
     assert B.recon_error_batch([], []).numel() == 0
+
+
+def run_python(code):
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    return subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=300)
+
+
+def test_an_exception_of_the_library_arrives_with_the_interpreter_locked(tmp_path):
+    """an entry point that throws in the place of the real one; a process of its own, which may end without a word otherwise"""
+    src, so = tmp_path / "throws.cpp", tmp_path / "throws.so"
+    src.write_text('#include <stdexcept>\nextern "C" int throws(int, const void *, void *) { throw std::runtime_error("no memory left"); }\n')
+    subprocess.run(["g++", "-shared", "-fPIC", str(src), "-o", str(so)], check=True)
+    r = run_python(f"""
+import ctypes
+from paper_2605_12245_amd import binding as B
+B.lib()
+f = ctypes.cast(ctypes.CDLL({str(so)!r}).throws, ctypes.c_void_p).value
+B._host.bind(*([f] * 7))
+try:
+    B._host.dequantize([], False, False, 0)
+except RuntimeError as e:
+    print("caught:", e)
+print("alive")
+""")
+    assert r.returncode == 0 and "caught: no memory left" in r.stdout and "alive" in r.stdout, (r.returncode, r.stdout, r.stderr[-400:])
 
 
 @pytest.mark.gpu
