@@ -4,8 +4,9 @@ Argument marshalling only: every step of the method runs inside the HIP
 kernels.  torch is used for device memory and streams.  Calls that bring no
 buffers of their own go through the compiled module ``soar_host``, which
 allocates them and makes the same C call.  There is no CPU fallback -- if
-``libsoar_hip.so`` or the module has not been built, or no GPU is present, the
-entry points raise.
+``libsoar_hip.so`` has not been built, or no GPU is present, the entry points
+raise; without the module (it belongs to one torch and one Python) only the
+calls that go through it do.
 """
 from __future__ import annotations
 
@@ -177,20 +178,31 @@ def lib():
 
 
 _host = None
+_host_error = None          # why the module could not be loaded
 
 
 def _bind_host(L):
-    """Load the compiled marshalling module and hand it the library's entry points (in the order of its EntryPoints)."""
-    global _host
+    """Load the compiled marshalling module and hand it the library's entry points (in the order of its EntryPoints).
+    The raw entry points and calls with buffers of their own do without it (see _host_module)."""
+    global _host, _host_error
     try:
         from . import soar_host
     except ImportError as e:
-        raise RuntimeError(f"the module soar_host could not be loaded ({e}): build it with `python -m paper_2605_12245_amd.build` "
-                           "(there is no CPU fallback)") from e
+        _host_error = e
+        return
     soar_host.bind(*(C.cast(f, C.c_void_p).value for f in (
         L.soar_workspace_bytes, L.soar_quantize_batch, L.soar_mxfp4_workspace_bytes, L.soar_mxfp4_quantize,
         L.soar_dequantize_batch, L.soar_mxfp4_dequantize_batch, L.soar_recon_error_batch)))
     _host = soar_host
+
+
+def _host_module():
+    if _host is None:
+        lib()
+    if _host is None:
+        raise RuntimeError(f"the module soar_host could not be loaded ({_host_error}): build it with `python -m paper_2605_12245_amd.build`, "
+                           "or bring output buffers and a workspace (there is no CPU fallback)") from _host_error
+    return _host
 
 
 # ------------------------------------------------------------------ raw entry points
@@ -453,7 +465,7 @@ def _quantize_new(w, params, trace: bool, amax_in, where: str) -> Quantized:
     """One tensor with new outputs and a workspace of its own."""
     if not w.is_cuda:
         _check_matrix(w)          # raises
-    *parts, rc = _host.quantize(w, C.addressof(params), trace, amax_in, _stream())
+    *parts, rc = _host_module().quantize(w, C.addressof(params), trace, amax_in, _stream())
     if rc != SOAR_OK:
         raise SoarError(2, "soar_workspace_bytes") if rc < 0 else SoarError(rc, where)
     return Quantized(*parts)
@@ -511,7 +523,6 @@ def quantize_iter(w: torch.Tensor, params: soar_params, workspace: Optional[torc
                   out: Optional[Quantized] = None) -> Quantized:
     """One tensor through the iterated path (soar_quantize_batch with n = 1), with the error trace."""
     if out is None and workspace is None and params.iters > 0:
-        lib()
         return _quantize_new(w, params, True, None, "soar_quantize_batch")
     rows, cols, _ = _check_matrix(w)
     if out is None:
@@ -572,8 +583,7 @@ def quantize_tensors(weights: Sequence[torch.Tensor], params: Optional[soar_para
 def _dequantize_new(qs: list, mx: bool, out_dtype, where: str) -> list:
     if out_dtype not in (torch.bfloat16, torch.float32):
         raise TypeError("weights must be bfloat16 or float32")
-    lib()
-    outs, rc = _host.dequantize(qs, mx, out_dtype == torch.float32, _stream())
+    outs, rc = _host_module().dequantize(qs, mx, out_dtype == torch.float32, _stream())
     if rc != SOAR_OK:
         raise SoarError(rc, where)
     return outs
@@ -584,8 +594,7 @@ def dequantize(q: Quantized, out_dtype=torch.bfloat16) -> torch.Tensor:
 
 
 def _recon_error_new(weights: list, qs: list, where: str) -> torch.Tensor:
-    lib()
-    sums, rc = _host.recon_error(weights, qs, _stream())
+    sums, rc = _host_module().recon_error(weights, qs, _stream())
     if rc != SOAR_OK:
         raise SoarError(rc, where)
     return sums
@@ -635,8 +644,7 @@ def mx_quantize(w: torch.Tensor, params: soar_mx_params, workspace: Optional[tor
                 out: Optional[Quantized] = None) -> Quantized:
     """MXFP4 conversion of one tensor (plain or with the decoupled scale search); scales are E8M0 bytes."""
     if out is None and workspace is None and w.is_cuda:
-        lib()
-        *parts, rc = _host.mx_quantize(w, C.addressof(params), _stream())
+        *parts, rc = _host_module().mx_quantize(w, C.addressof(params), _stream())
         if rc != SOAR_OK:
             raise SoarError(2, "soar_mxfp4_workspace_bytes") if rc < 0 else SoarError(rc, "soar_mxfp4_quantize")
         return Quantized(*parts)

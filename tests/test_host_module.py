@@ -59,6 +59,26 @@ print("alive")
     assert r.returncode == 0 and "caught: no memory left" in r.stdout and "alive" in r.stdout, (r.returncode, r.stdout, r.stderr[-400:])
 
 
+def test_the_library_is_there_without_the_module():
+    """as where the module was built for another torch or Python: the raw entry points need nothing of it"""
+    r = run_python("""
+import sys
+sys.modules["paper_2605_12245_amd.soar_host"] = None          # the import fails
+import torch
+from paper_2605_12245_amd import binding as B
+assert B.soar_version() >= 0x00010000
+assert B.soar_workspace_bytes(64, 64, B.soar_default_params()) > 0
+q = B.Quantized(*[torch.zeros(2, 2)] * 5)
+for call in (lambda: B.dequantize(q), lambda: B.recon_error(torch.zeros(2, 32), q)):
+    try:
+        call()
+    except RuntimeError as e:
+        assert "soar_host could not be loaded" in str(e), e
+        print("refused")
+""")
+    assert r.returncode == 0 and r.stdout.count("refused") == 2, (r.returncode, r.stdout, r.stderr[-800:])
+
+
 @pytest.mark.gpu
 def test_same_as_calls_that_bring_their_buffers():
     w = (torch.randn(37, 272, device=DEV) * 0.02).to(torch.bfloat16)[:, :256]
