@@ -260,7 +260,7 @@ PyObject *dequantize(PyObject *, PyObject *const *args, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// recon_error(list of weights, list of Quantized, stream) -> (one sum per tensor, status of the call)
+// recon_error(list of weights, list of at least as many Quantized, stream) -> (one sum per weight, status of the call)
 PyObject *recon_error(PyObject *, PyObject *const *args, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
@@ -270,14 +270,18 @@ PyObject *recon_error(PyObject *, PyObject *const *args, Py_ssize_t n)
     }
     void *stream = PyLong_AsVoidPtr(args[2]);
     if (PyErr_Occurred()) return nullptr;
-    const Py_ssize_t weights = PyList_GET_SIZE(args[0]), stored = PyList_GET_SIZE(args[1]), count = weights < stored ? weights : stored;
+    const Py_ssize_t weights = PyList_GET_SIZE(args[0]), stored = PyList_GET_SIZE(args[1]);
     if (weights == 0 || !is_matrix(PyList_GET_ITEM(args[0], 0), "weights")) {
         if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "no weights");
         return nullptr;
     }
+    if (stored < weights) {
+        PyErr_Format(PyExc_ValueError, "%zd weights, but only %zd stored tensors", weights, stored);
+        return nullptr;
+    }
     const at::Tensor sums = empty({weights}, at::kDouble, THPVariable_Unpack(PyList_GET_ITEM(args[0], 0)).device());
-    std::vector<soar_stored_desc> descs((size_t)count);
-    for (Py_ssize_t k = 0; k < count; ++k) {
+    std::vector<soar_stored_desc> descs((size_t)weights);
+    for (Py_ssize_t k = 0; k < weights; ++k) {
         soar_stored_desc &d = descs[(size_t)k];
         if (!is_matrix(PyList_GET_ITEM(args[0], k), "weights")) return nullptr;
         const at::Tensor &w = THPVariable_Unpack(PyList_GET_ITEM(args[0], k));
@@ -292,7 +296,7 @@ PyObject *recon_error(PyObject *, PyObject *const *args, Py_ssize_t n)
     int rc;
     {
         const Unlocked scope;
-        rc = entry.recon_error_batch((int32_t)count, descs.data(), stream);
+        rc = entry.recon_error_batch((int32_t)weights, descs.data(), stream);
     }
     const Ref o(THPVariable_Wrap(sums));
     return o.o ? Py_BuildValue("(Oi)", o.o, rc) : nullptr;

@@ -150,3 +150,12 @@ def test_a_number_of_iterations_out_of_range_is_a_parameter_error():
     for iters in (2**31 - 1, 2**31 - 2):
         with pytest.raises(B.SoarError, match="soar_workspace_bytes"):
             B.quantize_iter(w, B.soar_paper_params(iters=iters))
+
+
+@pytest.mark.gpu
+def test_every_weight_has_a_stored_tensor():
+    w = (torch.randn(16, 64, device=DEV) * 0.02).to(torch.bfloat16)
+    q = B.quantize(w)
+    with pytest.raises(ValueError, match="2 weights"):
+        B.recon_error_batch([w, w], [q])
+    assert torch.equal(B.recon_error_batch([w], [q, q]), B.recon_error(w, q))      # more of them: the first ones count
