@@ -552,15 +552,21 @@ soar_status launch_group(const Batch &b, uint32_t wg_absmax, uint32_t wg_stats, 
         SOAR_LAUNCH_CHECK();
     }
     if (method == SOAR_METHOD_SOAR) {
+        auto stats = k_stats<DT, false>;
+        auto search = k_search<DT, SOAR_METHOD_SOAR, false>;
+        if constexpr (DT == SOAR_BF16) {          // carries_ratios: no other type does
+            if (carry) {
+                stats = k_stats<DT, true>;
+                search = k_search<DT, SOAR_METHOD_SOAR, true>;
+            }
+        }
         {
             ScopedTimer t(SOAR_KERNEL_STATS, st);
-            if (carry) hipLaunchKernelGGL((k_stats<DT, true>), dim3(wg_stats), dim3(kWG), 0, st, b);
-            else hipLaunchKernelGGL((k_stats<DT, false>), dim3(wg_stats), dim3(kWG), 0, st, b);
+            hipLaunchKernelGGL(stats, dim3(wg_stats), dim3(kWG), 0, st, b);
             SOAR_LAUNCH_CHECK();
         }
         ScopedTimer t(SOAR_KERNEL_SEARCH, st);
-        if (carry) hipLaunchKernelGGL((k_search<DT, SOAR_METHOD_SOAR, true>), dim3(wg_search), dim3(kWG), 0, st, b);
-        else hipLaunchKernelGGL((k_search<DT, SOAR_METHOD_SOAR>), dim3(wg_search), dim3(kWG), 0, st, b);
+        hipLaunchKernelGGL(search, dim3(wg_search), dim3(kWG), 0, st, b);
         SOAR_LAUNCH_CHECK();
     } else {
         ScopedTimer t(SOAR_KERNEL_SEARCH, st);
@@ -850,11 +856,11 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         if (iterated)
             result = descs[i].dtype == SOAR_BF16 ? launch_group_iter<SOAR_BF16>(b, wg_absmax, wg, params->iters, nearest, lane_stream[lane])
                                                  : launch_group_iter<SOAR_FP32>(b, wg_absmax, wg, params->iters, nearest, lane_stream[lane]);
-        else if (descs[i].dtype == SOAR_BF16)
-            result = launch_group<SOAR_BF16>(b, wg_absmax, wg, wg_search, params->method, carries_ratios(SOAR_BF16, group_bytes),
-                                             lane_stream[lane]);
-        else
-            result = launch_group<SOAR_FP32>(b, wg_absmax, wg, wg_search, params->method, false, lane_stream[lane]);
+        else {
+            const bool carry = carries_ratios(descs[i].dtype, group_bytes);
+            result = descs[i].dtype == SOAR_BF16 ? launch_group<SOAR_BF16>(b, wg_absmax, wg, wg_search, params->method, carry, lane_stream[lane])
+                                                 : launch_group<SOAR_FP32>(b, wg_absmax, wg, wg_search, params->method, carry, lane_stream[lane]);
+        }
         i = j;
     }
     // always join, also after a failed launch, so that the caller's stream stays ordered
