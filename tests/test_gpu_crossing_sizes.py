@@ -20,15 +20,21 @@ def test_every_way_across_the_grid(dtype):
         for p in (B.soar_default_params(), B.soar_default_params(B.SOAR_METHOD_RTN, 0), B.soar_paper_params(iters=4, early_stop_rel=0.0, n_beta=21),
                   B.soar_arm_params(B.SOAR_METHOD_CJSO_ONLY, iters=5, early_stop_rel=0.0)):
             iterated = p.iters > 1
-            out = []
+            out, launches = [], []
             for resident in (B.SOAR_RESIDENT_AUTO, B.SOAR_RESIDENT_NEVER):
                 p.resident = resident
-                o = B.new_outputs(w.shape[0], 16, DEV, p.iters if iterated else 0)
                 ws = B.new_workspace(w.shape[0], 16, p, DEV)
-                for _ in range(2):                          # twice on one workspace
+                both = [B.new_outputs(w.shape[0], 16, DEV, p.iters if iterated else 0) for _ in range(2)]
+                B.soar_kernel_timing_enable(True)
+                for o in both:                              # twice on one workspace
                     B.quantize_batch([B.make_desc(w, o)], p, ws)
-                out.append(o)
-            torch.cuda.synchronize()
+                torch.cuda.synchronize()
+                launches.append(B.soar_kernel_timing_read(B.SOAR_KERNEL_RESIDENT)[1])
+                B.soar_kernel_timing_enable(False)
+                for f in ("codes", "scales", "global_scale", "status", "iters_run", "sse", "sse_trace"):
+                    assert getattr(both[0], f) is None or torch.equal(getattr(both[0], f), getattr(both[1], f)), (G, p.method, f)
+                out.append(both[0])
+            assert launches == [2, 0], (G, p.method)        # the one-launch kernel against the others
             a, b = out
             for f in ("codes", "scales", "global_scale", "status", "iters_run"):
                 assert getattr(a, f) is None or torch.equal(getattr(a, f), getattr(b, f)), (G, p.method, f)

@@ -32,3 +32,17 @@ def test_dealt_chunks_equal_one_chunk_per_workgroup(tiles, dtype):
             for f in ("codes", "scales", "global_scale", "sse", "status", "iters_run"):
                 assert torch.equal(getattr(a, f), getattr(b, f)), f
             assert torch.equal(a.sse_trace.nan_to_num(-1.0), b.sse_trace.nan_to_num(-1.0))
+
+
+@pytest.mark.gpu
+def test_chunks_of_more_than_four_tiles():
+    """a tensor of more than 4096 chunks of four tiles: eight tiles a chunk, the last one ragged, beside a small tensor"""
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    weights = [(torch.randn((rows, 16), generator=gen, device=DEV) * 0.02).to(torch.bfloat16) for rows in (256 * (4 * 4096 + 13) - 7, 256 * 9 - 1)]
+    p = B.soar_paper_params(iters=2)
+    dealt = run(weights, p)
+    for tiles_per_wg in (8, 16):
+        p.tiles_per_wg = tiles_per_wg
+        for a, b in zip(dealt, run(weights, p)):
+            for f in ("codes", "scales", "global_scale", "sse", "status", "iters_run", "sse_trace"):
+                assert torch.equal(getattr(a, f), getattr(b, f)), (tiles_per_wg, f)
