@@ -257,6 +257,7 @@ __device__ __forceinline__ float mx_factor_error(const float w[32], float t, flo
 // residual only changes its sign, computed errors are equal, the smaller factor keeps the tie -- or |y - m| is a whole unit of y's last
 // place, at least 2^-10, and the error rises by 2 |q - q'| |y - m| s^2 >= 2^-10 s^2: more than the rounding of two errors (34 units of
 // 2^-24 each) below 200 s^2.  So nothing above such a factor is evaluated; the factor below it is, because of the ties.
+constexpr float kEqualFactorError = 200.0f;      // of s^2
 template <bool GRID16>
 __device__ __forceinline__ float mx_best_factor(const float w[32], float x0, float ratio, const FactorGrid &grid, float s, bool wanted,
                                                 uint32_t nib[4], int &k)
@@ -272,7 +273,7 @@ __device__ __forceinline__ float mx_best_factor(const float w[32], float x0, flo
     }
     const float per_error = s * (1.0f / kFarSideRounding32), slack = s * (0x1p-21f * per_error);
     auto excluded = [&](float distance, float e) { return __builtin_fmaf(distance, per_error, -slack) > e; };
-    auto nothing_above = [&](float t, float e) { return excluded(t - s, e) || (GRID16 && t == s && e < 200.0f * (s * s)); };
+    auto nothing_above = [&](float t, float e) { return excluded(t - s, e) || (GRID16 && t == s && e < kEqualFactorError * (s * s)); };
     const float ta = x0 * grid.table[lo];
     float err = mx_factor_error(w, ta, s, nib);
     k = lo;
@@ -319,6 +320,7 @@ __device__ __forceinline__ float mx_best_factor(const float w[32], float x0, flo
 //    weight, 4 X0 or more, to take a code of 3.5 or less -- as it has to under X0 2^o -- the factor must exceed 1.
 // Pairs evaluated per block of the default grid: three (50 and 49 for X0, one for either side), where the two around every candidate
 // and the one beyond an equal factor were six.
+constexpr float kMissMargin = 0.9999f;
 template <bool GRID16>
 __device__ __forceinline__ void mx_search_nearest(const float w[32], float bmax, int e0, const FactorGrid &grid, int radius,
                                                   float &best_err, int &best_code, uint32_t best_nib[4])
@@ -349,7 +351,7 @@ __device__ __forceinline__ void mx_search_nearest(const float w[32], float bmax,
     for (int o = 1; o <= radius; ++o) {
         const float below = f_of((uint32_t)(127 - o) << 23), above = f_of((uint32_t)(127 + o) << 23);
         const float miss = fmaxf(__builtin_fmaf(below * x0, -6.0f, bmax), 0.0f);
-        bool lower = !(0.9999f * (miss * miss) > best_err), upper = !no_larger;
+        bool lower = !(kMissMargin * (miss * miss) > best_err), upper = !no_larger;
         // the lower one first, in a round of its own where a block asks for both
         while (__builtin_amdgcn_ballot_w64(lower || upper) != 0ull) {
             candidate(lower ? e0 - o : e0 + o, lower ? below : above, lower || upper);
