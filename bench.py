@@ -81,7 +81,8 @@ def alu_roofline(kernel, algorithm, workload, dtype, search, layers, steps_block
     part issues them unpacked (256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz: one 32-bit operation per lane and cycle; the
     published 157.3 TFLOP/s is this rate x 2 for fused multiply-add x 2 for packed FP32, which this build does not
     emit).  The executed count per (block, factor) comes from a SQ_INSTS_VALU counter run (profiles/pmc_table.json);
-    without one the plain loop's instruction count stands in and the line says so.  The method-definition
+    without one the plain loop's instruction count stands in and the line says so.  A count that would exceed the
+    peak rate is none of the kernel that ran, and no figure is given.  The method-definition
     floating-point rate is reported beside it; it counts every factor of the grid, most of which the nearest-factor
     search (--search auto) excludes without evaluating them, so there it is no rate of executed operations."""
     e, why = pmc_entry(algorithm, workload, dtype, kernel, layers, search)
@@ -93,8 +94,12 @@ def alu_roofline(kernel, algorithm, workload, dtype, search, layers, steps_block
         per_step, source = iter_lane_ops_per_block_beta(ncand, nelem), "modelled (plain loop): " + why
     lane_ops = steps_blocks_factors * per_step
     flops = steps_blocks_factors * iter_flops_per_block_beta(ncand, nelem)
-    return {"kernel": kernel, "bound": "alu", "achieved": lane_ops / t_kernel / 1e12, "peak": VALU_LANE_OPS_PEAK / 1e12,
-            "unit": "T lane-op/s", "frac": lane_ops / t_kernel / VALU_LANE_OPS_PEAK, "traffic": None,
+    achieved, frac = lane_ops / t_kernel / 1e12, lane_ops / t_kernel / VALU_LANE_OPS_PEAK
+    if frac > 1.0:                  # more than the part can issue: the count is of another kernel than the one that ran
+        source = f"rejected ({frac:.2f} of the peak rate): {source}"
+        achieved = frac = per_step = None
+    return {"kernel": kernel, "bound": "alu", "achieved": achieved, "peak": VALU_LANE_OPS_PEAK / 1e12,
+            "unit": "T lane-op/s", "frac": frac, "traffic": None,
             "executed_lane_insts_per_block_factor": per_step, "executed_count_source": source,
             "method_flops_per_block_factor": iter_flops_per_block_beta(ncand, nelem),
             "method_tflops": flops / t_kernel / 1e12,

@@ -303,3 +303,19 @@ def test_counter_table_that_bench_quotes_is_well_formed_and_points_at_committed_
     assert none is None and "subset" in why
     none, why = bench.traffic_per_launch("single-step", 9, "bf16", "k_nothing", 1.0)
     assert none is None and "no counter run" in why
+
+
+def test_no_rate_above_what_the_part_can_issue_is_reported():
+    """an instruction count that belongs to another kernel than the one that was timed gives no figure"""
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("bench_module", os.path.join(ROOT, "bench.py"))
+    bench = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(bench)
+    steps = 1e9
+    e, _ = bench.pmc_entry("mxfp4-dss", 4, "bf16", "k_mx")
+    at_peak = steps * e["valu_lane_insts_per_block_search"] / e["factors"] / bench.VALU_LANE_OPS_PEAK
+    for algorithm, workload, t in (("mxfp4-dss", 4, at_peak * 0.99), ("mxfp4-dss", 3, 1e-5)):      # counted; modelled, no counter run
+        r = bench.alu_roofline("k_mx", algorithm, workload, "bf16", "auto", 0, steps, 3, t, nelem=32)
+        assert r["frac"] is None and r["achieved"] is None and "rejected" in r["executed_count_source"], r
+    r = bench.alu_roofline("k_mx", "mxfp4-dss", 4, "bf16", "auto", 0, steps, 3, at_peak * 1.25, nelem=32)
+    assert r["frac"] == pytest.approx(0.8) and r["executed_count_source"] == e["source"]
