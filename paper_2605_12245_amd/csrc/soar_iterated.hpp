@@ -336,10 +336,10 @@ constexpr float kFarSideRounding16 = 1.0e-5f, kFarSideRounding32 = 1.8e-5f;
 // codes the smaller factor is the earlier one; pairs of the same codes belong to the same run of factors, and the
 // candidate tried first keeps the tie.
 // Needs an ascending factor table (checked on the host) and the reciprocal's range (FAST).
-// Bound by vector issue: 520 instructions per block and iteration with two candidates (69 for each of the four
-// pairs), where forming the codes of all 101 factors and the errors of those at which a block's codes change took
-// 8 500.  One decoder layer (seven tensors, 1.93e8 bf16 weights, 3 iterations): 7.65 -> 0.74 ms a call; with three
-// candidates on 4096 x 4096 fp32: 958 -> 169 us.
+// Mostly bound by vector issue (the vector units are busy for 70 % of an iteration's launch): 489 instructions per block and
+// iteration with two candidates, where forming the codes of all 101 factors and the errors of those at which a block's codes
+// change took 8 500; 941 with three.  One decoder layer (seven tensors, 1.93e8 bf16 weights, 3 iterations): 7.65 -> 0.72 ms a
+// call; with three candidates on 4096 x 4096 fp32: 0.96 -> 0.17 ms, 0.135 in one launch.
 struct FactorGrid {
     const float *table;          // LDS, n factors, ascending
     int n;

@@ -26,8 +26,8 @@ namespace {
 // tensor alone: all blocks are then its own R * G tiles (G rounded up to a power of two), the same tree, no crossings.  So a
 // call always finishes, as it does with a launch per iteration.  Beyond the first crossing every workgroup is running and the
 // waits last as long as the slowest one's share; their bound (later_ticks) is there for a machine that has stopped working.
-// 1024 x 4096 bf16, paper settings: 72-88 -> 42 us a call (loads 1, maximum 2, state 3, sums 3, an iteration 5-6 and
-// its crossing 4 us); 4096 x 4096 fp32, search-only arm: 169 -> 140 us, 33 of them an iteration's search.
+// 1024 x 4096 bf16, paper settings: 72-88 -> 41 us a call (loads 2, maximum 4, state 3, sums 4, an iteration 5-6 and
+// its crossing 4 us); 4096 x 4096 fp32, search-only arm: 169 -> 135 us, 32 of them an iteration's search.
 // The crossing words inside Task::part (where other kernels' words may lie: theirs carry other tokens)
 struct IterResidentWords {
     uint64_t max[kMaxEnd];
