@@ -79,6 +79,17 @@ for call in (lambda: B.dequantize(q), lambda: B.recon_error(torch.zeros(2, 32), 
     assert r.returncode == 0 and r.stdout.count("refused") == 2, (r.returncode, r.stdout, r.stderr[-800:])
 
 
+def test_a_build_whose_module_does_not_load_is_an_error():
+    r = run_python("""
+import sys
+sys.modules["paper_2605_12245_amd.soar_host"] = None
+import __graft_entry__, oracle.build, paper_2605_12245_amd.build
+oracle.build.build = paper_2605_12245_amd.build.build = lambda **more: None       # what is there has been built
+__graft_entry__.build()
+""")
+    assert r.returncode != 0 and "soar_host could not be loaded" in r.stderr, (r.returncode, r.stdout, r.stderr[-800:])
+
+
 @pytest.mark.gpu
 def test_same_as_calls_that_bring_their_buffers():
     w = (torch.randn(37, 272, device=DEV) * 0.02).to(torch.bfloat16)[:, :256]
