@@ -322,14 +322,30 @@ size_t per_block_bytes(int64_t rows, int64_t cols)
 // although the search alone is 5 % slower that way; plain NVFP4 (two passes) likes 8 in its search.
 struct WantedShapes { uint32_t absmax, stats, search; };
 constexpr int64_t kStatsEightTiles = 8192;       // tiles of a launch group from which the statistics take eight a workgroup
+// A group of fewer tiles than that gives its workgroups fewer each, so that there are kFillWg of them while the tiles last: a
+// workgroup walks its tiles one after the other, and a few tens of workgroups with 16 each kept a handful of compute units busy
+// for 25 us (a group of eight matrices of 256 columns; whole calls: four such layers 114 -> 71 us, four layers of
+// hidden 1024 137 -> 107, three of them in fp32 178 -> 121, four of hidden 2048 257 -> 247; 512 workgroups: 106, 122, 257; 2048: 119, 133, 250).
+// The one pass of a supplied maximum has a longer tail than that and less to do: half as many (1100 x 4096 fp32 17.3 -> 13.4 us;
+// 3000 x 4096 with four tiles a workgroup 19.2, with two 20.4).
+constexpr int64_t kFillWg = 1024, kFillWgOnePass = 512;
 WantedShapes wanted_shapes(bool several_groups, int method, bool iterated, bool one_pass, int64_t bytes, int64_t group_tiles)
 {
-    if (iterated || one_pass) return {(uint32_t)kStage, (uint32_t)kStage, (uint32_t)kStage};
-    if (!several_groups) return {(uint32_t)kStage, group_tiles >= kStatsEightTiles ? 8u : (uint32_t)kStage, (uint32_t)kStage};
-    // a tensor that is a launch group by itself and larger than the last-level cache streams from HBM in every
-    // pass; plain NVFP4 has two passes only
-    if (method == SOAR_METHOD_RTN || bytes > kLastLevelCache) return {(uint32_t)kStage, (uint32_t)kStage, 8u};
-    return {(uint32_t)kStage, 8u, 16u};
+    WantedShapes w = {(uint32_t)kStage, (uint32_t)kStage, (uint32_t)kStage};
+    if (iterated || one_pass) {
+    } else if (!several_groups) {
+        if (group_tiles >= kStatsEightTiles) w.stats = 8u;
+    } else if (method == SOAR_METHOD_RTN || bytes > kLastLevelCache) {
+        // a tensor that is a launch group by itself and larger than the last-level cache streams from HBM in every
+        // pass; plain NVFP4 has two passes only
+        w.search = 8u;
+    } else {
+        w.stats = 8u;
+        w.search = 16u;
+    }
+    for (uint32_t *tpw : {&w.absmax, &w.stats, &w.search})
+        while (*tpw > 1u && group_tiles < (int64_t)*tpw * (one_pass ? kFillWgOnePass : kFillWg)) *tpw >>= 1;
+    return w;
 }
 
 // Tiles per workgroup of an arithmetic-bound searching kernel over a launch of `tiles` tiles: as many as leave
