@@ -664,6 +664,11 @@ __device__ __forceinline__ void finish_iteration(const Batch &batch, const Task 
 // NEAREST: the pairs that can win are found without walking the grid (joint_search_nearest, see nearest_search);
 // otherwise the codes of every factor are formed and errors where they change (joint_search_changes), or every pair is
 // evaluated (joint_search).
+// bf16: a lane's next block is on its way into LDS while it searches this one, and the results of a block are stored when the
+// next one has been taken out: a wait for loads also waits for the stores before them, and both are a whole search old by then. The
+// ratio is read beside the weights, not after them.  One decoder layer 722 -> 703 us, 12288 x 4096 243 -> 237.  fp32 has no
+// LDS left for five workgroups with four tiles staged, and with two it is slower (929 -> 944; four workgroups 941): there the ratio is read first
+// (929 -> 924).
 template <int DT, bool NEAREST>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5 : 4, 8))) void k_iter(const Batch batch)
 {
@@ -672,6 +677,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5
     __shared__ double s_stack[3][32];
     __shared__ uint32_t s_last;
     double *s_tree = reinterpret_cast<double *>(s_blocks);      // trees_of_partials, after the last group
+    constexpr bool kAhead = DT == SOAR_BF16;
+    __shared__ u32x4 s_next[kAhead ? kWG * BlockStream<DT>::kP : 1];
     extern __shared__ __align__(16) unsigned char s_dyn[];      // the factor table, n_beta floats
     float *s_beta = reinterpret_cast<float *>(s_dyn);
 
@@ -695,24 +702,49 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5
 
     StagedTree<> tree{s_blocks, s_wave, s_stack};
     const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
+    const uint32_t blocks = amax_bits < 0x7F800000u ? t.nblk : 0u;
+    const BlockStream<DT> stream{s_next + (kAhead ? (tid >> 6) * (64 * BlockStream<DT>::kP) : 0u)};
+    float next_rho = 0.0f;
+    auto fetch = [&](uint32_t tile) {
+        const uint32_t i = tile * kWG + tid;
+        if (i < blocks) {
+            stream.fetch(t.w, block_offset(t, i));
+            next_rho = t.rho[i];
+        }
+    };
+    BlockState x;
+    uint32_t done = blocks;              // the block whose results x holds, not yet stored
+    auto store = [&]() {
+        if (done < blocks) {
+            store_block(t, done, x);
+            t.rho[done] = x.rho;
+        }
+    };
+    if constexpr (kAhead) fetch(lwg * t.tiles_per_wg);
     for (uint32_t chunk = lwg; chunk < t.n_chunks; chunk += t.n_wg) {
         const uint32_t tile0 = chunk * t.tiles_per_wg;
         for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
             for (uint32_t kk = 0; kk < T; ++kk) {
                 const uint32_t i = (tile0 + kg + kk) * kWG + tid;
-                BlockState x;
-                x.a = x.b = x.d = x.err = 0.0f;
-                if (i < t.nblk && amax_bits < 0x7F800000u) {
-                    float w[16];
+                float w[16], rho = 0.0f;
+                if constexpr (kAhead) {
+                    stream.take(w);
+                    rho = next_rho;
+                    store();
+                    const uint32_t at = kg + kk + 1u;
+                    const uint32_t next_chunk = at < t.tiles_per_wg ? chunk : chunk + t.n_wg;
+                    if (next_chunk < t.n_chunks) fetch(next_chunk * t.tiles_per_wg + (at < t.tiles_per_wg ? at : 0u));
+                } else if (i < blocks) {
+                    rho = t.rho[i];
                     load_block<DT>(t.w, block_offset(t, i), w);
-                    if (allzero) {
-                        zero_block(w, x);
-                    } else {
-                        iterate_block<NEAREST>(w, t.rho[i], js, x);
-                        t.rho[i] = x.rho;
-                    }
-                    store_block(t, i, x);
                 }
+                x.a = x.b = x.d = x.err = 0.0f;
+                done = i;
+                if (i < blocks) {
+                    if (allzero) zero_block(w, x);
+                    else iterate_block<NEAREST>(w, rho, js, x);
+                }
+                if constexpr (!kAhead) store();
                 tree.stage(kk, x.a, x.b, x.d, x.err);
             }
             tree.close(kg / T, T);
@@ -723,6 +755,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5
             publish(t.part + 2 * kMaxPartials + chunk, tree.wg[2]);
         }
     }
+    if constexpr (kAhead) store();
     uint32_t *counters = t.counters + 2 * kSlots * kSlotStride;
     if (tid == 0) s_last = arrive_is_last(counters, &t.ctrl->top[2], t.n_wg, lwg) ? 1u : 0u;
     __syncthreads();
