@@ -155,8 +155,8 @@ __device__ __forceinline__ void joint_search(const float w[16], float alpha, flo
     if (bracket) {
         const int lo = c0;
         const int hi = min(lo + 1, (int)kE4M3Max);           // hi == lo can never win
-        const float s_lo = alpha * e4m3_value((uint32_t)lo);
-        const float s_hi = alpha * e4m3_value((uint32_t)hi);
+        const float s_lo = alpha * e4m3_value_of(lo);
+        const float s_hi = alpha * e4m3_value_of(hi);
 #pragma unroll UNROLL
         for (int kb = 0; kb < n_beta; ++kb) {
             const float bk = s_beta[kb];
@@ -184,7 +184,7 @@ __device__ __forceinline__ void joint_search(const float w[16], float alpha, flo
             for (int c = 0; c <= 2 * radius; ++c) {
                 const int o = (c + 1) >> 1;
                 const int code = (c & 1) ? max(c0 - o, (int)kE4M3Min) : min(c0 + o, (int)kE4M3Max);
-                const float e = block_error(w, q, alpha * e4m3_value((uint32_t)code));
+                const float e = block_error(w, q, alpha * e4m3_value_of(code));
                 if (e < best) { best = e; best_beta = bk; best_code = code; }
             }
         }
@@ -264,8 +264,8 @@ __device__ __forceinline__ void joint_search_changes(const float w[16], float al
     float best_beta = s_beta[0];
     const int lo = c0;
     const int hi = min(lo + 1, (int)kE4M3Max);
-    const float s_lo = alpha * e4m3_value((uint32_t)lo);
-    const float s_hi = alpha * e4m3_value((uint32_t)hi);
+    const float s_lo = alpha * e4m3_value_of(lo);
+    const float s_hi = alpha * e4m3_value_of(hi);
     best_code = c0;
     for (int base = 0; base < n_beta; base += kStretch) {
         ChangeSet set;
@@ -296,7 +296,7 @@ __device__ __forceinline__ void joint_search_changes(const float w[16], float al
                     for (int c = 0; c <= 2 * radius; ++c) {
                         const int o = (c + 1) >> 1;
                         const int code = (c & 1) ? max(c0 - o, (int)kE4M3Min) : min(c0 + o, (int)kE4M3Max);
-                        const float e = block_error(w, q, alpha * e4m3_value((uint32_t)code));
+                        const float e = block_error(w, q, alpha * e4m3_value_of(code));
                         if (e < best) { best = e; best_beta = bk; best_code = code; }
                     }
                 }
@@ -402,11 +402,11 @@ __device__ __forceinline__ void joint_search_nearest(const float w[16], float al
     const float base_index = __builtin_amdgcn_rcpf(alpha * delta_star) * grid.index_per_beta;
     int best_k;
     best_code = c0;
-    best_err = best_factor(w, alpha, delta_star, base_index, grid, alpha * e4m3_value((uint32_t)c0), best_nib, best_k);
+    best_err = best_factor(w, alpha, delta_star, base_index, grid, alpha * e4m3_value_of(c0), best_nib, best_k);
     auto next = [&](int code) {
         uint32_t nib[2];
         int k;
-        const float err = best_factor(w, alpha, delta_star, base_index, grid, alpha * e4m3_value((uint32_t)code), nib, k);
+        const float err = best_factor(w, alpha, delta_star, base_index, grid, alpha * e4m3_value_of(code), nib, k);
         bool win = err < best_err;
         if (__builtin_amdgcn_ballot_w64(err == best_err) != 0ull) {
             asm volatile("");                    // rare: kept out of the straight line
@@ -561,7 +561,7 @@ __device__ __forceinline__ void iterate_block(const float w[16], float rho, cons
         const int c0 = js.bracket ? e4m3_floor_code(delta_star) : (int)e4m3_project(delta_star);
         joint_search_nearest(w, js.alpha, delta_star, js.grid, js.bracket, c0, js.radius, x.err, code, x.nib);
         code_sums(w, x.nib, x.a, x.b);
-        x.d = e4m3_value((uint32_t)code);
+        x.d = e4m3_value_of(code);
         const float ratio = div_midrange(x.a, x.b, rcp_midrange(x.b));
         x.rho = (x.b == 0.0f || js.dss_only) ? -x.d : ratio;
     } else {
@@ -585,7 +585,7 @@ __device__ __forceinline__ void iterate_block(const float w[16], float rho, cons
             joint_search<false, 4>(w, js.alpha, delta_star, js.grid.table, js.grid.n, js.bracket, c0, js.radius, x.err, code, x.nib, q);
         }
         block_sums(w, q, x.a, x.b);
-        x.d = e4m3_value((uint32_t)code);
+        x.d = e4m3_value_of(code);
         x.rho = (x.b == 0.0f || js.dss_only) ? -x.d : x.a / x.b;
     }
     x.code = (uint32_t)code;
@@ -598,7 +598,7 @@ __device__ __forceinline__ void closed_form_block(const float w[16], float rho, 
     float q[16];
     const float delta_star = (rho < 0.0f) ? -rho : quotient(rho, alpha, inv_alpha, fast);          // Eq. 6
     x.code = e4m3_project(delta_star);
-    x.d = e4m3_value(x.code);
+    x.d = e4m3_value_of((int)x.code);
     const float sd = alpha * x.d;
     assign_codes(w, sd, fast, x.nib, q);
     block_sums(w, q, x.a, x.b);

@@ -214,7 +214,7 @@ __global__ void k_e2m1_round(const float *x, int64_t n, uint8_t *out)
 __global__ void k_e4m3_project(const float *x, int64_t n, uint8_t *out)
 {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = (uint8_t)e4m3_project(x[i]);
+    if (i < n) out[i] = (uint8_t)e4m3_project(__builtin_canonicalizef(x[i]));      // quiet NaNs
 }
 
 __global__ void k_rcp_midrange(const float *x, int64_t n, float *out)
