@@ -618,6 +618,36 @@ bool nearest_search(int n_beta, float lo, float hi)
 bool nearest_pays(int n_beta, int radius) { return radius <= (n_beta >= 8 ? 48 : n_beta >= 6 ? 3 * n_beta - 13 : 2); }
 bool mx_nearest_pays(int n_beta, int radius) { return radius <= 6 && radius <= n_beta - 2; }
 
+// Iterations with a launch each; the ones after share a launch (k_iter_rest) where tensors stop by themselves.  Almost all have
+// after three or four (heavy-tailed and uniform weights, 1e-3).
+constexpr int kIterLaunches = 4;
+constexpr int kRestWgPerCu = 6;           // workgroups of k_iter_rest<., CLOSED_FORM> on a compute unit
+bool rest_in_one(const Batch &b, int iters)
+{
+    if (!(b.early_stop_rel > 0.0f) || iters < kIterLaunches + 2) return false;
+    for (uint32_t k = 0; k < b.n; ++k)
+        if (!has_rest_words(b.t[k].n_chunks)) return false;
+    return true;
+}
+
+// The closed-form arm has a workgroup for every chunk; a counter that hands them out one by one is served in 12 ns each, so its
+// shares are as many as workgroups are on the GPU at a time.
+uint32_t deal_shares(Batch &b)
+{
+    const int64_t places = (int64_t)kRestWgPerCu * (device_facts().compute_units > 0 ? device_facts().compute_units : 256);
+    int64_t chunks = 0;
+    for (uint32_t k = 0; k < b.n; ++k) chunks += b.t[k].n_chunks;
+    uint32_t wg = 0;
+    for (uint32_t k = 0; k < b.n; ++k) {
+        Task &t = b.t[k];
+        const int64_t share = places * (int64_t)t.n_chunks / chunks;
+        t.n_wg = (uint32_t)(share < 1 ? 1 : share < (int64_t)t.n_chunks ? share : (int64_t)t.n_chunks);
+        t.wg_begin = wg;
+        wg += t.n_wg;
+    }
+    return wg;
+}
+
 // absmax, the Eq. 1-2 state, then one launch per iteration; a tensor that has
 // stopped early (or is degenerate) makes its workgroups of the later launches return at once
 template <int DT>
@@ -637,11 +667,21 @@ soar_status launch_group_iter(Batch &b, uint32_t wg_absmax, uint32_t total_wg, i
     // one pair of timing events round all iterations of the group: launches that find their tensors stopped
     // last 2 to 3 us, less than what an event pair of their own would add (from one to the next it is about 5 us)
     ScopedTimer t(SOAR_KERNEL_ITER, st);
-    for (int it = 0; it < iters; ++it) {
+    const int launches = rest_in_one(b, iters) ? kIterLaunches : iters;
+    const bool closed = b.arm == SOAR_METHOD_CJSO_ONLY;
+    for (int it = 0; it < launches; ++it) {
         b.iter_t = it;
-        if (b.arm == SOAR_METHOD_CJSO_ONLY) hipLaunchKernelGGL(k_cjso<DT>, dim3(total_wg), dim3(kWG), 0, st, b);
+        if (closed) hipLaunchKernelGGL(k_cjso<DT>, dim3(total_wg), dim3(kWG), 0, st, b);
         else if (nearest) hipLaunchKernelGGL((k_iter<DT, true>), dim3(total_wg), dim3(kWG), table, st, b);
         else hipLaunchKernelGGL((k_iter<DT, false>), dim3(total_wg), dim3(kWG), table, st, b);
+        SOAR_LAUNCH_CHECK();
+    }
+    if (launches < iters) {
+        b.iter_t = launches;
+        if (closed) total_wg = deal_shares(b);
+        if (closed) hipLaunchKernelGGL((k_iter_rest<DT, Iterate::CLOSED_FORM>), dim3(total_wg), dim3(kWG), 0, st, b, iters);
+        else if (nearest) hipLaunchKernelGGL((k_iter_rest<DT, Iterate::NEAREST>), dim3(total_wg), dim3(kWG), table, st, b, iters);
+        else hipLaunchKernelGGL((k_iter_rest<DT, Iterate::OTHER>), dim3(total_wg), dim3(kWG), table, st, b, iters);
         SOAR_LAUNCH_CHECK();
     }
     return SOAR_OK;

@@ -443,6 +443,19 @@ __device__ __forceinline__ void init_block(const float w[16], const GlobalScale 
     rho = keep_scale ? -delta0 : block_ratio(a, b, delta0, g.fast);
 }
 
+// What the workgroups of one tensor share in k_iter_rest: cleared by k_iter_init, at the end of the partial sums, where a tensor
+// of fewer partials leaves room.
+struct RestWords {
+    uint32_t shares[kMaxIters][32];       // of an iteration: how many have been handed out
+    uint32_t finished[16][32];            // iterations carried out; copies, a waiting workgroup reads the one of its number
+};
+constexpr int kRestPartials = kMaxPartials - (int)(sizeof(RestWords) / sizeof(double));
+__host__ __device__ inline bool has_rest_words(uint32_t n_chunks) { return n_chunks <= (uint32_t)kRestPartials; }
+__device__ __forceinline__ RestWords &rest_words(const Task &t)
+{
+    return *reinterpret_cast<RestWords *>(t.part + 2 * kMaxPartials + kRestPartials);
+}
+
 // The Eq. 1-2 state of Algorithm 1 (Delta^q = Delta^d = Delta0) for the iterated
 // path: per block the ratio a/b for Eq. 6 and the error of that state; per tensor
 // the sums of Eq. 5 (-> the global scale of iteration 0) and the error before any
@@ -496,6 +509,8 @@ __global__ __launch_bounds__(kWG) void k_iter_init(const Batch batch)
     if (tid == 0) s_last = arrive_is_last(counters, &t.ctrl->top[1], t.n_wg, lwg) ? 1u : 0u;
     __syncthreads();
     if (!s_last) return;
+    if (has_rest_words(t.n_chunks))
+        for (uint32_t k = tid; k < sizeof(RestWords) / 4; k += kWG) reinterpret_cast<uint32_t *>(&rest_words(t))[k] = 0u;
     double NME[3];
     trees_of_partials<3>(t.part, t.n_chunks, s_tree, &s_stack[0][0], NME);
     const double N = NME[0], M = NME[1], E = NME[2];
@@ -623,9 +638,18 @@ __device__ __forceinline__ void store_block(const Task &t, uint32_t i, const Blo
     __builtin_nontemporal_store((uint8_t)x.code, t.scales + i);
 }
 
-// What the last workgroup of a tensor does after an iteration (one lane): the outputs that describe the
+// One store of a tensor-wide result.  AGENT: performed at the memory side, where the launch itself goes on to use it (k_iter_rest).
+template <bool AGENT, typename T>
+__device__ __forceinline__ void put(T *p, T v)
+{
+    if constexpr (AGENT) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+
+// What the last workgroup of a tensor does after iteration `it` (one lane): the outputs that describe the
 // tensor, the early-stop decision and the global scale the next iteration starts from (Eq. 5).
-__device__ __forceinline__ void finish_iteration(const Batch &batch, const Task &t, double N, double M, double cur, float alpha,
+template <bool AGENT = false>
+__device__ __forceinline__ void finish_iteration(const Batch &batch, const Task &t, int it, double N, double M, double cur, float alpha,
                                                  bool degenerate, bool allzero, bool dss_only)
 {
     if (degenerate) {
@@ -634,18 +658,18 @@ __device__ __forceinline__ void finish_iteration(const Batch &batch, const Task 
         if (t.status) *t.status = allzero ? SOAR_STATUS_ALLZERO : SOAR_STATUS_NONFINITE;
         if (t.iters_run) *t.iters_run = 0;
     } else {
-        const double prev = t.ctrl->prev_sse;
-        *t.gscale = alpha;
-        if (t.sse) *t.sse = cur;
-        if (t.status) *t.status = 0;
-        if (t.iters_run) *t.iters_run = batch.iter_t + 1;
-        if (t.trace) t.trace[batch.iter_t + 1] = cur;
+        const double prev = AGENT ? __hip_atomic_load(&t.ctrl->prev_sse, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : t.ctrl->prev_sse;
+        put<AGENT>(t.gscale, alpha);
+        if (t.sse) put<AGENT>(t.sse, cur);
+        if (t.status) put<AGENT>(t.status, (int32_t)0);
+        if (t.iters_run) put<AGENT>(t.iters_run, (int32_t)(it + 1));
+        if (t.trace) put<AGENT>(t.trace + it + 1, cur);
         const bool stop = batch.early_stop_rel > 0.0f && (prev - cur) < (double)batch.early_stop_rel * prev;
-        t.ctrl->stopped = stop ? 1u : 0u;
-        t.ctrl->prev_sse = cur;
-        t.ctrl->alpha1 = (M > 0.0 && !dss_only) ? (float)(N / M) : alpha;      // Eq. 5 for the next iteration
-        t.ctrl->N = N;
-        t.ctrl->M = M;
+        put<AGENT>(&t.ctrl->stopped, stop ? 1u : 0u);
+        put<AGENT>(&t.ctrl->prev_sse, cur);
+        put<AGENT>(&t.ctrl->alpha1, (M > 0.0 && !dss_only) ? (float)(N / M) : alpha);      // Eq. 5 for the next iteration
+        put<AGENT>(&t.ctrl->N, N);
+        put<AGENT>(&t.ctrl->M, M);
     }
 }
 
@@ -763,7 +787,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5
     double NME[3];
     trees_of_partials<3>(t.part, t.n_chunks, s_tree, &s_stack[0][0], NME);
     const double N = NME[0], M = NME[1], cur = NME[2];
-    if (tid == 0) finish_iteration(batch, t, N, M, cur, alpha, degenerate, allzero, dss_only);
+    if (tid == 0) finish_iteration(batch, t, batch.iter_t, N, M, cur, alpha, degenerate, allzero, dss_only);
     reset_counters(counters, &t.ctrl->top[2]);
 }
 
@@ -831,8 +855,115 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8))) void k
     double NME[3];
     trees_of_partials<3>(t.part, t.n_chunks, s_tree, &s_stack[0][0], NME);
     const double N = NME[0], M = NME[1], cur = NME[2];
-    if (tid == 0) finish_iteration(batch, t, N, M, cur, alpha, degenerate, allzero, false);
+    if (tid == 0) finish_iteration(batch, t, batch.iter_t, N, M, cur, alpha, degenerate, allzero, false);
     reset_counters(counters, &t.ctrl->top[2]);
+}
+
+// The iterations from batch.iter_t on in one launch: most tensors have stopped by then, and a launch that finds its tensors stopped
+// takes 2.4 us on the GPU and 4 to 5 on the host.  Nothing here depends on which workgroups are on the GPU: the shares of an
+// iteration (what a workgroup of k_iter does) are handed out by a counter, whoever has one carries it out without waiting for
+// anybody, and only a workgroup that finds none left waits -- for the ones that hold them.  So a share and the one before it on the same
+// blocks may belong to different compute dies: ratios, codes, scales and the tensor's results are read and written at
+// the memory side, and a share is counted as done when its stores have been performed there.
+// Three of fifteen iterations do work: one decoder layer 703 -> 683 us, 12288 x 4096 237 -> 221, a layer of hidden 512 108 -> 74, the closed-form
+// arm there 108 -> 64.  Where all fifteen do, an iteration here takes what one in a launch of its own takes (four matrices of 2 to 50 million
+// weights: 436 / 448, 2270 / 2255 us; the closed-form arm, whose stores are no longer combined in the caches, up to 6 % more).
+enum class Iterate { CLOSED_FORM, NEAREST, OTHER };
+template <int DT, Iterate KIND>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_iter_rest(const Batch batch, int iters)
+{
+    __shared__ float4 s_blocks[kStage * kWG];
+    __shared__ double s_wave[3][4];
+    __shared__ double s_stack[3][32];
+    __shared__ uint32_t s_last, s_share, s_stopped;
+    __shared__ float s_alpha;
+    double *s_tree = reinterpret_cast<double *>(s_blocks);      // trees_of_partials, after the last group
+    extern __shared__ __align__(16) unsigned char s_dyn[];      // the factor table, n_beta floats
+    float *s_beta = reinterpret_cast<float *>(s_dyn);
+    auto get = [](auto *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+
+    uint32_t lwg;
+    const Task t = batch.t[find_task(batch, lwg)];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t amax_bits = t.ctrl->amax_bits;
+    if (amax_bits == 0u || amax_bits >= 0x7F800000u) return;    // finished by the first iteration
+    if (tid == 0) s_stopped = get(&t.ctrl->stopped);
+    __syncthreads();
+    if (s_stopped) return;
+    RestWords &rest = rest_words(t);
+    const bool dss_only = batch.arm == SOAR_METHOD_DSS_ONLY;
+    if constexpr (KIND != Iterate::CLOSED_FORM)
+        for (int k = (int)tid; k < batch.n_beta; k += kWG) s_beta[k] = beta_factor(k, batch.n_beta, batch.beta_lo, batch.beta_hi);
+    JointSearch js{{s_beta, batch.n_beta, batch.beta_lo, batch.index_per_beta}, 0.0f, 0.0f, batch.radius,
+                   batch.dd_mode == SOAR_DD_BRACKET, dss_only, false, batch.full_search != 0 || batch.n_beta < kChangesMinBeta};
+
+    for (int it = batch.iter_t; it < iters; ++it) {
+        if (tid == 0) {
+            // the last share of the iteration before publishes this; a share is held by a workgroup that is running
+            if (it > batch.iter_t)
+                while (get(&rest.finished[lwg % 16u][0]) < (uint32_t)it) __builtin_amdgcn_s_sleep(32);
+            s_stopped = get(&t.ctrl->stopped);
+            s_alpha = get(&t.ctrl->alpha1);
+        }
+        __syncthreads();
+        if (s_stopped) return;
+        // of this iteration, or of a later one if this one has been finished meanwhile: then no share of it is left
+        const float alpha = s_alpha;
+        js.set_alpha(alpha, amax_bits);
+        for (;;) {
+            if (tid == 0) s_share = __hip_atomic_fetch_add(&rest.shares[it][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            const uint32_t share = s_share;
+            if (share >= t.n_wg) break;
+            StagedTree<> tree{s_blocks, s_wave, s_stack};
+            const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
+            for (uint32_t chunk = share; chunk < t.n_chunks; chunk += t.n_wg) {
+                for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
+                    for (uint32_t kk = 0; kk < T; ++kk) {
+                        const uint32_t i = (chunk * t.tiles_per_wg + kg + kk) * kWG + tid;
+                        BlockState x;
+                        x.a = x.b = x.d = x.err = 0.0f;
+                        if (i < t.nblk) {
+                            const float rho = get(t.rho + i);
+                            float w[16];
+                            load_block<DT>(t.w, block_offset(t, i), w);
+                            if constexpr (KIND == Iterate::CLOSED_FORM)
+                                closed_form_block(w, rho, alpha, js.inv_alpha, js.in_range && all_near_one(rho), x);
+                            else
+                                iterate_block<KIND == Iterate::NEAREST>(w, rho, js, x);
+                            put<true>(t.rho + i, x.rho);
+                            put<true>(reinterpret_cast<uint64_t *>(t.codes) + i, (uint64_t)x.nib[1] << 32 | x.nib[0]);
+                            put<true>(t.scales + i, (uint8_t)x.code);
+                        }
+                        tree.stage(kk, x.a, x.b, x.d, x.err);
+                    }
+                    tree.close(kg / T, T);
+                }
+                if (tid == 0) {
+                    publish(t.part + chunk, tree.wg[0]);
+                    publish(t.part + kMaxPartials + chunk, tree.wg[1]);
+                    publish(t.part + 2 * kMaxPartials + chunk, tree.wg[2]);
+                }
+            }
+            wait_then_read();                                   // every wave: its stores have been performed
+            __syncthreads();
+            uint32_t *counters = t.counters + 2 * kSlots * kSlotStride;
+            if (tid == 0) s_last = arrive_is_last(counters, &t.ctrl->top[2], t.n_wg, share) ? 1u : 0u;
+            __syncthreads();
+            if (s_last) {
+                double NME[3];
+                trees_of_partials<3>(t.part, t.n_chunks, s_tree, &s_stack[0][0], NME);
+                if (tid == 0) finish_iteration<true>(batch, t, it, NME[0], NME[1], NME[2], alpha, false, false, dss_only);
+                if (tid < kSlots) put<true>(counters + tid * kSlotStride, 0u);
+                if (tid == 0) put<true>(&t.ctrl->top[2], 0u);
+                wait_then_read();
+                __syncthreads();
+                if (tid < 16u) put<true>(&rest.finished[tid][0], (uint32_t)(it + 1));
+            }
+            __syncthreads();
+        }
+        __syncthreads();
+    }
 }
 
 }  // namespace
