@@ -79,9 +79,9 @@ typedef enum {
     SOAR_SEARCH_FULL = 1     /* evaluate all 2K+1 candidates                        */
 } soar_search_mode;
 
-/* the one-launch kernel for a single tensor, see soar_params.resident */
+/* the one-launch kernels for a single tensor or a few small ones, see soar_params.resident */
 typedef enum {
-    SOAR_RESIDENT_AUTO = 0,  /* used when the tensor fits and the grid fits the GPU     */
+    SOAR_RESIDENT_AUTO = 0,  /* used when the tensors fit and the grid fits the GPU     */
     SOAR_RESIDENT_NEVER = 1  /* always the path of several launches                     */
 } soar_resident_mode;
 
@@ -100,8 +100,8 @@ typedef enum {
                                      get all of its workgroups onto the GPU within
                                      resident_wait_us.  Single-step: outputs unspecified; run
                                      the call again, or with resident = SOAR_RESIDENT_NEVER.
-                                     Iterated path: set only if resident_wait_us was; the
-                                     outputs are complete                              */
+                                     Iterated path, and batches: set only if
+                                     resident_wait_us was; the outputs are complete    */
 
 typedef struct {
     uint32_t struct_size;    /* sizeof(soar_params), for forward compatibility      */
@@ -142,6 +142,10 @@ typedef struct {
                                   or there is none: at most 16384 blocks per compute unit
                                   (2^22 blocks), re-read from the caches; not while the call
                                   is being captured into a graph.
+                                - a batch of 2 to 40 tensors of one element type, method SOAR,
+                                  single-step settings: as long as all of them together fit
+                                  4096 blocks per compute unit, tensors rounded up to whole
+                                  workgroups; not while the call is being captured.
                                 The launch needs every workgroup of its grid (at most one per
                                 compute unit) on the GPU at the same time and waits for that
                                 at most resident_wait_us.  A call that arrives on another
@@ -155,14 +159,15 @@ typedef struct {
                                 after which a workgroup of that kernel stops waiting for the
                                 others to arrive (every workgroup then does).  Single-step: all
                                 leave and set SOAR_STATUS_GAVE_UP; the bound covers everything
-                                a workgroup does until its waits are over.  Iterated path: it
+                                a workgroup does until its waits are over.  Iterated path, and
+                                batches (tensor by tensor): it
                                 counts from where a workgroup has read its blocks and begins to
                                 wait; one of them, the last to leave, finishes the tensor by
                                 itself (a compute unit's speed), so the outputs are complete;
                                 the status says SOAR_STATUS_GAVE_UP beside its other bits if
                                 this field was set, and is that of a call that did not wait if
-                                it was 0.  Once all workgroups have arrived, the iterated path
-                                waits for as long as they work (at most the greater of the
+                                it was 0.  Once all workgroups have arrived, these
+                                wait for as long as they work (at most the greater of the
                                 bound and 10 s a time)                                        */
     int32_t  tiles_per_wg_absmax; /* single-step path: the maximum pass and the search pass   */
     int32_t  tiles_per_wg_search; /* have launch shapes of their own (the library picks them by

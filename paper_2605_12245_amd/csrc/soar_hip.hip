@@ -136,6 +136,24 @@ bool resident_plan(int64_t nblk, int cu, ResidentPlan &plan)
     return true;
 }
 
+// The same for a batch: one shape for all of its tensors, at most one workgroup per compute unit in all.
+bool resident_batch_plan(int32_t n, const soar_tensor_desc *descs, int cu, ResidentPlan &plan)
+{
+    const int64_t wgs = cu < kResMaxWG ? cu : kResMaxWG;
+    for (const ResidentPlan &shape : {ResidentPlan{256, 1, 0}, ResidentPlan{1024, 1, 0}, ResidentPlan{1024, 2, 0}, ResidentPlan{1024, 4, 0}}) {
+        static_assert(kResMaxPer == 4, "the shapes of k_resident_batch");
+        const int64_t per_wg = (int64_t)shape.L * shape.R;
+        int64_t total = 0;
+        for (int32_t k = 0; k < n && total <= wgs; ++k) total += (descs[k].rows * (descs[k].cols / 16) + per_wg - 1) / per_wg;
+        if (total <= wgs) {
+            plan = shape;
+            plan.G = (uint32_t)total;
+            return true;
+        }
+    }
+    return false;
+}
+
 // Two one-launch kernels that start at the same time on two streams can each take part of the compute
 // units and then wait for the rest in vain (until the bounded wait gives up).  Calls on one stream are
 // ordered by the stream.  For calls that arrive on a different stream than the one-launch kernel before
@@ -178,6 +196,16 @@ void launch_resident(const ResidentPlan &plan, const Task &t, const ResidentArgs
     else if (plan.R == 1) hipLaunchKernelGGL((k_resident<DT, METHOD, 1024, 1>), grid, dim3(1024), 0, st, t, a);
     else if (plan.R == 2) hipLaunchKernelGGL((k_resident<DT, METHOD, 1024, 2>), grid, dim3(1024), 0, st, t, a);
     else hipLaunchKernelGGL((k_resident<DT, METHOD, 1024, 4>), grid, dim3(1024), 0, st, t, a);
+}
+
+template <int DT>
+void launch_resident_batch(const ResidentPlan &plan, const ResidentBatch &b, hipStream_t st)
+{
+    const dim3 grid(plan.G);
+    if (plan.L == 256) hipLaunchKernelGGL((k_resident_batch<DT, 256, 1>), grid, dim3(256), 0, st, b);
+    else if (plan.R == 1) hipLaunchKernelGGL((k_resident_batch<DT, 1024, 1>), grid, dim3(1024), 0, st, b);
+    else if (plan.R == 2) hipLaunchKernelGGL((k_resident_batch<DT, 1024, 2>), grid, dim3(1024), 0, st, b);
+    else hipLaunchKernelGGL((k_resident_batch<DT, 1024, 4>), grid, dim3(1024), 0, st, b);
 }
 
 // The same for the iterated path (k_iter_resident).  A power of two tiles per workgroup can leave compute units
@@ -719,6 +747,13 @@ ResidentArgs resident_args(const soar_params *params)
     return a;
 }
 
+// the bound of a wait once all workgroups have arrived
+uint64_t later_ticks(const ResidentArgs &a)
+{
+    const uint64_t ten_seconds = 10000ull * (uint64_t)device_facts().wall_clock_khz;
+    return a.wait_ticks > ten_seconds ? a.wait_ticks : ten_seconds;
+}
+
 soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_params *params, void *d_workspace,
                       size_t workspace_bytes, hipStream_t st)
 {
@@ -761,6 +796,45 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
             if (rtn) launch_resident<SOAR_FP32, SOAR_METHOD_RTN>(plan, t, a, st);
             else launch_resident<SOAR_FP32, SOAR_METHOD_SOAR>(plan, t, a, st);
         }
+        SOAR_LAUNCH_CHECK();
+        return SOAR_OK;
+    }
+
+    // a few small tensors: the same in one launch for all of them (see k_resident_batch).  Not under capture: the token is the
+    // nonce alone, which replays share.
+    bool one_dtype = true;
+    for (int32_t k = 1; k < n; ++k) one_dtype = one_dtype && descs[k].dtype == descs[0].dtype;
+    if (n > 1 && n <= kResidentTensors && one_dtype && !iterated && params->method == SOAR_METHOD_SOAR && params->tiles_per_wg == 0 &&
+        params->tiles_per_wg_absmax == 0 && params->tiles_per_wg_search == 0 && params->resident == SOAR_RESIDENT_AUTO &&
+        resident_batch_plan(n, descs, device_facts().compute_units, plan) && !being_captured(st) && resident_may_start(st)) {
+        ResidentBatch b;
+        std::memset(&b, 0, sizeof(b));
+        b.slots = static_cast<char *>(d_workspace);
+        b.n = (uint32_t)n;
+        b.tell = params->resident_wait_us > 0 ? (uint32_t)SOAR_STATUS_GAVE_UP : 0u;
+        b.r = resident_args(params);
+        b.later_ticks = later_ticks(b.r);
+        uint32_t wg = 0;
+        for (int32_t k = 0; k < n; ++k) {
+            const soar_tensor_desc &d = descs[k];
+            ResidentTensor &t = b.t[k];
+            t.w = d.d_w;
+            t.codes = d.d_codes;
+            t.scales = d.d_scales;
+            t.gscale = d.d_global_scale;
+            t.sse = d.d_sse;
+            t.status = d.d_status;
+            t.ld = d.ld_elems;
+            t.bpr = (uint32_t)(d.cols / 16);
+            t.nblk = (uint32_t)(d.rows * (d.cols / 16));
+            t.wg_begin = wg;
+            const uint32_t per_wg = (uint32_t)(plan.L * plan.R);
+            t.n_wg = (t.nblk + per_wg - 1) / per_wg;
+            wg += t.n_wg;
+        }
+        ScopedTimer tm(SOAR_KERNEL_RESIDENT, st);
+        if (descs[0].dtype == SOAR_BF16) launch_resident_batch<SOAR_BF16>(plan, b, st);
+        else launch_resident_batch<SOAR_FP32>(plan, b, st);
         SOAR_LAUNCH_CHECK();
         return SOAR_OK;
     }
@@ -813,8 +887,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         a.early_stop_rel = params->early_stop_rel;
         a.tiles = (uint32_t)plan.R;
         a.tell = params->resident_wait_us > 0 ? (uint32_t)SOAR_STATUS_GAVE_UP : 0u;
-        const uint64_t ten_seconds = 10000ull * (uint64_t)device_facts().wall_clock_khz;
-        a.later_ticks = a.r.wait_ticks > ten_seconds ? a.r.wait_ticks : ten_seconds;
+        a.later_ticks = later_ticks(a.r);
         ScopedTimer tm(SOAR_KERNEL_RESIDENT, st);
         if (d.dtype == SOAR_BF16) launch_iter_resident<SOAR_BF16>(plan, t, a, st);
         else launch_iter_resident<SOAR_FP32>(plan, t, a, st);

@@ -492,12 +492,15 @@ struct ResidentArgs {
     int32_t  radius, full_search;
     uint64_t nonce;                       // new for every call
     uint64_t wait_ticks;                  // in ticks of the wall clock: k_resident, bound of the waits of a workgroup together;
-                                          // k_iter_resident, of its wait for the grid to arrive
+                                          // k_iter_resident and k_resident_batch, of its wait for the grid to arrive
     unsigned long long *search_stats;     // null, or the diagnostic counters of count_search
 };
 
-template <int DT, int METHOD, int L, int R>
-__global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs args)
+// BATCH: workgroup g of the G that work on one tensor of a batch (k_resident_batch, which finishes every tensor: false, all outputs
+// unwritten, where this one has to be done again); otherwise the launch is one tensor's.
+template <int DT, int METHOD, int L, int R, bool BATCH>
+__device__ __forceinline__ bool resident_body(const Task &t, const ResidentArgs &args, ResidentWords *batch_words = nullptr, uint32_t batch_g = 0u,
+                                              uint32_t batch_G = 0u, uint64_t later_ticks = 0)
 {
     static_assert(L == 256 || L == 1024, "workgroup of 4 or 16 waves");
     static_assert(R == 1 || R == 2 || R == 4, "blocks per lane");
@@ -517,7 +520,7 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
     __shared__ float s_alpha1;
     __shared__ uint32_t s_amax, s_gone;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    const uint32_t wave_first = (blockIdx.x * (uint32_t)L + wave * 64u) * (uint32_t)R;   // first block of this wave
+    const uint32_t wave_first = ((BATCH ? batch_g : blockIdx.x) * (uint32_t)L + wave * 64u) * (uint32_t)R;   // first block of this wave
     // block k (0 .. R-1) of this lane: packet k / kX of the wave, there the lane's kX adjacent blocks
     auto blk = [&](int k) -> uint32_t {
         return wave_first + (uint32_t)(k / kX) * (64u * kX) + lane * (uint32_t)kX + (uint32_t)(k % kX);
@@ -525,15 +528,15 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
     uint64_t *epoch_p = &t.ctrl->epoch;
 
     ResidentGrid grid;
-    grid.g = blockIdx.x;
-    grid.G = gridDim.x;
-    grid.tok = grid.base = 0;
+    grid.g = BATCH ? batch_g : blockIdx.x;
+    grid.G = BATCH ? batch_G : gridDim.x;
+    grid.tok = grid.base = BATCH ? args.nonce : 0;
     grid.t0 = 0;
     grid.ticks = args.wait_ticks;
-    ResidentWords &words = *reinterpret_cast<ResidentWords *>(t.part);
+    ResidentWords &words = *(BATCH ? batch_words : reinterpret_cast<ResidentWords *>(t.part));
     grid.words = words.max;
     uint64_t epoch = 0;
-    if (grid.G > 1u) {
+    if (!BATCH && grid.G > 1u) {
         epoch = __hip_atomic_load(epoch_p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         grid.tok = grid.base = args.nonce ^ (epoch * kResOdd);
         grid.t0 = (uint64_t)wall_clock64();
@@ -544,10 +547,12 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
         const uint64_t gone = ~grid.tok << kResSumBits;
         leave_max(grid, ~grid.tok << kMaxBits);
         leave_sums(grid, words.nm, gone);
-        __hip_atomic_store(words.err + grid.g, gone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // any change of the epoch will do for the next launch
-        __hip_atomic_fetch_add(epoch_p, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (t.status) *t.status = SOAR_STATUS_GAVE_UP;
+        if constexpr (!BATCH) {
+            __hip_atomic_store(words.err + grid.g, gone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            // any change of the epoch will do for the next launch
+            __hip_atomic_fetch_add(epoch_p, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (t.status) *t.status = SOAR_STATUS_GAVE_UP;
+        }
     };
 
     // ---- the blocks of this lane, as loaded; Eq. 1 maximum
@@ -591,18 +596,21 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
         bool ok = true;
         if (grid.G > 1u) {
             uint32_t value = DT == SOAR_BF16 ? amax >> 16 : amax;
+            if constexpr (BATCH) grid.t0 = (uint64_t)wall_clock64();
             ok = cross_max<kMaxBits>(grid, value);
             amax = DT == SOAR_BF16 ? value << 16 : value;
             if (lane == 0) {
                 if (!ok) give_up();
-                else if (grid.g == 0u)     // every workgroup has read the epoch by now: the next launch gets a new token
+                else if (!BATCH && grid.g == 0u)     // every workgroup has read the epoch by now: the next launch gets a new token
                     __hip_atomic_store(epoch_p, epoch + 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         if (lane == 0) { s_amax = amax; s_gone = ok ? 0u : 1u; }
     }
     __syncthreads();
-    if (s_gone) return;
+    if (s_gone) return false;
+    // from here on every workgroup is running: the waits last as long as the slowest one's share
+    if constexpr (BATCH) grid.ticks = later_ticks;
     const uint32_t amax_bits = s_amax;
     const bool allzero = amax_bits == 0u;
     const bool degenerate = allzero || amax_bits >= 0x7F800000u;
@@ -678,6 +686,7 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
                 double NM[2] = {workgroup_sum(0), workgroup_sum(1)};
                 bool ok = true;
                 if (grid.G > 1u) {
+                    if constexpr (BATCH) grid.t0 = (uint64_t)wall_clock64();
                     ok = cross_sums<2>(grid, words.nm, s_cross, NM);
                     if (!ok && lane == 0) give_up();
                 }
@@ -687,12 +696,27 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
                 }
             }
             __syncthreads();
-            if (s_gone) return;
+            if (s_gone) return false;
             alpha1 = s_alpha1;
-        } else if (allzero) {
-            alpha1 = 1.0f;
+        } else {
+            if constexpr (BATCH) {
+                // nobody may finish here while others have given up: a crossing (of no sums) tells
+                if (wave == 0) {
+                    double none[2] = {0.0, 0.0};
+                    bool ok = true;
+                    if (grid.G > 1u) {
+                        grid.t0 = (uint64_t)wall_clock64();
+                        ok = cross_sums<2>(grid, words.nm, s_cross, none);
+                        if (!ok && lane == 0) give_up();
+                    }
+                    if (lane == 0) s_gone = ok ? 0u : 1u;
+                }
+                __syncthreads();
+                if (s_gone) return false;
+            }
+            if (allzero) alpha1 = 1.0f;
         }
-        if (blockIdx.x == 0u && tid == 0) *t.gscale = alpha1;
+        if ((BATCH ? batch_g : blockIdx.x) == 0u && tid == 0) *t.gscale = alpha1;
     }
     const float inv_alpha1 = 1.0f / alpha1;
     const bool fast = gs.fast && near_one(alpha1);
@@ -775,21 +799,207 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
     }
     wave_sum_to_lds(2, terr);
     __syncthreads();
-    if (wave != 0) return;
+    if (wave != 0) return true;
     // ---- error sum and status: workgroup 0 collects
     double total = workgroup_sum(2);
     bool ok = true;
     if (grid.G > 1u) {
         if (t.sse) publish_sum(grid, words.err, total);
-        if (grid.g != 0u) return;
+        if (grid.g != 0u) return true;
+        if constexpr (BATCH) grid.t0 = (uint64_t)wall_clock64();
         if (t.sse) ok = collect_sum(grid, words.err, total);
     }
     if (lane == 0) {
-        if (!ok) { give_up(); return; }
+        if (!ok) {
+            give_up();
+            if constexpr (BATCH)
+                if (t.status) *t.status = SOAR_STATUS_GAVE_UP;       // the machine has stopped working: the sum is missing
+            return true;
+        }
         if (t.sse) *t.sse = total;
         if (t.status) *t.status = (amax_bits >= 0x7F800000u ? SOAR_STATUS_NONFINITE : 0) | (allzero ? SOAR_STATUS_ALLZERO : 0);
         if (METHOD == SOAR_METHOD_RTN) *t.gscale = allzero ? 1.0f : alpha0;
     }
+    return true;
+}
+
+template <int DT, int METHOD, int L, int R>
+__global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs args)
+{
+    resident_body<DT, METHOD, L, R, false>(t, args);
+}
+
+// ------------------------------------------------------------------ one launch, a batch of small tensors
+// A call with a few small tensors pays four launches that keep a fraction of the GPU busy; together they fit the registers of
+// the GPU as one tensor does.  k_resident_batch gives every tensor its workgroups (all of one shape, at most one per compute unit
+// in all), its own crossing words and its own token; tensors do not wait for one another.  The call always finishes, as it does
+// with several launches: a tensor whose workgroups do not arrive together within the bound is done by the last of them to leave,
+// alone (as in k_iter_resident).
+// Whole calls, several launches / one: a layer of hidden 256 (seven matrices) 21.8 / 9.4 us, four of them 70 / 11, four of hidden 512 in fp32 105 / 22.7,
+// one of hidden 1024 34 / 20.6, of 1120 (99 % of the places) 38.5 / 20.5.
+constexpr int kResidentTensors = 40;
+constexpr int kWordsPerSlot = 5;          // tensors whose crossing words lie side by side in the partial sums of one slot
+struct BatchWords {
+    ResidentWords cross;
+    uint64_t left;                        // how many workgroups have given up
+};
+static_assert(kWordsPerSlot * sizeof(BatchWords) <= kPartialsBytes && kResidentTensors <= kWordsPerSlot * kGroupMax && kResidentTensors <= 64,
+              "layout of the crossing words");
+
+struct ResidentTensor {
+    const void *w;
+    uint8_t  *codes, *scales;
+    float    *gscale;
+    double   *sse;
+    int32_t  *status;
+    int64_t  ld;
+    uint32_t bpr, nblk, wg_begin, n_wg;
+};
+struct ResidentBatch {
+    ResidentTensor t[kResidentTensors];
+    char    *slots;                       // the workspace
+    uint32_t n;
+    uint32_t tell;                        // status bit of a call that gave up and was finished all the same
+    uint64_t later_ticks;                 // bound of every wait after the first crossing
+    ResidentArgs r;
+};
+static_assert(sizeof(ResidentBatch) <= 4096, "kernel arguments");
+
+// One lane of a workgroup that gives up: the number of workgroups that have, this one included.  The word may hold
+// anything before the launch's first: the count stands beside 48 bits of the token.  An exchange fails only where
+// another workgroup's has succeeded, so the loop ends.
+__device__ __forceinline__ uint32_t count_out(uint64_t *word, uint64_t token)
+{
+    uint64_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), next;
+    do next = token << 16 | ((seen >> 16 == (token << 16) >> 16 ? seen & 0xFFFFull : 0ull) + 1ull);
+    while (!__hip_atomic_compare_exchange_strong(word, &seen, next, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return (uint32_t)(next & 0xFFFFull);
+}
+
+// The single-step path of one tensor by one workgroup, a tile of L blocks after the other: the same trees, the same bytes.
+template <int DT, int L>
+__device__ __forceinline__ void single_step_alone(const Task &t, const ResidentArgs &args, uint32_t tell)
+{
+    constexpr int kWaves = L / 64;
+    __shared__ double s_part[2][kWaves], s_stack[2][32], s_sums[2];
+    __shared__ uint32_t s_max[kWaves];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    uint32_t tiles = 1;                                      // a power of two: the tree's
+    while ((uint64_t)tiles * L < t.nblk) tiles <<= 1;
+    auto load = [&](uint32_t i, float w[16]) { load_block<DT>(t.w, block_offset(t, i), w); };
+    // tile k of two sums; after the last one s_sums holds them
+    auto add_tile = [&](uint32_t k, double x, double y) {
+        x = wave_pair_tree(x);
+        y = wave_pair_tree(y);
+        __syncthreads();
+        if (lane == 0) { s_part[0][wave] = x; s_part[1][wave] = y; }
+        __syncthreads();
+        if (wave == 0) {
+#pragma unroll
+            for (int n = 0; n < 2; ++n) {
+                double v = wave_pair_tree(lane < (uint32_t)kWaves ? s_part[n][lane] : 0.0);
+                if (lane == 0) {
+                    uint32_t lvl = 0;
+                    while ((k >> lvl) & 1u) { v = s_stack[n][lvl] + v; ++lvl; }
+                    s_stack[n][lvl] = s_sums[n] = v;
+                }
+            }
+        }
+    };
+    uint32_t m = 0;
+    for (uint32_t i = tid; i < t.nblk; i += L) {
+        float w[16];
+        load(i, w);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) m = max(m, __float_as_uint(w[j]) & 0x7FFFFFFFu);
+    }
+    m = wave_max_u32(m);
+    if (lane == 0) s_max[wave] = m;
+    __syncthreads();
+    const uint32_t amax_bits = wave_max_u32(lane < (uint32_t)kWaves ? s_max[lane] : 0u);
+    const bool allzero = amax_bits == 0u, degenerate = allzero || amax_bits >= 0x7F800000u;
+    const GlobalScale gs(amax_bits);
+    auto ratio = [&](const float w[16], float &a, float &b, float &delta0) {
+        uint32_t nib[2], c0;
+        block_init(w, gs, c0, delta0, nib);
+        code_sums(w, nib, a, b);
+        return block_ratio(a, b, delta0, gs.fast);
+    };
+    float alpha1 = allzero ? 1.0f : gs.alpha0;
+    if (!degenerate) {
+        for (uint32_t k = 0; k < tiles; ++k) {
+            const uint32_t i = k * (uint32_t)L + tid;
+            float a = 0.0f, b = 0.0f, delta0 = 0.0f;
+            if (i < t.nblk) {
+                float w[16];
+                load(i, w);
+                ratio(w, a, b, delta0);
+            }
+            add_tile(k, (double)a * (double)delta0, ((double)b * (double)delta0) * (double)delta0);
+        }
+        __syncthreads();
+        if (s_sums[1] > 0.0) alpha1 = (float)(s_sums[0] / s_sums[1]);
+        __syncthreads();
+    }
+    const float inv_alpha1 = 1.0f / alpha1;
+    const bool fast = gs.fast && near_one(alpha1);
+    for (uint32_t k = 0; k < tiles; ++k) {
+        const uint32_t i = k * (uint32_t)L + tid;
+        float err = 0.0f;
+        if (i < t.nblk) {
+            float w[16], q[16];
+            uint32_t nib[2];
+            int best = (int)kE4M3Min;
+            load(i, w);
+            if (allzero) {
+                nib[0] = fp4x8(w);
+                nib[1] = fp4x8(w + 8);
+            } else {
+                float a, b, delta0;
+                const int centre = new_codes(w, degenerate ? 0.0f : ratio(w, a, b, delta0), alpha1, inv_alpha1, fast, nib, q);
+                if (args.full_search || !search_certified(w, q, alpha1, inv_alpha1, centre, args.radius, best, err))
+                    search_full(w, q, alpha1, centre, args.radius, best, err);
+            }
+            __builtin_nontemporal_store((uint64_t)nib[1] << 32 | nib[0], reinterpret_cast<uint64_t *>(t.codes) + i);
+            __builtin_nontemporal_store((uint8_t)best, t.scales + i);
+        }
+        add_tile(k, (double)err, 0.0);
+    }
+    if (tid == 0) {
+        *t.gscale = alpha1;
+        if (t.sse) *t.sse = s_sums[0];
+        if (t.status) *t.status = (int32_t)tell | (amax_bits >= 0x7F800000u ? SOAR_STATUS_NONFINITE : 0) | (allzero ? SOAR_STATUS_ALLZERO : 0);
+    }
+}
+
+template <int DT, int L, int R>
+__global__ __launch_bounds__(L) void k_resident_batch(const ResidentBatch batch)
+{
+    __shared__ uint32_t s_last;
+    const uint32_t lane = threadIdx.x & 63u;
+    // which tensor: the last one that begins at or before this workgroup
+    const uint32_t begin = lane < batch.n ? batch.t[lane].wg_begin : 0xFFFFFFFFu;
+    const uint32_t which = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(begin <= blockIdx.x)) - 1u;
+    const ResidentTensor &x = batch.t[which];
+    BatchWords &words = reinterpret_cast<BatchWords *>(batch.slots + (size_t)(which / kWordsPerSlot) * kSlotBytes + kZeroedBytes)[which % kWordsPerSlot];
+    Task t;
+    t.w = x.w;
+    t.codes = x.codes;
+    t.scales = x.scales;
+    t.gscale = x.gscale;
+    t.sse = x.sse;
+    t.status = x.status;
+    t.ld = x.ld;
+    t.bpr = x.bpr;
+    t.nblk = x.nblk;
+    t.contiguous = x.ld == (int64_t)x.bpr * 16 ? 1u : 0u;
+    t.ctrl = nullptr;
+    if (resident_body<DT, SOAR_METHOD_SOAR, L, R, true>(t, batch.r, &words.cross, blockIdx.x - x.wg_begin, x.n_wg, batch.later_ticks)) return;
+    // given up, here or elsewhere, before any output was written: the last one to leave does the tensor
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = count_out(&words.left, batch.r.nonce) == x.n_wg ? 1u : 0u;
+    __syncthreads();
+    if (s_last) single_step_alone<DT, L>(t, batch.r, batch.tell);
 }
 
 }  // namespace

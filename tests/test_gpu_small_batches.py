@@ -44,3 +44,107 @@ def test_small_groups_equal_forced_shapes(tiles, dtype):
         p.tiles_per_wg = 8
         same(got, run(ws, p))
         same([got[0], got[-1]], [B.quantize(w, method, p.dss_radius) for w in (ws[0], ws[-1])])
+
+
+# ------------------------------------------------------------------ one launch for the whole batch (k_resident_batch)
+def mixed(rows, dtype, seed, cols=32):
+    """every other tensor a slice of wider rows"""
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    return [(torch.randn((r, cols + 16 * (k % 2)), generator=gen, device=DEV) * 0.02 * (k % 3 + 1)).to(dtype)[:, :cols] for k, r in enumerate(rows)]
+
+
+def launches_of(kernel, fn):
+    B.soar_kernel_timing_enable(True)
+    fn()
+    torch.cuda.synchronize()
+    n = B.soar_kernel_timing_read(kernel)[1]
+    B.soar_kernel_timing_enable(False)
+    return n
+
+
+# rows of two blocks; workgroups of 256 x 1, 1024 x 1, x 2, x 4 blocks, full to the last place, one tensor of a single workgroup
+# (no crossing), of 16 and 17, 64 and 65 (direct and grouped crossings), the most tensors a launch takes
+BATCHES = [(1, 1), (128 * 100, 128 * 156), (128 * 100 + 1, 128 * 155, 5), (512 * 17, 512 * 16 - 3, 512 * 200, 7), (512 * 65, 1, 512 * 64),
+           (512 * 300 - 1, 512 * 64, 512 * 65, 512 * 2), (512 * 4 * 100, 512 * 4 * 150, 512 * 4 * 6), tuple(range(1, 1600, 41))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("rows", BATCHES, ids=lambda r: f"{len(r)}x{r[0]}-{sum(r)}")
+def test_one_launch_for_a_batch_equals_several(rows, dtype):
+    ws = mixed(rows, dtype, sum(rows))
+    p = B.soar_default_params()
+    outs = [B.new_outputs(w.shape[0], w.shape[1], DEV) for w in ws]
+    assert launches_of(B.SOAR_KERNEL_RESIDENT, lambda: run(ws, p, outs)) == 1
+    p.resident = B.SOAR_RESIDENT_NEVER
+    want = run(ws, p)
+    same(outs, want)
+    p.resident = B.SOAR_RESIDENT_AUTO
+    p.search_mode = B.SOAR_SEARCH_FULL
+    same(run(ws, p), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("rows", BATCHES[:-1], ids=lambda r: f"{len(r)}x{r[0]}-{sum(r)}")
+def test_a_batch_that_gives_up_is_finished(rows, dtype):
+    """a bound of 1 us: most workgroups leave, and the last one of every tensor does it alone"""
+    ws = mixed(rows, dtype, sum(rows)) + [torch.zeros(700, 32, dtype=dtype, device=DEV)[:sum(rows) % 700 + 1]]
+    if sum(-(-w.shape[0] * 2 // 4096) for w in ws) > 256:
+        ws.pop()
+    p = B.soar_default_params()
+    p.resident = B.SOAR_RESIDENT_NEVER
+    want = run(ws, p)
+    p.resident = B.SOAR_RESIDENT_AUTO
+    p.resident_wait_us = 1
+    for turn in range(3):
+        got = run(ws, p)
+        for o in got:
+            o.status &= ~B.SOAR_STATUS_GAVE_UP
+        same(got, want)
+    p.resident_wait_us = 0
+    same(run(ws, p), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+def test_one_launch_degenerate_tensors_and_workspaces_holding_anything(dtype):
+    ws = mixed((513, 5000, 40, 9000, 300), dtype, 9)
+    ws[0] = torch.zeros_like(ws[0])
+    ws[2] = ws[2].clone()
+    ws[2][3, 3] = float("nan")
+    ws[4] = ws[4] * 2.0 ** -120
+    p = B.soar_default_params()
+    p.resident = B.SOAR_RESIDENT_NEVER
+    want = run(ws, p)
+    p.resident = B.SOAR_RESIDENT_AUTO
+    outs = [B.new_outputs(w.shape[0], w.shape[1], DEV) for w in ws]
+    descs = [B.make_desc(w, o) for w, o in zip(ws, outs)]
+    space = B.new_batch_workspace(descs, p, DEV)
+    for fill in (0x00, 0xFF, 0x5A, None, None):
+        if fill is not None:
+            space.fill_(fill)
+        B.quantize_batch(descs, p, space)
+        torch.cuda.synchronize()
+        keep = [k for k in range(5) if k != 2]
+        same([outs[k] for k in keep], [want[k] for k in keep])
+        assert int(outs[2].status.item()) == B.SOAR_STATUS_NONFINITE
+        never = B.soar_default_params()
+        never.resident = B.SOAR_RESIDENT_NEVER
+        B.quantize_batch(descs, never, space)               # the launches of the other path on the same workspace
+        torch.cuda.synchronize()
+        same([outs[k] for k in keep], [want[k] for k in keep])
+
+
+@pytest.mark.gpu
+def test_batches_that_keep_to_several_launches():
+    p = B.soar_default_params()
+    small = mixed((100, 200), torch.bfloat16, 1)
+    both = [small[0], small[1].float()]
+    many = mixed((3,) * 41, torch.bfloat16, 2)
+    large = mixed((512 * 4 * 255, 512 * 4 + 1), torch.bfloat16, 3)
+    for ws in (both, many, large):
+        assert launches_of(B.SOAR_KERNEL_RESIDENT, lambda: run(ws, p)) == 0
+        same(run(ws, p)[:2], [B.quantize(w) for w in ws[:2]])
+    p.resident = B.SOAR_RESIDENT_NEVER
+    assert launches_of(B.SOAR_KERNEL_RESIDENT, lambda: run(small, p)) == 0
