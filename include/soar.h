@@ -189,9 +189,8 @@ void soar_paper_params(soar_params *p);
 /*
  * Bytes of device workspace soar_quantize needs for a rows x cols tensor
  * (control words, per-workgroup partial sums of the tensor-wide reductions of
- * Eq. 5, and 4 bytes per block for the block ratio a/b: the iterated path keeps it
- * there, the other carries it from the statistics pass to the search pass where that
- * is the faster way; the size does not depend on it).  The workspace must be 256-byte aligned; its
+ * Eq. 5, and 4 bytes per block for the block ratio a/b, which the iterated path keeps
+ * there; the size does not depend on the path).  The workspace must be 256-byte aligned; its
  * contents need no initialisation and are undefined afterwards.  Returns 0 on a
  * bad argument.
  */

@@ -470,7 +470,7 @@ constexpr int64_t kOnePassByteCap = (int64_t)1 << 29;    // larger launches gain
 struct GroupCaps { int64_t bf16, fp32; };
 
 // Two launch groups are on the machine at once (see SecondLane), and how much of the 256 MiB last-level cache each takes
-// -- weights, ratios, outputs -- decides what the later passes still find there.  256 MiB of fp32 weights hold half the
+// -- weights, outputs, the ratios of the iterated path -- decides what the later passes still find there.  256 MiB of fp32 weights hold half the
 // blocks of as many bytes of bf16.  Measured as 208 / 256 MiB over ten layer widths, hidden 2560 to 8192 (us a call, two
 // to four runs that differ by less than 1 %):
 //   bf16, three passes, 8 layers   12288 wide 1660 / 1733, 14336 1941 / 2075, 11008 1708 / 1785, 13824 2742 / 2887, 8192
@@ -579,16 +579,9 @@ SecondLane *second_lane()
     return lanes[dev].usable ? &lanes[dev] : nullptr;
 }
 
-// Whether the statistics pass leaves every block's ratio (4 bytes) for the search pass.  Where both passes read from HBM, half a byte
-// per weight of traffic costs more than the hundred instructions that form the ratio again (28672 x 8192: bf16 carried 297.3 us,
-// formed again 291.7, fp32 580 / 558; four 12288 wide layers of fp32 1635 / 1603; two 360 MB matrices 22016 wide a layer 3219 / 3094).
-// bf16 weights of a launch group that stays in the last-level cache are nearer the issue rate: a 36 layer model 7.15 / 7.27 ms,
-// 11008 wide 1728 / 1743 us, 14336 wide 1948 / 2051; alone on the GPU the same.
-bool carries_ratios(int dtype, int64_t group_bytes) { return dtype == SOAR_BF16 && group_bytes <= kLastLevelCache; }
-
 // grids: every pass has its own number of workgroups (Task::absmax, the base shape, Task::search)
 template <int DT>
-soar_status launch_group(const Batch &b, uint32_t wg_absmax, uint32_t wg_stats, uint32_t wg_search, int method, bool carry, hipStream_t st)
+soar_status launch_group(const Batch &b, uint32_t wg_absmax, uint32_t wg_stats, uint32_t wg_search, int method, hipStream_t st)
 {
     if (b.t[0].amax_in == nullptr) {       // all tensors of a batch supply their maximum, or none does
         ScopedTimer t(SOAR_KERNEL_ABSMAX, st);
@@ -596,21 +589,13 @@ soar_status launch_group(const Batch &b, uint32_t wg_absmax, uint32_t wg_stats, 
         SOAR_LAUNCH_CHECK();
     }
     if (method == SOAR_METHOD_SOAR) {
-        auto stats = k_stats<DT, false>;
-        auto search = k_search<DT, SOAR_METHOD_SOAR, false>;
-        if constexpr (DT == SOAR_BF16) {          // carries_ratios: no other type does
-            if (carry) {
-                stats = k_stats<DT, true>;
-                search = k_search<DT, SOAR_METHOD_SOAR, true>;
-            }
-        }
         {
             ScopedTimer t(SOAR_KERNEL_STATS, st);
-            hipLaunchKernelGGL(stats, dim3(wg_stats), dim3(kWG), 0, st, b);
+            hipLaunchKernelGGL(k_stats<DT>, dim3(wg_stats), dim3(kWG), 0, st, b);
             SOAR_LAUNCH_CHECK();
         }
         ScopedTimer t(SOAR_KERNEL_SEARCH, st);
-        hipLaunchKernelGGL(search, dim3(wg_search), dim3(kWG), 0, st, b);
+        hipLaunchKernelGGL((k_search<DT, SOAR_METHOD_SOAR>), dim3(wg_search), dim3(kWG), 0, st, b);
         SOAR_LAUNCH_CHECK();
     } else {
         ScopedTimer t(SOAR_KERNEL_SEARCH, st);
@@ -939,11 +924,10 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         // search and streams like the single-step kernels.
         const bool searching = iterated && params->method != SOAR_METHOD_CJSO_ONLY;
         const uint32_t tpw = (uint32_t)params->tiles_per_wg;
-        int64_t group_tiles = 0, largest_tiles = 0, group_bytes = 0;
+        int64_t group_tiles = 0, largest_tiles = 0;
         for (int32_t k = i; k < j; ++k) {
             const int64_t tiles = (descs[k].rows * (descs[k].cols / 16) + kWG - 1) / kWG;
             group_tiles += tiles;
-            group_bytes += weight_bytes(descs[k]);
             largest_tiles = tiles > largest_tiles ? tiles : largest_tiles;
         }
         const uint32_t searching_tpw = searching ? search_tiles_per_wg(group_tiles) : 0u;
@@ -985,11 +969,9 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         if (iterated)
             result = descs[i].dtype == SOAR_BF16 ? launch_group_iter<SOAR_BF16>(b, wg_absmax, wg, params->iters, nearest, lane_stream[lane])
                                                  : launch_group_iter<SOAR_FP32>(b, wg_absmax, wg, params->iters, nearest, lane_stream[lane]);
-        else {
-            const bool carry = carries_ratios(descs[i].dtype, group_bytes);
-            result = descs[i].dtype == SOAR_BF16 ? launch_group<SOAR_BF16>(b, wg_absmax, wg, wg_search, params->method, carry, lane_stream[lane])
-                                                 : launch_group<SOAR_FP32>(b, wg_absmax, wg, wg_search, params->method, carry, lane_stream[lane]);
-        }
+        else
+            result = descs[i].dtype == SOAR_BF16 ? launch_group<SOAR_BF16>(b, wg_absmax, wg, wg_search, params->method, lane_stream[lane])
+                                                 : launch_group<SOAR_FP32>(b, wg_absmax, wg, wg_search, params->method, lane_stream[lane]);
         i = j;
     }
     // always join, also after a failed launch, so that the caller's stream stays ordered

@@ -105,9 +105,7 @@ __global__ __launch_bounds__(kWG) void k_absmax(const Batch batch)
 // of kStage consecutive tiles are staged in LDS; lane t then folds the kStage
 // adjacent terms t*kStage.. in registers and one wave tree finishes the group,
 // which is the same adjacent-pair tree at a fraction of the cross-lane work.
-// CARRY: each block's a/b -- or -Delta0 when its codes are all zero -- is kept for the
-// search kernel, which otherwise forms it again (see carries_ratios).
-template <int DT, bool CARRY>
+template <int DT>
 __global__ __launch_bounds__(kWG) void k_stats(const Batch batch)
 {
     __shared__ double2 s_terms[kStage * kWG];
@@ -134,20 +132,15 @@ __global__ __launch_bounds__(kWG) void k_stats(const Batch batch)
         for (uint32_t kk = 0; kk < T; ++kk) {
             const uint32_t i = (tile0 + kg + kk) * kWG + tid;
             double tN = 0.0, tM = 0.0;
-            if (i < t.nblk) {
-                float rho = 0.0f;
-                if (!degenerate) {
-                    float w[16], q[16];
-                    uint32_t nib[2], c0;
-                    float delta0, a, b;
-                    load_block<DT, kStreamStats>(t.w, block_offset(t, i), w);
-                    block_init(w, gs, c0, delta0, nib, q);
-                    block_sums(w, q, a, b);
-                    rho = block_ratio(a, b, delta0, gs.fast);
-                    tN = (double)a * (double)delta0;
-                    tM = ((double)b * (double)delta0) * (double)delta0;
-                }
-                if constexpr (CARRY) __builtin_nontemporal_store(rho, t.rho + i);
+            if (i < t.nblk && !degenerate) {
+                float w[16], q[16];
+                uint32_t nib[2], c0;
+                float delta0, a, b;
+                load_block<DT, kStreamStats>(t.w, block_offset(t, i), w);
+                block_init(w, gs, c0, delta0, nib, q);
+                block_sums(w, q, a, b);
+                tN = (double)a * (double)delta0;
+                tM = ((double)b * (double)delta0) * (double)delta0;
             }
             s_terms[kk * kWG + tid] = make_double2(tN, tM);
         }
@@ -335,9 +328,12 @@ __device__ __forceinline__ int new_codes(const float w[16], float rho, float alp
 
 // Eq. 6, projection, new assignment, Eq. 8 search, packing, error sum.
 // METHOD RTN emits the Eq. 1-2 state instead.
+// Each block's a/b is formed again: a hundred instructions where the statistics would leave it in memory, 4 bytes a block written and read.  Carried /
+// formed again: four decoder layers 863 / 830 us, one 256 / 246, four of hidden 2048 248 / 239, 12288 x 4096 75 / 73, 28672 x 8192
+// 299 / 285, 36 layers 7.13 / 7.04 ms.
 // (bf16: held to 64 registers, eight waves per SIMD; left to itself the compiler takes 83 for a shorter schedule and loses more in
 // occupancy than it gains)
-template <int DT, int METHOD, bool CARRY = false>
+template <int DT, int METHOD>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(DT == SOAR_BF16 ? 8 : 4))) void k_search(const Batch batch)
 {
     __shared__ double s_wave[4];
@@ -407,9 +403,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(DT == SOAR_
             out_err = block_error(w, q, alpha0 * delta0);
         } else {
             float rho = 0.0f;                                                       // a / b >= 0, or -Delta0 where b == 0
-            if constexpr (CARRY) {
-                rho = __builtin_nontemporal_load(t.rho + i);
-            } else if (amax_bits < 0x7F800000u) {
+            if (amax_bits < 0x7F800000u) {
                 uint32_t c0;
                 float delta0, a, b;
                 block_init(w, gs, c0, delta0, nib, q);
