@@ -1000,7 +1000,7 @@ soar_status check_mx_shape(int64_t rows, int64_t cols, int64_t ld)
     return SOAR_OK;
 }
 
-// ---- Eq. 3 / Eq. 4 on stored tensors: up to kGroupMax tensors of one element type and at most
+// ---- Eq. 3 / Eq. 4 on stored tensors: up to kStoredMax tensors of one element type and at most
 // kStoredByteCap bytes of weights per launch
 soar_status validate_stored(const soar_stored_desc &d, bool recon)
 {
@@ -1021,7 +1021,7 @@ int32_t stored_group_end(int32_t n, const soar_stored_desc *descs, int32_t i)
 {
     int64_t bytes = 0;
     int32_t j = i;
-    while (j < n && j - i < kGroupMax && descs[j].dtype == descs[i].dtype) {
+    while (j < n && j - i < kStoredMax && descs[j].dtype == descs[i].dtype) {
         const int64_t b = descs[j].rows * descs[j].cols * (descs[j].dtype == SOAR_BF16 ? 2 : 4);
         if (j > i && bytes + b > kStoredByteCap) break;
         bytes += b;
