@@ -1290,6 +1290,12 @@ static int32_t mx_group_end(int32_t n, const soar_mx_tensor_desc *descs, int32_t
     return j;
 }
 
+// Whether the launch groups of a call alternate between two streams.  Forking and joining them costs 10 us, the overlap of a group's tail
+// with the next one's ramp gives a few us a group.  Two streams / one, bf16 unless said: two groups 33 / 21.4 us (two layers of hidden 512),
+// 41.6 / 33 (1024), 80 / 73 (2048); four groups 79 / 87 (four layers of hidden 1024 in fp32, 4600 tiles), 146 / 156 (2048).
+constexpr int64_t kMxLaneTiles = 2048;
+static bool mx_two_lanes(int32_t groups, int64_t tiles) { return groups > 2 && tiles >= kMxLaneTiles; }
+
 static int32_t mx_group_count(int32_t n, const soar_mx_tensor_desc *descs)
 {
     int32_t groups = 0;
@@ -1319,7 +1325,9 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
     const int32_t groups = mx_group_count(n, descs);
     const int ws_lanes = groups > 1 ? kLanes : 1;
     if (workspace_bytes < (size_t)ws_lanes * slots * kSlotBytes) return SOAR_ERR_WORKSPACE;
-    const int lanes = (groups > 1 && params->streams != 1) ? kLanes : 1;
+    int64_t all_tiles = 0;
+    for (int32_t k = 0; k < n; ++k) all_tiles += (descs[k].rows * (descs[k].cols / 32) + kWG - 1) / kWG;
+    const int lanes = (params->streams != 1 && mx_two_lanes(groups, all_tiles)) ? kLanes : 1;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     char *base = static_cast<char *>(d_workspace);
     // launch groups alternate between the caller's stream and one internal stream (forked and joined with

@@ -1,4 +1,5 @@
-"""Batches of stored tensors, around the number that shares a launch: every tensor as when it is handed over alone."""
+"""Batches of stored tensors, around the number that shares a launch, and MXFP4 batches around the numbers of groups and tiles from which
+they use two streams: every tensor as when it is handed over alone."""
 import pytest
 import torch
 
@@ -25,3 +26,20 @@ def test_stored_batches_equal_every_tensor_alone(n, dtype):
         assert torch.equal(mx_backs[k], B.mx_dequantize(mx[k], dtype)), k
         assert abs(sums[k].item() - qs[k].sse.item()) <= 1e-12 * qs[k].sse.item(), k
 
+
+# groups of eight: two, three below 2048 tiles, three from there on
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,rows", [(9, 40), (16, 70000), (17, 30000), (17, 40000), (24, 22000)], ids=str)
+def test_mx_batches_on_one_and_two_streams(n, rows):
+    ws = weights_of(n, torch.bfloat16, lambda k: rows // (1 + k % 3) + k)
+    outs = [B.mx_new_outputs(w.shape[0], w.shape[1], DEV) for w in ws]
+    descs = [B.mx_make_desc(w, o) for w, o in zip(ws, outs)]
+    p = B.soar_mx_default_params(n_beta=11)
+    for turn in range(2):
+        B.mx_quantize_batch(descs, p)
+        torch.cuda.synchronize()
+        for k, (w, o) in enumerate(zip(ws, outs)):
+            one = B.mx_quantize(w, p)
+            for f in ("codes", "scales", "sse", "status"):
+                assert torch.equal(getattr(o, f), getattr(one, f)), (turn, k, f)
+            o.codes.fill_(0)
