@@ -1030,6 +1030,17 @@ int32_t stored_group_end(int32_t n, const soar_stored_desc *descs, int32_t i)
     return j;
 }
 
+// a launch with kernel arguments of the size that it needs
+template <typename Launch>
+void launch_stored(const StoredBatch<kStoredMax> &b, Launch launch)
+{
+    if (b.n > (uint32_t)kStoredFew) return launch(b);
+    StoredBatch<kStoredFew> few;
+    std::memcpy(few.t, b.t, sizeof(few.t));
+    few.n = b.n;
+    launch(few);
+}
+
 soar_status run_stored_batch(int32_t n, const soar_stored_desc *descs, bool recon, hipStream_t st)
 {
     if (n < 0) return SOAR_ERR_SHAPE;
@@ -1050,7 +1061,7 @@ soar_status run_stored_batch(int32_t n, const soar_stored_desc *descs, bool reco
     }
     for (int32_t i = 0; i < n;) {
         const int32_t j = stored_group_end(n, descs, i);
-        StoredBatch b;
+        StoredBatch<kStoredMax> b;
         std::memset(&b, 0, sizeof(b));
         b.n = (uint32_t)(j - i);
         uint32_t wg = 0;
@@ -1071,13 +1082,16 @@ soar_status run_stored_batch(int32_t n, const soar_stored_desc *descs, bool reco
         }
         const bool bf16 = descs[i].dtype == SOAR_BF16;
         ScopedTimer tm(recon ? SOAR_KERNEL_RECON : SOAR_KERNEL_DEQUANT, st);
-        if (recon) {
-            if (bf16) hipLaunchKernelGGL(k_recon<SOAR_BF16>, dim3(wg), dim3(kReconWG), 0, st, b);
-            else hipLaunchKernelGGL(k_recon<SOAR_FP32>, dim3(wg), dim3(kReconWG), 0, st, b);
-        } else {
-            if (bf16) hipLaunchKernelGGL(k_dequant<SOAR_BF16>, dim3(wg), dim3(kWG), 0, st, b);
-            else hipLaunchKernelGGL(k_dequant<SOAR_FP32>, dim3(wg), dim3(kWG), 0, st, b);
-        }
+        launch_stored(b, [&](const auto &args) {
+            constexpr int kMax = sizeof(args.t) / sizeof(args.t[0]);
+            if (recon) {
+                if (bf16) hipLaunchKernelGGL((k_recon<SOAR_BF16, kMax>), dim3(wg), dim3(kReconWG), 0, st, args);
+                else hipLaunchKernelGGL((k_recon<SOAR_FP32, kMax>), dim3(wg), dim3(kReconWG), 0, st, args);
+            } else {
+                if (bf16) hipLaunchKernelGGL((k_dequant<SOAR_BF16, kMax>), dim3(wg), dim3(kWG), 0, st, args);
+                else hipLaunchKernelGGL((k_dequant<SOAR_FP32, kMax>), dim3(wg), dim3(kWG), 0, st, args);
+            }
+        });
         SOAR_LAUNCH_CHECK();
         i = j;
     }
@@ -1461,7 +1475,7 @@ soar_status soar_mxfp4_dequantize_batch(int32_t n, const soar_stored_desc *descs
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     for (int32_t i = 0; i < n;) {
         const int32_t j = stored_group_end(n, descs, i);
-        StoredBatch b;
+        StoredBatch<kStoredMax> b;
         std::memset(&b, 0, sizeof(b));
         b.n = (uint32_t)(j - i);
         uint32_t wg = 0;
@@ -1478,8 +1492,11 @@ soar_status soar_mxfp4_dequantize_batch(int32_t n, const soar_stored_desc *descs
             wg += t.n_wg;
         }
         ScopedTimer tm(SOAR_KERNEL_DEQUANT, st);
-        if (descs[i].dtype == SOAR_BF16) hipLaunchKernelGGL(k_mx_dequant<SOAR_BF16>, dim3(wg), dim3(kWG), 0, st, b);
-        else hipLaunchKernelGGL(k_mx_dequant<SOAR_FP32>, dim3(wg), dim3(kWG), 0, st, b);
+        launch_stored(b, [&](const auto &args) {
+            constexpr int kMax = sizeof(args.t) / sizeof(args.t[0]);
+            if (descs[i].dtype == SOAR_BF16) hipLaunchKernelGGL((k_mx_dequant<SOAR_BF16, kMax>), dim3(wg), dim3(kWG), 0, st, args);
+            else hipLaunchKernelGGL((k_mx_dequant<SOAR_FP32, kMax>), dim3(wg), dim3(kWG), 0, st, args);
+        });
         SOAR_LAUNCH_CHECK();
         i = j;
     }

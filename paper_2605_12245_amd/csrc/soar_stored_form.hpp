@@ -23,29 +23,33 @@ struct StoredTask {
     uint32_t wg_begin, n_wg;
 };
 
+// MAX: kStoredMax, or kStoredFew where that holds the launch (a sixth of the kernel arguments)
+constexpr int kStoredFew = 8;
+template <int MAX>
 struct StoredBatch {
-    StoredTask t[kStoredMax];
+    StoredTask t[MAX];
     uint32_t n;
 };
-static_assert(sizeof(StoredBatch) <= 4096, "kernel arguments");
+static_assert(sizeof(StoredBatch<kStoredMax>) <= 4096, "kernel arguments");
 
 // the last tensor that begins at or before this workgroup, by halving: scalar loads (one of all beginnings at once, a tensor per
 // lane, is a trip to memory that every one of these short workgroups waits for: a decoder layer 81.5 -> 86.6 us)
-__device__ __forceinline__ uint32_t find_task(const StoredBatch &b, uint32_t &lwg)
+template <int MAX>
+__device__ __forceinline__ uint32_t find_task(const StoredBatch<MAX> &b, uint32_t &lwg)
 {
-    static_assert(kStoredMax <= 64, "six halvings");
+    static_assert(MAX == kStoredFew || (MAX > 32 && MAX <= 64), "three halvings, or six");
     const uint32_t id = blockIdx.x;
     uint32_t k = 0;
 #pragma unroll
-    for (uint32_t step = 32; step > 0; step >>= 1)
+    for (uint32_t step = MAX == kStoredFew ? 4 : 32; step > 0; step >>= 1)
         if (k + step < b.n && id >= b.t[k + step].wg_begin) k += step;
     lwg = id - b.t[k].wg_begin;
     return k;
 }
 
 // Eq. 3
-template <int DT>
-__global__ __launch_bounds__(kWG) void k_dequant(const StoredBatch batch)
+template <int DT, int MAX>
+__global__ __launch_bounds__(kWG) void k_dequant(const StoredBatch<MAX> batch)
 {
     constexpr int kP = pieces_per_block<DT, 16>();
     __shared__ u32x4 s_x[kWG * kP];                    // store_wave_blocks: one region per wave
@@ -95,8 +99,8 @@ __global__ __launch_bounds__(kWG) void k_dequant(const StoredBatch batch)
 }
 
 // MXFP4: w^ = q * 2^(e-127) per block of 32 (bpr counts blocks of 32; gscale is unused)
-template <int DT>
-__global__ __launch_bounds__(kWG) void k_mx_dequant(const StoredBatch batch)
+template <int DT, int MAX>
+__global__ __launch_bounds__(kWG) void k_mx_dequant(const StoredBatch<MAX> batch)
 {
     constexpr int kP = pieces_per_block<DT, 32>();
     __shared__ u32x4 s_x[kWG * kP];                    // store_wave_blocks: one region per wave
@@ -177,8 +181,8 @@ __global__ __launch_bounds__(kZeroMax) void k_zero_sums(const ZeroBatch batch)
 // kReconGrid per tensor.
 constexpr int kReconWG = 1024;
 constexpr uint32_t kReconGrid = 256;      // 512: 5 % slower on the full-model workload, 8 % on 448 MiB tensors; 64-128: as 256
-template <int DT>
-__global__ __launch_bounds__(kReconWG) void k_recon(const StoredBatch batch)
+template <int DT, int MAX>
+__global__ __launch_bounds__(kReconWG) void k_recon(const StoredBatch<MAX> batch)
 {
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
     constexpr int kP = pieces_per_block<DT, 16>();
