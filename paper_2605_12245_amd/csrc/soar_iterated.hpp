@@ -702,7 +702,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5
     __shared__ uint32_t s_last;
     double *s_tree = reinterpret_cast<double *>(s_blocks);      // trees_of_partials, after the last group
     constexpr bool kAhead = DT == SOAR_BF16;
-    __shared__ u32x4 s_next[kAhead ? kWG * BlockStream<DT>::kP : 1];
+    __shared__ u32x4 s_next[kAhead ? kWG * BlockStream::kP : 1];
     extern __shared__ __align__(16) unsigned char s_dyn[];      // the factor table, n_beta floats
     float *s_beta = reinterpret_cast<float *>(s_dyn);
 
@@ -727,7 +727,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5
     StagedTree<> tree{s_blocks, s_wave, s_stack};
     const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
     const uint32_t blocks = amax_bits < 0x7F800000u ? t.nblk : 0u;
-    const BlockStream<DT> stream{s_next + (kAhead ? (tid >> 6) * (64 * BlockStream<DT>::kP) : 0u)};
+    const BlockStream stream{s_next + (kAhead ? (tid >> 6) * (64 * BlockStream::kP) : 0u)};
     float next_rho = 0.0f;
     auto fetch = [&](uint32_t tile) {
         const uint32_t i = tile * kWG + tid;
