@@ -887,13 +887,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const uint32_t tid = threadIdx.x;
     const uint32_t amax_bits = t.ctrl->amax_bits;
     if (amax_bits == 0u || amax_bits >= 0x7F800000u) return;    // finished by the first iteration
-    if (tid == 0) s_stopped = get(&t.ctrl->stopped);
-    __syncthreads();
-    if (s_stopped) return;
     RestWords &rest = rest_words(t);
     const bool dss_only = batch.arm == SOAR_METHOD_DSS_ONLY;
-    if constexpr (KIND != Iterate::CLOSED_FORM)
-        for (int k = (int)tid; k < batch.n_beta; k += kWG) s_beta[k] = beta_factor(k, batch.n_beta, batch.beta_lo, batch.beta_hi);
     JointSearch js{{s_beta, batch.n_beta, batch.beta_lo, batch.index_per_beta}, 0.0f, 0.0f, batch.radius,
                    batch.dd_mode == SOAR_DD_BRACKET, dss_only, false, batch.full_search != 0 || batch.n_beta < kChangesMinBeta};
 
@@ -906,9 +901,12 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             s_alpha = get(&t.ctrl->alpha1);
         }
         __syncthreads();
-        if (s_stopped) return;
+        if (s_stopped) return;             // lane 0 writes it again only behind the barriers below
         // of this iteration, or of a later one if this one has been finished meanwhile: then no share of it is left
         const float alpha = s_alpha;
+        if constexpr (KIND != Iterate::CLOSED_FORM)
+            if (it == batch.iter_t)
+                for (int k = (int)tid; k < batch.n_beta; k += kWG) s_beta[k] = beta_factor(k, batch.n_beta, batch.beta_lo, batch.beta_hi);
         js.set_alpha(alpha, amax_bits);
         for (;;) {
             if (tid == 0) s_share = __hip_atomic_fetch_add(&rest.shares[it][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

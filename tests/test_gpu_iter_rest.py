@@ -104,3 +104,41 @@ def test_rest_beside_degenerate_and_stopped_tensors_and_in_a_graph():
         g.replay()
         check(turn)
         torch.ones(1 << 16, device=DEV).sum().item()
+
+
+def without_stopping(w, p, rel):
+    """what a launch per iteration gives (no early stop, as many iterations as the trace says): outputs, and how many those are"""
+    q = B.soar_params.from_buffer_copy(p)
+    q.early_stop_rel, q.resident = 0.0, B.SOAR_RESIDENT_NEVER
+    t = B.quantize_iter(w, q).sse_trace.cpu().tolist()
+    run = next((k for k in range(1, p.iters + 1) if t[k - 1] - t[k] < np.float32(rel) * t[k - 1]), p.iters)
+    q.iters = run
+    return B.quantize_iter(w, q), run
+
+
+# a tensor that stops inside the shared launch while workgroups of it still arrive: 1992 and 1329 shares of one tile ("every pair"), as many
+# shares as places otherwise; against one launch per iteration
+@pytest.mark.gpu
+@pytest.mark.parametrize("arm", ["paper", "every pair", "closed"])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
+def test_rest_stops_while_workgroups_arrive(dtype, arm):
+    p = params(arm)
+    p.resident = B.SOAR_RESIDENT_NEVER
+    ws = weights_of((170000, 113400, 900), dtype, 5)
+    probe = B.quantize_iter(ws[0], p).sse_trace.cpu().tolist()
+    for at in (5, 6, 8):                                     # a relative gain between those of two iterations: stops at the later one
+        gains = [(probe[k - 1] - probe[k]) / probe[k - 1] for k in range(1, p.iters + 1) if probe[k] == probe[k]]
+        rel = gains[at - 1] * 1.001
+        p.early_stop_rel = rel
+        outs, descs = outputs(ws, p)
+        B.quantize_batch(descs, p, B.new_batch_workspace(descs, p, DEV))
+        torch.cuda.synchronize()
+        runs = []
+        for k, (w, o) in enumerate(zip(ws, outs)):
+            want, run = without_stopping(w, p, rel)
+            runs.append(run)
+            assert int(o.iters_run.item()) == run, (at, k)
+            for f in ("codes", "scales", "global_scale", "status", "sse"):
+                assert torch.equal(getattr(o, f), getattr(want, f)), (at, k, f)
+            assert torch.equal(o.sse_trace[:run + 1], want.sse_trace[:run + 1]), (at, k)
+        assert 4 < runs[0] <= at
