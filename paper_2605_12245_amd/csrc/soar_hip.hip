@@ -38,6 +38,7 @@
 #include <vector>
 
 #include "soar.h"
+#include "soar_turn.hpp"
 #include "soar_device.hpp"
 #include "soar_single_step.hpp"
 #include "soar_iterated.hpp"
@@ -154,39 +155,30 @@ bool resident_batch_plan(int32_t n, const soar_tensor_desc *descs, int cu, Resid
     return false;
 }
 
-// Two one-launch kernels that start at the same time on two streams can each take part of the compute
-// units and then wait for the rest in vain (until the bounded wait gives up).  Calls on one stream are
-// ordered by the stream.  For calls that arrive on a different stream than the one-launch kernel before
-// them, this asks whether that earlier stream has drained; if it has not (or the question cannot be asked:
-// either stream is being captured into a graph), the caller takes the three-pass path for this call.
-// Best effort: replays of captured graphs and other processes on the same GPU are not seen here; the
-// bounded wait and SOAR_STATUS_GAVE_UP cover those.
-bool resident_may_start(hipStream_t st)
-{
-    static std::mutex mu[kMaxDevices];
-    static hipStream_t last[kMaxDevices] = {};
-    static bool have_last[kMaxDevices] = {};
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return false;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) return false;
-    if (cap != hipStreamCaptureStatusNone) return true;      // recorded, not started: nothing to track
-    std::lock_guard<std::mutex> lock(mu[dev]);
-    if (have_last[dev] && last[dev] != st) {
-        hipStreamCaptureStatus cap_last = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(last[dev], &cap_last) == hipSuccess) {
-            if (cap_last != hipStreamCaptureStatusNone) return false;     // a query would break that capture
-            const hipError_t q = hipStreamQuery(last[dev]);
-            if (q == hipErrorNotReady) return false;          // may still be running: do not start beside it
-            if (q != hipSuccess) (void)hipGetLastError();
-        } else {
-            (void)hipGetLastError();                          // a stream that no longer exists has nothing in flight
-        }
+struct HipStreams {
+    using Stream = hipStream_t;
+    static constexpr int kMaxDevices = ::kMaxDevices;
+    static int device()
+    {
+        int dev = -1;
+        return hipGetDevice(&dev) == hipSuccess ? dev : -1;
     }
-    last[dev] = st;
-    have_last[dev] = true;
-    return true;
-}
+    static int capturing(hipStream_t st)
+    {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+            (void)hipGetLastError();       // the question's error, not one of the launches that follow
+            return -1;
+        }
+        return cap != hipStreamCaptureStatusNone ? 1 : 0;
+    }
+    static bool busy(hipStream_t st)
+    {
+        const hipError_t q = hipStreamQuery(st);
+        if (q != hipSuccess && q != hipErrorNotReady) (void)hipGetLastError();
+        return q == hipErrorNotReady;
+    }
+};
 
 template <int DT, int METHOD>
 void launch_resident(const ResidentPlan &plan, const Task &t, const ResidentArgs &a, hipStream_t st)
@@ -230,15 +222,8 @@ bool iter_resident_plan(int64_t nblk, int cu, int ncand, ResidentPlan &plan)
     return 8 * (int64_t)plan.G >= eighths * wgs;
 }
 
-bool being_captured(hipStream_t st)
-{
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-        (void)hipGetLastError();       // the question's error, not one of the launches that follow
-        return true;
-    }
-    return cap != hipStreamCaptureStatusNone;
-}
+// (a stream that cannot be asked counts as one)
+bool being_captured(hipStream_t st) { return HipStreams::capturing(st) != 0; }
 
 template <int DT>
 void launch_iter_resident(const ResidentPlan &plan, const Task &t, const IterResidentArgs &a, hipStream_t st)
@@ -765,10 +750,11 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
     // one tensor, single-step settings, default launch shape: the whole path in one launch that keeps the
     // tensor in registers, if its grid fits the GPU (see k_resident); only the slot's flag words are used
     ResidentPlan plan;
+    ResidentTurn<HipStreams> turn;
     if (n == 1 && !iterated && !descs[0].d_amax_in && params->tiles_per_wg == 0 && params->tiles_per_wg_absmax == 0 &&
         params->tiles_per_wg_search == 0 && params->resident == SOAR_RESIDENT_AUTO &&
         resident_plan(descs[0].rows * (descs[0].cols / 16), device_facts().compute_units, plan) &&
-        (plan.G == 1 || resident_may_start(st))) {
+        (plan.G == 1 || turn.take(st))) {
         const soar_tensor_desc &d = descs[0];
         const Task t = single_task(d, d_workspace);
         const ResidentArgs a = resident_args(params);
@@ -791,7 +777,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
     for (int32_t k = 1; k < n; ++k) one_dtype = one_dtype && descs[k].dtype == descs[0].dtype;
     if (n > 1 && n <= kResidentTensors && one_dtype && !iterated && params->method == SOAR_METHOD_SOAR && params->tiles_per_wg == 0 &&
         params->tiles_per_wg_absmax == 0 && params->tiles_per_wg_search == 0 && params->resident == SOAR_RESIDENT_AUTO &&
-        resident_batch_plan(n, descs, device_facts().compute_units, plan) && !being_captured(st) && resident_may_start(st)) {
+        resident_batch_plan(n, descs, device_facts().compute_units, plan) && !being_captured(st) && turn.take(st)) {
         ResidentBatch b;
         std::memset(&b, 0, sizeof(b));
         b.slots = static_cast<char *>(d_workspace);
@@ -854,7 +840,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         (params->method == SOAR_METHOD_CJSO_ONLY || (nearest && params->n_beta <= kIterResMaxBeta)) &&
         iter_resident_plan(descs[0].rows * (descs[0].cols / 16), device_facts().compute_units,
                            params->dd_mode == SOAR_DD_BRACKET ? 2 : 2 * params->dss_radius + 1, plan) && !being_captured(st) &&
-        (plan.G == 1 || resident_may_start(st))) {
+        (plan.G == 1 || turn.take(st))) {
         const soar_tensor_desc &d = descs[0];
         Task t = single_task(d, d_workspace);
         t.iters_run = d.d_iters_run;
