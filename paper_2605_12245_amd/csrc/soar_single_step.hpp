@@ -988,7 +988,10 @@ __global__ __launch_bounds__(L) void k_resident_batch(const ResidentBatch batch)
     t.nblk = x.nblk;
     t.contiguous = x.ld == (int64_t)x.bpr * 16 ? 1u : 0u;
     t.ctrl = nullptr;
-    if (resident_body<DT, SOAR_METHOD_SOAR, L, R, true>(t, batch.r, &words.cross, blockIdx.x - x.wg_begin, x.n_wg, batch.later_ticks)) return;
+    const bool finished = resident_body<DT, SOAR_METHOD_SOAR, L, R, true>(t, batch.r, &words.cross, blockIdx.x - x.wg_begin, x.n_wg, batch.later_ticks);
+    // One value for the workgroup, and nothing that is carried past this point: otherwise the code below comes to lie between a lane's
+    // blocks and their search and takes registers of theirs to scratch memory.
+    if (__builtin_amdgcn_readfirstlane(finished ? 1 : 0) != 0) return;
     // given up, here or elsewhere, before any output was written: the last one to leave does the tensor
     __syncthreads();
     if (threadIdx.x == 0) s_last = count_out(&words.left, batch.r.nonce) == x.n_wg ? 1u : 0u;

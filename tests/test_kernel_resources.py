@@ -1,0 +1,35 @@
+"""What the built kernels take of the machine, from the notes that the compiler leaves in the library: no register of theirs is kept in
+scratch memory, and those whose speed rests on how many of their waves run at a time leave room for them."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2605_12245_amd import build
+
+LLVM = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(build.HIPCC))), "lib", "llvm", "bin")
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """name -> notes of every kernel"""
+    at = tmp_path_factory.mktemp("notes")
+    run = lambda *cmd: subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True).stdout
+    run("objcopy", "-O", "binary", "--only-section=.hip_fatbin", build.OUT, str(at / "fatbin"))
+    run(f"{LLVM}/clang-offload-bundler", "--unbundle", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={at}/fatbin",
+        f"--output={at}/code")
+    notes = run(f"{LLVM}/llvm-readelf", "--notes", str(at / "code"))
+    found = {}
+    for entry in notes.split("  - .agpr_count:")[1:]:
+        name = run("c++filt", re.search(r"\.name:\s+(\S+)", entry)[1]).strip()
+        name = re.sub(r"^void |\(anonymous namespace\)::", "", name)
+        found[name[:name.rindex("(")]] = {k: int(v) for k, v in re.findall(r"\.(\w+):\s+(\d+)\s", entry)}
+    assert len(found) > 40
+    return found
+
+
+def test_no_register_of_a_batch_kernel_lies_in_scratch_memory(kernels):
+    batch = {k: v for k, v in kernels.items() if k.startswith("k_resident_batch<")}
+    assert len(batch) == 8
+    assert not {k: v for k, v in batch.items() if v["vgpr_spill_count"] or v["private_segment_fixed_size"]}
