@@ -15,7 +15,8 @@
  *     owns, per GPU and until the process ends: the fixed array inside its device
  *     image that soar_quantize_static uses, four diagnostic counters, and -- created
  *     by the first batch call that is spread over two streams (see `streams`) -- one
- *     internal stream of default priority with two events;
+ *     internal stream of default priority with two events; and an event that the first
+ *     one-launch kernel (see `resident`) on a stream other than the default one brings;
  *   - work is enqueued on `hip_stream` (a hipStream_t passed as void*, NULL =
  *     the default stream) and the call returns without synchronising; results
  *     (global scale, error, data-dependent status) stay in device memory;
@@ -253,7 +254,8 @@ soar_status soar_quantize(const void *d_w, soar_dtype dtype, int64_t rows, int64
  * the workspace: the control words and the 4 bytes per block come from a fixed array inside the
  * library's device image (SOAR_STATIC_MAX_BLOCKS blocks, about 19 MiB on every GPU the library
  * runs on, held until the process ends).  The call allocates and frees nothing -- no device
- * memory, no stream, no event (per-kernel timing is not recorded for it).
+ * memory, no stream, no event (per-kernel timing is not recorded for it; on a stream other than the
+ * default one it takes one launch only once another entry point has brought the event for it).
  *   - rows * cols / 16 > SOAR_STATIC_MAX_BLOCKS returns SOAR_ERR_TOO_LARGE before anything is
  *     enqueued;
  *   - all calls on one GPU share that array, which keeps the previous call's contents (the

@@ -29,6 +29,7 @@
 // float operation below is a separate IEEE binary32 operation unless written as
 // __builtin_fmaf, divisions are correctly rounded, subnormals are kept.
 #include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
 
 #include <cstdint>
 #include <atomic>
@@ -155,8 +156,11 @@ bool resident_batch_plan(int32_t n, const soar_tensor_desc *descs, int cu, Resid
     return false;
 }
 
+thread_local bool t_no_events = false;            // set while an entry point that must not create events runs
+
 struct HipStreams {
     using Stream = hipStream_t;
+    using Event = hipEvent_t;
     static constexpr int kMaxDevices = ::kMaxDevices;
     static int device()
     {
@@ -178,26 +182,50 @@ struct HipStreams {
         if (q != hipSuccess && q != hipErrorNotReady) (void)hipGetLastError();
         return q == hipErrorNotReady;
     }
+    static bool always_there(hipStream_t st) { return st == nullptr; }
+    static bool one_per_thread(hipStream_t st) { return st == hipStreamPerThread; }
+    static bool make_event(hipEvent_t &ev)
+    {
+        if (t_no_events) return false;
+        if (hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess) return true;
+        (void)hipGetLastError();
+        ev = nullptr;
+        return false;
+    }
+    static bool has_happened(hipEvent_t ev)
+    {
+        const hipError_t q = hipEventQuery(ev);
+        if (q != hipSuccess && q != hipErrorNotReady) (void)hipGetLastError();
+        return q == hipSuccess;
+    }
 };
 
+// a launch that completes `done`, if there is one
+template <typename Kernel, typename... Args>
+void launch_and_mark(Kernel kernel, dim3 grid, int lanes, hipStream_t st, hipEvent_t done, const Args &...args)
+{
+    if (done) hipExtLaunchKernelGGL(kernel, grid, dim3(lanes), 0, st, nullptr, done, 0, args...);
+    else hipLaunchKernelGGL(kernel, grid, dim3(lanes), 0, st, args...);
+}
+
 template <int DT, int METHOD>
-void launch_resident(const ResidentPlan &plan, const Task &t, const ResidentArgs &a, hipStream_t st)
+void launch_resident(const ResidentPlan &plan, const Task &t, const ResidentArgs &a, hipStream_t st, hipEvent_t done)
 {
     const dim3 grid(plan.G);
-    if (plan.L == 256) hipLaunchKernelGGL((k_resident<DT, METHOD, 256, 1>), grid, dim3(256), 0, st, t, a);
-    else if (plan.R == 1) hipLaunchKernelGGL((k_resident<DT, METHOD, 1024, 1>), grid, dim3(1024), 0, st, t, a);
-    else if (plan.R == 2) hipLaunchKernelGGL((k_resident<DT, METHOD, 1024, 2>), grid, dim3(1024), 0, st, t, a);
-    else hipLaunchKernelGGL((k_resident<DT, METHOD, 1024, 4>), grid, dim3(1024), 0, st, t, a);
+    if (plan.L == 256) launch_and_mark((k_resident<DT, METHOD, 256, 1>), grid, 256, st, done, t, a);
+    else if (plan.R == 1) launch_and_mark((k_resident<DT, METHOD, 1024, 1>), grid, 1024, st, done, t, a);
+    else if (plan.R == 2) launch_and_mark((k_resident<DT, METHOD, 1024, 2>), grid, 1024, st, done, t, a);
+    else launch_and_mark((k_resident<DT, METHOD, 1024, 4>), grid, 1024, st, done, t, a);
 }
 
 template <int DT>
-void launch_resident_batch(const ResidentPlan &plan, const ResidentBatch &b, hipStream_t st)
+void launch_resident_batch(const ResidentPlan &plan, const ResidentBatch &b, hipStream_t st, hipEvent_t done)
 {
     const dim3 grid(plan.G);
-    if (plan.L == 256) hipLaunchKernelGGL((k_resident_batch<DT, 256, 1>), grid, dim3(256), 0, st, b);
-    else if (plan.R == 1) hipLaunchKernelGGL((k_resident_batch<DT, 1024, 1>), grid, dim3(1024), 0, st, b);
-    else if (plan.R == 2) hipLaunchKernelGGL((k_resident_batch<DT, 1024, 2>), grid, dim3(1024), 0, st, b);
-    else hipLaunchKernelGGL((k_resident_batch<DT, 1024, 4>), grid, dim3(1024), 0, st, b);
+    if (plan.L == 256) launch_and_mark((k_resident_batch<DT, 256, 1>), grid, 256, st, done, b);
+    else if (plan.R == 1) launch_and_mark((k_resident_batch<DT, 1024, 1>), grid, 1024, st, done, b);
+    else if (plan.R == 2) launch_and_mark((k_resident_batch<DT, 1024, 2>), grid, 1024, st, done, b);
+    else launch_and_mark((k_resident_batch<DT, 1024, 4>), grid, 1024, st, done, b);
 }
 
 // The same for the iterated path (k_iter_resident).  A power of two tiles per workgroup can leave compute units
@@ -226,17 +254,15 @@ bool iter_resident_plan(int64_t nblk, int cu, int ncand, ResidentPlan &plan)
 bool being_captured(hipStream_t st) { return HipStreams::capturing(st) != 0; }
 
 template <int DT>
-void launch_iter_resident(const ResidentPlan &plan, const Task &t, const IterResidentArgs &a, hipStream_t st)
+void launch_iter_resident(const ResidentPlan &plan, const Task &t, const IterResidentArgs &a, hipStream_t st, hipEvent_t done)
 {
     const dim3 grid(plan.G);
     const bool closed = a.arm == SOAR_METHOD_CJSO_ONLY;
-    if (plan.L == 256 && closed) hipLaunchKernelGGL((k_iter_resident<DT, 256, true>), grid, dim3(256), 0, st, t, a);
-    else if (plan.L == 256) hipLaunchKernelGGL((k_iter_resident<DT, 256, false>), grid, dim3(256), 0, st, t, a);
-    else if (closed) hipLaunchKernelGGL((k_iter_resident<DT, 1024, true>), grid, dim3(1024), 0, st, t, a);
-    else hipLaunchKernelGGL((k_iter_resident<DT, 1024, false>), grid, dim3(1024), 0, st, t, a);
+    if (plan.L == 256 && closed) launch_and_mark((k_iter_resident<DT, 256, true>), grid, 256, st, done, t, a);
+    else if (plan.L == 256) launch_and_mark((k_iter_resident<DT, 256, false>), grid, 256, st, done, t, a);
+    else if (closed) launch_and_mark((k_iter_resident<DT, 1024, true>), grid, 1024, st, done, t, a);
+    else launch_and_mark((k_iter_resident<DT, 1024, false>), grid, 1024, st, done, t, a);
 }
-
-thread_local bool t_no_event_timing = false;      // set while an entry point that must not create events runs
 
 struct Timing {
     bool enabled = false;
@@ -250,7 +276,7 @@ struct ScopedTimer {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     ScopedTimer(int id_, hipStream_t st_) : id(id_), st(st_)
     {
-        if (!g_timing.enabled || t_no_event_timing) return;
+        if (!g_timing.enabled || t_no_events) return;
         // timing only: no system-scope fence (cache write-back and invalidation) with the record, which would be
         // charged to the kernel between the two events and to the one after
         if (hipEventCreateWithFlags(&e0, hipEventDisableSystemFence) != hipSuccess ||
@@ -761,11 +787,11 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         const bool rtn = params->method == SOAR_METHOD_RTN;
         ScopedTimer tm(SOAR_KERNEL_RESIDENT, st);
         if (d.dtype == SOAR_BF16) {
-            if (rtn) launch_resident<SOAR_BF16, SOAR_METHOD_RTN>(plan, t, a, st);
-            else launch_resident<SOAR_BF16, SOAR_METHOD_SOAR>(plan, t, a, st);
+            if (rtn) launch_resident<SOAR_BF16, SOAR_METHOD_RTN>(plan, t, a, st, turn.done());
+            else launch_resident<SOAR_BF16, SOAR_METHOD_SOAR>(plan, t, a, st, turn.done());
         } else {
-            if (rtn) launch_resident<SOAR_FP32, SOAR_METHOD_RTN>(plan, t, a, st);
-            else launch_resident<SOAR_FP32, SOAR_METHOD_SOAR>(plan, t, a, st);
+            if (rtn) launch_resident<SOAR_FP32, SOAR_METHOD_RTN>(plan, t, a, st, turn.done());
+            else launch_resident<SOAR_FP32, SOAR_METHOD_SOAR>(plan, t, a, st, turn.done());
         }
         SOAR_LAUNCH_CHECK();
         return SOAR_OK;
@@ -804,8 +830,8 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
             wg += t.n_wg;
         }
         ScopedTimer tm(SOAR_KERNEL_RESIDENT, st);
-        if (descs[0].dtype == SOAR_BF16) launch_resident_batch<SOAR_BF16>(plan, b, st);
-        else launch_resident_batch<SOAR_FP32>(plan, b, st);
+        if (descs[0].dtype == SOAR_BF16) launch_resident_batch<SOAR_BF16>(plan, b, st, turn.done());
+        else launch_resident_batch<SOAR_FP32>(plan, b, st, turn.done());
         SOAR_LAUNCH_CHECK();
         return SOAR_OK;
     }
@@ -860,8 +886,8 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         a.tell = params->resident_wait_us > 0 ? (uint32_t)SOAR_STATUS_GAVE_UP : 0u;
         a.later_ticks = later_ticks(a.r);
         ScopedTimer tm(SOAR_KERNEL_RESIDENT, st);
-        if (d.dtype == SOAR_BF16) launch_iter_resident<SOAR_BF16>(plan, t, a, st);
-        else launch_iter_resident<SOAR_FP32>(plan, t, a, st);
+        if (d.dtype == SOAR_BF16) launch_iter_resident<SOAR_BF16>(plan, t, a, st, turn.done());
+        else launch_iter_resident<SOAR_FP32>(plan, t, a, st, turn.done());
         SOAR_LAUNCH_CHECK();
         return SOAR_OK;
     }
@@ -1185,9 +1211,9 @@ soar_status soar_quantize_static(const void *d_w, soar_dtype dtype, int64_t rows
     if (rows * (cols / 16) > kStaticMaxBlocks) return SOAR_ERR_TOO_LARGE;
     void *ws = static_scratch_address();
     if (!ws) return SOAR_ERR_HIP;
-    t_no_event_timing = true;
+    t_no_events = true;
     s = run_batch(1, &d, params, ws, kStaticScratchBytes, static_cast<hipStream_t>(hip_stream));
-    t_no_event_timing = false;
+    t_no_events = false;
     return s;
 }
 

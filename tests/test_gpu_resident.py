@@ -5,6 +5,7 @@ one ragged), both element types, both methods; on workspaces holding anything; r
 tensors of changing size; and its bounded wait, forced to give up from the host with a tiny limit (every
 workgroup then leaves by itself: nothing hangs).
 Bar: codes and scale bytes bit-exact, global scale bit-identical, error within 1e-6 relative."""
+import ctypes
 import math
 
 import numpy as np
@@ -240,3 +241,40 @@ def test_two_streams_at_once():
             same_bytes(o, ra, f"stream a, repetition {rep}")
         for o in ob:
             same_bytes(o, rb, f"stream b, repetition {rep}")
+
+
+def test_a_stream_that_is_gone_and_a_capture_on_another():
+    """after a call on a stream of the program's own that has been destroyed since, and while another stream is being captured"""
+    p = params()
+    w = heavy(1023, 4096, 41, torch.bfloat16)
+    want = run(w, params(resident=B.SOAR_RESIDENT_NEVER))
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL("libamdhip64.so")
+    own = ctypes.c_void_p()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(own), 1) == 0            # hipStreamNonBlocking
+    with torch.cuda.stream(torch.cuda.ExternalStream(own.value)):
+        on_own = run(w, p)
+    torch.cuda.synchronize()
+    assert hip.hipStreamDestroy(own) == 0
+    same_bytes(on_own, want, "a stream of the program's own")
+    same_bytes(run(w, p), want, "the next call")
+    # an eager call on one stream, then a capture on a second and an eager call on a third
+    a, b, c = (torch.cuda.Stream() for _ in range(3))
+    ws_b, ws_c = (B.new_workspace(1023, 4096, p, DEV) for _ in range(2))
+    out_b, out_c = (B.new_outputs(1023, 4096, DEV) for _ in range(2))
+    with torch.cuda.stream(b):
+        B.quantize(w, workspace=ws_b, out=out_b)
+    with torch.cuda.stream(a):
+        on_a = run(w, p)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=b):
+        B.quantize(w, workspace=ws_b, out=out_b)
+        with torch.cuda.stream(c):
+            B.quantize(w, workspace=ws_c, out=out_c)
+    for turn in range(3):
+        out_b.codes.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        for o in (on_a, out_b, out_c):
+            same_bytes(o, want, turn)
