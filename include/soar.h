@@ -156,20 +156,21 @@ typedef struct {
                                 processes or long-running kernels keep part of the GPU busy
                                 for longer than the bound, or the stream is restricted to
                                 some compute units, SOAR_RESIDENT_NEVER is the better choice */
-    int32_t  resident_wait_us; /* 0 = library default (2 s); > 0: the bound, in microseconds,
-                                after which a workgroup of that kernel stops waiting for the
-                                others to arrive (every workgroup then does).  Single-step: all
-                                leave and set SOAR_STATUS_GAVE_UP; the bound covers everything
-                                a workgroup does until its waits are over.  Iterated path, and
-                                batches (tensor by tensor): it
-                                counts from where a workgroup has read its blocks and begins to
-                                wait; one of them, the last to leave, finishes the tensor by
-                                itself (a compute unit's speed), so the outputs are complete;
-                                the status says SOAR_STATUS_GAVE_UP beside its other bits if
-                                this field was set, and is that of a call that did not wait if
-                                it was 0.  Once all workgroups have arrived, these
-                                wait for as long as they work (at most the greater of the
-                                bound and 10 s a time)                                        */
+    int32_t  resident_wait_us; /* 0 = library default (2 s; batches 50 us); > 0: the bound, in
+                                microseconds, after which a workgroup of that kernel stops waiting
+                                for the others to arrive (every workgroup then does).
+                                One tensor, single-step: all leave and set SOAR_STATUS_GAVE_UP; the
+                                bound covers everything a workgroup does until its waits are over.
+                                Iterated path, and batches (tensor by tensor): it counts from
+                                where a workgroup has read its blocks and begins to wait.  The
+                                outputs are complete all the same: on the iterated path one
+                                workgroup, the last to leave, finishes the tensor by itself (a
+                                compute unit's speed), in a batch the workgroups that the GPU has
+                                places for do.  The status says SOAR_STATUS_GAVE_UP beside its
+                                other bits if this field was set, and is that of a call that did
+                                not wait if it was 0.  Once all workgroups have arrived, these
+                                wait for as long as they work (iterated path: at most the greater
+                                of the bound and 10 s a time)                                 */
     int32_t  tiles_per_wg_absmax; /* single-step path: the maximum pass and the search pass   */
     int32_t  tiles_per_wg_search; /* have launch shapes of their own (the library picks them by
                                 the schedule: kernels of two launch groups share the GPU in a

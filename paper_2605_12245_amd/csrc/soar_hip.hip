@@ -731,17 +731,21 @@ Task single_task(const soar_tensor_desc &d, void *d_workspace)
     return t;
 }
 
-ResidentArgs resident_args(const soar_params *params)
+ResidentArgs resident_args(const soar_params *params, uint64_t default_wait_us = 2000000ull)
 {
     ResidentArgs a;
     a.radius = params->dss_radius;
     a.full_search = params->search_mode == SOAR_SEARCH_FULL ? 1 : 0;
     a.search_stats = search_stats_address();
     a.nonce = next_nonce();
-    const uint64_t us = params->resident_wait_us > 0 ? (uint64_t)params->resident_wait_us : 2000000ull;
+    const uint64_t us = params->resident_wait_us > 0 ? (uint64_t)params->resident_wait_us : default_wait_us;
     a.wait_ticks = us * (uint64_t)device_facts().wall_clock_khz / 1000ull;
     return a;
 }
+
+// A batch waits a short time: workgroups on an idle GPU arrive within 10 us of one another, and the ones that are there then do the work
+// themselves (finish_together).
+constexpr uint64_t kBatchWaitUs = 50;
 
 // the bound of a wait once all workgroups have arrived
 uint64_t later_ticks(const ResidentArgs &a)
@@ -809,8 +813,7 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
         b.slots = static_cast<char *>(d_workspace);
         b.n = (uint32_t)n;
         b.tell = params->resident_wait_us > 0 ? (uint32_t)SOAR_STATUS_GAVE_UP : 0u;
-        b.r = resident_args(params);
-        b.later_ticks = later_ticks(b.r);
+        b.r = resident_args(params, kBatchWaitUs);
         uint32_t wg = 0;
         for (int32_t k = 0; k < n; ++k) {
             const soar_tensor_desc &d = descs[k];

@@ -36,6 +36,17 @@ struct IterResidentWords {
 };
 static_assert(sizeof(IterResidentWords) <= kPartialsBytes, "layout of the crossing words");
 
+// One lane of a workgroup that gives up: the number of workgroups that have, this one included.  The word may hold
+// anything before the launch's first: the count stands beside 48 bits of the token.  An exchange fails only where
+// another workgroup's has succeeded, so the loop ends.
+__device__ __forceinline__ uint32_t count_out(uint64_t *word, uint64_t token)
+{
+    uint64_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), next;
+    do next = token << 16 | ((seen >> 16 == (token << 16) >> 16 ? seen & 0xFFFFull : 0ull) + 1ull);
+    while (!__hip_atomic_compare_exchange_strong(word, &seen, next, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    return (uint32_t)(next & 0xFFFFull);
+}
+
 constexpr int kIterResMaxBeta = 2048;     // factor table in LDS
 constexpr int kIterResMaxTiles = 16;      // R
 

@@ -494,7 +494,7 @@ struct ResidentArgs {
 // unwritten, where this one has to be done again); otherwise the launch is one tensor's.
 template <int DT, int METHOD, int L, int R, bool BATCH>
 __device__ __forceinline__ bool resident_body(const Task &t, const ResidentArgs &args, ResidentWords *batch_words = nullptr, uint32_t batch_g = 0u,
-                                              uint32_t batch_G = 0u, uint64_t later_ticks = 0)
+                                              uint32_t batch_G = 0u, uint64_t *crowded = nullptr)
 {
     static_assert(L == 256 || L == 1024, "workgroup of 4 or 16 waves");
     static_assert(R == 1 || R == 2 || R == 4, "blocks per lane");
@@ -535,6 +535,9 @@ __device__ __forceinline__ bool resident_body(const Task &t, const ResidentArgs 
         grid.tok = grid.base = args.nonce ^ (epoch * kResOdd);
         grid.t0 = (uint64_t)wall_clock64();
     }
+    // a tensor of this batch has waited in vain already
+    bool no_room = false;
+    if constexpr (BATCH) no_room = __hip_atomic_load(crowded, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == grid.base;
     // one lane: leave the launch and tell the others -- whoever gathers this workgroup's words, now or at a
     // later crossing, finds the complemented token in the first of them
     auto give_up = [&]() {
@@ -591,11 +594,12 @@ __device__ __forceinline__ bool resident_body(const Task &t, const ResidentArgs 
         if (grid.G > 1u) {
             uint32_t value = DT == SOAR_BF16 ? amax >> 16 : amax;
             if constexpr (BATCH) grid.t0 = (uint64_t)wall_clock64();
-            ok = cross_max<kMaxBits>(grid, value);
+            ok = !no_room && cross_max<kMaxBits>(grid, value);
             amax = DT == SOAR_BF16 ? value << 16 : value;
             if (lane == 0) {
                 if (!ok) give_up();
-                else if (!BATCH && grid.g == 0u)     // every workgroup has read the epoch by now: the next launch gets a new token
+                if (BATCH && !ok) __hip_atomic_store(crowded, grid.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (!BATCH && ok && grid.g == 0u)    // every workgroup has read the epoch by now: the next launch gets a new token
                     __hip_atomic_store(epoch_p, epoch + 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
@@ -603,8 +607,9 @@ __device__ __forceinline__ bool resident_body(const Task &t, const ResidentArgs 
     }
     __syncthreads();
     if (s_gone) return false;
-    // from here on every workgroup is running: the waits last as long as the slowest one's share
-    if constexpr (BATCH) grid.ticks = later_ticks;
+    // from here on every workgroup is running, and either goes on or has given up and said so at this crossing's words and the next
+    // one's: the waits end by themselves, and nobody gives up for any other reason than that somebody has
+    if constexpr (BATCH) grid.ticks = ~0ull;
     const uint32_t amax_bits = s_amax;
     const bool allzero = amax_bits == 0u;
     const bool degenerate = allzero || amax_bits >= 0x7F800000u;
@@ -680,7 +685,6 @@ __device__ __forceinline__ bool resident_body(const Task &t, const ResidentArgs 
                 double NM[2] = {workgroup_sum(0), workgroup_sum(1)};
                 bool ok = true;
                 if (grid.G > 1u) {
-                    if constexpr (BATCH) grid.t0 = (uint64_t)wall_clock64();
                     ok = cross_sums<2>(grid, words.nm, s_cross, NM);
                     if (!ok && lane == 0) give_up();
                 }
@@ -699,7 +703,6 @@ __device__ __forceinline__ bool resident_body(const Task &t, const ResidentArgs 
                     double none[2] = {0.0, 0.0};
                     bool ok = true;
                     if (grid.G > 1u) {
-                        grid.t0 = (uint64_t)wall_clock64();
                         ok = cross_sums<2>(grid, words.nm, s_cross, none);
                         if (!ok && lane == 0) give_up();
                     }
@@ -800,14 +803,11 @@ __device__ __forceinline__ bool resident_body(const Task &t, const ResidentArgs 
     if (grid.G > 1u) {
         if (t.sse) publish_sum(grid, words.err, total);
         if (grid.g != 0u) return true;
-        if constexpr (BATCH) grid.t0 = (uint64_t)wall_clock64();
         if (t.sse) ok = collect_sum(grid, words.err, total);
     }
     if (lane == 0) {
-        if (!ok) {
+        if (!BATCH && !ok) {
             give_up();
-            if constexpr (BATCH)
-                if (t.status) *t.status = SOAR_STATUS_GAVE_UP;       // the machine has stopped working: the sum is missing
             return true;
         }
         if (t.sse) *t.sse = total;
@@ -827,15 +827,23 @@ __global__ __launch_bounds__(L) void k_resident(const Task t, const ResidentArgs
 // A call with a few small tensors pays four launches that keep a fraction of the GPU busy; together they fit the registers of
 // the GPU as one tensor does.  k_resident_batch gives every tensor its workgroups (all of one shape, at most one per compute unit
 // in all), its own crossing words and its own token; tensors do not wait for one another.  The call always finishes, as it does
-// with several launches: a tensor whose workgroups do not arrive together within the bound is done by the last of them to leave,
-// alone (as in k_iter_resident).
+// with several launches, at the speed of the compute units that it gets: where the workgroups of a tensor do not arrive together within the
+// bound, those that run do it together, share by share (finish_together); the tensors after it then do not wait.  On a stream of 64 compute units,
+// 15 million weights in five tensors: 0.50 ms a call, several launches 0.09 (waiting 2 s a tensor, which its last workgroup then did alone: 4.0 s).
 // Whole calls, several launches / one: a layer of hidden 256 (seven matrices) 21.8 / 9.4 us, four of them 70 / 11, four of hidden 512 in fp32 105 / 22.7,
 // one of hidden 1024 34 / 20.6, of 1120 (99 % of the places) 38.5 / 20.5.
 constexpr int kResidentTensors = 40;
 constexpr int kWordsPerSlot = 5;          // tensors whose crossing words lie side by side in the partial sums of one slot
+// What the workgroups of one tensor share once they have given up: of every share, the last phase for which it has been taken and the last one in which
+// it has been carried out (phase_token), and what it gives.
+struct TogetherWords {
+    uint64_t taken[kResMaxWG], done[kResMaxWG];
+    uint64_t max[kResMaxWG], sums[3][kResMaxWG];
+};
 struct BatchWords {
     ResidentWords cross;
-    uint64_t left;                        // how many workgroups have given up
+    TogetherWords together;
+    uint64_t crowded;                     // the first tensor's serves all: the token once the workgroups of some tensor have not come together
 };
 static_assert(kWordsPerSlot * sizeof(BatchWords) <= kPartialsBytes && kResidentTensors <= kWordsPerSlot * kGroupMax && kResidentTensors <= 64,
               "layout of the crossing words");
@@ -854,34 +862,82 @@ struct ResidentBatch {
     char    *slots;                       // the workspace
     uint32_t n;
     uint32_t tell;                        // status bit of a call that gave up and was finished all the same
-    uint64_t later_ticks;                 // bound of every wait after the first crossing
     ResidentArgs r;
 };
 static_assert(sizeof(ResidentBatch) <= 4096, "kernel arguments");
 
-// One lane of a workgroup that gives up: the number of workgroups that have, this one included.  The word may hold
-// anything before the launch's first: the count stands beside 48 bits of the token.  An exchange fails only where
-// another workgroup's has succeeded, so the loop ends.
-__device__ __forceinline__ uint32_t count_out(uint64_t *word, uint64_t token)
-{
-    uint64_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), next;
-    do next = token << 16 | ((seen >> 16 == (token << 16) >> 16 ? seen & 0xFFFFull : 0ull) + 1ull);
-    while (!__hip_atomic_compare_exchange_strong(word, &seen, next, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    return (uint32_t)(next & 0xFFFFull);
-}
+// The single-step path of one tensor by those of its workgroups that are on the GPU, all of which have given up: the same trees, the
+// same bytes.  Each of the three phases -- maximum, sums, search -- has the G shares that the workgroups would have had; a workgroup takes its own
+// first and then others that nobody has taken, carries them out without waiting for anybody, and waits only when none is left, for the ones that
+// hold them: they run.  One that comes late finds what is left, or nothing.  Every share has words of its own: with counters that hand them
+// out and count them back the call measured below took 0.77 ms.
+__device__ __forceinline__ uint64_t phase_token(uint64_t token, uint32_t phase) { return token + (phase + 1u) * kResOdd; }
 
-// The single-step path of one tensor by one workgroup, a tile of L blocks after the other: the same trees, the same bytes.
-template <int DT, int L>
-__device__ __forceinline__ void single_step_alone(const Task &t, const ResidentArgs &args, uint32_t tell)
+template <int DT, int L, int R>
+__device__ __forceinline__ void finish_together(const Task &t, const ResidentArgs &args, TogetherWords &words, uint32_t g, uint32_t G, uint32_t tell)
 {
     constexpr int kWaves = L / 64;
-    __shared__ double s_part[2][kWaves], s_stack[2][32], s_sums[2];
-    __shared__ uint32_t s_max[kWaves];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-    uint32_t tiles = 1;                                      // a power of two: the tree's
-    while ((uint64_t)tiles * L < t.nblk) tiles <<= 1;
+    __shared__ double s_part[2][kWaves], s_sums[2];
+    __shared__ uint32_t s_max[kWaves], s_share;
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));         // nothing computed from it is carried here in registers from before
+    const uint32_t lane = tid & 63u, wave = tid >> 6;
+    const uint64_t token = args.nonce;
     auto load = [&](uint32_t i, float w[16]) { load_block<DT>(t.w, block_offset(t, i), w); };
-    // tile k of two sums; after the last one s_sums holds them
+    auto put = [&](uint64_t *p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto get = [&](const uint64_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    // a word of taken or done: this phase's, or a later one's
+    auto reached = [&](uint64_t seen, uint32_t phase) -> bool {
+        bool yes = false;
+        for (uint32_t p = phase; p < 3u; ++p) yes = yes || seen == phase_token(token, p);
+        return yes;
+    };
+    // every lane: a share of this phase that has now been taken for this workgroup, G where none is left
+    auto next = [&](uint32_t phase) -> uint32_t {
+        __syncthreads();
+        if (wave == 0) {
+            uint32_t share = G;
+            bool mine = false;
+            for (uint32_t first = 0; first < G && !mine;) {          // 64 shares at a time, the own one first
+                const uint32_t at = first + lane < G ? (g + first + lane) % G : G;
+                uint64_t seen = at < G ? get(words.taken + at) : 0ull;
+                const uint64_t left = __builtin_amdgcn_ballot_w64(at < G && !reached(seen, phase));
+                if (left == 0ull) {
+                    first += 64u;
+                    continue;
+                }
+                // (where another workgroup was faster, look again: that share is no longer left)
+                const bool chosen = lane == (uint32_t)__builtin_ctzll(left);
+                bool won = false;
+                if (chosen)
+                    won = __hip_atomic_compare_exchange_strong(words.taken + at, &seen, phase_token(token, phase), __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT);
+                mine = __builtin_amdgcn_ballot_w64(won) != 0ull;
+                share = (uint32_t)__builtin_amdgcn_readlane((int)at, __builtin_ctzll(left));
+            }
+            if (lane == 0) s_share = mine ? share : G;
+        }
+        __syncthreads();
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)s_share);
+    };
+    // one lane, whose stores of the share's results come before
+    auto carried_out = [&](uint32_t phase, uint32_t share) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        put(words.done + share, phase_token(token, phase));
+    };
+    // wave 0: have all shares of a phase been carried out?
+    auto complete = [&](uint32_t phase) -> bool {
+        bool yes = true;
+        for (uint32_t k = lane; k < G; k += 64u) yes = yes && reached(get(words.done + k), phase);
+        return __builtin_amdgcn_ballot_w64(!yes) == 0ull;
+    };
+    auto all_done = [&](uint32_t phase) {
+        if (wave == 0)
+            while (!complete(phase)) __builtin_amdgcn_s_sleep(32);
+        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    };
+    // tile k of a share of two sums, in workgroup order; s_sums holds them after the last one, for lane 0
     auto add_tile = [&](uint32_t k, double x, double y) {
         x = wave_pair_tree(x);
         y = wave_pair_tree(y);
@@ -889,6 +945,7 @@ __device__ __forceinline__ void single_step_alone(const Task &t, const ResidentA
         if (lane == 0) { s_part[0][wave] = x; s_part[1][wave] = y; }
         __syncthreads();
         if (wave == 0) {
+            __shared__ double s_stack[2][3];
 #pragma unroll
             for (int n = 0; n < 2; ++n) {
                 double v = wave_pair_tree(lane < (uint32_t)kWaves ? s_part[n][lane] : 0.0);
@@ -900,17 +957,41 @@ __device__ __forceinline__ void single_step_alone(const Task &t, const ResidentA
             }
         }
     };
-    uint32_t m = 0;
-    for (uint32_t i = tid; i < t.nblk; i += L) {
-        float w[16];
-        load(i, w);
+    // wave 0: the tree over the shares
+    auto sum_of = [&](const uint64_t *part) -> double {
+        double v[kResMaxWG / 64];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) m = max(m, __float_as_uint(w[j]) & 0x7FFFFFFFu);
+        for (int k = 0; k < kResMaxWG / 64; ++k)
+            v[k] = wave_pair_tree(lane + 64u * k < G ? __longlong_as_double((long long)get(part + lane + 64u * k)) : 0.0);
+        static_assert(kResMaxWG == 256, "the tree over the groups of 64 is written out");
+        return (v[0] + v[1]) + (v[2] + v[3]);
+    };
+
+    for (uint32_t share; (share = next(0u)) < G;) {
+        uint32_t m = 0;
+#pragma unroll 1
+        for (uint32_t k = 0; k < (uint32_t)R; ++k) {
+            const uint32_t i = (share * R + k) * (uint32_t)L + tid;
+            if (i < t.nblk) {
+                float w[16];
+                load(i, w);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) m = max(m, __float_as_uint(w[j]) & 0x7FFFFFFFu);
+            }
+        }
+        m = wave_max_u32(m);
+        if (lane == 0) s_max[wave] = m;
+        __syncthreads();
+        m = wave_max_u32(lane < (uint32_t)kWaves ? s_max[lane] : 0u);
+        if (tid == 0) {
+            put(words.max + share, m);
+            carried_out(0u, share);
+        }
     }
-    m = wave_max_u32(m);
-    if (lane == 0) s_max[wave] = m;
-    __syncthreads();
-    const uint32_t amax_bits = wave_max_u32(lane < (uint32_t)kWaves ? s_max[lane] : 0u);
+    all_done(0u);
+    uint32_t amax_bits = 0;
+    for (uint32_t k = lane; k < G; k += 64u) amax_bits = max(amax_bits, (uint32_t)get(words.max + k));
+    amax_bits = wave_max_u32(amax_bits);
     const bool allzero = amax_bits == 0u, degenerate = allzero || amax_bits >= 0x7F800000u;
     const GlobalScale gs(amax_bits);
     auto ratio = [&](const float w[16], float &a, float &b, float &delta0) {
@@ -921,61 +1002,87 @@ __device__ __forceinline__ void single_step_alone(const Task &t, const ResidentA
     };
     float alpha1 = allzero ? 1.0f : gs.alpha0;
     if (!degenerate) {
-        for (uint32_t k = 0; k < tiles; ++k) {
-            const uint32_t i = k * (uint32_t)L + tid;
-            float a = 0.0f, b = 0.0f, delta0 = 0.0f;
-            if (i < t.nblk) {
-                float w[16];
-                load(i, w);
-                ratio(w, a, b, delta0);
+        for (uint32_t share; (share = next(1u)) < G;) {
+#pragma unroll 1
+            for (uint32_t k = 0; k < (uint32_t)R; ++k) {
+                const uint32_t i = (share * R + k) * (uint32_t)L + tid;
+                float a = 0.0f, b = 0.0f, delta0 = 0.0f;
+                if (i < t.nblk) {
+                    float w[16];
+                    load(i, w);
+                    ratio(w, a, b, delta0);
+                }
+                add_tile(k, (double)a * (double)delta0, ((double)b * (double)delta0) * (double)delta0);
             }
-            add_tile(k, (double)a * (double)delta0, ((double)b * (double)delta0) * (double)delta0);
+            if (tid == 0) {
+                for (int n = 0; n < 2; ++n) put(words.sums[n] + share, (uint64_t)__double_as_longlong(s_sums[n]));
+                carried_out(1u, share);
+            }
+        }
+        all_done(1u);
+        if (wave == 0) {
+            const double N = sum_of(words.sums[0]), M = sum_of(words.sums[1]);
+            if (lane == 0) { s_sums[0] = N; s_sums[1] = M; }
         }
         __syncthreads();
         if (s_sums[1] > 0.0) alpha1 = (float)(s_sums[0] / s_sums[1]);
-        __syncthreads();
     }
     const float inv_alpha1 = 1.0f / alpha1;
     const bool fast = gs.fast && near_one(alpha1);
-    for (uint32_t k = 0; k < tiles; ++k) {
-        const uint32_t i = k * (uint32_t)L + tid;
-        float err = 0.0f;
-        if (i < t.nblk) {
-            float w[16], q[16];
-            uint32_t nib[2];
-            int best = (int)kE4M3Min;
-            load(i, w);
-            if (allzero) {
-                nib[0] = fp4x8(w);
-                nib[1] = fp4x8(w + 8);
-            } else {
-                float a, b, delta0;
-                const int centre = new_codes(w, degenerate ? 0.0f : ratio(w, a, b, delta0), alpha1, inv_alpha1, fast, nib, q);
-                if (args.full_search || !search_certified(w, q, alpha1, inv_alpha1, centre, args.radius, best, err))
-                    search_full(w, q, alpha1, centre, args.radius, best, err);
+    for (uint32_t share; (share = next(2u)) < G;) {
+#pragma unroll 1
+        for (uint32_t k = 0; k < (uint32_t)R; ++k) {
+            const uint32_t i = (share * R + k) * (uint32_t)L + tid;
+            float err = 0.0f;
+            if (i < t.nblk) {
+                float w[16], q[16];
+                uint32_t nib[2];
+                int best = (int)kE4M3Min;
+                load(i, w);
+                if (allzero) {
+                    nib[0] = fp4x8(w);
+                    nib[1] = fp4x8(w + 8);
+                } else {
+                    float a, b, delta0;
+                    const int centre = new_codes(w, degenerate ? 0.0f : ratio(w, a, b, delta0), alpha1, inv_alpha1, fast, nib, q);
+                    if (args.full_search || !search_certified(w, q, alpha1, inv_alpha1, centre, args.radius, best, err))
+                        search_full(w, q, alpha1, centre, args.radius, best, err);
+                }
+                __builtin_nontemporal_store((uint64_t)nib[1] << 32 | nib[0], reinterpret_cast<uint64_t *>(t.codes) + i);
+                __builtin_nontemporal_store((uint8_t)best, t.scales + i);
             }
-            __builtin_nontemporal_store((uint64_t)nib[1] << 32 | nib[0], reinterpret_cast<uint64_t *>(t.codes) + i);
-            __builtin_nontemporal_store((uint8_t)best, t.scales + i);
+            add_tile(k, (double)err, 0.0);
         }
-        add_tile(k, (double)err, 0.0);
+        if (tid == 0) {
+            put(words.sums[2] + share, (uint64_t)__double_as_longlong(s_sums[0]));
+            carried_out(2u, share);
+        }
     }
-    if (tid == 0) {
-        *t.gscale = alpha1;
-        if (t.sse) *t.sse = s_sums[0];
-        if (t.status) *t.status = (int32_t)tell | (amax_bits >= 0x7F800000u ? SOAR_STATUS_NONFINITE : 0) | (allzero ? SOAR_STATUS_ALLZERO : 0);
+    // the workgroup whose share was the last finds all of them carried out; others that do write the same
+    wait_then_read();
+    if (wave == 0 && complete(2u)) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        const double total = sum_of(words.sums[2]);
+        if (lane == 0) {
+            *t.gscale = alpha1;
+            if (t.sse) *t.sse = total;
+            if (t.status) *t.status = (int32_t)tell | (amax_bits >= 0x7F800000u ? SOAR_STATUS_NONFINITE : 0) | (allzero ? SOAR_STATUS_ALLZERO : 0);
+        }
     }
 }
 
 template <int DT, int L, int R>
 __global__ __launch_bounds__(L) void k_resident_batch(const ResidentBatch batch)
 {
-    __shared__ uint32_t s_last;
     const uint32_t lane = threadIdx.x & 63u;
     // which tensor: the last one that begins at or before this workgroup
     const uint32_t begin = lane < batch.n ? batch.t[lane].wg_begin : 0xFFFFFFFFu;
     const uint32_t which = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(begin <= blockIdx.x)) - 1u;
     const ResidentTensor &x = batch.t[which];
-    BatchWords &words = reinterpret_cast<BatchWords *>(batch.slots + (size_t)(which / kWordsPerSlot) * kSlotBytes + kZeroedBytes)[which % kWordsPerSlot];
+    auto words_of = [&](uint32_t k) -> BatchWords & {
+        return reinterpret_cast<BatchWords *>(batch.slots + (size_t)(k / kWordsPerSlot) * kSlotBytes + kZeroedBytes)[k % kWordsPerSlot];
+    };
+    BatchWords &words = words_of(which), &first = words_of(0);
     Task t;
     t.w = x.w;
     t.codes = x.codes;
@@ -988,15 +1095,11 @@ __global__ __launch_bounds__(L) void k_resident_batch(const ResidentBatch batch)
     t.nblk = x.nblk;
     t.contiguous = x.ld == (int64_t)x.bpr * 16 ? 1u : 0u;
     t.ctrl = nullptr;
-    const bool finished = resident_body<DT, SOAR_METHOD_SOAR, L, R, true>(t, batch.r, &words.cross, blockIdx.x - x.wg_begin, x.n_wg, batch.later_ticks);
-    // One value for the workgroup, and nothing that is carried past this point: otherwise the code below comes to lie between a lane's
-    // blocks and their search and takes registers of theirs to scratch memory.
-    if (__builtin_amdgcn_readfirstlane(finished ? 1 : 0) != 0) return;
-    // given up, here or elsewhere, before any output was written: the last one to leave does the tensor
-    __syncthreads();
-    if (threadIdx.x == 0) s_last = count_out(&words.left, batch.r.nonce) == x.n_wg ? 1u : 0u;
-    __syncthreads();
-    if (s_last) single_step_alone<DT, L>(t, batch.r, batch.tell);
+    const bool finished = resident_body<DT, SOAR_METHOD_SOAR, L, R, true>(t, batch.r, &words.cross, blockIdx.x - x.wg_begin, x.n_wg,
+                                                                                    &first.crowded);
+    // Given up, here or elsewhere, before any output was written.  One value for the workgroup, and nothing that is carried past this
+    // point: otherwise the code below comes to lie between a lane's blocks and their search and takes registers of theirs to scratch memory.
+    if (__builtin_amdgcn_readfirstlane(finished ? 0 : 1) != 0) finish_together<DT, L, R>(t, batch.r, words.together, blockIdx.x - x.wg_begin, x.n_wg, batch.tell);
 }
 
 }  // namespace

@@ -1,5 +1,8 @@
 """Batches of small tensors, at the numbers of tiles (256 blocks) where their launches change shape: the bytes of a call with forced
 shapes and those of every tensor handed over alone."""
+import ctypes
+import time
+
 import pytest
 import torch
 
@@ -84,26 +87,78 @@ def test_one_launch_for_a_batch_equals_several(rows, dtype):
     same(run(ws, p), want)
 
 
+def with_degenerate(rows, zero, bad, dtype, seed):
+    """tensors of `rows` rows, an all-zero one (signed) and a non-finite one"""
+    ws = mixed(tuple(rows) + (zero, bad), dtype, seed)
+    ws[-2] = torch.zeros_like(ws[-2])
+    ws[-2][zero - 1, 31] = -0.0
+    ws[-1] = ws[-1].clone()
+    ws[-1][bad // 2, 3] = float("nan")
+    return ws
+
+
+def same_with_degenerate(got, want):
+    """but for the non-finite tensor, whose outputs are unspecified"""
+    same(got[:-1], want[:-1])
+    assert int(got[-2].status.item()) == B.SOAR_STATUS_ALLZERO and int(got[-1].status.item()) == B.SOAR_STATUS_NONFINITE
+
+
+# workgroups of a tensor, for each of the four shapes: two-level crossings with and without a remainder, one workgroup (which waits for
+# nobody), direct crossings; the degenerate ones span several
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
-@pytest.mark.parametrize("rows", BATCHES[:-1], ids=lambda r: f"{len(r)}x{r[0]}-{sum(r)}")
-def test_a_batch_that_gives_up_is_finished(rows, dtype):
-    """a bound of 1 us: most workgroups leave, and the last one of every tensor does it alone"""
-    ws = mixed(rows, dtype, sum(rows)) + [torch.zeros(700, 32, dtype=dtype, device=DEV)[:sum(rows) % 700 + 1]]
-    if sum(-(-w.shape[0] * 2 // 4096) for w in ws) > 256:
-        ws.pop()
+@pytest.mark.parametrize("unit", [128, 512, 1024, 2048], ids=["256x1", "1024x1", "1024x2", "1024x4"])
+@pytest.mark.parametrize("sizes,zero,bad", [((100, 100.5, 0.1), 20.3, 17), ((16, 17, 64, 65, 0.1), 33, 19.5)], ids=["two large", "four"])
+def test_a_batch_that_gives_up_is_finished(sizes, zero, bad, unit, dtype):
+    """a bound of 1 us: the workgroups of the larger tensors leave, and do their tensor together"""
+    ws = with_degenerate([max(1, int(unit * n)) for n in sizes], int(unit * zero), int(unit * bad), dtype, unit)
     p = B.soar_default_params()
     p.resident = B.SOAR_RESIDENT_NEVER
     want = run(ws, p)
     p.resident = B.SOAR_RESIDENT_AUTO
-    p.resident_wait_us = 1
-    for turn in range(3):
-        got = run(ws, p)
+    several = [n for n, w in enumerate(ws) if w.shape[0] > unit]
+    seen = set()
+    for turn in range(12):
+        p.resident_wait_us = 1
+        p.search_mode = turn % 2                 # SOAR_SEARCH_AUTO and SOAR_SEARCH_FULL
+        outs = [B.new_outputs(w.shape[0], w.shape[1], DEV) for w in ws]
+        assert turn > 0 or launches_of(B.SOAR_KERNEL_RESIDENT, lambda: run(ws, p, outs)) == 1
+        got = run(ws, p, outs)
+        left = {n for n, o in enumerate(got) if int(o.status.item()) & B.SOAR_STATUS_GAVE_UP}
+        assert left <= set(several)              # a single workgroup has nobody to wait for
+        seen |= left
         for o in got:
             o.status &= ~B.SOAR_STATUS_GAVE_UP
-        same(got, want)
-    p.resident_wait_us = 0
-    same(run(ws, p), want)
+        same_with_degenerate(got, want)
+        if turn > 1 and seen == set(several):
+            break
+    assert seen == set(several)
+    p.resident_wait_us = p.search_mode = 0
+    same_with_degenerate(run(ws, p), want)
+
+
+@pytest.mark.gpu
+def test_a_batch_on_a_stream_of_few_compute_units_is_finished_by_them():
+    """240 workgroups of which 64 find a place: the call takes what the units need, not the seconds of a wait for the others"""
+    ws = with_degenerate([2048 * 100, 2048 * 100 + 1, 5], 2048 * 20, 2048 * 17, torch.bfloat16, 3)
+    p = B.soar_default_params()
+    p.resident = B.SOAR_RESIDENT_NEVER
+    want = run(ws, p)
+    p.resident = B.SOAR_RESIDENT_AUTO
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream, mask = ctypes.c_void_p(), (ctypes.c_uint32 * 8)(*[0xFFFFFFFF, 0xFFFFFFFF, 0, 0, 0, 0, 0, 0])
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, mask) == 0
+    try:
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream.value)):
+            for turn in range(3):
+                t = time.perf_counter()
+                got = run(ws, p)
+                took = time.perf_counter() - t
+                same_with_degenerate(got, want)
+                assert took < 1.0, took
+    finally:
+        torch.cuda.synchronize()
+        hip.hipStreamDestroy(stream)
 
 
 @pytest.mark.gpu
