@@ -645,7 +645,7 @@ bool mx_nearest_pays(int n_beta, int radius) { return radius <= 6 && radius <= n
 // Iterations with a launch each; the ones after share a launch (k_iter_rest) where tensors stop by themselves.  Almost all have
 // after three or four (heavy-tailed and uniform weights, 1e-3).
 constexpr int kIterLaunches = 4;
-constexpr int kRestWgPerCu = 6;           // workgroups of k_iter_rest<., CLOSED_FORM> on a compute unit
+constexpr int kRestWgPerCu = 5, kRestWgPerCuClosed = 6;      // workgroups of k_iter_rest on a compute unit (with and without a search)
 bool rest_in_one(const Batch &b, int iters)
 {
     if (!(b.early_stop_rel > 0.0f) || iters < kIterLaunches + 2) return false;
@@ -654,11 +654,13 @@ bool rest_in_one(const Batch &b, int iters)
     return true;
 }
 
-// The closed-form arm has a workgroup for every chunk; a counter that hands them out one by one is served in 12 ns each, so its
-// shares are as many as workgroups are on the GPU at a time.
-uint32_t deal_shares(Batch &b)
+// k_iter_rest: as many workgroups, and shares, as are on the GPU at a time, so that a share rarely waits for the workgroup that it belongs to
+// (the launches before it have a workgroup for every chunk or two, but for the nearest-factor search).
+uint32_t deal_shares(Batch &b, bool closed)
 {
-    const int64_t places = (int64_t)kRestWgPerCu * (device_facts().compute_units > 0 ? device_facts().compute_units : 256);
+    const int cu = device_facts().compute_units > 0 ? device_facts().compute_units : 256;
+    int64_t places = (int64_t)(closed ? kRestWgPerCuClosed : kRestWgPerCu) * cu;
+    if (places > (int64_t)kRestShares) places = kRestShares;
     int64_t chunks = 0;
     for (uint32_t k = 0; k < b.n; ++k) chunks += b.t[k].n_chunks;
     uint32_t wg = 0;
@@ -702,7 +704,7 @@ soar_status launch_group_iter(Batch &b, uint32_t wg_absmax, uint32_t total_wg, i
     }
     if (launches < iters) {
         b.iter_t = launches;
-        if (closed) total_wg = deal_shares(b);
+        total_wg = deal_shares(b, closed);
         if (closed) hipLaunchKernelGGL((k_iter_rest<DT, Iterate::CLOSED_FORM>), dim3(total_wg), dim3(kWG), 0, st, b, iters);
         else if (nearest) hipLaunchKernelGGL((k_iter_rest<DT, Iterate::NEAREST>), dim3(total_wg), dim3(kWG), table, st, b, iters);
         else hipLaunchKernelGGL((k_iter_rest<DT, Iterate::OTHER>), dim3(total_wg), dim3(kWG), table, st, b, iters);

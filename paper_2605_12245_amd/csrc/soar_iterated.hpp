@@ -444,10 +444,13 @@ __device__ __forceinline__ void init_block(const float w[16], const GlobalScale 
 }
 
 // What the workgroups of one tensor share in k_iter_rest: cleared by k_iter_init, at the end of the partial sums, where a tensor
-// of fewer partials leaves room.
+// of fewer partials leaves room.  (at most kRestShares shares: deal_shares)
+constexpr uint32_t kRestShares = 2048, kRestStopped = 0xFFFFFFFFu;
+constexpr uint32_t kRestLooks = 64;       // looks for the next iteration, about 1 us each, between two for shares that nobody has taken
 struct RestWords {
-    uint32_t shares[kMaxIters][32];       // of an iteration: how many have been handed out
-    uint32_t finished[16][32];            // iterations carried out; copies, a waiting workgroup reads the one of its number
+    uint64_t next[16][16];                // the iteration to carry out next (0: the launch's first) or kRestStopped; its global scale in the upper
+                                          // half.  Copies: a workgroup reads the one of its number
+    uint32_t taken[kRestShares];          // of a share: one more than the last iteration for which it has been taken
 };
 constexpr int kRestPartials = kMaxPartials - (int)(sizeof(RestWords) / sizeof(double));
 __host__ __device__ inline bool has_rest_words(uint32_t n_chunks) { return n_chunks <= (uint32_t)kRestPartials; }
@@ -649,7 +652,7 @@ __device__ __forceinline__ void put(T *p, T v)
 // What the last workgroup of a tensor does after iteration `it` (one lane): the outputs that describe the
 // tensor, the early-stop decision and the global scale the next iteration starts from (Eq. 5).
 template <bool AGENT = false>
-__device__ __forceinline__ void finish_iteration(const Batch &batch, const Task &t, int it, double N, double M, double cur, float alpha,
+__device__ __forceinline__ uint64_t finish_iteration(const Batch &batch, const Task &t, int it, double N, double M, double cur, float alpha,
                                                  bool degenerate, bool allzero, bool dss_only)
 {
     if (degenerate) {
@@ -667,10 +670,13 @@ __device__ __forceinline__ void finish_iteration(const Batch &batch, const Task 
         const bool stop = batch.early_stop_rel > 0.0f && (prev - cur) < (double)batch.early_stop_rel * prev;
         put<AGENT>(&t.ctrl->stopped, stop ? 1u : 0u);
         put<AGENT>(&t.ctrl->prev_sse, cur);
-        put<AGENT>(&t.ctrl->alpha1, (M > 0.0 && !dss_only) ? (float)(N / M) : alpha);      // Eq. 5 for the next iteration
+        const float next = (M > 0.0 && !dss_only) ? (float)(N / M) : alpha;                // Eq. 5 for the next iteration
+        put<AGENT>(&t.ctrl->alpha1, next);
         put<AGENT>(&t.ctrl->N, N);
         put<AGENT>(&t.ctrl->M, M);
+        return (uint64_t)__float_as_uint(next) << 32 | (stop ? kRestStopped : (uint32_t)(it + 1));
     }
+    return kRestStopped;
 }
 
 // One iteration of Algorithm 1.  On entry ctrl->alpha1 holds the Eq. 5 global
@@ -860,14 +866,16 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(8))) void k
 }
 
 // The iterations from batch.iter_t on in one launch: most tensors have stopped by then, and a launch that finds its tensors stopped
-// takes 2.4 us on the GPU and 4 to 5 on the host.  Nothing here depends on which workgroups are on the GPU: the shares of an
-// iteration (what a workgroup of k_iter does) are handed out by a counter, whoever has one carries it out without waiting for
-// anybody, and only a workgroup that finds none left waits -- for the ones that hold them.  So a share and the one before it on the same
-// blocks may belong to different compute dies: ratios, codes, scales and the tensor's results are read and written at
-// the memory side, and a share is counted as done when its stores have been performed there.
-// Three of fifteen iterations do work: one decoder layer 703 -> 683 us, 12288 x 4096 237 -> 221, a layer of hidden 512 108 -> 74, the closed-form
-// arm there 108 -> 64.  Where all fifteen do, an iteration here takes what one in a launch of its own takes (four matrices of 2 to 50 million
-// weights: 436 / 448, 2270 / 2255 us; the closed-form arm, whose stores are no longer combined in the caches, up to 6 % more).
+// takes 2.4 us on the GPU and 4 to 5 on the host.  Nothing here depends on which workgroups are on the GPU: an iteration has a share
+// for every workgroup (what a workgroup of k_iter does); each takes its own, whoever has one carries it out without waiting for
+// anybody, and only a workgroup that has none waits -- for the ones that hold them, which run, and it looks now and then for shares
+// whose workgroups are not there and carries those out as well.  So a share and the one before it on the same blocks may belong to
+// different compute dies: ratios, codes, scales and the tensor's results are read and written at the memory side, and a share is
+// counted as done when its stores have been performed there.
+// Three of fifteen iterations do work (a launch for each / one for all after the fourth): 12288 x 4096 240 / 219 us, a layer of hidden 512 108 / 74,
+// the closed-form arm there 108 / 64.  All of them do (early_stop_rel 1e-30): four matrices of 2 million weights 253 / 226 us, two of 17 million
+// 664 / 640, one of 50 million 407 / 382, the closed-form arm there 393 / 378.  With one counter that hands the shares out, which is served in 12 ns a
+// workgroup, and the stop flag and the scale read from the same line by all, those took 276, 760, 416 and 521.
 enum class Iterate { CLOSED_FORM, NEAREST, OTHER };
 template <int DT, Iterate KIND>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_iter_rest(const Batch batch, int iters)
@@ -875,7 +883,8 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     __shared__ float4 s_blocks[kStage * kWG];
     __shared__ double s_wave[3][4];
     __shared__ double s_stack[3][32];
-    __shared__ uint32_t s_last, s_share, s_stopped;
+    __shared__ uint32_t s_last, s_share, s_it;
+    __shared__ uint64_t s_next;
     __shared__ float s_alpha;
     double *s_tree = reinterpret_cast<double *>(s_blocks);      // trees_of_partials, after the last group
     extern __shared__ __align__(16) unsigned char s_dyn[];      // the factor table, n_beta floats
@@ -884,83 +893,128 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
 
     uint32_t lwg;
     const Task t = batch.t[find_task(batch, lwg)];
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t amax_bits = t.ctrl->amax_bits;
     if (amax_bits == 0u || amax_bits >= 0x7F800000u) return;    // finished by the first iteration
     RestWords &rest = rest_words(t);
     const bool dss_only = batch.arm == SOAR_METHOD_DSS_ONLY;
     JointSearch js{{s_beta, batch.n_beta, batch.beta_lo, batch.index_per_beta}, 0.0f, 0.0f, batch.radius,
                    batch.dd_mode == SOAR_DD_BRACKET, dss_only, false, batch.full_search != 0 || batch.n_beta < kChangesMinBeta};
+    // wave 0: takes a share of iteration `it` if it is left (the same in every lane)
+    auto take = [&](uint32_t share, uint32_t it) -> bool {
+        uint32_t before = 0u;
+        if (lane == 0) before = __hip_atomic_fetch_max(&rest.taken[share], it + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return (uint32_t)__builtin_amdgcn_readfirstlane((int)before) <= it;
+    };
 
-    for (int it = batch.iter_t; it < iters; ++it) {
-        if (tid == 0) {
-            // the last share of the iteration before publishes this; a share is held by a workgroup that is running
-            if (it > batch.iter_t)
-                while (get(&rest.finished[lwg % 16u][0]) < (uint32_t)it) __builtin_amdgcn_s_sleep(32);
-            s_stopped = get(&t.ctrl->stopped);
-            s_alpha = get(&t.ctrl->alpha1);
-        }
-        __syncthreads();
-        if (s_stopped) return;             // lane 0 writes it again only behind the barriers below
-        // of this iteration, or of a later one if this one has been finished meanwhile: then no share of it is left
-        const float alpha = s_alpha;
-        if constexpr (KIND != Iterate::CLOSED_FORM)
-            if (it == batch.iter_t)
-                for (int k = (int)tid; k < batch.n_beta; k += kWG) s_beta[k] = beta_factor(k, batch.n_beta, batch.beta_lo, batch.beta_hi);
-        js.set_alpha(alpha, amax_bits);
-        for (;;) {
-            if (tid == 0) s_share = __hip_atomic_fetch_add(&rest.shares[it][0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __syncthreads();
-            const uint32_t share = s_share;
-            if (share >= t.n_wg) break;
-            StagedTree<> tree{s_blocks, s_wave, s_stack};
-            const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
-            for (uint32_t chunk = share; chunk < t.n_chunks; chunk += t.n_wg) {
-                for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
-                    for (uint32_t kk = 0; kk < T; ++kk) {
-                        const uint32_t i = (chunk * t.tiles_per_wg + kg + kk) * kWG + tid;
-                        BlockState x;
-                        x.a = x.b = x.d = x.err = 0.0f;
-                        if (i < t.nblk) {
-                            const float rho = get(t.rho + i);
-                            float w[16];
-                            load_block<DT>(t.w, block_offset(t, i), w);
-                            if constexpr (KIND == Iterate::CLOSED_FORM)
-                                closed_form_block(w, rho, alpha, js.inv_alpha, js.in_range && all_near_one(rho), x);
-                            else
-                                iterate_block<KIND == Iterate::NEAREST>(w, rho, js, x);
-                            put<true>(t.rho + i, x.rho);
-                            put<true>(reinterpret_cast<uint64_t *>(t.codes) + i, (uint64_t)x.nib[1] << 32 | x.nib[0]);
-                            put<true>(t.scales + i, (uint8_t)x.code);
+    bool filled = false, helping = false;    // helping: some workgroups were not there before
+    // read before a share of the launch's first iteration is taken: as long as one is left, that iteration has not been finished
+    const uint32_t stopped = t.ctrl->stopped;
+    const float first_alpha = t.ctrl->alpha1;
+    for (uint32_t asked = 0u;;) {            // one more than the last iteration of which this workgroup has asked for its share
+        if (tid < 64u) {
+            uint32_t it, share = lwg;
+            float alpha;
+            for (uint32_t looks = helping ? kRestLooks - 1u : 0u;; ++looks) {
+                const uint64_t next = get(&rest.next[lwg % 16u][0]);
+                it = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)next);
+                alpha = f_of((uint32_t)(next >> 32));
+                if (it == 0u) {
+                    it = stopped ? kRestStopped : (uint32_t)batch.iter_t;
+                    alpha = first_alpha;
+                }
+                if (it >= (uint32_t)iters) break;
+                if (it >= asked) {
+                    asked = it + 1u;
+                    share = lwg;
+                    if (take(share, it)) break;
+                } else if (looks % kRestLooks == kRestLooks - 1u) {
+                    bool found = false;
+                    // 64 at a time, every workgroup from a place of its own on and another one of those that are left
+                    uint32_t me = lane;
+                    asm volatile("" : "+v"(me));     // what is computed from it is not kept in registers through the search
+                    const uint32_t start = lwg * 0x9E3779B1u % t.n_wg;
+                    for (uint32_t first = 0; first < t.n_wg && !found;) {
+                        const uint32_t at = (start + first + me) % t.n_wg;
+                        const bool is_left = first + me < t.n_wg && get(&rest.taken[at]) <= it;
+                        const uint64_t left = __builtin_amdgcn_ballot_w64(is_left);
+                        if (left == 0ull) {
+                            first += 64u;
+                            continue;
                         }
-                        tree.stage(kk, x.a, x.b, x.d, x.err);
+                        const uint32_t rank = (uint32_t)__builtin_popcountll(left & ((1ull << me) - 1ull));
+                        const uint64_t mine = __builtin_amdgcn_ballot_w64(is_left && rank == lwg % (uint32_t)__builtin_popcountll(left));
+                        share = (uint32_t)__builtin_amdgcn_readlane((int)at, (int)__builtin_ctzll(mine));
+                        found = take(share, it);     // (where another one was faster, it is no longer left)
                     }
-                    tree.close(kg / T, T);
+                    helping = helping || found;
+                    if (found) break;
                 }
-                if (tid == 0) {
-                    publish(t.part + chunk, tree.wg[0]);
-                    publish(t.part + kMaxPartials + chunk, tree.wg[1]);
-                    publish(t.part + 2 * kMaxPartials + chunk, tree.wg[2]);
-                }
+                __builtin_amdgcn_s_sleep(16);
             }
-            wait_then_read();                                   // every wave: its stores have been performed
-            __syncthreads();
-            uint32_t *counters = t.counters + 2 * kSlots * kSlotStride;
-            if (tid == 0) s_last = arrive_is_last(counters, &t.ctrl->top[2], t.n_wg, share) ? 1u : 0u;
-            __syncthreads();
-            if (s_last) {
-                double NME[3];
-                trees_of_partials<3>(t.part, t.n_chunks, s_tree, &s_stack[0][0], NME);
-                if (tid == 0) finish_iteration<true>(batch, t, it, NME[0], NME[1], NME[2], alpha, false, false, dss_only);
-                if (tid < kSlots) put<true>(counters + tid * kSlotStride, 0u);
-                if (tid == 0) put<true>(&t.ctrl->top[2], 0u);
-                wait_then_read();
-                __syncthreads();
-                if (tid < 16u) put<true>(&rest.finished[tid][0], (uint32_t)(it + 1));
+            if (tid == 0) {
+                s_it = it;
+                s_share = share;
+                s_alpha = alpha;
             }
-            __syncthreads();
         }
         __syncthreads();
+        const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_it);
+        const uint32_t share = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_share);
+        const float alpha = f_of((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(s_alpha)));
+        if (it >= (uint32_t)iters) return;
+        if constexpr (KIND != Iterate::CLOSED_FORM)
+            for (int k = filled ? batch.n_beta : (int)tid; k < batch.n_beta; k += kWG) s_beta[k] = beta_factor(k, batch.n_beta, batch.beta_lo, batch.beta_hi);
+        __syncthreads();                     // the factors; and what this workgroup has been told has been read
+        filled = true;
+        js.set_alpha(alpha, amax_bits);
+        StagedTree<> tree{s_blocks, s_wave, s_stack};
+        const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
+        for (uint32_t chunk = share; chunk < t.n_chunks; chunk += t.n_wg) {
+            for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
+                for (uint32_t kk = 0; kk < T; ++kk) {
+                    const uint32_t i = (chunk * t.tiles_per_wg + kg + kk) * kWG + tid;
+                    BlockState x;
+                    x.a = x.b = x.d = x.err = 0.0f;
+                    if (i < t.nblk) {
+                        const float rho = get(t.rho + i);
+                        float w[16];
+                        load_block<DT>(t.w, block_offset(t, i), w);
+                        if constexpr (KIND == Iterate::CLOSED_FORM)
+                            closed_form_block(w, rho, alpha, js.inv_alpha, js.in_range && all_near_one(rho), x);
+                        else
+                            iterate_block<KIND == Iterate::NEAREST>(w, rho, js, x);
+                        put<true>(t.rho + i, x.rho);
+                        put<true>(reinterpret_cast<uint64_t *>(t.codes) + i, (uint64_t)x.nib[1] << 32 | x.nib[0]);
+                        put<true>(t.scales + i, (uint8_t)x.code);
+                    }
+                    tree.stage(kk, x.a, x.b, x.d, x.err);
+                }
+                tree.close(kg / T, T);
+            }
+            if (tid == 0) {
+                publish(t.part + chunk, tree.wg[0]);
+                publish(t.part + kMaxPartials + chunk, tree.wg[1]);
+                publish(t.part + 2 * kMaxPartials + chunk, tree.wg[2]);
+            }
+        }
+        wait_then_read();                                   // every wave: its stores have been performed
+        __syncthreads();
+        uint32_t *counters = t.counters + 2 * kSlots * kSlotStride;
+        if (tid == 0) s_last = arrive_is_last(counters, &t.ctrl->top[2], t.n_wg, share) ? 1u : 0u;
+        __syncthreads();
+        if (s_last) {
+            double NME[3];
+            trees_of_partials<3>(t.part, t.n_chunks, s_tree, &s_stack[0][0], NME);
+            if (tid == 0) s_next = finish_iteration<true>(batch, t, (int)it, NME[0], NME[1], NME[2], alpha, false, false, dss_only);
+            if (tid < kSlots) put<true>(counters + tid * kSlotStride, 0u);
+            if (tid == 0) put<true>(&t.ctrl->top[2], 0u);
+            wait_then_read();
+            __syncthreads();
+            uint32_t copy = tid;
+            asm volatile("" : "+v"(copy));   // its address is not kept in registers from before the search
+            if (copy < 16u) put<true>(&rest.next[copy][0], s_next);
+        }
     }
 }
 

@@ -1,5 +1,7 @@
 """The iterations after the fourth share a launch (k_iter_rest): the bytes, traces and counts of every tensor handed over alone (one
 launch of its own, or the oracle), on workspaces holding anything, twice on each, replayed from a graph."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -116,12 +118,11 @@ def without_stopping(w, p, rel):
     return B.quantize_iter(w, q), run
 
 
-# a tensor that stops inside the shared launch while workgroups of it still arrive: 1992 and 1329 shares of one tile ("every pair"), as many
-# shares as places otherwise; against one launch per iteration
+# tensors that stop inside the shared launch, which has as many workgroups as places; against one launch per iteration
 @pytest.mark.gpu
 @pytest.mark.parametrize("arm", ["paper", "every pair", "closed"])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "fp32"])
-def test_rest_stops_while_workgroups_arrive(dtype, arm):
+def test_rest_stops_inside_the_shared_launch(dtype, arm):
     p = params(arm)
     p.resident = B.SOAR_RESIDENT_NEVER
     ws = weights_of((170000, 113400, 900), dtype, 5)
@@ -142,3 +143,33 @@ def test_rest_stops_while_workgroups_arrive(dtype, arm):
                 assert torch.equal(getattr(o, f), getattr(want, f)), (at, k, f)
             assert torch.equal(o.sse_trace[:run + 1], want.sse_trace[:run + 1]), (at, k)
         assert 4 < runs[0] <= at
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("arm", ["paper", "every pair", "closed"])
+def test_rest_on_a_stream_of_few_compute_units(arm):
+    """four fifths of the workgroups find no place: the ones that do carry out their shares"""
+    p = params(arm)
+    p.resident = B.SOAR_RESIDENT_NEVER
+    ws = weights_of((170000, 170001, 5), torch.bfloat16, 8)
+    outs, descs = outputs(ws, p)
+    space = B.new_batch_workspace(descs, p, DEV)
+    want, wanted = outputs(ws, p)
+    B.quantize_batch(wanted, p, B.new_batch_workspace(wanted, p, DEV))
+    torch.cuda.synchronize()
+    assert max(int(a.iters_run.item()) for a in want) > 4
+    hip = ctypes.CDLL("libamdhip64.so")
+    stream, mask = ctypes.c_void_p(), (ctypes.c_uint32 * 8)(*[0xFFFFFFFF, 0xFFFFFFFF, 0, 0, 0, 0, 0, 0])
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, mask) == 0
+    try:
+        with torch.cuda.stream(torch.cuda.ExternalStream(stream.value)):
+            for turn in range(3):
+                for o in outs:
+                    o.codes.fill_(0xAA)
+                B.quantize_batch(descs, p, space)
+                torch.cuda.synchronize()
+                for k, (o, a) in enumerate(zip(outs, want)):
+                    same(o, a, (turn, k))
+    finally:
+        torch.cuda.synchronize()
+        hip.hipStreamDestroy(stream)

@@ -33,3 +33,14 @@ def test_no_register_of_a_batch_kernel_lies_in_scratch_memory(kernels):
     batch = {k: v for k, v in kernels.items() if k.startswith("k_resident_batch<")}
     assert len(batch) == 8
     assert not {k: v for k, v in batch.items() if v["vgpr_spill_count"] or v["private_segment_fixed_size"]}
+
+
+def test_no_register_of_the_shared_launch_of_the_later_iterations_lies_in_scratch_memory(kernels):
+    """and as many of its workgroups are on a compute unit as deal_shares gives shares to: 512 registers a lane and four workgroups' waves share a SIMD"""
+    rest = {k: v for k, v in kernels.items() if k.startswith("k_iter_rest<")}
+    assert len(rest) == 6
+    assert not {k: v for k, v in rest.items() if v["vgpr_spill_count"] or v["private_segment_fixed_size"]}
+    for name, v in rest.items():
+        closed = "(Iterate)0" in name or "CLOSED_FORM" in name
+        assert 512 // (-(-v["vgpr_count"] // 8) * 8) >= (6 if closed else 5), name
+        assert 160 * 1024 // (v["group_segment_fixed_size"] + 2048 * 4 * (not closed)) >= (6 if closed else 5), name
