@@ -1399,7 +1399,7 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
         b.n = (uint32_t)(j - i);
         b.once = once ? 1u : 0u;
         if (once) b.once_args.nonce = next_nonce();
-        uint32_t wg = 0;
+        uint32_t wg = 0, most_tiles = 0;
         int64_t group_tiles = 0;
         for (int32_t k = i; k < j; ++k) group_tiles += (descs[k].rows * (descs[k].cols / 32) + kWG - 1) / kWG;
         for (int32_t k = i; k < j; ++k) {
@@ -1420,6 +1420,7 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
             while (tpw > 1 && tpw > tiles) tpw >>= 1;
             if (params->tiles_per_wg) tpw = (uint32_t)params->tiles_per_wg;
             while ((tiles + tpw - 1) / tpw > (uint32_t)kMaxPartials) tpw <<= 1;
+            most_tiles = tpw > most_tiles ? tpw : most_tiles;
             t.tiles_per_wg = tpw;
             t.n_wg = (tiles + tpw - 1) / tpw;
             t.wg_begin = wg;
@@ -1435,13 +1436,14 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
             t.index_per_beta = nearest ? (float)(params->n_beta - 1) / (params->beta_hi - params->beta_lo) : 0.0f;
         }
         ScopedTimer tm(SOAR_KERNEL_MX, lst);
-        // an instantiation each: the plain conversion needs half the registers of a search
+        // an instantiation each: the plain conversion needs half the registers of a search (STAGED: see k_mx)
         const bool bf16 = descs[i].dtype == SOAR_BF16;
         auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(wg), dim3(kWG), lds, lst, b); };
-        if (!params->dss) launch(bf16 ? k_mx<SOAR_BF16, Mx::PLAIN> : k_mx<SOAR_FP32, Mx::PLAIN>);
-        else if (nearest) launch(bf16 ? k_mx<SOAR_BF16, Mx::NEAREST> : k_mx<SOAR_FP32, Mx::NEAREST>);
-        else if (every) launch(bf16 ? k_mx<SOAR_BF16, Mx::EVERY> : k_mx<SOAR_FP32, Mx::EVERY>);
-        else launch(bf16 ? k_mx<SOAR_BF16, Mx::CHANGES> : k_mx<SOAR_FP32, Mx::CHANGES>);
+        if (!params->dss) launch(bf16 ? k_mx<SOAR_BF16, Mx::PLAIN, false> : k_mx<SOAR_FP32, Mx::PLAIN, false>);
+        else if (nearest && most_tiles > 1u) launch(bf16 ? k_mx<SOAR_BF16, Mx::NEAREST, true> : k_mx<SOAR_FP32, Mx::NEAREST, true>);
+        else if (nearest) launch(bf16 ? k_mx<SOAR_BF16, Mx::NEAREST, false> : k_mx<SOAR_FP32, Mx::NEAREST, false>);
+        else if (every) launch(bf16 ? k_mx<SOAR_BF16, Mx::EVERY, false> : k_mx<SOAR_FP32, Mx::EVERY, false>);
+        else launch(bf16 ? k_mx<SOAR_BF16, Mx::CHANGES, false> : k_mx<SOAR_FP32, Mx::CHANGES, false>);
         if (hipGetLastError() != hipSuccess) result = SOAR_ERR_HIP;
         i = j;
     }

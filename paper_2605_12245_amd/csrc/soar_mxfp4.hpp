@@ -362,8 +362,7 @@ __device__ __forceinline__ void mx_search_nearest(const float w[32], float bmax,
 }
 
 // TileTree<1> at a fraction of the cross-lane work and the barriers: terms of up to kStage consecutive tiles are staged in LDS, a lane
-// folds adjacent ones, and one wave tree finishes the group (as StagedTree does for three sums).  The searches take it: one decoder
-// layer 136 -> 130 us, 12288 x 4096 fp32 58.7 -> 56.9; the plain conversion, which waits for memory, is up to 7 % slower with it.
+// folds adjacent ones, and one wave tree finishes the group (as StagedTree does for three sums).
 struct StagedSum {
     double *s_terms;             // [kStage * kWG]
     double (*s_wave)[4];
@@ -391,9 +390,12 @@ struct StagedSum {
     }
 };
 
-// (the searches are held to four waves per SIMD: left to itself the compiler takes three for the staged sum)
-template <int DT, Mx MODE>
-__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(MODE == Mx::PLAIN ? 1 : 4))) void k_mx(const MxBatch batch)
+// STAGED: the nearest-factor search where a workgroup has several tiles: one decoder layer 136 -> 130 us, 6000 tiles of fp32 57.8 -> 55.8, 20000
+// of them 193 -> 176.  With one tile there is nothing to fold, and the same kernel is slower than one without the staging (3094 tiles of bf16 24.9 us / 24.0, 4000
+// 29.2 / 28.2); so are the searches that walk the grid (3094 tiles 577 / 571 us, 12000 2002 / 1982) and the plain conversion (up to 7 %).
+// (held to four waves per SIMD: left to itself the compiler takes three for the staged sum)
+template <int DT, Mx MODE, bool STAGED>
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(STAGED ? 4 : 1))) void k_mx(const MxBatch batch)
 {
     constexpr bool DSS = MODE != Mx::PLAIN;
     __shared__ double s_wave[1][4];
@@ -417,7 +419,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(MODE == Mx:
 
     const FactorGrid grid{s_beta, n_beta, t.beta_lo, t.index_per_beta};
     TileTree<1> tree{s_wave, s_stack};
-    __shared__ double s_terms[DSS ? kStage * kWG : 1];
+    __shared__ double s_terms[STAGED ? kStage * kWG : 1];
     StagedSum staged{s_terms, s_wave, s_stack};
     const uint32_t T = t.tiles_per_wg < (uint32_t)kStage ? t.tiles_per_wg : (uint32_t)kStage;   // power of two
     uint64_t epoch = 0;
@@ -487,14 +489,14 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(MODE == Mx:
             __builtin_nontemporal_store(packed, reinterpret_cast<u32x4 *>(t.codes) + i);
             __builtin_nontemporal_store((uint8_t)code, t.scales + i);
         }
-        if constexpr (DSS) {
+        if constexpr (STAGED) {
             staged.stage(k & (T - 1u), term[0]);
             if ((k & (T - 1u)) == T - 1u) staged.close(k / T, T);
         } else {
             tree.add_tile(k, term);
         }
     }
-    if constexpr (DSS) tree.wg[0] = staged.wg;
+    if constexpr (STAGED) tree.wg[0] = staged.wg;
     if (batch.once) {
         bool flag = __syncthreads_or(nonfinite ? 1 : 0) != 0;
         if (tid >= 64u) return;

@@ -44,3 +44,12 @@ def test_no_register_of_the_shared_launch_of_the_later_iterations_lies_in_scratc
         closed = "(Iterate)0" in name or "CLOSED_FORM" in name
         assert 512 // (-(-v["vgpr_count"] // 8) * 8) >= (6 if closed else 5), name
         assert 160 * 1024 // (v["group_segment_fixed_size"] + 2048 * 4 * (not closed)) >= (6 if closed else 5), name
+
+
+def test_an_mxfp4_search_of_one_tile_has_no_place_for_more(kernels):
+    """the kernel for workgroups of one tile stages no sums: LDS for the trees only"""
+    lds = {k: v["group_segment_fixed_size"] for k, v in kernels.items() if k.startswith("k_mx<")}
+    assert len(lds) == 10
+    staged = {k for k in lds if k.endswith("true>")}
+    assert len(staged) == 2 and all(lds[k] > 8 * 1024 for k in staged)
+    assert all(v < 4 * 1024 for k, v in lds.items() if k not in staged and "(Mx)0" not in k)
