@@ -697,8 +697,10 @@ __device__ __forceinline__ uint64_t finish_iteration(const Batch &batch, const T
 // bf16: a lane's next block is on its way into LDS while it searches this one, and the results of a block are stored when the
 // next one has been taken out: a wait for loads also waits for the stores before them, and both are a whole search old by then. The
 // ratio is read beside the weights, not after them.  One decoder layer 722 -> 703 us, 12288 x 4096 243 -> 237.  fp32 has no
-// LDS left for five workgroups with four tiles staged, and with two it is slower (929 -> 944; four workgroups 941): there the ratio is read first
-// (929 -> 924).
+// LDS left for five workgroups with four tiles staged, and with two it is slower (929 -> 944; four workgroups 941): there the nearest-factor search
+// reads the ratio first (929 -> 924).  The other searches take longer for a schedule in fewer registers that the compiler finds where the ratio
+// or the results are variables of the whole loop: every pair of 4096 x 4096 fp32, three iterations, 990 us, as below 959.  On bf16 the look-ahead
+// costs them a wave of five per SIMD and gains all the same (985 -> 949).
 template <int DT, bool NEAREST>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5 : 4, 8))) void k_iter(const Batch batch)
 {
@@ -756,26 +758,39 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(NEAREST ? 5
         for (uint32_t kg = 0; kg < t.tiles_per_wg; kg += T) {
             for (uint32_t kk = 0; kk < T; ++kk) {
                 const uint32_t i = (tile0 + kg + kk) * kWG + tid;
-                float w[16], rho = 0.0f;
                 if constexpr (kAhead) {
+                    float w[16];
                     stream.take(w);
-                    rho = next_rho;
+                    const float rho = next_rho;
                     store();
                     const uint32_t at = kg + kk + 1u;
                     const uint32_t next_chunk = at < t.tiles_per_wg ? chunk : chunk + t.n_wg;
                     if (next_chunk < t.n_chunks) fetch(next_chunk * t.tiles_per_wg + (at < t.tiles_per_wg ? at : 0u));
-                } else if (i < blocks) {
-                    rho = t.rho[i];
-                    load_block<DT>(t.w, block_offset(t, i), w);
+                    x.a = x.b = x.d = x.err = 0.0f;
+                    done = i;
+                    if (i < blocks) {
+                        if (allzero) zero_block(w, x);
+                        else iterate_block<NEAREST>(w, rho, js, x);
+                    }
+                    tree.stage(kk, x.a, x.b, x.d, x.err);
+                } else {
+                    BlockState y;
+                    y.a = y.b = y.d = y.err = 0.0f;
+                    if (i < t.nblk && amax_bits < 0x7F800000u) {
+                        float w[16], rho = 0.0f;
+                        if constexpr (NEAREST) rho = t.rho[i];
+                        load_block<DT>(t.w, block_offset(t, i), w);
+                        if (allzero) {
+                            zero_block(w, y);
+                        } else {
+                            if constexpr (!NEAREST) rho = t.rho[i];
+                            iterate_block<NEAREST>(w, rho, js, y);
+                            t.rho[i] = y.rho;
+                        }
+                        store_block(t, i, y);
+                    }
+                    tree.stage(kk, y.a, y.b, y.d, y.err);
                 }
-                x.a = x.b = x.d = x.err = 0.0f;
-                done = i;
-                if (i < blocks) {
-                    if (allzero) zero_block(w, x);
-                    else iterate_block<NEAREST>(w, rho, js, x);
-                }
-                if constexpr (!kAhead) store();
-                tree.stage(kk, x.a, x.b, x.d, x.err);
             }
             tree.close(kg / T, T);
         }
