@@ -146,7 +146,9 @@ typedef struct {
                                 - a batch of 2 to 40 tensors of one element type, method SOAR,
                                   single-step settings: as long as all of them together fit
                                   4096 blocks per compute unit, tensors rounded up to whole
-                                  workgroups; not while the call is being captured.
+                                  workgroups; not while the call is being captured.  On a
+                                  stream restricted to some compute units these count, unless
+                                  resident_wait_us is set.
                                 The launch needs every workgroup of its grid (at most one per
                                 compute unit) on the GPU at the same time and waits for that
                                 at most resident_wait_us.  A call that arrives on another

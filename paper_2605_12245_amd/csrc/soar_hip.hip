@@ -200,6 +200,22 @@ struct HipStreams {
     }
 };
 
+// The compute units that work on a stream may use.  Asked for batches, which went to whatever units are there before they took one launch: a
+// stream of 64 of 256, a layer of hidden 512 35.7 us in one launch that does not find its places, 30.8 in several; hidden 1024 68.7 / 59.8.
+int stream_compute_units(hipStream_t st)
+{
+    const int all = device_facts().compute_units;
+    if (HipStreams::always_there(st)) return all;
+    uint32_t mask[16] = {};
+    if (hipExtStreamGetCUMask(st, 16, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return all;
+    }
+    int units = 0;
+    for (uint32_t m : mask) units += __builtin_popcount(m);
+    return units > 0 && units < all ? units : all;
+}
+
 // a launch that completes `done`, if there is one
 template <typename Kernel, typename... Args>
 void launch_and_mark(Kernel kernel, dim3 grid, int lanes, hipStream_t st, hipEvent_t done, const Args &...args)
@@ -809,7 +825,8 @@ soar_status run_batch(int32_t n, const soar_tensor_desc *descs, const soar_param
     for (int32_t k = 1; k < n; ++k) one_dtype = one_dtype && descs[k].dtype == descs[0].dtype;
     if (n > 1 && n <= kResidentTensors && one_dtype && !iterated && params->method == SOAR_METHOD_SOAR && params->tiles_per_wg == 0 &&
         params->tiles_per_wg_absmax == 0 && params->tiles_per_wg_search == 0 && params->resident == SOAR_RESIDENT_AUTO &&
-        resident_batch_plan(n, descs, device_facts().compute_units, plan) && !being_captured(st) && turn.take(st)) {
+        resident_batch_plan(n, descs, params->resident_wait_us > 0 ? device_facts().compute_units : stream_compute_units(st), plan) &&
+        !being_captured(st) && turn.take(st)) {
         ResidentBatch b;
         std::memset(&b, 0, sizeof(b));
         b.slots = static_cast<char *>(d_workspace);

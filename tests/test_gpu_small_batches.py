@@ -139,7 +139,8 @@ def test_a_batch_that_gives_up_is_finished(sizes, zero, bad, unit, dtype):
 
 @pytest.mark.gpu
 def test_a_batch_on_a_stream_of_few_compute_units_is_finished_by_them():
-    """240 workgroups of which 64 find a place: the call takes what the units need, not the seconds of a wait for the others"""
+    """240 workgroups of which 64 find a place: several launches, as where there is no one launch for a batch; with a bound of the
+    caller's, the one launch, which takes what the units need, not the seconds of a wait for the others.  A batch that the units hold takes one."""
     ws = with_degenerate([2048 * 100, 2048 * 100 + 1, 5], 2048 * 20, 2048 * 17, torch.bfloat16, 3)
     p = B.soar_default_params()
     p.resident = B.SOAR_RESIDENT_NEVER
@@ -150,12 +151,28 @@ def test_a_batch_on_a_stream_of_few_compute_units_is_finished_by_them():
     assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, mask) == 0
     try:
         with torch.cuda.stream(torch.cuda.ExternalStream(stream.value)):
+            assert launches_of(B.SOAR_KERNEL_RESIDENT, lambda: run(ws, p)) == 0
+            same_with_degenerate(run(ws, p), want)
+            p.resident_wait_us = 50
+            assert launches_of(B.SOAR_KERNEL_RESIDENT, lambda: run(ws, p)) == 1
             for turn in range(3):
                 t = time.perf_counter()
                 got = run(ws, p)
                 took = time.perf_counter() - t
+                left = [int(o.status.item()) & B.SOAR_STATUS_GAVE_UP for o in got]
+                assert left[0] and left[1] and not left[2]
+                for o in got:
+                    o.status &= ~B.SOAR_STATUS_GAVE_UP
                 same_with_degenerate(got, want)
                 assert took < 1.0, took
+            p.resident_wait_us = 0
+            few = ws[:2] + ws[2:3]
+            few = [w[:2048 * 25] for w in few]
+            assert launches_of(B.SOAR_KERNEL_RESIDENT, lambda: run(few, p)) == 1
+            p.resident = B.SOAR_RESIDENT_NEVER
+            bare = run(few, p)
+            p.resident = B.SOAR_RESIDENT_AUTO
+            same(run(few, p), bare)
     finally:
         torch.cuda.synchronize()
         hip.hipStreamDestroy(stream)
