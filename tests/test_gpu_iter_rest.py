@@ -146,10 +146,12 @@ def test_rest_stops_inside_the_shared_launch(dtype, arm):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("arm", ["paper", "every pair", "closed"])
+@pytest.mark.parametrize("arm", ["paper", "every pair", "closed", "large table"])
 def test_rest_on_a_stream_of_few_compute_units(arm):
-    """four fifths of the workgroups find no place: the ones that do carry out their shares"""
-    p = params(arm)
+    """with a large factor table in LDS some workgroups find no place, also on the whole GPU: the ones that do carry out their shares"""
+    p = params("paper" if arm == "large table" else arm)
+    if arm == "large table":
+        p.n_beta, p.iters = 4096, 7
     p.resident = B.SOAR_RESIDENT_NEVER
     ws = weights_of((170000, 170001, 5), torch.bfloat16, 8)
     outs, descs = outputs(ws, p)
