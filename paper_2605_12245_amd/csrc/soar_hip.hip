@@ -1326,24 +1326,35 @@ size_t soar_mxfp4_workspace_bytes(int64_t rows, int64_t cols, const soar_mx_para
     return kSlotBytes;
 }
 
+static int64_t mx_weight_bytes(const soar_mx_tensor_desc &d) { return d.rows * d.cols * (d.dtype == SOAR_BF16 ? 2 : 4); }
+
 static int32_t mx_group_end(int32_t n, const soar_mx_tensor_desc *descs, int32_t i)
 {
-    auto bytes_of = [](const soar_mx_tensor_desc &d) { return d.rows * d.cols * (d.dtype == SOAR_BF16 ? 2 : 4); };
-    int64_t bytes = bytes_of(descs[i]);
+    int64_t bytes = mx_weight_bytes(descs[i]);
     int32_t j = i + 1;
     while (j < n && j - i < kGroupMax && descs[j].dtype == descs[i].dtype &&
-           bytes + bytes_of(descs[j]) <= kOnePassByteCap) {
-        bytes += bytes_of(descs[j]);
+           bytes + mx_weight_bytes(descs[j]) <= kOnePassByteCap) {
+        bytes += mx_weight_bytes(descs[j]);
         ++j;
     }
     return j;
 }
 
-// Whether the launch groups of a call alternate between two streams.  Forking and joining them costs 10 us, the overlap of a group's tail
-// with the next one's ramp gives a few us a group.  Two streams / one, bf16 unless said: two groups 33 / 21.4 us (two layers of hidden 512),
-// 41.6 / 33 (1024), 80 / 73 (2048); four groups 79 / 87 (four layers of hidden 1024 in fp32, 4600 tiles), 146 / 156 (2048).
-constexpr int64_t kMxLaneTiles = 2048;
-static bool mx_two_lanes(int32_t groups, int64_t tiles) { return groups > 2 && tiles >= kMxLaneTiles; }
+// Whether the launch groups of a call alternate between two streams.  A call of small groups takes what the host needs to launch them: forking and
+// joining are 10 to 20 us of that (they vary by a fifth from run to run).  Larger groups gain a few us each where the tail of one
+// overlaps the ramp of the next.  Two streams / one, 8 tensors a group, us:
+//   2 groups, search: 2400 tiles bf16 41 / 29, 19200 119 / 118, 40000 215 / 217, 80000 385 / 408; fp32 9600 105 / 103, 19200 178 / 182, 40000 327 / 350
+//     plain: 40000 tiles bf16 162 / 157, 80000 295 / 302; fp32 40000 292 / 292, 80000 567 / 583
+//   3 and 4, search: 2000 tiles bf16 41 / 34 and 52 / 42, 3200 44 / 42 and 53 / 50, 4800 49 / 51 and 55 / 57; fp32 1200 49 / 41 and 55 / 53, 2000 47 / 48 and
+//     55 / 56, 2400 48 / 52 and 57 / 62
+//   6, search: 2000 tiles bf16 70 / 62, 2600 69 / 65; fp32 1200 70 / 70, 2000 68 / 81; plain: 2000 tiles bf16 73 / 69, fp32 62 / 61
+//   8, search: 600 tiles bf16 72 / 73, 2600 72 / 81; fp32 600 72 / 87, 2000 76 / 93; plain: 600 tiles bf16 73 / 80, 2000 75 / 92; fp32 600 70 / 73
+constexpr int64_t kMxTwoGroupBytes = (int64_t)640 << 20, kMxTwoGroupBytesPlain = (int64_t)1280 << 20;
+static bool mx_two_lanes(int32_t groups, int64_t tiles, int64_t bytes, bool search)
+{
+    if (groups == 2) return bytes >= (search ? kMxTwoGroupBytes : kMxTwoGroupBytesPlain);
+    return groups > 6 || (groups > 2 && tiles >= (groups > 4 ? 1536 : 2048));
+}
 
 static int32_t mx_group_count(int32_t n, const soar_mx_tensor_desc *descs)
 {
@@ -1374,9 +1385,12 @@ soar_status soar_mxfp4_quantize_batch(int32_t n, const soar_mx_tensor_desc *desc
     const int32_t groups = mx_group_count(n, descs);
     const int ws_lanes = groups > 1 ? kLanes : 1;
     if (workspace_bytes < (size_t)ws_lanes * slots * kSlotBytes) return SOAR_ERR_WORKSPACE;
-    int64_t all_tiles = 0;
-    for (int32_t k = 0; k < n; ++k) all_tiles += (descs[k].rows * (descs[k].cols / 32) + kWG - 1) / kWG;
-    const int lanes = (params->streams != 1 && mx_two_lanes(groups, all_tiles)) ? kLanes : 1;
+    int64_t all_tiles = 0, all_bytes = 0;
+    for (int32_t k = 0; k < n; ++k) {
+        all_tiles += (descs[k].rows * (descs[k].cols / 32) + kWG - 1) / kWG;
+        all_bytes += mx_weight_bytes(descs[k]);
+    }
+    const int lanes = (params->streams != 1 && mx_two_lanes(groups, all_tiles, all_bytes, params->dss != 0)) ? kLanes : 1;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     char *base = static_cast<char *>(d_workspace);
     // launch groups alternate between the caller's stream and one internal stream (forked and joined with

@@ -186,6 +186,25 @@ def test_batch_entry_point_equals_separate_calls():
                 assert float(o.sse.item()) == ref.sse and int(o.status.item()) == 0, (dss, rep, k)
 
 
+@pytest.mark.parametrize("dss", [False, True], ids=["plain", "search"])
+@pytest.mark.parametrize("n", [16, 17, 33, 48, 49, 56])
+def test_launch_groups_on_two_streams_equal_those_on_one(n, dss):
+    """two to seven launch groups of eight small ragged tensors (38 to 44 tiles each): on one stream by rule, or on two"""
+    g = torch.Generator(device="cpu").manual_seed(n)
+    ws_list = [(torch.randn(301 + k, 1024, generator=g) * 0.02).to(torch.bfloat16).to(DEV) for k in range(n)]
+    got = []
+    for streams in (0, 1):
+        p = B.soar_mx_default_params(dss=dss, streams=streams)
+        outs = [B.mx_new_outputs(w.shape[0], w.shape[1], DEV) for w in ws_list]
+        descs = [B.mx_make_desc(w, o) for w, o in zip(ws_list, outs)]
+        B.mx_quantize_batch(descs, p, torch.empty(B.soar_mxfp4_batch_workspace_bytes(descs, p), dtype=torch.uint8, device=DEV))
+        torch.cuda.synchronize()
+        got.append(outs)
+    for a, b in zip(*got):
+        assert torch.equal(a.codes, b.codes) and torch.equal(a.scales, b.scales) and a.sse.item() == b.sse.item()
+        assert int(a.status.item()) == 0 and a.sse.item() > 0.0
+
+
 def test_two_pass_search_equals_the_single_pass():
     spec = synth.workload_specs(2, 2)[0]
     w = synth.make_weight(spec, DEV)
