@@ -611,7 +611,7 @@ def bench_stored_form(args, torch, B, synth, dev):
                     "algorithmic_bytes_per_weight": per_w,
                     "weights_per_launch": E / (n / n_prof), "avg_launch_us": ms / n * 1e3,
                     "note": "per-launch HIP-event durations on the launch stream, "
-                            + ("one launch per tensor" if one_by_one else "up to 8 tensors per launch")
+                            + ("one launch per tensor" if one_by_one else "up to 48 tensors per launch")
                             + ("" if deq else " (with the small launch that clears the sums)")}
     extra = {}
     if not deq:

@@ -308,7 +308,8 @@ typedef struct {
  * soar_batch_workspace_bytes().  Consecutive tensors of one element type are
  * served by the same kernel launches: up to 8 tensors and 256 MiB of weights per
  * launch (208 MiB of bf16 weights outside SOAR_METHOD_RTN, unless 256 MiB hold the
- * whole call; 512 MiB where the maxima are supplied and one pass remains), each
+ * whole call; 512 MiB where the maxima are supplied and one pass remains; up to 40
+ * small tensors in one launch for the whole call: soar_params.resident), each
  * tensor with its own tensor-wide reductions; results are those
  * of n separate soar_quantize calls.  `descs` is HOST memory and is not
  * referenced after the call returns.  All descriptors are validated before
@@ -341,7 +342,7 @@ soar_status soar_recon_error(const void *d_w, soar_dtype dtype, int64_t rows, in
 
 /*
  * Eq. 3 and Eq. 4 for the stored tensors of a whole model in a handful of launches:
- * up to 8 tensors of one element type share a launch, as in soar_quantize_batch.
+ * up to 48 tensors of one element type share a launch.
  * All pointers are device pointers, owned by the caller; nothing is allocated;
  * everything is enqueued on hip_stream.
  *
@@ -408,7 +409,9 @@ typedef struct {
                                 1: evaluate every factor.  Same bytes.                      */
     int32_t  streams;        /* soar_mxfp4_quantize_batch: 0 = launch groups alternate between
                                 the caller's stream and one internal stream (forked and joined
-                                by events); 1 = everything on the caller's stream            */
+                                by events) where the library finds that faster (more than two
+                                groups that are not small, two large ones); 1 = everything on
+                                the caller's stream                                          */
 } soar_mx_params;
 
 /* dss = 1, 101 factors in [0.5, 1.5], K = 1 */
@@ -463,7 +466,7 @@ soar_status soar_mxfp4_dequantize(const uint8_t *d_codes, const uint8_t *d_scale
                                   int64_t cols, soar_dtype out_dtype, void *d_out, int64_t ld_elems,
                                   void *hip_stream);
 
-/* The same for n stored tensors in a handful of launches (up to 8 tensors of one element type
+/* The same for n stored tensors in a handful of launches (up to 48 tensors of one element type
  * per launch): soar_stored_desc with d_codes (16-byte aligned), d_scales (E8M0 bytes), rows, cols
  * (a multiple of 32), ld_elems, dtype and d_out; the other fields are not read.  The bytes are
  * those of n one-tensor calls; errors are found before anything is enqueued. */

@@ -244,8 +244,8 @@ __device__ __forceinline__ int search_rank(int code, int centre)
 // candidate on that side is evaluated as well and (i) is asked of the three.
 // Returns false when a condition cannot be shown; the caller then runs the
 // exhaustive search, so the result never depends on this shortcut.
-// One error chain instead of two, with the projections by conversion (e4m3_project): 4096 x 4096 in one launch 23.3 -> 22.2 us, 5003 x 3120
-// fp32 29.5 -> 28.8, 28672 x 8192, whose search is bound by its vector instructions, 292 -> 283; batches of cached tensors, which are not: no change.
+// One error chain instead of two, with the projections by conversion (e4m3_project), whole calls: 4096 x 4096 in one launch 23.8 -> 23.2 us, 5003 x 3120
+// fp32 29.1 -> 28.6, 28672 x 8192, whose search is bound by its vector instructions, 291 -> 282; batches of cached tensors, which are not: no change.
 __device__ __forceinline__ bool search_certified(const float w[16], const float q[16], float alpha1,
                                                  float inv_alpha1, int centre, int radius, int &best,
                                                  float &best_err)

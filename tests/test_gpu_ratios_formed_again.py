@@ -1,5 +1,5 @@
-"""The search pass with the ratios of the statistics pass carried through memory and formed again (fp32 weights, launch groups larger
-than the last-level cache): the same bytes as the iterated path gives for the same settings, which always carries them."""
+"""The search pass, which forms the ratios of the statistics pass again (tensors smaller and larger than the last-level cache, both
+types): the same bytes as the iterated path gives for the same settings, which carries the ratios through memory."""
 import pytest
 import torch
 
@@ -11,7 +11,7 @@ DEV = "cuda:0"
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,rows,cols", [(torch.bfloat16, 16385, 8192), (torch.bfloat16, 2049, 4112), (torch.float32, 2049, 4112),
                                              (torch.float32, 8193, 8192)], ids=str)
-def test_formed_again_equals_carried(dtype, rows, cols):
+def test_formed_again_equals_the_iterated_path(dtype, rows, cols):
     gen = torch.Generator(device=DEV).manual_seed(rows)
     w = torch.randn((rows, cols), generator=gen, device=DEV, dtype=dtype) * 0.02
     w[:, ::256] *= 20.0
