@@ -650,7 +650,8 @@ __device__ __forceinline__ void put(T *p, T v)
 }
 
 // What the last workgroup of a tensor does after iteration `it` (one lane): the outputs that describe the
-// tensor, the early-stop decision and the global scale the next iteration starts from (Eq. 5).
+// tensor, the early-stop decision and the global scale the next iteration starts from (Eq. 5).  Returned: those two as RestWords::next has
+// them, which is the only place for them in k_iter_rest (its workgroups read the control words as the launches before left them).
 template <bool AGENT = false>
 __device__ __forceinline__ uint64_t finish_iteration(const Batch &batch, const Task &t, int it, double N, double M, double cur, float alpha,
                                                  bool degenerate, bool allzero, bool dss_only)
@@ -668,12 +669,14 @@ __device__ __forceinline__ uint64_t finish_iteration(const Batch &batch, const T
         if (t.iters_run) put<AGENT>(t.iters_run, (int32_t)(it + 1));
         if (t.trace) put<AGENT>(t.trace + it + 1, cur);
         const bool stop = batch.early_stop_rel > 0.0f && (prev - cur) < (double)batch.early_stop_rel * prev;
-        put<AGENT>(&t.ctrl->stopped, stop ? 1u : 0u);
-        put<AGENT>(&t.ctrl->prev_sse, cur);
         const float next = (M > 0.0 && !dss_only) ? (float)(N / M) : alpha;                // Eq. 5 for the next iteration
-        put<AGENT>(&t.ctrl->alpha1, next);
-        put<AGENT>(&t.ctrl->N, N);
-        put<AGENT>(&t.ctrl->M, M);
+        put<AGENT>(&t.ctrl->prev_sse, cur);
+        if constexpr (!AGENT) {
+            t.ctrl->stopped = stop ? 1u : 0u;
+            t.ctrl->alpha1 = next;
+            t.ctrl->N = N;
+            t.ctrl->M = M;
+        }
         return (uint64_t)__float_as_uint(next) << 32 | (stop ? kRestStopped : (uint32_t)(it + 1));
     }
     return kRestStopped;
@@ -911,6 +914,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t amax_bits = t.ctrl->amax_bits;
     if (amax_bits == 0u || amax_bits >= 0x7F800000u) return;    // finished by the first iteration
+    if (t.ctrl->stopped) return;                                // by a launch before: this one does not write it
     RestWords &rest = rest_words(t);
     const bool dss_only = batch.arm == SOAR_METHOD_DSS_ONLY;
     JointSearch js{{s_beta, batch.n_beta, batch.beta_lo, batch.index_per_beta}, 0.0f, 0.0f, batch.radius,
@@ -923,8 +927,6 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     };
 
     bool filled = false, helping = false;    // helping: some workgroups were not there before
-    // read before a share of the launch's first iteration is taken: as long as one is left, that iteration has not been finished
-    const uint32_t stopped = t.ctrl->stopped;
     const float first_alpha = t.ctrl->alpha1;
     for (uint32_t asked = 0u;;) {            // one more than the last iteration of which this workgroup has asked for its share
         if (tid < 64u) {
@@ -935,7 +937,7 @@ __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                 it = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)next);
                 alpha = f_of((uint32_t)(next >> 32));
                 if (it == 0u) {
-                    it = stopped ? kRestStopped : (uint32_t)batch.iter_t;
+                    it = (uint32_t)batch.iter_t;
                     alpha = first_alpha;
                 }
                 if (it >= (uint32_t)iters) break;
